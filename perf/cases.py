@@ -243,3 +243,98 @@ def tolerance(case):
     order rounds the other way: 1e-5 of the norm between two orders, 1.7e-3 to the unrounded result."""
     return {"step": {"rel": 1e-2}, "compact": {"rel": 1e-2}, "micro": {"rel": 1e-2}, "fp8": {"rel": 1e-2},
             "shard": {"rel": 1e-2}, "score": {"rel": 2e-6}, "around": {"rel": 1e-3}}[case["path"]]
+
+
+# ------------------------------------------------------------------------------------------ in 64 bits
+
+def _e4m3_values(x):
+    """The float64 values that a bf16 matrix keeps after block-wise E4M3: blocks of 128 columns, the
+    scale amax / 448 rounded up to a power of two, clamp, round to nearest even."""
+    rows, cols = x.shape
+    b = x.double().view(rows, cols // 128, 128)
+    amax = b.abs().amax(dim=2, keepdim=True)
+    e = torch.where(amax > 0, torch.ceil(torch.log2(amax / 448.0)), torch.zeros_like(amax)).clamp_(-127, 127)
+    scale = torch.exp2(e)
+    q = (b / scale).clamp_(-448.0, 448.0).float().to(torch.float8_e4m3fn)
+    return (q.double() * scale).view(rows, cols)
+
+
+def _row_blocks(W, values):
+    """W in blocks of rows, each as float64 `values` of it and as plain float64."""
+    for v0 in range(0, W.shape[0], 4096):
+        w = W[v0:v0 + 4096]
+        yield v0, values(w), w.double()
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in 64 bits throughout, vocabulary block by block."""
+    if case["path"] == "around":
+        return _exact_around(prepare(case, seed))
+    s = prepare(case, seed)
+    N, V, path = case["N"], case["V"], case["path"]
+    values = _e4m3_values if path == "fp8" else torch.Tensor.double
+    H, W, y = s["H"].double(), s["W"], s["y"].long()
+    Hz = values(s["H"])
+    V_total = V * case.get("parts", 1)
+    eps, lam = (0.1, 1e-4) if path == "micro" else (0.0, 0.0)
+    valid = y != IGN
+    rows = torch.arange(N, device=DEV)
+
+    m = torch.full((N,), -math.inf, dtype=torch.float64, device=DEV)
+    d, zy, zsum = (torch.zeros(N, dtype=torch.float64, device=DEV) for _ in range(3))
+    for v0, wz, _ in _row_blocks(W, values):
+        z = Hz @ wz.t()
+        mn = torch.maximum(m, z.amax(dim=1))
+        d = d * torch.exp(m - mn) + torch.exp(z - mn[:, None]).sum(dim=1)
+        m = mn
+        zsum += z.sum(dim=1)
+        here = (y >= v0) & (y < v0 + wz.shape[0])
+        zy[here] = z[rows[here], y[here] - v0]
+    if path == "shard":
+        for other in s["stats"][1:].double():
+            mn = torch.maximum(m, other[:, 0])
+            d = d * torch.exp(m - mn) + other[:, 1] * torch.exp(other[:, 0] - mn)
+            m, zy = mn, zy + other[:, 2]
+    zero = torch.zeros_like(m)
+    lse = torch.where(valid, m + torch.log(d), zero)
+    loss = torch.where(valid, (1 - eps) * (lse - zy) + eps * (lse - zsum / V_total) + lam * lse * lse, zero)
+    out = dict(loss=loss, lse=lse)
+    n_valid = max(int(valid.sum()), 1)
+    if path in ("micro", "score", "shard"):
+        out["mean"] = loss.sum() / n_valid
+    if path == "score":
+        return out
+
+    g_row = torch.where(valid, s["dloss"].double() if "dloss" in s else zero + 1.0 / n_valid, zero)
+    dH = torch.zeros_like(H)
+    dW = torch.empty(W.shape, dtype=torch.float64, device=DEV)
+    for v0, wz, w in _row_blocks(W, values):
+        g = torch.exp(Hz @ wz.t() - lse[:, None]) * (1 + 2 * lam * lse)[:, None] - eps / V_total
+        here = (y >= v0) & (y < v0 + w.shape[0])
+        g[rows[here], y[here] - v0] -= 1 - eps
+        g *= g_row[:, None]
+        dH += g @ w
+        torch.mm(g.t(), H, out=dW[v0:v0 + w.shape[0]])
+    if path == "micro":
+        dW += s["dW"].double()
+    out.update(dH=dH, dW=dW)
+    return out
+
+
+def _exact_around(s):
+    eps, lr, wd, b1, b2, adam_eps, t = 1e-6, 1e-3, 0.1, 0.9, 0.999, 1e-8, 100
+    h = s["x"].double() + s["residual"].double()
+    hb, gamma, dy = h.float().bfloat16().double(), s["gamma"].double(), s["dy"].double()    # the norm acts on the stored bf16 sum
+    rstd = (hb.square().mean(dim=1) + eps).rsqrt()
+    xhat = hb * rstd[:, None]
+    dx = rstd[:, None] * (dy * gamma - xhat * (dy * gamma * xhat).mean(dim=1, keepdim=True))
+    g = s["grad"].double()
+    sumsq = g.square().sum()
+    coef = torch.clamp(1.0 / (sumsq.sqrt() + 1e-6), max=1.0)
+    g *= coef
+    m = b1 * s["m"].double() + (1 - b1) * g
+    v = b2 * s["v"].double() + (1 - b2) * g * g
+    p = s["master"].double() * (1 - lr * wd)
+    p -= lr * (m / (1 - b1 ** t)) / ((v / (1 - b2 ** t)).sqrt() + adam_eps)
+    return dict(h=h, y=xhat * gamma, rstd=rstd, dx=dx, dgamma=(dy * xhat).sum(dim=0), sumsq=sumsq, coef=coef,
+                master=p, weight=p, m=m, v=v)
