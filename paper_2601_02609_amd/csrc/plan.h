@@ -81,6 +81,35 @@ struct Knobs {
     }
 };
 
+// Completion time of n1 jobs of length c1 followed by n2 jobs of length c2 <= c1, handed in that
+// order to `cus` units, each taking the next job when it becomes free.  The searches start where
+// no unit would ever be idle, which is where the answer usually is: a plan asks this thousands of
+// times, and counting up from the first job made the first call of a new shape wait up to 3 ms.
+static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
+    const int64_t full = n1 / cus, rem = n1 % cus;
+    const double tA = (double)full * c1;                     // units without a long job in the last round
+    const double tB = (double)(rem ? full + 1 : full) * c1;
+    if (n2 == 0) return tB;
+    const int64_t nA = cus - rem, nB = rem;
+    const double t0 = ((double)n2 * c2 + (double)nA * tA + (double)nB * tB) / (double)cus;
+    auto first_k = [&](double from) { const int64_t k = (int64_t)((t0 - from) / c2) - 1; return k > 1 ? k : (int64_t)1; };
+    // smallest t with nA * floor((t - tA) / c2) + nB * floor((t - tB) / c2) >= n2
+    double best = 1e300;
+    for (int64_t k = first_k(tA); k <= n2; ++k) {            // t = tA + k c2
+        const double t = tA + (double)k * c2;
+        const int64_t fromB = t > tB ? (int64_t)((t - tB) / c2) : 0;
+        if (nA * k + nB * fromB >= n2) { best = t; break; }
+    }
+    if (nB > 0) {
+        for (int64_t k = first_k(tB); k <= n2; ++k) {        // t = tB + k c2
+            const double t = tB + (double)k * c2;
+            if (t >= best) break;
+            if (nA * (int64_t)((t - tA) / c2) + nB * k >= n2) { best = t; break; }
+        }
+    }
+    return best > tB ? best : tB;
+}
+
 // Rough time model of the backward pipeline, in microseconds, used only to rank tilings.
 // One compute unit runs one workgroup at a time.  Measured on MI355X with random bf16 data:
 // a 256 x 256 x 64 slice of the main loop takes about 2 us, a 256 x 128 x 64 one about 1.1 us;
@@ -92,40 +121,14 @@ struct BackwardModel {
     double t_gemm(int k_tiles) const { return (double)(k_tiles * 4) * tile.us_per_slice + 4.0; }
     int d_tiles() const { return (int)((D + tile.bn - 1) / tile.bn); }
 
-    // Completion time of n1 jobs of length c1 followed by n2 jobs of length c2 <= c1, handed in
-    // that order to `cus` units, each taking the next job when it becomes free.
-    double two_class_makespan(int n1, double c1, int n2, double c2) const {
-        const int full = n1 / cus, rem = n1 % cus;
-        const double tA = full * c1;                 // units without a long job in the last round
-        const double tB = (rem ? full + 1 : full) * c1;
-        if (n2 == 0) return tB;
-        const int nA = cus - rem, nB = rem;
-        // smallest t with nA * floor((t - tA) / c2) + nB * floor((t - tB) / c2) >= n2
-        double best = 1e300;
-        for (int k = 1; k <= n2; ++k) {             // t = tA + k c2
-            const double t = tA + k * c2;
-            const double fromB = t > tB ? (double)(int64_t)((t - tB) / c2) : 0.0;
-            if ((double)nA * k + (double)nB * fromB >= n2) { best = t; break; }
-        }
-        if (nB > 0) {
-            for (int k = 1; k <= n2; ++k) {         // t = tB + k c2
-                const double t = tB + k * c2;
-                if (t >= best) break;
-                const double fromA = (double)(int64_t)((t - tA) / c2);
-                if ((double)nA * fromA + (double)nB * k >= n2) { best = t; break; }
-            }
-        }
-        return best > tB ? best : tB;
-    }
-
     // One step = the gradient tiles, then the contractions, of an [a x b] block of 256 x 256
     // tiles: two launches that follow each other on the caller's stream.
     double step(int a, int b, bool dw_beta) const {
         const int dt = d_tiles(), per256 = 256 / tile.bm;
         const int n_dh = a * per256 * dt, n_dw = b * per256 * dt;
         const double c_dh = t_gemm(b), c_dw = t_gemm(a);
-        const double mk = (c_dh >= c_dw) ? two_class_makespan(n_dh, c_dh, n_dw, c_dw)
-                                          : two_class_makespan(n_dw, c_dw, n_dh, c_dh);
+        const double mk = (c_dh >= c_dw) ? two_class_makespan(cus, n_dh, c_dh, n_dw, c_dw)
+                                          : two_class_makespan(cus, n_dw, c_dw, n_dh, c_dh);
         // fp32 accumulator traffic of the step at ~3 TB/s
         const double bytes = (double)a * 256 * D * 8.0 + (dw_beta ? (double)b * 256 * D * 8.0 : (double)b * 256 * D * 4.0);
         return ((a * b + cus - 1) / cus) * t_tile() + mk + bytes / 3.0e6 + 4.0;
@@ -139,11 +142,15 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
     if (N <= 0 || D <= 0 || V <= 0) return false;
     const Knobs knobs = Knobs::read();
     const int cus = device_cu_count();
+    // A row-skipping call asks for two plans (all rows, the valid ones) in its forward and again in its
+    // backward, so the cache holds several; the oldest entry goes first.
     struct Key { int64_t N, D, V, B; int cus, fa, fb, fc, fs; Plan plan; bool valid; };
-    static thread_local Key cache = {0, 0, 0, 0, 0, 0, 0, 0, 0, {}, false};
-    if (cache.valid && cache.N == N && cache.D == D && cache.V == V && cache.B == budget_rows && cache.cus == cus &&
-        cache.fa == knobs.row_tiles && cache.fb == knobs.vocab_tiles && cache.fc == knobs.gemm_cols &&
-        cache.fs == knobs.split_acc) { *p = cache.plan; return true; }
+    constexpr int kCached = 8;
+    static thread_local Key cache[kCached] = {};
+    static thread_local int cache_next = 0;
+    for (const Key& k : cache)
+        if (k.valid && k.N == N && k.D == D && k.V == V && k.B == budget_rows && k.cus == cus && k.fa == knobs.row_tiles &&
+            k.fb == knobs.vocab_tiles && k.fc == knobs.gemm_cols && k.fs == knobs.split_acc) { *p = k.plan; return true; }
     const bool compact = budget_rows != 0;
 
     const int64_t Np = round_up(N, 256), Vp = round_up(V, 256);
@@ -269,7 +276,8 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
         p->off_zero_row = p->off_fb_c + scalar_bytes;
         p->total = p->off_zero_row + zero_row_bytes;
     }
-    cache = {N, D, V, budget_rows, cus, knobs.row_tiles, knobs.vocab_tiles, knobs.gemm_cols, knobs.split_acc, *p, true};
+    cache[cache_next] = {N, D, V, budget_rows, cus, knobs.row_tiles, knobs.vocab_tiles, knobs.gemm_cols, knobs.split_acc, *p, true};
+    cache_next = (cache_next + 1) % kCached;
     return true;
 }
 
