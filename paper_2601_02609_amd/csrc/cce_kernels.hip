@@ -544,22 +544,45 @@ static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRo
 //   that the accumulator costs 2 instead of 4 workspace bytes per element; the split is exact.
 //   It costs ~2 us per launch (8-byte instead of 16-byte accesses) and is used only where the
 //   smaller accumulator buys a better tiling.
+//
+// K split: a job with few output tiles and a long reduction is cut into n_split parts of split_k
+// (a multiple of 256; the last part may be shorter), each a set of work items of its own.  Part 0
+// goes to out_f32, part s >= 1 to the fp32 plane part + (s - 1) * part_stride; part s adds to what
+// its output holds when s < beta_n.  The planes are summed by a later launch in a fixed order.
+// What it is for: at N = 509, D = 896, V = 151936 the dH job is 14 tiles whose reduction of 2376
+// slices lasted 1.7 ms while 242 compute units had nothing to do; in 6 parts (84 items beside the
+// dW job's) the whole step went from 1825 to 778 us.  Where the reductions of both jobs fill the
+// GPU anyway a split only adds plane traffic: the planner (plan.h) prices both.
 struct GemmJob {
     int a_kmajor;               // 1: A is K-major (the dH job), 0: A is K-slow (the dW job)
     const uint16_t* A; int lda; int a_free_n; int a_k_n;
     const void* B; int ldb; int b_k_n; int k_total;
     int n_tiles; int n_work; int m_valid; int n_valid;
-    float* out_f32; int64_t ld_out; int beta;
+    int n_split; int split_k; float* part; int64_t part_stride;
+    float* out_f32; int64_t ld_out; int beta_n;
     uint16_t* out_hi; uint16_t* out_lo; int final;
     const int32_t* row_map;     // row skipping: out_hi row of tile row r is row_map[r] (-1: none); else nullptr
     const char* zero_row;       // row skipping: a row of zeros, read by the dW job for k-rows that map to no row
 };
 
 // MODE bit 0: the launch's dH job uses the split running sum; bit 1: its bf16 rows go through
-// row_map (row skipping).  Launch-wide constants, compiled as separate kernels so that the plain
-// form carries none of their code.
+// row_map and the dW job reads hidden rows through it (row skipping in the caller's tensors);
+// MODE 4: only the bf16 rows go through row_map (row skipping on a gathered copy of the hidden
+// rows).  Launch-wide constants, compiled as separate kernels so that the plain form carries none
+// of their code.  K split exists in modes 0 and 4.
 template <class Cfg, bool A_KMAJOR, int MODE>
 __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS char* smem) {
+    constexpr bool KSPLIT = (MODE & 3) == 0;
+    int part = 0;
+    if (KSPLIT && j.n_split > 1) {
+        const int per = j.n_work / j.n_split;
+        part = item / per;
+        item -= part * per;
+    }
+    const int k0 = KSPLIT ? part * j.split_k : 0;
+    const int k_len = !KSPLIT ? j.k_total : (j.k_total - k0 < j.split_k ? j.k_total - k0 : j.split_k);
+    float* const out_f32 = part == 0 ? j.out_f32 : j.part + (size_t)(part - 1) * j.part_stride;
+    const bool beta = part < j.beta_n;
     const int mi = item / j.n_tiles, ni = item % j.n_tiles;    // consecutive items share the A band
 
     f32x16 acc[Cfg::TM][Cfg::TN];
@@ -573,8 +596,8 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
     constexpr bool kMappedB = (MODE & 2) != 0 && !A_KMAJOR;        // row skipping, dW job
     OperandTile<A_KMAJOR, Cfg::BM> Aop;
     OperandTile<false, Cfg::BN, kMappedB> Bop;
-    Aop.init(j.A, j.lda, mi * Cfg::BM, j.a_free_n, j.a_k_n);
-    Bop.init(j.B, j.ldb, ni * Cfg::BN, j.n_valid, j.b_k_n);
+    Aop.init(j.A + (A_KMAJOR ? (size_t)k0 : (size_t)k0 * j.lda), j.lda, mi * Cfg::BM, j.a_free_n, j.a_k_n - k0);
+    Bop.init((const uint16_t*)j.B + (size_t)k0 * j.ldb, j.ldb, ni * Cfg::BN, j.n_valid, j.b_k_n - k0);
     if constexpr ((MODE & 2) != 0 && !A_KMAJOR) {
         // row skipping, dW job: the reduction runs over the compact rows of the block, whose hidden
         // rows are scattered over the original tensor.  The block's row map is copied into LDS
@@ -586,7 +609,7 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
         Bop.kmap = tab;
         Bop.kzero = j.zero_row;
     }
-    gemm_mainloop<Cfg, A_KMAJOR, false, true>(acc, Aop, Bop, j.k_total, smem);
+    gemm_mainloop<Cfg, A_KMAJOR, false, true>(acc, Aop, Bop, k_len, smem);
 
     // Epilogue through LDS so that global memory sees 16-byte accesses along full rows:
     // the fp32 tile is staged [rows][BN + 8 floats] (the padding keeps the two 128-byte
@@ -613,7 +636,7 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
     // the previous pass -- so that their latency hides under the staging through LDS
     // (whose barriers wait for LDS traffic only).
     // (split form: words 0-1 of old[] hold the upper-half plane, words 2-3 the lower-half plane)
-    constexpr bool SPLIT = (MODE & 1) != 0, ROWMAP = (MODE & 2) != 0;
+    constexpr bool SPLIT = (MODE & 1) != 0, ROWMAP = (MODE & 6) != 0;
     const bool split = SPLIT && j.out_lo != nullptr;
     // row of out_hi that tile row `row` goes to (-1: a padding row of the compact row space)
     auto hi_row = [&](int row) { return ROWMAP && j.row_map ? j.row_map[row] : row; };
@@ -623,14 +646,14 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
         for (int it = 0; it < kIters; ++it) {
             const int row = mi * Cfg::BM + pr0 + it * kRowsPerIter + my_row;
             old[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (j.beta && col_ok && row < j.m_valid) {
+            if (beta && col_ok && row < j.m_valid) {
                 if (split) {
                     const int orow = hi_row(row);
                     const u32x2 hi = orow >= 0 ? *(const u32x2*)(j.out_hi + (size_t)orow * j.ld_out + col) : u32x2{0u, 0u};
                     const u32x2 lo = *(const u32x2*)(j.out_lo + (size_t)row * j.ld_out + col);
                     old[it] = __builtin_bit_cast(f32x4, u32x4{hi.x, hi.y, lo.x, lo.y});
                 } else {
-                    old[it] = *(const f32x4*)(j.out_f32 + (size_t)row * j.ld_out + col);
+                    old[it] = *(const f32x4*)(out_f32 + (size_t)row * j.ld_out + col);
                 }
             }
         }
@@ -707,7 +730,7 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
                 const int orow = hi_row(row);
                 if (orow >= 0) *(u32x2*)(j.out_hi + (size_t)orow * j.ld_out + col) = cv.u;
             } else if (!split) {
-                *(f32x4*)(j.out_f32 + (size_t)row * j.ld_out + col) = v[it];
+                *(f32x4*)(out_f32 + (size_t)row * j.ld_out + col) = v[it];
             } else {
                 const u32x4 b = __builtin_bit_cast(u32x4, v[it]);
                 const u32x2 hi = {(b.y & 0xffff0000u) | (b.x >> 16), (b.w & 0xffff0000u) | (b.z >> 16)};
@@ -740,6 +763,36 @@ __global__ __launch_bounds__(kThreads) void grad_gemm_kernel(const GemmJob first
     const GemmJob& j = in_first ? first : second;
     if (j.a_kmajor) run_gemm_job<Cfg, true, MODE>(j, item, smem);
     else run_gemm_job<Cfg, false, (MODE & 2)>(j, item, smem);
+}
+
+// ------------------------------------------------------------------------------------------
+// Sums of the K-split planes (fixed order: reproducible).  One 16-byte group per thread; a few
+// megabytes that the contraction has just written, i.e. cache traffic bound by the launch itself.
+// ------------------------------------------------------------------------------------------
+// dHidden row row_map[r] (or r) = bf16(sum of the planes' row r); D4 = D / 4 groups per row.
+__global__ __launch_bounds__(256) void dh_planes_kernel(const float* __restrict__ planes, int n_planes, int64_t stride,
+                                                        int64_t groups, int D4, uint16_t* __restrict__ dhidden,
+                                                        const int32_t* __restrict__ row_map) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= groups) return;
+    f32x4 s = *(const f32x4*)(planes + i * 4);
+    for (int p = 1; p < n_planes; ++p) s += *(const f32x4*)(planes + (size_t)p * stride + i * 4);
+    union { __bf16 h[4]; u32x2 u; } cv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) cv.h[e] = (__bf16)s[e];
+    const int64_t row = i / D4;
+    const int64_t to = row_map ? (int64_t)row_map[row] : row;
+    if (to >= 0) *(u32x2*)(dhidden + (to * D4 + (i - row * D4)) * 4) = cv.u;
+}
+
+// dW += sum of the planes.
+__global__ __launch_bounds__(256) void dw_planes_kernel(float* __restrict__ dw, const float* __restrict__ planes,
+                                                        int n_planes, int64_t stride, int64_t groups) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= groups) return;
+    f32x4 s = *(const f32x4*)(dw + i * 4);
+    for (int p = 0; p < n_planes; ++p) s += *(const f32x4*)(planes + (size_t)p * stride + i * 4);
+    *(f32x4*)(dw + i * 4) = s;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -820,7 +873,8 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
 // (b) zero rows of dHidden for every row that takes no part: label not valid, or a valid row that
 //     the compaction dropped because the caller's bound was too small (the compaction is stable, so
 //     those are the valid rows behind the last kept one) -- one wavefront per original row.
-// Grid: enough workgroups of 256 for both, i.e. max(ceil(rows_pad / 256), ceil(N / 4)).
+// Grid: enough workgroups of 256 for both, i.e. max(ceil(rows_pad / 256), ceil(N / 4)).  rows_pad = 0
+// leaves (a) out, dhidden = nullptr (b).
 __global__ __launch_bounds__(256) void compact_prepare_backward_kernel(
         const int32_t* __restrict__ perm, const int32_t* __restrict__ count, int rows_pad,
         const int32_t* __restrict__ labels, int N, int V, int32_t ignore_index, int32_t* __restrict__ labels_c,
@@ -835,7 +889,7 @@ __global__ __launch_bounds__(256) void compact_prepare_backward_kernel(
     }
     const int l = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= N) return;
+    if (!dhidden || row >= N) return;
     const int32_t y = labels[row];
     const int kept = count[0];
     const int last_kept = kept > 0 ? perm[kept - 1] : -1;
@@ -843,6 +897,20 @@ __global__ __launch_bounds__(256) void compact_prepare_backward_kernel(
     u32x4* dr = (u32x4*)(dhidden + (size_t)row * D);
     const u32x4 z = {0u, 0u, 0u, 0u};
     for (int c = l; c < (D >> 3); c += 64) dr[c] = z;
+}
+
+// Copy of the hidden rows that take part, in compact order; rows that stand for none become zeros
+// (their gradient is zero, but whatever a skipped row holds -- NaN included -- would meet that zero
+// in the dW product).  One wavefront per row.
+__global__ __launch_bounds__(256) void compact_gather_kernel(const uint16_t* __restrict__ hidden, const int32_t* __restrict__ perm,
+                                                             int rows, int D, uint16_t* __restrict__ out) {
+    const int l = threadIdx.x & 63;
+    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= rows) return;
+    const int from = perm[r];
+    const u32x4* src = (const u32x4*)(hidden + (size_t)(from < 0 ? 0 : from) * D);
+    u32x4* dst = (u32x4*)(out + (size_t)r * D);
+    for (int c = l; c < (D >> 3); c += 64) dst[c] = from < 0 ? u32x4{0u, 0u, 0u, 0u} : src[c];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -935,6 +1003,8 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_tile_kernel<true>, kGradTileLds)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 0>, kGemmLdsBig)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 0>, kGemmLdsNarrow)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileBig, 4>, kGemmLdsBig)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 4>, kGemmLdsNarrow)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 1>, kGemmLdsBig)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 1>, kGemmLdsNarrow)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 2>, kGemmLdsBig + kRowTableBytes)) return false;
@@ -943,6 +1013,17 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 3>, kGemmLdsNarrow + kRowTableBytes)) return false;
     done[dev] = true;
     return true;
+}
+
+// A launch of one or both contractions (modes 0 and 4 of grad_gemm_kernel).
+template <int MODE>
+static void launch_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+    const int work = first.n_work + second.n_work;
+    ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
+    if (kind == 0)
+        hipLaunchKernelGGL((grad_gemm_kernel<TileBig, MODE>), dim3(work), dim3(kThreads), kGemmLdsBig, stream, first, second);
+    else
+        hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, MODE>), dim3(work), dim3(kThreads), kGemmLdsNarrow, stream, first, second);
 }
 
 }  // namespace cce
@@ -987,6 +1068,17 @@ struct CompactCtx {
     Plan plan;                  // made for the compact rows
     const int32_t* perm;        // device: original row of each compact row, -1 for padding
     const char* zero_row = nullptr;   // device: D bf16 zeros (backward only)
+    // backward only: the caller's rows and labels, for the zero rows of dHidden
+    int64_t all_rows = 0;
+    const int32_t* all_labels = nullptr;
+    const int32_t* count = nullptr;
+    int D = 0, V = 0;
+    int32_t ignore_index = 0;
+    void zero_skipped(hipStream_t stream, void* dHidden) const {
+        hipLaunchKernelGGL(compact_prepare_backward_kernel, dim3((unsigned)((all_rows + 3) / 4)), dim3(256), 0, stream,
+                           perm, count, 0, all_labels, (int)all_rows, V, ignore_index, (int32_t*)nullptr,
+                           (const float*)nullptr, (float*)nullptr, (const float*)nullptr, (float*)nullptr, D, (uint16_t*)dHidden);
+    }
 };
 
 // Forward over the V rows of `weight`, which are the rows [v_off, v_off + V) of the full
@@ -1138,6 +1230,118 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
                         0, nullptr, false, nullptr, ws, p.total, stream_, nullptr, status);
 }
 
+// The backward in the order of a Schedule (plan.h); arguments as in backward_impl, checked there.
+// Row skipping: the hidden rows that take part are gathered first -- for one row block into dHidden,
+// which is as large and is not written before the last contraction; per row block into the workspace.
+static int run_schedule(const Schedule& sc, const void* hidden, const void* weight, const int32_t* labels,
+                        const float* lse, const float* dloss, const float* mean_scale,
+                        int64_t N, int64_t D, int64_t V, int64_t v_off, int64_t V_total, int32_t ignore_index,
+                        float label_smoothing, float z_loss, void* dHidden, float* dW, int accumulate_dW,
+                        const void* logit_hidden, const void* logit_weight, const Fp8Scales* fp8,
+                        char* ws, hipStream_t stream, const CompactCtx* cc) {
+    const Fp8Scales scales = fp8 ? *fp8 : Fp8Scales{nullptr, nullptr, 0, 0};
+    const GemmTile gt = gemm_tile_of_kind(sc.kind);
+    const int d_tiles = (int)((D + gt.bn - 1) / gt.bn);
+    const int64_t block = (int64_t)sc.a * 256;
+    float* planes = (float*)(ws + sc.off_acc);
+    float* part_w = (float*)(ws + sc.off_part_w);
+    const bool one_block = block >= N;
+    for (int64_t r0 = 0; r0 < N; r0 += block) {
+        const int64_t rows = N - r0 < block ? N - r0 : block;
+        const int row_tiles = (int)((rows + 255) / 256);
+        // hidden rows of this block, densely
+        const uint16_t* h_rows = (const uint16_t*)hidden + (size_t)r0 * D;
+        if (cc) {
+            uint16_t* hc = one_block ? (uint16_t*)dHidden : (uint16_t*)(ws + sc.off_hc);
+            hipLaunchKernelGGL(compact_gather_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream,
+                               (const uint16_t*)hidden, cc->perm + r0, (int)rows, (int)D, hc);
+            h_rows = hc;
+        }
+        int planes_written = 0;
+        for (int64_t v0 = 0; v0 < V; ) {
+            bool in_tail = false;
+            const int v_tiles = (int)schedule_chunk_tiles(sc, D, V - v0, &in_tail);
+            const int64_t cols = V - v0 < (int64_t)v_tiles * 256 ? V - v0 : (int64_t)v_tiles * 256;
+            const bool last = v0 + cols >= V;
+            const int ldg = v_tiles * 256;
+            const size_t g_bytes = (size_t)row_tiles * 256 * (size_t)ldg * 2;
+            uint16_t* G = in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
+                                  : (uint16_t*)(ws + sc.off_g);
+            {
+                // tokens are counted inside the block: its rows and per-row scalars are contiguous
+                ProfSpan span(CCE_KERNEL_GRAD_TILE, stream);
+                const dim3 grid((unsigned)(row_tiles * v_tiles));
+                if (fp8)
+                    hipLaunchKernelGGL(grad_tile_kernel<true>, grid, dim3(kThreads), kGradTileLds, stream,
+                                       logit_hidden, logit_weight, labels, lse, dloss, mean_scale, (int)N, (int)D, (int)V,
+                                       ignore_index, label_smoothing, z_loss, (int)r0, row_tiles, (int)v0, v_tiles, G, ldg,
+                                       (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
+                else
+                    hipLaunchKernelGGL(grad_tile_kernel<false>, grid, dim3(kThreads), kGradTileLds, stream,
+                                       (const void*)h_rows, weight, labels + r0, lse + r0, dloss ? dloss + r0 : dloss, mean_scale,
+                                       (int)rows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
+                                       v_tiles, G, ldg, (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
+            }
+            // parts of the two reductions, in whole tiles of 256
+            const int kh = (v_tiles + sc.split_h - 1) / sc.split_h, kw = (row_tiles + sc.split_w - 1) / sc.split_w;
+            GemmJob dh;
+            dh.a_kmajor = 1;
+            dh.A = G; dh.lda = ldg; dh.a_free_n = row_tiles * 256; dh.a_k_n = ldg;
+            dh.B = (const void*)((const uint16_t*)weight + (size_t)v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)cols;
+            dh.k_total = ldg; dh.n_tiles = d_tiles; dh.split_k = kh * 256; dh.n_split = (v_tiles + kh - 1) / kh;
+            dh.n_work = row_tiles * (256 / gt.bm) * d_tiles * dh.n_split;
+            dh.m_valid = (int)rows; dh.n_valid = (int)D;
+            dh.out_f32 = planes; dh.part = planes + sc.plane_h; dh.part_stride = sc.plane_h; dh.ld_out = D;
+            dh.beta_n = planes_written;
+            dh.final = last && sc.split_h == 1 ? 1 : 0;
+            dh.out_hi = (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)r0 * D); dh.out_lo = nullptr;
+            dh.row_map = cc ? cc->perm + r0 : (const int32_t*)nullptr;
+            dh.zero_row = nullptr;
+            planes_written = planes_written > dh.n_split ? planes_written : dh.n_split;
+            GemmJob dw;
+            dw.a_kmajor = 0;
+            dw.A = G; dw.lda = ldg; dw.a_free_n = ldg; dw.a_k_n = row_tiles * 256;
+            dw.B = (const void*)h_rows; dw.ldb = (int)D; dw.b_k_n = (int)rows;
+            dw.k_total = row_tiles * 256; dw.n_tiles = d_tiles; dw.split_k = kw * 256; dw.n_split = (row_tiles + kw - 1) / kw;
+            dw.n_work = v_tiles * (256 / gt.bm) * d_tiles * dw.n_split;
+            dw.m_valid = (int)cols; dw.n_valid = (int)D;
+            dw.out_f32 = dW + (size_t)v0 * D; dw.part = part_w; dw.part_stride = sc.plane_w; dw.ld_out = D;
+            dw.beta_n = (r0 > 0 || accumulate_dW) ? 1 : 0;
+            dw.final = 0; dw.out_hi = nullptr; dw.out_lo = nullptr; dw.row_map = nullptr; dw.zero_row = nullptr;
+
+            if (dh.final && cc && one_block) {
+                // this dH job writes dHidden, which still holds the rows the dW job reads
+                GemmJob none = dh;
+                none.n_work = 0;
+                launch_contractions<0>(sc.kind, dw, none, stream);
+                launch_contractions<4>(sc.kind, dh, none, stream);
+            } else {
+                const bool dh_first = kh >= kw;                          // longer items first
+                const GemmJob& first = dh_first ? dh : dw;
+                const GemmJob& second = dh_first ? dw : dh;
+                if (dh.final && cc) launch_contractions<4>(sc.kind, first, second, stream);
+                else launch_contractions<0>(sc.kind, first, second, stream);
+            }
+            if (dw.n_split > 1) {
+                const int64_t groups = cols * (D / 4);
+                hipLaunchKernelGGL(dw_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream,
+                                   dW + (size_t)v0 * D, (const float*)part_w, dw.n_split - 1, sc.plane_w, groups);
+            }
+            v0 += cols;
+        }
+        if (sc.split_h > 1) {
+            const int64_t groups = rows * (D / 4);
+            hipLaunchKernelGGL(dh_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream,
+                               (const float*)planes, planes_written, sc.plane_h, groups, (int)(D / 4),
+                               (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)r0 * D), cc ? cc->perm + r0 : (const int32_t*)nullptr);
+        }
+    }
+    // the gathered rows overwrote the zeros of dHidden's skipped rows
+    if (cc && one_block) cc->zero_skipped(stream, dHidden);
+    if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
+    return CCE_OK;
+}
+
 // Backward over the V rows of `weight`, which are the rows [v_off, v_off + V) of a matrix of
 // V_total rows that `labels`, label smoothing and the validity of a row refer to.
 static int backward_impl(const void* hidden, const void* weight, const int32_t* labels,
@@ -1185,6 +1389,13 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
     const int d_tiles = (int)((D + gt.bn - 1) / gt.bn);
     const int per256 = 256 / gt.bm;                               // contraction row tiles per 256 rows
 
+    Schedule sc;
+    make_schedule(p, N, D, V, cc != nullptr, !accumulate_dW, &sc);
+    if (sc.use)
+        return run_schedule(sc, hidden, weight, labels, lse, dloss, mean_scale, N, D, V, v_off, V_total, ignore_index,
+                            label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
+                            ws, stream, cc);
+
     // The [row block x vocabulary chunk] steps in execution order.
     struct Step { int64_t r0, rows, v0, cols; int row_tiles, v_tiles; bool first_chunk, last_chunk; };
     std::vector<Step> steps;
@@ -1227,11 +1438,12 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         dh.B = (const void*)((const uint16_t*)weight + (size_t)st.v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)st.cols;
         dh.k_total = ldg; dh.n_tiles = d_tiles; dh.n_work = st.row_tiles * per256 * d_tiles;
         dh.m_valid = (int)st.rows; dh.n_valid = (int)D;
-        dh.out_f32 = p.split_acc ? (float*)nullptr : (float*)(ws + p.off_dhacc); dh.ld_out = D; dh.beta = st.first_chunk ? 0 : 1;
+        dh.out_f32 = p.split_acc ? (float*)nullptr : (float*)(ws + p.off_dhacc); dh.ld_out = D; dh.beta_n = st.first_chunk ? 0 : 1;
         dh.out_hi = (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)st.r0 * D); dh.out_lo = p.split_acc ? dh_lo : (uint16_t*)nullptr;
         dh.final = st.last_chunk ? 1 : 0;
         dh.row_map = cc ? cc->perm + st.r0 : (const int32_t*)nullptr;
         dh.zero_row = nullptr;
+        dh.n_split = 1; dh.split_k = dh.k_total; dh.part = nullptr; dh.part_stride = 0;
         // dW chunk (+)= G^T * H_block   (M = chunk columns, K = rows, N = D)
         GemmJob dw;
         dw.a_kmajor = 0;
@@ -1240,10 +1452,11 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         dw.B = cc ? hidden : (const void*)((const uint16_t*)hidden + (size_t)st.r0 * D); dw.ldb = (int)D; dw.b_k_n = (int)st.rows;
         dw.k_total = st.row_tiles * 256; dw.n_tiles = d_tiles; dw.n_work = st.v_tiles * per256 * d_tiles;
         dw.m_valid = (int)st.cols; dw.n_valid = (int)D;
-        dw.out_f32 = dW + (size_t)st.v0 * D; dw.ld_out = D; dw.beta = (st.r0 > 0 || accumulate_dW) ? 1 : 0;
+        dw.out_f32 = dW + (size_t)st.v0 * D; dw.ld_out = D; dw.beta_n = (st.r0 > 0 || accumulate_dW) ? 1 : 0;
         dw.out_hi = nullptr; dw.out_lo = nullptr; dw.final = 0;
         dw.row_map = cc ? cc->perm + st.r0 : (const int32_t*)nullptr;
         dw.zero_row = cc ? cc->zero_row : (const char*)nullptr;
+        dw.n_split = 1; dw.split_k = dw.k_total; dw.part = nullptr; dw.part_stride = 0;
         const bool dh_first = dh.k_total >= dw.k_total;          // longer reduction first
         const GemmJob& first = dh_first ? dh : dw;
         const GemmJob& second = dh_first ? dw : dh;
@@ -1281,7 +1494,8 @@ int cce_backward_ex(const void* hidden, const void* weight, const int32_t* label
 
 // Row skipping pays when enough rows can be skipped: the compact row space costs a label scan and
 // a few small launches, and its tiling may fit the launches worse.  The plan for the compact rows is used when the time model rates it
-// at least 2 % faster than the plan for all rows (plus ~30 us for the extra small kernels);
+// at least 2 % faster than the plan for all rows (plus ~30 us for the extra small kernels) -- by the
+// schedules' model where one of the two backward passes runs a Schedule;
 // otherwise every row is processed, exactly as cce_forward / cce_backward do.
 static bool choose_compact_plan(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows, Plan* p, bool* use_compact) {
     Plan plain, comp;
@@ -1291,8 +1505,18 @@ static bool choose_compact_plan(int64_t N, int64_t D, int64_t V, int64_t max_val
     *use_compact = false;
     *p = plain;
     const int force = g_force_row_skipping.load(std::memory_order_relaxed);
-    if (M < N && force != 1 && make_plan(M, D, V, &comp, N) &&
-        (force == 2 || comp.model_us + 30.0 < 0.98 * plain.model_us)) {
+    if (M >= N || force == 1 || !make_plan(M, D, V, &comp, N)) return true;
+    double plain_us = plain.model_us, comp_us = comp.model_us;
+    Schedule ps, cs;
+    make_schedule(plain, N, D, V, false, true, &ps);
+    make_schedule(comp, M, D, V, true, true, &cs);
+    if (ps.use || cs.use) {
+        // a schedule replaces the backward of one of the plans: both sides by the schedules' model
+        const ForwardCost fwd{device_cu_count(), D};
+        plain_us = ps.us + fwd.us(plain);
+        comp_us = cs.us + fwd.us(comp);
+    }
+    if (force == 2 || comp_us + 30.0 < 0.98 * plain_us) {
         *use_compact = true;
         *p = comp;
     }
@@ -1438,6 +1662,8 @@ int cce_backward_compact_ex(const void* hidden, const void* weight, const int32_
     }
     cc.perm = perm;
     cc.zero_row = ws + p.off_zero_row;
+    cc.all_rows = N; cc.all_labels = labels; cc.count = (const int32_t*)(ws + p.off_count);
+    cc.D = (int)D; cc.V = (int)V; cc.ignore_index = ignore_index;
     // mean reduction (dloss == NULL) counts the compact labels: the rows that take part
     return backward_impl(hidden, weight, labels_c, lse_c, dloss ? dloss_c : (const float*)nullptr, grad_scale, M, D, V, 0, V,
                          ignore_index, label_smoothing, z_loss,

@@ -281,4 +281,192 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
     return true;
 }
 
+// ------------------------------------------------------------------------------------------
+// Schedules of the backward.  A Plan walks [row block x vocabulary chunk] steps whose gradient
+// chunk and dH sums share 1 % of the logits' size.  Two things make other orders faster where they
+// fit the same workspace:
+//   * When dW is overwritten, the rows of dW behind the current vocabulary chunk hold nothing yet.
+//     A step over ALL rows can keep its gradient chunk there: far larger chunks, hence fewer
+//     launches, and dW is written once instead of being added to by every row block.  The chunks
+//     shrink with the rest of dW; the last ones use the workspace.
+//   * A contraction with few output tiles (few rows, or a small vocabulary) leaves most of the
+//     GPU idle for the length of its reduction; its K range is split into parts that write planes
+//     of their own, summed by a small launch.
+// ------------------------------------------------------------------------------------------
+struct Schedule {
+    bool use;                   // false: the Plan's row blocks and chunks
+    int kind;                   // contraction tile
+    int a;                      // row tiles per block (all of them: one row block)
+    int b;                      // vocabulary tiles per chunk, at most
+    int split_h, split_w;       // K parts of the dH / dW contraction, at most
+    bool tail;                  // gradient chunks in the unwritten rows of dW where they fit
+    int64_t plane_h, plane_w;   // fp32 elements per plane
+    size_t off_acc, off_part_w, off_hc, off_g;      // workspace: dH planes, dW planes, gathered rows, gradient chunk
+    size_t g_bytes;
+    double us;                  // modelled time of the backward
+    double plan_us;             // ... and of the Plan's order, same model
+};
+
+// Vocabulary tiles of the chunk that starts `rest` columns before the end of the vocabulary.
+static inline int64_t schedule_chunk_tiles(const Schedule& sc, int64_t D, int64_t rest, bool* in_tail) {
+    const int64_t row_bytes = (int64_t)sc.a * 256 * 2;               // of one vocabulary column of the chunk
+    const int64_t rest_tiles = (rest + 255) / 256;
+    const int64_t in_ws = (int64_t)sc.g_bytes / (row_bytes * 256);
+    // the chunk's b x 256 columns lie behind dW's own b x 256 rows (256 B for the alignment)
+    const int64_t behind = sc.tail ? (rest * D * 4 - 256) / (256 * (row_bytes + D * 4)) : 0;
+    int64_t b = in_ws > behind ? in_ws : behind;
+    b = b < sc.b ? b : sc.b;
+    b = b < rest_tiles ? b : rest_tiles;
+    *in_tail = b > in_ws;
+    return b;
+}
+
+// Time model of the schedules, microseconds, from launches timed on MI355X with random data: a
+// 256 x 256 x 64 slice 1.58, a 256 x 128 x 64 one 0.79; a gradient tile adds 7 to its slices, a
+// contraction tile 13 / 9 (first slice, epilogue) and 2 more where it adds to its output; a
+// launch boundary 4; HBM 4.5 TB/s where a step moves more than it computes.  (Checked against forced tilings: 8192 x
+// 896 x 151936 in steps of 16 x 16 tiles 7.47 ms modelled, 7.33 measured; of 32 x 32 6.3 and 6.45.)
+struct ScheduleModel {
+    int cus; int64_t D; GemmTile tile;
+    double slice() const { return tile.kind == 0 ? 1.58 : 0.79; }
+    double item(int64_t slices, bool beta) const { return (double)slices * slice() + (tile.kind == 0 ? 13.0 : 9.0) + (beta ? 2.0 : 0.0); }
+    int64_t d_tiles() const { return (D + tile.bn - 1) / tile.bn; }
+    // one step over a x b tiles
+    double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta) const {
+        const int64_t dt = d_tiles();
+        const int64_t kh = (b + split_h - 1) / split_h, kw = (a + split_w - 1) / split_w;       // K tiles per part
+        const int64_t n_dh = a * dt * ((b + kh - 1) / kh), n_dw = b * dt * ((a + kw - 1) / kw);
+        const double c_dh = item(kh * 4, dh_beta), c_dw = item(kw * 4, dw_beta);
+        const double mk = kh >= kw ? two_class_makespan(cus, n_dh, c_dh, n_dw, c_dw) : two_class_makespan(cus, n_dw, c_dw, n_dh, c_dh);
+        const double g = (double)(a * b) * 131072.0, w = (double)b * 512.0 * (double)D;
+        const double tiles_us = (double)((a * b + cus - 1) / cus) * ((double)(D / 64) * 1.55 + 7.0);
+        const double tiles_mem = (g + w) / 4.5e6;
+        const double gemm_mem = (g * 2.0 + w * (dw_beta ? 5.0 : 3.0)) / 4.5e6;
+        double t = (tiles_us > tiles_mem ? tiles_us : tiles_mem) + (mk > gemm_mem ? mk : gemm_mem) + 8.0;
+        if (split_w > 1) t += 4.0 + w * 2.0 * (double)(split_w + 1) / 4.0e6;
+        return t;
+    }
+};
+
+// The forward under the same constants: rounds of workgroups that walk their vocabulary tiles.
+struct ForwardCost {
+    int cus; int64_t D;
+    double us(const Plan& p) const {
+        const int64_t rounds = ((int64_t)p.TT * p.S + cus - 1) / cus;
+        return (double)(rounds * ((p.VT + p.S - 1) / p.S)) * ((double)(D / 64) * 1.55 + 4.0);
+    }
+};
+
+// The schedule of a backward over N rows (row skipping: the compact ones) for the workspace laid out
+// by `p`.  dw_free: dW is overwritten, so its unwritten rows may hold a gradient chunk.  Forced
+// tilings, tiles and accumulators keep the Plan's order.
+static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out) {
+    const Knobs knobs = Knobs::read();
+    const int cus = device_cu_count();
+    struct Key { int64_t N, D, V; size_t total; int cus, forced; bool compact, dw_free, valid; Schedule s; };
+    constexpr int kCached = 8;
+    static thread_local Key cache[kCached] = {};
+    static thread_local int cache_next = 0;
+    const int forced = (knobs.row_tiles || knobs.vocab_tiles || knobs.gemm_cols || knobs.split_acc) ? 1 : 0;
+    for (const Key& k : cache)
+        if (k.valid && k.N == N && k.D == D && k.V == V && k.total == p.total && k.cus == cus && k.forced == forced &&
+            k.compact == compact && k.dw_free == dw_free) { *out = k.s; return; }
+
+    Schedule best = {};
+    const int TT = p.TT, VT = p.VT;
+    const size_t region = (compact ? p.off_count : p.total) - p.off_dhacc;
+    {   // the Plan's order under the same model
+        const ScheduleModel m{cus, D, gemm_tile_of_kind(p.gemm_kind)};
+        const int64_t a = p.Nb / 256, b = p.Vc / 256;
+        for (int64_t r = 0; r < TT; r += a) {
+            const int64_t aa = TT - r < a ? TT - r : a;
+            const int64_t nch = (VT + b - 1) / b;
+            best.plan_us += (double)(nch - 1) * m.step(aa, b, 1, 1, true, r > 0) + m.step(aa, VT - (nch - 1) * b, 1, 1, nch > 1, r > 0);
+            if (p.split_acc) best.plan_us += (double)nch * (compact ? 9.0 : 2.0);
+        }
+    }
+    // A schedule has to be rated 10 % faster: the model is that far off between orders of much
+    // different chunk sizes (6963 rows x 896 x 151936 was rated 8 % faster and measured 1 % slower).
+    best.us = 0.90 * best.plan_us;
+    const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
+    const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+    auto try_one = [&](int kind, int a, int bcap, int sh, int sw) {
+        const ScheduleModel m{cus, D, gemm_tile_of_kind(kind)};
+        Schedule sc = {};
+        sc.kind = kind; sc.a = a; sc.split_h = sh; sc.split_w = sw;
+        sc.b = bcap < VT ? bcap : VT;
+        sc.tail = dw_free && a == TT;
+        const bool one_chunk = a < TT;          // row blocks: the whole vocabulary in one chunk, no running sums
+        if (one_chunk && bcap < VT) return;
+        const int64_t rows = (int64_t)a * 256;
+        const int64_t cols_max = (int64_t)sc.b * 256 < V ? (int64_t)sc.b * 256 : V;
+        sc.plane_h = (rows < N ? rows : N) * D;
+        sc.plane_w = cols_max * D;
+        auto lay_out = [&](int planes) {
+            sc.off_acc = p.off_dhacc;
+            sc.off_part_w = sc.off_acc + (size_t)round_up((int64_t)planes * sc.plane_h * 4, 256);
+            sc.off_hc = sc.off_part_w + (size_t)round_up((int64_t)(sw - 1) * sc.plane_w * 4, 256);
+            sc.off_g = sc.off_hc + (compact && a < TT ? (size_t)round_up(rows * D * 2, 256) : (size_t)0);
+            const size_t used = sc.off_g - p.off_dhacc;
+            sc.g_bytes = used < region ? region - used : 0;
+            return used <= region;
+        };
+        bool tail = false;
+        // without running sums if the whole vocabulary is one chunk, else with a plane per part
+        bool ok = sh == 1 && lay_out(0) && schedule_chunk_tiles(sc, D, V, &tail) == VT;
+        if (!ok) ok = lay_out(sh) && (!one_chunk || schedule_chunk_tiles(sc, D, V, &tail) == VT);
+        if (!ok) return;
+        double block_us[2] = {0.0, 0.0};        // first row block, later ones (they add to dW)
+        for (int later = 0; later < (one_chunk ? 2 : 1); ++later) {
+            int64_t last_b = -1; double last_us = 0.0;
+            for (int64_t v = 0; v < V; ) {
+                const int64_t b = schedule_chunk_tiles(sc, D, V - v, &tail);
+                if (b < 1 || (int64_t)a * b * 131072 >= ((int64_t)1 << 32)) return;
+                if (b != last_b) { last_us = m.step(a, b, sh, sw, v > 0, later > 0 || !dw_free); last_b = b; }
+                block_us[later] += last_us;
+                if (block_us[later] >= best.us) return;
+                v += b * 256;
+            }
+        }
+        const int nblk = (TT + a - 1) / a;
+        sc.us = block_us[0] + (double)(nblk - 1) * block_us[1];
+        if (sh > 1) sc.us += (double)nblk * (8.0 + (double)sh * (double)sc.plane_h * 4.0 / 4.0e6);
+        if (compact) sc.us += (double)nblk * 5.0 + (double)N * (double)D * 4.0 / 4.0e6;
+        if (sc.us < best.us) {
+            const double plan_us = best.plan_us;
+            best = sc;
+            best.plan_us = plan_us;
+            best.use = true;
+        }
+    };
+    if (!forced) {
+        for (int kind = 0; kind < 2; ++kind) {
+            const int64_t dt = (D + gemm_tile_of_kind(kind).bn - 1) / gemm_tile_of_kind(kind).bn;
+            if (kind == 0 && dt * 256 * 7 > D * 8) continue;           // more than an eighth of the columns wasted
+            for (int sh : splits) {
+                if (sh > 1 && (sh > VT || TT * dt * (sh / 2) > 2 * cus)) break;     // parts beyond two rounds of tiles
+                for (int sw : splits) {
+                    if (sw > 1 && (sw > TT || VT * dt * (sw / 2) > 2 * cus)) break;
+                    int prev = 0;
+                    for (int cap : caps) {
+                        const int b = cap < VT ? cap : VT;
+                        if (b == prev) break;
+                        prev = b;
+                        try_one(kind, TT, b, sh, sw);
+                    }
+                    // row blocks over the whole vocabulary
+                    for (int nblk = 2; nblk <= 64 && nblk <= TT; ++nblk) {
+                        const int a = (TT + nblk - 1) / nblk;
+                        if ((int64_t)a * VT * 131072 <= (int64_t)region) try_one(kind, a, VT, sh, sw);
+                    }
+                }
+            }
+        }
+    }
+    if (!best.use) best.us = best.plan_us;
+    *out = best;
+    cache[cache_next] = {N, D, V, p.total, cus, forced, compact, dw_free, true, best};
+    cache_next = (cache_next + 1) % kCached;
+}
+
 }  // namespace cce

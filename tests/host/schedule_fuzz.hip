@@ -1,0 +1,93 @@
+// Host-only check of the backward's schedules (csrc/plan.h), built and run by tests/test_schedule_host.py
+// with AddressSanitizer and UndefinedBehaviorSanitizer on the host side: over seeded shapes every step
+// of a schedule covers the vocabulary once, keeps its gradient chunk inside the workspace or behind the
+// rows of dW that are written by then, and gives its K parts whole, non-empty ranges.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+
+namespace cce { thread_local int g_last_hip_error = 0; }
+#include "../../paper_2601_02609_amd/csrc/plan.h"
+
+using namespace cce;
+
+static uint64_t state = 0x2545F4914F6CDD1Dull;
+static int64_t pick(int64_t lo, int64_t hi) {
+    state ^= state << 13; state ^= state >> 7; state ^= state << 17;
+    return lo + (int64_t)(state % (uint64_t)(hi - lo + 1));
+}
+static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0;
+#define CHECK(cond) do { if (!(cond)) { ++failures; fprintf(stderr, "FAIL %d: %s | N=%lld D=%lld V=%lld B=%lld free=%d\n", __LINE__, #cond, \
+    (long long)N, (long long)D, (long long)V, (long long)B, (int)dw_free); } } while (0)
+
+static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
+    Plan p; Schedule s;
+    if (!make_plan(N, D, V, &p, B)) return false;
+    make_schedule(p, N, D, V, B != 0, dw_free, &s);
+    if (!s.use) return false;
+    ++used;
+    const int64_t block = (int64_t)s.a * 256;
+    const size_t ws_end = B ? p.off_count : p.total;
+    CHECK(s.us < s.plan_us);
+    CHECK(s.a >= 1 && s.a <= p.TT && s.b >= 1 && s.b <= p.VT);
+    CHECK(s.off_acc >= p.off_dhacc && s.off_part_w >= s.off_acc && s.off_hc >= s.off_part_w && s.off_g >= s.off_hc);
+    CHECK(s.off_g + s.g_bytes <= ws_end);
+    CHECK(((s.off_acc | s.off_part_w | s.off_hc | s.off_g) & 255) == 0);
+    if (s.a < p.TT) { ++blocks; CHECK(!s.tail); if (B) CHECK(s.off_g - s.off_hc >= (size_t)(block * D * 2)); }
+    for (int64_t r0 = 0; r0 < N; r0 += block) {
+        const int64_t rows = N - r0 < block ? N - r0 : block, row_tiles = (rows + 255) / 256;
+        int steps = 0, planes = 0;
+        for (int64_t v0 = 0; v0 < V; ++steps) {
+            bool tail = false;
+            const int64_t t = schedule_chunk_tiles(s, D, V - v0, &tail);
+            CHECK(t >= 1);
+            if (t < 1) return true;
+            const int64_t cols = V - v0 < t * 256 ? V - v0 : t * 256;
+            const int64_t g = row_tiles * 256 * t * 512;
+            CHECK(g < ((int64_t)1 << 32));
+            if (tail) {
+                ++in_tails;
+                CHECK(dw_free && r0 == 0 && row_tiles == p.TT);
+                const int64_t at = (V * D * 4 - g) & ~(int64_t)255;
+                CHECK(at >= (v0 + cols) * D * 4 && at + g <= V * D * 4);
+            } else {
+                CHECK((size_t)g <= s.g_bytes);
+            }
+            const int64_t kh = (t + s.split_h - 1) / s.split_h, kw = (row_tiles + s.split_w - 1) / s.split_w;
+            const int64_t nh = (t + kh - 1) / kh, nw = (row_tiles + kw - 1) / kw;
+            CHECK(nh >= 1 && nh <= s.split_h && (nh - 1) * kh < t && nw >= 1 && nw <= s.split_w && (nw - 1) * kw < row_tiles);
+            // an operand's last part starts inside its valid extent
+            CHECK((nh - 1) * kh * 256 < cols && (nw - 1) * kw * 256 < rows);
+            planes = planes > nh ? planes : (int)nh;
+            if (nw > 1) { ++split_ws; CHECK(s.off_hc - s.off_part_w >= (size_t)((nw - 1) * s.plane_w * 4) && s.plane_w >= cols * D); }
+            v0 += cols;
+        }
+        // one chunk and one part need no fp32 plane: the result is final at once
+        if (steps > 1 || s.split_h > 1) CHECK(s.off_part_w - s.off_acc >= (size_t)(planes * s.plane_h * 4) && s.plane_h >= rows * D);
+        if (s.split_h > 1) ++split_hs;
+    }
+    return true;
+}
+
+int main(int argc, char** argv) {
+    const int iters = argc > 1 ? atoi(argv[1]) : 2000;
+    // shapes the schedules exist for: few rows against a full vocabulary; a small vocabulary
+    bool dw_free = true; int64_t N = 509, D = 896, V = 151936, B = 0;
+    CHECK(check(N, D, V, B, dw_free));
+    N = 19823; D = 64; V = 1136;
+    CHECK(check(N, D, V, B, dw_free));
+    for (int it = 0; it < iters; ++it) {
+        const int64_t n = it % 2 ? pick(1, 3000) : pick(1, 40000), d = 64 * (it % 3 ? pick(1, 16) : pick(1, 64));
+        const int64_t v = it % 4 == 0 ? pick(1, 3000) : pick(1, 160000);
+        if (v * d * 2 >= ((int64_t)1 << 32) || n * d * 2 >= ((int64_t)1 << 32)) continue;
+        check(n, d, v, 0, true);
+        check(n, d, v, 0, false);
+        check(pick(1, n), d, v, n, it % 5 != 0);
+    }
+    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d\n", used, in_tails, split_hs, split_ws, blocks);
+    if (!in_tails || !split_hs || !split_ws) { fprintf(stderr, "a form was never taken\n"); return 1; }
+    if (failures) { fprintf(stderr, "%d failures\n", failures); return 1; }
+    printf("schedule_fuzz: %d iterations ok\n", iters);
+    return 0;
+}
