@@ -1015,7 +1015,7 @@ static bool ensure_kernel_attributes() {
     return true;
 }
 
-// A launch of one or both contractions (modes 0 and 4 of grad_gemm_kernel).
+// A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
 template <int MODE>
 static void launch_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
     const int work = first.n_work + second.n_work;
@@ -1248,7 +1248,6 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
     const bool one_block = block >= N;
     for (int64_t r0 = 0; r0 < N; r0 += block) {
         const int64_t rows = N - r0 < block ? N - r0 : block;
-        const int row_tiles = (int)((rows + 255) / 256);
         // hidden rows of this block, densely
         const uint16_t* h_rows = (const uint16_t*)hidden + (size_t)r0 * D;
         if (cc) {
@@ -1258,78 +1257,95 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
             h_rows = hc;
         }
         int planes_written = 0;
+        bool summed = false;                                     // dHidden written by the contractions themselves
         for (int64_t v0 = 0; v0 < V; ) {
-            bool in_tail = false;
-            const int v_tiles = (int)schedule_chunk_tiles(sc, D, V - v0, &in_tail);
+            const ScheduleChunk ch = schedule_chunk(sc, D, V - v0);
+            const int v_tiles = (int)ch.b;
             const int64_t cols = V - v0 < (int64_t)v_tiles * 256 ? V - v0 : (int64_t)v_tiles * 256;
             const bool last = v0 + cols >= V;
             const int ldg = v_tiles * 256;
-            const size_t g_bytes = (size_t)row_tiles * 256 * (size_t)ldg * 2;
-            uint16_t* G = in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
-                                  : (uint16_t*)(ws + sc.off_g);
-            {
-                // tokens are counted inside the block: its rows and per-row scalars are contiguous
-                ProfSpan span(CCE_KERNEL_GRAD_TILE, stream);
-                const dim3 grid((unsigned)(row_tiles * v_tiles));
-                if (fp8)
-                    hipLaunchKernelGGL(grad_tile_kernel<true>, grid, dim3(kThreads), kGradTileLds, stream,
-                                       logit_hidden, logit_weight, labels, lse, dloss, mean_scale, (int)N, (int)D, (int)V,
-                                       ignore_index, label_smoothing, z_loss, (int)r0, row_tiles, (int)v0, v_tiles, G, ldg,
-                                       (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
-                else
-                    hipLaunchKernelGGL(grad_tile_kernel<false>, grid, dim3(kThreads), kGradTileLds, stream,
-                                       (const void*)h_rows, weight, labels + r0, lse + r0, dloss ? dloss + r0 : dloss, mean_scale,
-                                       (int)rows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
-                                       v_tiles, G, ldg, (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
-            }
-            // parts of the two reductions, in whole tiles of 256
-            const int kh = (v_tiles + sc.split_h - 1) / sc.split_h, kw = (row_tiles + sc.split_w - 1) / sc.split_w;
-            GemmJob dh;
-            dh.a_kmajor = 1;
-            dh.A = G; dh.lda = ldg; dh.a_free_n = row_tiles * 256; dh.a_k_n = ldg;
-            dh.B = (const void*)((const uint16_t*)weight + (size_t)v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)cols;
-            dh.k_total = ldg; dh.n_tiles = d_tiles; dh.split_k = kh * 256; dh.n_split = (v_tiles + kh - 1) / kh;
-            dh.n_work = row_tiles * (256 / gt.bm) * d_tiles * dh.n_split;
-            dh.m_valid = (int)rows; dh.n_valid = (int)D;
-            dh.out_f32 = planes; dh.part = planes + sc.plane_h; dh.part_stride = sc.plane_h; dh.ld_out = D;
-            dh.beta_n = planes_written;
-            dh.final = last && sc.split_h == 1 ? 1 : 0;
-            dh.out_hi = (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)r0 * D); dh.out_lo = nullptr;
-            dh.row_map = cc ? cc->perm + r0 : (const int32_t*)nullptr;
-            dh.zero_row = nullptr;
-            planes_written = planes_written > dh.n_split ? planes_written : dh.n_split;
-            GemmJob dw;
-            dw.a_kmajor = 0;
-            dw.A = G; dw.lda = ldg; dw.a_free_n = ldg; dw.a_k_n = row_tiles * 256;
-            dw.B = (const void*)h_rows; dw.ldb = (int)D; dw.b_k_n = (int)rows;
-            dw.k_total = row_tiles * 256; dw.n_tiles = d_tiles; dw.split_k = kw * 256; dw.n_split = (row_tiles + kw - 1) / kw;
-            dw.n_work = v_tiles * (256 / gt.bm) * d_tiles * dw.n_split;
-            dw.m_valid = (int)cols; dw.n_valid = (int)D;
-            dw.out_f32 = dW + (size_t)v0 * D; dw.part = part_w; dw.part_stride = sc.plane_w; dw.ld_out = D;
-            dw.beta_n = (r0 > 0 || accumulate_dW) ? 1 : 0;
-            dw.final = 0; dw.out_hi = nullptr; dw.out_lo = nullptr; dw.row_map = nullptr; dw.zero_row = nullptr;
+            const int kh = (v_tiles + sc.split_h - 1) / sc.split_h;
+            const int n_split_h = (v_tiles + kh - 1) / kh;
+            // Steps over ch.rows row tiles each, all of the block's rows where the chunk is wide enough.
+            for (int64_t s0 = 0; s0 < rows; s0 += (int64_t)ch.rows * 256) {
+                const int64_t srows = rows - s0 < (int64_t)ch.rows * 256 ? rows - s0 : (int64_t)ch.rows * 256;
+                const int row_tiles = (int)((srows + 255) / 256);
+                const int64_t row0 = r0 + s0;
+                const uint16_t* h_step = h_rows + (size_t)s0 * D;
+                const size_t g_bytes = (size_t)row_tiles * 256 * (size_t)ldg * 2;
+                uint16_t* G = ch.in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
+                                         : (uint16_t*)(ws + sc.off_g);
+                {
+                    // tokens are counted inside the step: its rows and per-row scalars are contiguous
+                    ProfSpan span(CCE_KERNEL_GRAD_TILE, stream);
+                    const dim3 grid((unsigned)(row_tiles * v_tiles));
+                    if (fp8)
+                        hipLaunchKernelGGL(grad_tile_kernel<true>, grid, dim3(kThreads), kGradTileLds, stream,
+                                           logit_hidden, logit_weight, labels, lse, dloss, mean_scale, (int)N, (int)D, (int)V,
+                                           ignore_index, label_smoothing, z_loss, (int)row0, row_tiles, (int)v0, v_tiles, G, ldg,
+                                           (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
+                    else
+                        hipLaunchKernelGGL(grad_tile_kernel<false>, grid, dim3(kThreads), kGradTileLds, stream,
+                                           (const void*)h_step, weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
+                                           (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
+                                           v_tiles, G, ldg, (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
+                }
+                // parts of the two reductions, in whole tiles of 256
+                const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
+                GemmJob dh;
+                dh.a_kmajor = 1;
+                dh.A = G; dh.lda = ldg; dh.a_free_n = row_tiles * 256; dh.a_k_n = ldg;
+                dh.B = (const void*)((const uint16_t*)weight + (size_t)v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)cols;
+                dh.k_total = ldg; dh.n_tiles = d_tiles; dh.split_k = kh * 256; dh.n_split = n_split_h;
+                dh.n_work = row_tiles * (256 / gt.bm) * d_tiles * dh.n_split;
+                dh.m_valid = (int)srows; dh.n_valid = (int)D; dh.ld_out = D;
+                dh.out_f32 = sc.split_acc ? (float*)nullptr : planes + (size_t)s0 * D;
+                dh.part = planes + sc.plane_h + (size_t)s0 * D; dh.part_stride = sc.plane_h;
+                dh.beta_n = planes_written;
+                // (gathered rows in dHidden: it is written by the contraction only where that is the one step)
+                dh.final = last && sc.split_h == 1 && !(cc && one_block && (v0 > 0 || row_tiles < sc.a)) ? 1 : 0;
+                summed = dh.final != 0;
+                dh.out_hi = (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)row0 * D);
+                dh.out_lo = sc.split_acc ? (uint16_t*)planes + (size_t)s0 * D : (uint16_t*)nullptr;
+                dh.row_map = cc ? cc->perm + row0 : (const int32_t*)nullptr;
+                dh.zero_row = nullptr;
+                GemmJob dw;
+                dw.a_kmajor = 0;
+                dw.A = G; dw.lda = ldg; dw.a_free_n = ldg; dw.a_k_n = row_tiles * 256;
+                dw.B = (const void*)h_step; dw.ldb = (int)D; dw.b_k_n = (int)srows;
+                dw.k_total = row_tiles * 256; dw.n_tiles = d_tiles; dw.split_k = kw * 256; dw.n_split = (row_tiles + kw - 1) / kw;
+                dw.n_work = v_tiles * (256 / gt.bm) * d_tiles * dw.n_split;
+                dw.m_valid = (int)cols; dw.n_valid = (int)D;
+                dw.out_f32 = dW + (size_t)v0 * D; dw.part = part_w; dw.part_stride = sc.plane_w; dw.ld_out = D;
+                dw.beta_n = (row0 > 0 || accumulate_dW) ? 1 : 0;
+                dw.final = 0; dw.out_hi = nullptr; dw.out_lo = nullptr; dw.row_map = nullptr; dw.zero_row = nullptr;
 
-            if (dh.final && cc && one_block) {
-                // this dH job writes dHidden, which still holds the rows the dW job reads
-                GemmJob none = dh;
-                none.n_work = 0;
-                launch_contractions<0>(sc.kind, dw, none, stream);
-                launch_contractions<4>(sc.kind, dh, none, stream);
-            } else {
                 const bool dh_first = kh >= kw;                          // longer items first
                 const GemmJob& first = dh_first ? dh : dw;
                 const GemmJob& second = dh_first ? dw : dh;
-                if (dh.final && cc) launch_contractions<4>(sc.kind, first, second, stream);
-                else launch_contractions<0>(sc.kind, first, second, stream);
+                if (dh.final && cc && one_block) {
+                    // this dH job writes dHidden, which still holds the rows the dW job reads
+                    GemmJob none = dh;
+                    none.n_work = 0;
+                    launch_contractions<0>(sc.kind, dw, none, stream);
+                    launch_contractions<4>(sc.kind, dh, none, stream);
+                } else if (dh.final && cc) {
+                    launch_contractions<4>(sc.kind, first, second, stream);
+                } else if (sc.split_acc) {
+                    launch_contractions<1>(sc.kind, first, second, stream);
+                } else {
+                    launch_contractions<0>(sc.kind, first, second, stream);
+                }
+                if (dw.n_split > 1) {
+                    const int64_t groups = cols * (D / 4);
+                    hipLaunchKernelGGL(dw_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream,
+                                       dW + (size_t)v0 * D, (const float*)part_w, dw.n_split - 1, sc.plane_w, groups);
+                }
             }
-            if (dw.n_split > 1) {
-                const int64_t groups = cols * (D / 4);
-                hipLaunchKernelGGL(dw_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream,
-                                   dW + (size_t)v0 * D, (const float*)part_w, dw.n_split - 1, sc.plane_w, groups);
-            }
+            planes_written = planes_written > n_split_h ? planes_written : n_split_h;
             v0 += cols;
         }
-        if (sc.split_h > 1) {
+        if (!summed) {
             const int64_t groups = rows * (D / 4);
             hipLaunchKernelGGL(dh_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream,
                                (const float*)planes, planes_written, sc.plane_h, groups, (int)(D / 4),

@@ -288,7 +288,9 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
 //   * When dW is overwritten, the rows of dW behind the current vocabulary chunk hold nothing yet.
 //     A step over ALL rows can keep its gradient chunk there: far larger chunks, hence fewer
 //     launches, and dW is written once instead of being added to by every row block.  The chunks
-//     shrink with the rest of dW; the last ones use the workspace.
+//     shrink with the rest of dW, and a step over all rows of a narrow chunk has few dW tiles with a
+//     long reduction: below a width the chunk is taken in row_parts steps over part of the rows
+//     each, whose chunks are that much wider.  The last ones use the workspace.
 //   * A contraction with few output tiles (few rows, or a small vocabulary) leaves most of the
 //     GPU idle for the length of its reduction; its K range is split into parts that write planes
 //     of their own, summed by a small launch.
@@ -300,6 +302,8 @@ struct Schedule {
     int b;                      // vocabulary tiles per chunk, at most
     int split_h, split_w;       // K parts of the dH / dW contraction, at most
     bool tail;                  // gradient chunks in the unwritten rows of dW where they fit
+    int row_parts, b_min;       // chunks of fewer than b_min tiles are taken in row_parts steps
+    int split_acc;              // dH running sum as two 16-bit planes (see GemmJob); split_h = 1
     int64_t plane_h, plane_w;   // fp32 elements per plane
     size_t off_acc, off_part_w, off_hc, off_g;      // workspace: dH planes, dW planes, gathered rows, gradient chunk
     size_t g_bytes;
@@ -307,18 +311,24 @@ struct Schedule {
     double plan_us;             // ... and of the Plan's order, same model
 };
 
-// Vocabulary tiles of the chunk that starts `rest` columns before the end of the vocabulary.
-static inline int64_t schedule_chunk_tiles(const Schedule& sc, int64_t D, int64_t rest, bool* in_tail) {
-    const int64_t row_bytes = (int64_t)sc.a * 256 * 2;               // of one vocabulary column of the chunk
+// The chunk that starts `rest` columns before the end of the vocabulary: b tiles wide, in steps over
+// `rows` row tiles each.
+struct ScheduleChunk { int64_t b; int rows; bool in_tail; };
+static inline ScheduleChunk schedule_chunk(const Schedule& sc, int64_t D, int64_t rest) {
     const int64_t rest_tiles = (rest + 255) / 256;
-    const int64_t in_ws = (int64_t)sc.g_bytes / (row_bytes * 256);
-    // the chunk's b x 256 columns lie behind dW's own b x 256 rows (256 B for the alignment)
-    const int64_t behind = sc.tail ? (rest * D * 4 - 256) / (256 * (row_bytes + D * 4)) : 0;
-    int64_t b = in_ws > behind ? in_ws : behind;
-    b = b < sc.b ? b : sc.b;
-    b = b < rest_tiles ? b : rest_tiles;
-    *in_tail = b > in_ws;
-    return b;
+    ScheduleChunk c = {0, 0, false};
+    for (int parts = 1; ; parts = sc.row_parts) {
+        const int rows = (sc.a + parts - 1) / parts;
+        const int64_t row_bytes = (int64_t)rows * 256 * 2;           // of one vocabulary column of the chunk
+        const int64_t in_ws = (int64_t)sc.g_bytes / (row_bytes * 256);
+        // the chunk's b x 256 columns lie behind dW's own b x 256 rows (256 B for the alignment)
+        const int64_t behind = sc.tail ? (rest * D * 4 - 256) / (256 * (row_bytes + D * 4)) : 0;
+        int64_t b = in_ws > behind ? in_ws : behind;
+        b = b < sc.b ? b : sc.b;
+        b = b < rest_tiles ? b : rest_tiles;
+        c = {b, rows, b > in_ws};
+        if (parts == sc.row_parts || b >= sc.b_min || b == rest_tiles) return c;
+    }
 }
 
 // Time model of the schedules, microseconds, from launches timed on MI355X with random data: a
@@ -390,12 +400,13 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     best.us = 0.90 * best.plan_us;
     const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
-    auto try_one = [&](int kind, int a, int bcap, int sh, int sw) {
+    auto try_one = [&](int kind, int a, int bcap, int sh, int sw, int row_parts, int b_min, int split_acc) {
         const ScheduleModel m{cus, D, gemm_tile_of_kind(kind)};
         Schedule sc = {};
         sc.kind = kind; sc.a = a; sc.split_h = sh; sc.split_w = sw;
         sc.b = bcap < VT ? bcap : VT;
         sc.tail = dw_free && a == TT;
+        sc.row_parts = row_parts; sc.b_min = b_min; sc.split_acc = split_acc;
         const bool one_chunk = a < TT;          // row blocks: the whole vocabulary in one chunk, no running sums
         if (one_chunk && bcap < VT) return;
         const int64_t rows = (int64_t)a * 256;
@@ -404,28 +415,32 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         sc.plane_w = cols_max * D;
         auto lay_out = [&](int planes) {
             sc.off_acc = p.off_dhacc;
-            sc.off_part_w = sc.off_acc + (size_t)round_up((int64_t)planes * sc.plane_h * 4, 256);
+            sc.off_part_w = sc.off_acc + (size_t)round_up((int64_t)planes * sc.plane_h * (split_acc ? 2 : 4), 256);
             sc.off_hc = sc.off_part_w + (size_t)round_up((int64_t)(sw - 1) * sc.plane_w * 4, 256);
             sc.off_g = sc.off_hc + (compact && a < TT ? (size_t)round_up(rows * D * 2, 256) : (size_t)0);
             const size_t used = sc.off_g - p.off_dhacc;
             sc.g_bytes = used < region ? region - used : 0;
             return used <= region;
         };
-        bool tail = false;
         // without running sums if the whole vocabulary is one chunk, else with a plane per part
-        bool ok = sh == 1 && lay_out(0) && schedule_chunk_tiles(sc, D, V, &tail) == VT;
-        if (!ok) ok = lay_out(sh) && (!one_chunk || schedule_chunk_tiles(sc, D, V, &tail) == VT);
+        bool ok = sh == 1 && !split_acc && row_parts == 1 && lay_out(0) && schedule_chunk(sc, D, V).b == VT;
+        if (!ok) ok = lay_out(sh) && (!one_chunk || schedule_chunk(sc, D, V).b == VT);
         if (!ok) return;
         double block_us[2] = {0.0, 0.0};        // first row block, later ones (they add to dW)
         for (int later = 0; later < (one_chunk ? 2 : 1); ++later) {
-            int64_t last_b = -1; double last_us = 0.0;
+            ScheduleChunk last = {-1, 0, false}; double last_us = 0.0;
             for (int64_t v = 0; v < V; ) {
-                const int64_t b = schedule_chunk_tiles(sc, D, V - v, &tail);
-                if (b < 1 || (int64_t)a * b * 131072 >= ((int64_t)1 << 32)) return;
-                if (b != last_b) { last_us = m.step(a, b, sh, sw, v > 0, later > 0 || !dw_free); last_b = b; }
+                const ScheduleChunk c = schedule_chunk(sc, D, V - v);
+                if (c.b < 1 || (int64_t)c.rows * c.b * 131072 >= ((int64_t)1 << 32)) return;
+                if (c.b != last.b || c.rows != last.rows) {
+                    last_us = 0.0;
+                    for (int r = 0; r < a; r += c.rows)
+                        last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free) + (split_acc ? 2.0 : 0.0);
+                    last = c;
+                }
                 block_us[later] += last_us;
                 if (block_us[later] >= best.us) return;
-                v += b * 256;
+                v += c.b * 256;
             }
         }
         const int nblk = (TT + a - 1) / a;
@@ -452,12 +467,17 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                         const int b = cap < VT ? cap : VT;
                         if (b == prev) break;
                         prev = b;
-                        try_one(kind, TT, b, sh, sw);
+                        try_one(kind, TT, b, sh, sw, 1, 0, 0);
+                        if (sh > 1 || sw > 1 || TT < 8) continue;
+                        for (int acc = 0; acc < (compact ? 1 : 2); ++acc)
+                            for (int parts = acc ? 1 : 2; parts <= 4; ++parts)
+                                for (int b_min : {8, 12, 16, 24, 1 << 30})
+                                    if (parts > 1 || b_min == 8) try_one(kind, TT, b, sh, sw, parts, b_min, acc);
                     }
                     // row blocks over the whole vocabulary
                     for (int nblk = 2; nblk <= 64 && nblk <= TT; ++nblk) {
                         const int a = (TT + nblk - 1) / nblk;
-                        if ((int64_t)a * VT * 131072 <= (int64_t)region) try_one(kind, a, VT, sh, sw);
+                        if ((int64_t)a * VT * 131072 <= (int64_t)region) try_one(kind, a, VT, sh, sw, 1, 0, 0);
                     }
                 }
             }

@@ -17,7 +17,7 @@ static int64_t pick(int64_t lo, int64_t hi) {
     state ^= state << 13; state ^= state >> 7; state ^= state << 17;
     return lo + (int64_t)(state % (uint64_t)(hi - lo + 1));
 }
-static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0;
+static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0;
 #define CHECK(cond) do { if (!(cond)) { ++failures; fprintf(stderr, "FAIL %d: %s | N=%lld D=%lld V=%lld B=%lld free=%d\n", __LINE__, #cond, \
     (long long)N, (long long)D, (long long)V, (long long)B, (int)dw_free); } } while (0)
 
@@ -35,37 +35,43 @@ static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
     CHECK(s.off_g + s.g_bytes <= ws_end);
     CHECK(((s.off_acc | s.off_part_w | s.off_hc | s.off_g) & 255) == 0);
     if (s.a < p.TT) { ++blocks; CHECK(!s.tail); if (B) CHECK(s.off_g - s.off_hc >= (size_t)(block * D * 2)); }
+    CHECK(s.row_parts >= 1 && (!s.split_acc || (s.split_h == 1 && !B)));
     for (int64_t r0 = 0; r0 < N; r0 += block) {
-        const int64_t rows = N - r0 < block ? N - r0 : block, row_tiles = (rows + 255) / 256;
+        const int64_t rows = N - r0 < block ? N - r0 : block;
         int steps = 0, planes = 0;
-        for (int64_t v0 = 0; v0 < V; ++steps) {
-            bool tail = false;
-            const int64_t t = schedule_chunk_tiles(s, D, V - v0, &tail);
-            CHECK(t >= 1);
-            if (t < 1) return true;
+        for (int64_t v0 = 0; v0 < V; ) {
+            const ScheduleChunk c = schedule_chunk(s, D, V - v0);
+            const int64_t t = c.b;
+            CHECK(t >= 1 && c.rows >= 1 && c.rows <= s.a);
+            if (t < 1 || c.rows < 1) return true;
             const int64_t cols = V - v0 < t * 256 ? V - v0 : t * 256;
-            const int64_t g = row_tiles * 256 * t * 512;
-            CHECK(g < ((int64_t)1 << 32));
-            if (tail) {
-                ++in_tails;
-                CHECK(dw_free && r0 == 0 && row_tiles == p.TT);
-                const int64_t at = (V * D * 4 - g) & ~(int64_t)255;
-                CHECK(at >= (v0 + cols) * D * 4 && at + g <= V * D * 4);
-            } else {
-                CHECK((size_t)g <= s.g_bytes);
+            const int64_t kh = (t + s.split_h - 1) / s.split_h, nh = (t + kh - 1) / kh;
+            for (int64_t s0 = 0; s0 < rows; s0 += (int64_t)c.rows * 256, ++steps) {
+                const int64_t srows = rows - s0 < (int64_t)c.rows * 256 ? rows - s0 : (int64_t)c.rows * 256, row_tiles = (srows + 255) / 256;
+                const int64_t g = row_tiles * 256 * t * 512;
+                CHECK(g < ((int64_t)1 << 32));
+                if (c.in_tail) {
+                    ++in_tails;
+                    CHECK(dw_free && s.a == p.TT);
+                    const int64_t at = (V * D * 4 - g) & ~(int64_t)255;
+                    CHECK(at >= (v0 + cols) * D * 4 && at + g <= V * D * 4);
+                } else {
+                    CHECK((size_t)g <= s.g_bytes);
+                }
+                const int64_t kw = (row_tiles + s.split_w - 1) / s.split_w, nw = (row_tiles + kw - 1) / kw;
+                CHECK(nh >= 1 && nh <= s.split_h && (nh - 1) * kh < t && nw >= 1 && nw <= s.split_w && (nw - 1) * kw < row_tiles);
+                // an operand's last part starts inside its valid extent
+                CHECK((nh - 1) * kh * 256 < cols && (nw - 1) * kw * 256 < srows);
+                if (nw > 1) { ++split_ws; CHECK(s.off_hc - s.off_part_w >= (size_t)((nw - 1) * s.plane_w * 4) && s.plane_w >= cols * D); }
+                if (c.rows < s.a) ++parts;
             }
-            const int64_t kh = (t + s.split_h - 1) / s.split_h, kw = (row_tiles + s.split_w - 1) / s.split_w;
-            const int64_t nh = (t + kh - 1) / kh, nw = (row_tiles + kw - 1) / kw;
-            CHECK(nh >= 1 && nh <= s.split_h && (nh - 1) * kh < t && nw >= 1 && nw <= s.split_w && (nw - 1) * kw < row_tiles);
-            // an operand's last part starts inside its valid extent
-            CHECK((nh - 1) * kh * 256 < cols && (nw - 1) * kw * 256 < rows);
             planes = planes > nh ? planes : (int)nh;
-            if (nw > 1) { ++split_ws; CHECK(s.off_hc - s.off_part_w >= (size_t)((nw - 1) * s.plane_w * 4) && s.plane_w >= cols * D); }
             v0 += cols;
         }
-        // one chunk and one part need no fp32 plane: the result is final at once
-        if (steps > 1 || s.split_h > 1) CHECK(s.off_part_w - s.off_acc >= (size_t)(planes * s.plane_h * 4) && s.plane_h >= rows * D);
+        // one step and one part need no running sum: the result is final at once
+        if (steps > 1 || s.split_h > 1) CHECK(s.off_part_w - s.off_acc >= (size_t)(planes * s.plane_h * (s.split_acc ? 2 : 4)) && s.plane_h >= rows * D);
         if (s.split_h > 1) ++split_hs;
+        if (s.split_acc) ++split_accs;
     }
     return true;
 }
@@ -85,8 +91,8 @@ int main(int argc, char** argv) {
         check(n, d, v, 0, false);
         check(pick(1, n), d, v, n, it % 5 != 0);
     }
-    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d\n", used, in_tails, split_hs, split_ws, blocks);
-    if (!in_tails || !split_hs || !split_ws) { fprintf(stderr, "a form was never taken\n"); return 1; }
+    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs);
+    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs) { fprintf(stderr, "a form was never taken\n"); return 1; }
     if (failures) { fprintf(stderr, "%d failures\n", failures); return 1; }
     printf("schedule_fuzz: %d iterations ok\n", iters);
     return 0;

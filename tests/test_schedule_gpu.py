@@ -61,3 +61,48 @@ def test_schedule_matches_oracle(shape):
         e = rel_fro(gH, o_dH), rel_fro(gW, o_dW)
         print(f"[schedule] {form}: relF(dH)={e[0]:.2e} relF(dW)={e[1]:.2e}", flush=True)
         assert e[0] <= GRAD_RTOL and e[1] <= GRAD_RTOL
+
+
+@pytest.mark.parametrize("form", ["rows", "compact"])
+@pytest.mark.parametrize("shape", [(8001, 896, 150001), (7500, 640, 90001)])
+def test_schedule_matches_forced_tiling(shape, form):
+    """Wide chunks in dW, then row parts, then the workspace (the order large shapes run in) against the
+    same backward with a forced 16 x 16 tiling.  Both round the same gradient tiles, so dW differs by
+    the order of fp32 sums over at most 8001 terms (sqrt(8001) 2^-24 = 5e-6; 2e-5 allowed) and dHidden
+    by the values whose rounding to bf16 flips (each within 2^-8, two roundings 2^-9 apart: 2e-3)."""
+    from paper_2601_02609_amd import binding as B
+    N, D, V = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    H = torch.randn(N, D, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, D, device="cuda", generator=g) * (2.5 / D ** 0.5)).bfloat16()
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    y[torch.randperm(N, device="cuda", generator=g)[:N // 7]] = IGN
+    n = N - N // 7
+    dl = torch.rand(N, device="cuda", generator=g) / n
+    got = []
+    for forced in (False, True):
+        try:
+            if forced:
+                B.set_backward_tiling(16, 16)
+            dW = torch.full((V, D), float("nan"), device="cuda")
+            if form == "rows":
+                ws = B.alloc_workspace(N, D, V)
+                _, lse = B.cce_forward(H, W, y, IGN, workspace=ws)
+                dH, dW = B.cce_backward(H, W, y, lse, dl, IGN, workspace=ws, d_weight=dW)
+            else:
+                B.set_row_skipping(2)
+                ws = B.alloc_compact_workspace(N, D, V, n)
+                _, lse = B.cce_forward_compact(H, W, y, n, IGN, workspace=ws)
+                dH, dW = B.cce_backward_compact(H, W, y, lse, dl, n, IGN, workspace=ws, d_weight=dW)
+            torch.cuda.synchronize()
+            assert B.read_status(ws) == 0
+            got.append((dH.double(), dW.double()))
+        finally:
+            B.set_row_skipping(0)
+            B.set_backward_tiling(0, 0)
+    (h0, w0), (h1, w1) = got
+    assert float((h0[y == IGN]).abs().max()) == 0.0
+    e = float((h0 - h1).norm() / h1.norm()), float((w0 - w1).norm() / w1.norm())
+    print(f"[schedule] {form} N={N} D={D} V={V}: relF(dH)={e[0]:.2e} relF(dW)={e[1]:.2e}", flush=True)
+    assert e[0] <= 2e-3 and e[1] <= 2e-5
