@@ -1391,8 +1391,6 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
     hipStream_t stream = (hipStream_t)stream_;
     char* ws = (char*)workspace;
-    uint16_t* dh_lo = (uint16_t*)(ws + p.off_dhacc);     // lower halves of the fp32 dH sums (see GemmJob)
-    uint16_t* G = (uint16_t*)(ws + p.off_g);
     // mean reduction: the common upstream gradient grad_scale / n_valid lives in the status block
     float* mean_scale = (float*)(ws + p.off_status + 64);
     if (!cc) drop_stale_hip_error();
@@ -1401,10 +1399,6 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                            labels, (int)N, (int)V_total, ignore_index, grad_scale, mean_scale);
     const int grad_lds = kGradTileLds;
 
-    const GemmTile gt = gemm_tile_of_kind(p.gemm_kind);
-    const int d_tiles = (int)((D + gt.bn - 1) / gt.bn);
-    const int per256 = 256 / gt.bm;                               // contraction row tiles per 256 rows
-
     Schedule sc;
     make_schedule(p, N, D, V, cc != nullptr, !accumulate_dW, &sc);
     if (sc.use)
@@ -1412,22 +1406,36 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                             label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
                             ws, stream, cc);
 
-    // The [row block x vocabulary chunk] steps in execution order.
-    struct Step { int64_t r0, rows, v0, cols; int row_tiles, v_tiles; bool first_chunk, last_chunk; };
+    // The [row block x vocabulary chunk] steps in execution order: the Plan's blocks from the first to
+    // the last, or those of a schedule that keeps sums or chunks in dHidden, from the last to the first.
+    struct Step { int64_t r0, rows, v0, cols; int row_tiles, v_tiles; bool first_chunk, last_chunk, first_block; const RowBlock* block; };
+    std::vector<RowBlock> blocks;
+    if (sc.n_blocks) blocks.assign(sc.blocks, sc.blocks + sc.n_blocks);
+    else
+        for (int r = 0; r < p.TT; r += (int)(p.Nb / 256))
+            blocks.push_back({r, (int)(p.Nb / 256), (int)(p.Vc / 256), p.gemm_kind, p.split_acc, false, false, p.off_dhacc, p.off_g});
     std::vector<Step> steps;
-    const int64_t nchunks = (V + p.Vc - 1) / p.Vc;
-    for (int64_t r0 = 0; r0 < N; r0 += p.Nb) {
-        const int64_t rows = (N - r0 < p.Nb) ? (N - r0) : p.Nb;
-        for (int64_t c = 0; c < nchunks; ++c) {
-            const int64_t v0 = c * p.Vc;
-            const int64_t cols = (V - v0 < p.Vc) ? (V - v0) : p.Vc;
-            steps.push_back({r0, rows, v0, cols, (int)((rows + 255) / 256), (int)((cols + 255) / 256), c == 0, c == nchunks - 1});
+    bool dh_scratch = false;
+    for (const RowBlock& k : blocks) {
+        const int64_t r0 = (int64_t)k.r0 * 256, block = (int64_t)k.a * 256, chunk = (int64_t)k.b * 256;
+        const int64_t rows = (N - r0 < block) ? (N - r0) : block;
+        dh_scratch = dh_scratch || k.acc_in_dh || k.g_in_dh;
+        for (int64_t v0 = 0; v0 < V; v0 += chunk) {
+            const int64_t cols = (V - v0 < chunk) ? (V - v0) : chunk;
+            steps.push_back({r0, rows, v0, cols, (int)((rows + 255) / 256), (int)((cols + 255) / 256), v0 == 0, v0 + cols >= V,
+                             &k == &blocks[0], &k});
         }
     }
     const int K = (int)steps.size();
 
     for (int k = 0; k < K; ++k) {
         const Step& st = steps[k];
+        const RowBlock& blk = *st.block;
+        const GemmTile gt = gemm_tile_of_kind(blk.kind);
+        const int d_tiles = (int)((D + gt.bn - 1) / gt.bn);
+        const int per256 = 256 / gt.bm;                           // contraction row tiles per 256 rows
+        uint16_t* G = (uint16_t*)((blk.g_in_dh ? (char*)dHidden : ws) + blk.off_g);
+        char* acc = (blk.acc_in_dh ? (char*)dHidden : ws) + blk.off_acc;     // fp32 dH sums, or their lower halves (see GemmJob)
         const int ldg = st.v_tiles * 256;                       // the chunk is stored densely padded
         const int n_rows_h = (int)N;
         // 1. gradient tiles of this [row block x chunk]
@@ -1454,8 +1462,8 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         dh.B = (const void*)((const uint16_t*)weight + (size_t)st.v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)st.cols;
         dh.k_total = ldg; dh.n_tiles = d_tiles; dh.n_work = st.row_tiles * per256 * d_tiles;
         dh.m_valid = (int)st.rows; dh.n_valid = (int)D;
-        dh.out_f32 = p.split_acc ? (float*)nullptr : (float*)(ws + p.off_dhacc); dh.ld_out = D; dh.beta_n = st.first_chunk ? 0 : 1;
-        dh.out_hi = (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)st.r0 * D); dh.out_lo = p.split_acc ? dh_lo : (uint16_t*)nullptr;
+        dh.out_f32 = blk.split_acc ? (float*)nullptr : (float*)acc; dh.ld_out = D; dh.beta_n = st.first_chunk ? 0 : 1;
+        dh.out_hi = (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)st.r0 * D); dh.out_lo = blk.split_acc ? (uint16_t*)acc : (uint16_t*)nullptr;
         dh.final = st.last_chunk ? 1 : 0;
         dh.row_map = cc ? cc->perm + st.r0 : (const int32_t*)nullptr;
         dh.zero_row = nullptr;
@@ -1468,7 +1476,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         dw.B = cc ? hidden : (const void*)((const uint16_t*)hidden + (size_t)st.r0 * D); dw.ldb = (int)D; dw.b_k_n = (int)st.rows;
         dw.k_total = st.row_tiles * 256; dw.n_tiles = d_tiles; dw.n_work = st.v_tiles * per256 * d_tiles;
         dw.m_valid = (int)st.cols; dw.n_valid = (int)D;
-        dw.out_f32 = dW + (size_t)st.v0 * D; dw.ld_out = D; dw.beta_n = (st.r0 > 0 || accumulate_dW) ? 1 : 0;
+        dw.out_f32 = dW + (size_t)st.v0 * D; dw.ld_out = D; dw.beta_n = (!st.first_block || accumulate_dW) ? 1 : 0;
         dw.out_hi = nullptr; dw.out_lo = nullptr; dw.final = 0;
         dw.row_map = cc ? cc->perm + st.r0 : (const int32_t*)nullptr;
         dw.zero_row = cc ? cc->zero_row : (const char*)nullptr;
@@ -1480,7 +1488,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
 
         {
             ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
-            const int mode = (p.split_acc ? 1 : 0) | (cc ? 2 : 0);
+            const int mode = (blk.split_acc ? 1 : 0) | (cc ? 2 : 0);
 #define CCE_LAUNCH_GEMM(CFG, MODE, LDS) \
     hipLaunchKernelGGL((grad_gemm_kernel<CFG, MODE>), dim3(work), dim3(kThreads), (LDS) + ((MODE) >= 2 ? kRowTableBytes : 0), stream, first, second)
             if (gt.kind == 0) {
@@ -1493,6 +1501,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
 #undef CCE_LAUNCH_GEMM
         }
     }
+    if (cc && dh_scratch) cc->zero_skipped(stream, dHidden);      // scratch was kept in the zeros of the skipped rows
     if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
     return CCE_OK;
 }
@@ -1526,7 +1535,7 @@ static bool choose_compact_plan(int64_t N, int64_t D, int64_t V, int64_t max_val
     Schedule ps, cs;
     make_schedule(plain, N, D, V, false, true, &ps);
     make_schedule(comp, M, D, V, true, true, &cs);
-    if (ps.use || cs.use) {
+    if (ps.use || cs.use || ps.n_blocks || cs.n_blocks) {
         // a schedule replaces the backward of one of the plans: both sides by the schedules' model
         const ForwardCost fwd{device_cu_count(), D};
         plain_us = ps.us + fwd.us(plain);

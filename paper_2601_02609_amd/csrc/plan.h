@@ -294,12 +294,25 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
 //     shrink with the rest of dW, and a step over all rows of a narrow chunk has few dW tiles with a
 //     long reduction: below a width the chunk is taken in row_parts steps over part of the rows
 //     each, whose chunks are that much wider.  The last ones use the workspace.
+//   * The rows of dHidden in front of the current row block are final only once their own block has
+//     run.  With the blocks taken from the last to the first, a block may keep its gradient chunk or
+//     its dH sums there -- also under row skipping, where compact row r goes to a row >= r.
 //   * A contraction with few output tiles (few rows, or a small vocabulary) leaves most of the
 //     GPU idle for the length of its reduction; its K range is split into parts that write planes
 //     of their own, summed by a small launch.
 // ------------------------------------------------------------------------------------------
+// One row block of an order with dHidden as scratch: a row tiles, chunks of b vocabulary tiles.
+struct RowBlock {
+    int r0, a, b, kind, split_acc;      // r0: first row tile
+    bool acc_in_dh, g_in_dh;            // dH sums / gradient chunk in the front rows of dHidden
+    size_t off_acc, off_g;              // from the workspace or from dHidden
+};
+constexpr int kMaxRowBlocks = 48;
+
 struct Schedule {
-    bool use;                   // false: the Plan's row blocks and chunks
+    bool use;                   // false: the Plan's row blocks and chunks, or blocks[]
+    int n_blocks;               // > 0: blocks[], in execution order
+    RowBlock blocks[kMaxRowBlocks];
     int kind;                   // contraction tile
     int a;                      // row tiles per block (all of them: one row block)
     int b;                      // vocabulary tiles per chunk, at most
@@ -367,6 +380,63 @@ struct ForwardCost {
     double us(const Plan& p) const {
         const int64_t rounds = ((int64_t)p.TT * p.S + cus - 1) / cus;
         return (double)(rounds * ((p.VT + p.S - 1) / p.S)) * ((double)(D / 64) * 1.55 + 4.0);
+    }
+};
+
+// Row blocks from the last to the first with dHidden's front rows as scratch: the partition of the
+// row tiles with the least modelled time (f(R) = min over a of [block of rows R - a .. R] + f(R - a)).
+struct RowBlockPlanner {
+    const ScheduleModel m[2];
+    int TT, VT; int64_t D; size_t region, off0; bool compact, dw_free;
+    struct State { double us; RowBlock block; bool known; };
+    State states[1 + 256];
+
+    double block_us(const RowBlock& k, bool beta) const {
+        const int64_t nch = (VT + k.b - 1) / k.b;
+        const ScheduleModel& mm = m[k.kind];
+        double t = (double)(nch - 1) * mm.step(k.a, k.b, 1, 1, true, beta) + mm.step(k.a, VT - (nch - 1) * k.b, 1, 1, nch > 1, beta);
+        if (k.split_acc) t += (double)nch * (compact ? 9.0 : 2.0);
+        return t;
+    }
+    double best(int R) {
+        if (R == 0) return 0.0;
+        State& st = states[R];
+        if (st.known) return st.us;
+        st.known = true;
+        st.us = 1e300;
+        const int sizes[] = {R, (R + 1) / 2, (R + 2) / 3, 4, 6, 8, 10, 12, 14, 16, 20, 24, 32};
+        for (int i = 0; i < 13; ++i) {
+            const int a = sizes[i];
+            if (a > R || a > 64 || (compact && a > kCompactMaxRowTiles)) continue;
+            const int64_t front = (int64_t)(R - a) * 256 * D * 2, ws = (int64_t)region, tile = (int64_t)a * 131072;
+            for (int split = 0; split < 2; ++split) {
+                const int64_t acc = round_up((int64_t)a * 256 * D * (split ? 2 : 4), 256);
+                // where the chunk gets widest: sums in front of the block, chunk in front of it, both in the workspace
+                RowBlock k = {R - a, a, 0, 0, split, false, false, off0, off0};
+                int64_t cap = 0;
+                if (acc <= front && ws / tile > cap) { cap = ws / tile; k.acc_in_dh = true; k.g_in_dh = false; k.off_acc = 0; k.off_g = off0; }
+                if (acc <= ws && front / tile > cap) { cap = front / tile; k.acc_in_dh = false; k.g_in_dh = true; k.off_acc = off0; k.off_g = 0; }
+                if (acc < ws && (ws - acc) / tile > cap) { cap = (ws - acc) / tile; k.acc_in_dh = k.g_in_dh = false; k.off_acc = off0; k.off_g = off0 + (size_t)acc; }
+                if (cap > VT) cap = VT;
+                if (cap > 30000 / a) cap = 30000 / a;                    // 32-bit chunk offsets
+                if (cap < 1) continue;
+                const int64_t nch = (VT + cap - 1) / cap;
+                const int64_t rounds = a * cap / m[0].cus;
+                const int64_t bs[3] = {cap, (VT + nch - 1) / nch, rounds ? rounds * m[0].cus / a : cap};
+                for (int kind = 0; kind < 2; ++kind) {
+                    if (kind == 0 && m[0].d_tiles() * 256 * 7 > D * 8) continue;
+                    k.kind = kind;
+                    for (int j = 0; j < 3; ++j) {
+                        if (j > 0 && bs[j] == bs[j - 1]) continue;
+                        k.b = (int)bs[j];
+                        if (k.b < 1 || k.b > cap) continue;
+                        const double t = block_us(k, R < TT || !dw_free) + best(R - a);
+                        if (t < st.us) { st.us = t; st.block = k; }
+                    }
+                }
+            }
+        }
+        return st.us;
     }
 };
 
@@ -486,7 +556,21 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
             }
         }
     }
-    if (!best.use) best.us = best.plan_us;
+    if (!forced && TT > 1 && TT <= 256) {
+        RowBlockPlanner rp = {{{cus, D, gemm_tile_of_kind(0)}, {cus, D, gemm_tile_of_kind(1)}}, TT, VT, D, region, p.off_dhacc, compact, dw_free, {}};
+        const double us = rp.best(TT);
+        // 5 %: steps like the Plan's own, which the model ranks more closely than chunks of other widths
+        if (us < best.us || (!best.use && us < 0.95 * best.plan_us)) {
+            int n = 0, R = TT;
+            bool front = false;
+            for (; R > 0 && n < kMaxRowBlocks; R -= best.blocks[n++].a) {
+                best.blocks[n] = rp.states[R].block;
+                front = front || best.blocks[n].acc_in_dh || best.blocks[n].g_in_dh;
+            }
+            if (R == 0 && front) { best.n_blocks = n; best.use = false; best.us = us; }
+        }
+    }
+    if (!best.use && !best.n_blocks) best.us = best.plan_us;
     *out = best;
     cache[cache_next] = {N, D, V, p.total, cus, forced, compact, dw_free, true, best};
     cache_next = (cache_next + 1) % kCached;

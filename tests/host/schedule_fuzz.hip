@@ -17,7 +17,7 @@ static int64_t pick(int64_t lo, int64_t hi) {
     state ^= state << 13; state ^= state >> 7; state ^= state << 17;
     return lo + (int64_t)(state % (uint64_t)(hi - lo + 1));
 }
-static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0;
+static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0, fronts = 0;
 #define CHECK(cond) do { if (!(cond)) { ++failures; fprintf(stderr, "FAIL %d: %s | N=%lld D=%lld V=%lld B=%lld free=%d\n", __LINE__, #cond, \
     (long long)N, (long long)D, (long long)V, (long long)B, (int)dw_free); } } while (0)
 
@@ -25,6 +25,26 @@ static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
     Plan p; Schedule s;
     if (!make_plan(N, D, V, &p, B)) return false;
     make_schedule(p, N, D, V, B != 0, dw_free, &s);
+    if (s.n_blocks) {
+        ++fronts;
+        CHECK(!s.use && s.us < s.plan_us);
+        const size_t end = B ? p.off_count : p.total;
+        int R = p.TT;
+        for (int i = 0; i < s.n_blocks; ++i) {
+            const RowBlock& k = s.blocks[i];
+            CHECK(k.a >= 1 && k.r0 == R - k.a && k.b >= 1 && k.b <= p.VT && (!B || k.a <= kCompactMaxRowTiles));
+            R -= k.a;
+            // dHidden's rows in front of the block are free; sums and chunk never share an area
+            const size_t front = (size_t)k.r0 * 256 * (size_t)D * 2;
+            const size_t acc = (size_t)k.a * 256 * (size_t)D * (k.split_acc ? 2 : 4), g = (size_t)k.a * (size_t)k.b * 131072;
+            CHECK(g < ((size_t)1 << 32) && !(k.acc_in_dh && k.g_in_dh));
+            CHECK(((k.off_acc | k.off_g) & 255) == 0);
+            if (k.acc_in_dh) CHECK(k.off_acc + acc <= front); else CHECK(k.off_acc >= p.off_dhacc && k.off_acc + acc <= end);
+            if (k.g_in_dh) CHECK(k.off_g + g <= front); else CHECK(k.off_g >= p.off_dhacc && k.off_g + g <= end);
+            if (!k.acc_in_dh && !k.g_in_dh) CHECK(k.off_g >= k.off_acc + acc);
+        }
+        CHECK(R == 0);
+    }
     if (!s.use) return false;
     ++used;
     const int64_t block = (int64_t)s.a * 256;
@@ -91,8 +111,8 @@ int main(int argc, char** argv) {
         check(n, d, v, 0, false);
         check(pick(1, n), d, v, n, it % 5 != 0);
     }
-    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs);
-    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs) { fprintf(stderr, "a form was never taken\n"); return 1; }
+    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d, orders with dHidden %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs, fronts);
+    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs || !fronts) { fprintf(stderr, "a form was never taken\n"); return 1; }
     if (failures) { fprintf(stderr, "%d failures\n", failures); return 1; }
     printf("schedule_fuzz: %d iterations ok\n", iters);
     return 0;
