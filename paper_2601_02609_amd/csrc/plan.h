@@ -354,6 +354,7 @@ static inline ScheduleChunk schedule_chunk(const Schedule& sc, int64_t D, int64_
 // 896 x 151936 in steps of 16 x 16 tiles 7.47 ms modelled, 7.33 measured; of 32 x 32 6.3 and 6.45.)
 struct ScheduleModel {
     int cus; int64_t D; GemmTile tile;
+    bool mapped = false;        // the dW job reads hidden rows through the row map: 0.85 us a slice against 0.76
     double slice() const { return tile.kind == 0 ? 1.58 : 0.79; }
     double item(int64_t slices, bool beta) const { return (double)slices * slice() + (tile.kind == 0 ? 13.0 : 9.0) + (beta ? 2.0 : 0.0); }
     int64_t d_tiles() const { return (D + tile.bn - 1) / tile.bn; }
@@ -362,8 +363,8 @@ struct ScheduleModel {
         const int64_t dt = d_tiles();
         const int64_t kh = (b + split_h - 1) / split_h, kw = (a + split_w - 1) / split_w;       // K tiles per part
         const int64_t n_dh = a * dt * ((b + kh - 1) / kh), n_dw = b * dt * ((a + kw - 1) / kw);
-        const double c_dh = item(kh * 4, dh_beta), c_dw = item(kw * 4, dw_beta);
-        const double mk = kh >= kw ? two_class_makespan(cus, n_dh, c_dh, n_dw, c_dw) : two_class_makespan(cus, n_dw, c_dw, n_dh, c_dh);
+        const double c_dh = item(kh * 4, dh_beta), c_dw = item(kw * 4, dw_beta) + (mapped ? (double)(kw * 4) * 0.11 * slice() : 0.0);
+        const double mk = c_dh >= c_dw ? two_class_makespan(cus, n_dh, c_dh, n_dw, c_dw) : two_class_makespan(cus, n_dw, c_dw, n_dh, c_dh);
         const double g = (double)(a * b) * 131072.0, w = (double)b * 512.0 * (double)D;
         const double tiles_us = (double)((a * b + cus - 1) / cus) * ((double)(D / 64) * 1.55 + 7.0);
         const double tiles_mem = (g + w) / 4.5e6;
@@ -459,7 +460,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     const int TT = p.TT, VT = p.VT;
     const size_t region = (compact ? p.off_count : p.total) - p.off_dhacc;
     {   // the Plan's order under the same model
-        const ScheduleModel m{cus, D, gemm_tile_of_kind(p.gemm_kind)};
+        const ScheduleModel m{cus, D, gemm_tile_of_kind(p.gemm_kind), compact};
         const int64_t a = p.Nb / 256, b = p.Vc / 256;
         for (int64_t r = 0; r < TT; r += a) {
             const int64_t aa = TT - r < a ? TT - r : a;
@@ -557,7 +558,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         }
     }
     if (!forced && TT > 1 && TT <= 256) {
-        RowBlockPlanner rp = {{{cus, D, gemm_tile_of_kind(0)}, {cus, D, gemm_tile_of_kind(1)}}, TT, VT, D, region, p.off_dhacc, compact, dw_free, {}};
+        RowBlockPlanner rp = {{{cus, D, gemm_tile_of_kind(0), compact}, {cus, D, gemm_tile_of_kind(1), compact}}, TT, VT, D, region, p.off_dhacc, compact, dw_free, {}};
         const double us = rp.best(TT);
         // 5 %: steps like the Plan's own, which the model ranks more closely than chunks of other widths
         if (us < best.us || (!best.use && us < 0.95 * best.plan_us)) {
