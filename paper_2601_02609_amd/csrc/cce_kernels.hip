@@ -74,10 +74,16 @@ template <bool SUMZ, bool FP8>
 __global__ __launch_bounds__(kThreads) void lse_partial_kernel(
         const void* __restrict__ H, const void* __restrict__ W,
         int N, int D, int V, int TT, int VT, int S, float2* __restrict__ partials,
-        float* __restrict__ partial_sumz, const Fp8Scales fp8, const int32_t* __restrict__ perm) {
+        float* __restrict__ partial_sumz, const Fp8Scales fp8, const int32_t* __restrict__ perm,
+        int32_t* __restrict__ status) {
     typedef TileBig Cfg;
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
+
+    // The status word starts at zero (status: null where the label scan has written it).  The first
+    // launch behind this one that sets bits in it is finalize_kernel: no clearing launch is needed
+    // (it took 1.4 us and a launch boundary of about 2 at the smallest shapes).
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;
 
     // Work index -> (token tile, vocabulary split).  The 32 workgroups that share an XCD (and
     // its 4 MB L2) take a panel of 4 token tiles x all splits: per K slice they touch 4 H
@@ -302,15 +308,17 @@ __global__ __launch_bounds__(256) void shard_merge_kernel(
     loss[tok] = t;
 }
 
-__global__ void clear_status_kernel(int32_t* status) { if (threadIdx.x == 0) status[0] = 0; }
-
 // Number of rows that take part in the loss (label in range and not ignore_index), counted by
 // one workgroup.  Integer counting: the result does not depend on the order.
 __device__ __forceinline__ int count_valid_rows(const int32_t* labels, int N, int V, int32_t ignore_index, int* scratch) {
+    constexpr int U = 8;            // loads in flight per thread: one workgroup, bound by their latency
     int c = 0;
-    for (int i = threadIdx.x; i < N; i += blockDim.x) {
-        const int32_t y = labels[i];
-        c += (y != ignore_index && y >= 0 && y < V) ? 1 : 0;
+    for (int i = threadIdx.x; i < N; i += U * blockDim.x) {
+        int32_t y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = i + u * (int)blockDim.x < N ? labels[i + u * (int)blockDim.x] : ignore_index;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c += (y[u] != ignore_index && y[u] >= 0 && y[u] < V) ? 1 : 0;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
@@ -342,8 +350,15 @@ __global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict
     __shared__ int scratch[16];
     __shared__ float fsum[16];
     const int n = kept ? kept[0] : count_valid_rows(labels, N, V, ignore_index, scratch);
+    constexpr int U = 8;            // loads in flight per thread
     float a = 0.f;
-    for (int i = threadIdx.x; i < N; i += blockDim.x) a += loss[i];     // ignored rows hold 0
+    for (int i = threadIdx.x; i < N; i += U * blockDim.x) {              // ignored rows hold 0
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = i + u * (int)blockDim.x < N ? loss[i + u * (int)blockDim.x] : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) a += v[u];
+    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
     if ((threadIdx.x & 63) == 0) fsum[threadIdx.x >> 6] = a;
@@ -808,33 +823,35 @@ __global__ __launch_bounds__(256) void dw_planes_kernel(float* __restrict__ dw, 
 // contribution from a dropped row, not stale memory).  zero_row (optional): zero_row_len bf16 zeros
 // are written there.  The status word is WRITTEN here (bad label / bound bits or 0): the scan is the
 // first launch of a row-skipping call and needs no clearing launch in front of it.
-// Each thread owns a contiguous run of rows; counts are scanned inside a wavefront with shuffles,
-// the sixteen wavefront totals through LDS: one barrier.
+// Each wavefront owns a contiguous run of rows and takes 64 at a time, coalesced, positions from the
+// ballot; the sixteen wavefront totals go through LDS: one barrier.  Eight label loads are in flight per
+// lane.  One workgroup against the latency of its loads is all that bounds it: with a run of rows per
+// THREAD (uncoalesced, one load after another) it took 28.7 us for 16384 rows, now 9.8.
 __global__ __launch_bounds__(1024) void row_scan_kernel(
         const int32_t* __restrict__ labels, int N, int V, int32_t ignore_index, int max_rows, int rows_pad,
         int32_t* __restrict__ perm, int32_t* __restrict__ count_out, int32_t* __restrict__ status,
         float* __restrict__ loss, float* __restrict__ lse, uint16_t* __restrict__ zero_row, int zero_row_len) {
     __shared__ int wave_total[16];
     __shared__ int wave_bad[16];
+    constexpr int U = 8;                              // 64-row groups a wavefront has in flight
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (N + 1023) / 1024;
-    const int i0 = tid * per < N ? tid * per : N, i1 = i0 + per < N ? i0 + per : N;
-    int c = 0, bad = 0;
-    for (int i = i0; i < i1; ++i) {
-        const int32_t y = labels[i];
-        const bool in_range = y >= 0 && y < V;
-        c += (y != ignore_index && in_range) ? 1 : 0;
-        bad |= (y != ignore_index && !in_range) ? 1 : 0;
-    }
-    int incl = c;                                     // inclusive scan over the lanes of the wavefront
+    const int per = ((N + 1023) / 1024) * 64;         // rows per wavefront
+    const int i0 = wave * per < N ? wave * per : N, i1 = i0 + per < N ? i0 + per : N;
+    auto is_valid = [&](int32_t y) { return y != ignore_index && y >= 0 && y < V; };
+    int c = 0;
+    bool bad = false;
+    for (int i = i0; i < i1; i += 64 * U) {
+        int32_t y[U];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o);
-        if (lane >= o) incl += v;
+        for (int u = 0; u < U; ++u) y[u] = i + 64 * u + lane < i1 ? labels[i + 64 * u + lane] : ignore_index;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c += __popcll(__ballot(is_valid(y[u])));  // the same in every lane
+            bad = bad || (y[u] != ignore_index && !is_valid(y[u]));
+        }
     }
-    const bool wave_has_bad = __ballot(bad != 0) != 0;
-    if (lane == 63) wave_total[wave] = incl;
-    if (lane == 0) wave_bad[wave] = wave_has_bad ? 1 : 0;
+    const bool wave_has_bad = __ballot(bad) != 0;
+    if (lane == 0) { wave_total[wave] = c; wave_bad[wave] = wave_has_bad ? 1 : 0; }
     __syncthreads();
     int before = 0, total = 0, any_bad = 0;
 #pragma unroll
@@ -844,17 +861,24 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
         total += t;
         any_bad |= wave_bad[w];
     }
-    int pos = before + incl - c;                      // valid rows in front of this thread's run
-    for (int i = i0; i < i1; ++i) {
-        const int32_t y = labels[i];
-        bool zero = true;
-        if (y != ignore_index && y >= 0 && y < V) {
-            if (pos < max_rows) { perm[pos] = i; zero = false; }
-            ++pos;
-        }
-        if (zero && loss) {
-            loss[i] = 0.f;
-            lse[i] = 0.f;
+    int pos = before;                                 // valid rows in front of the group
+    for (int i = i0; i < i1; i += 64 * U) {
+        int32_t y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = i + 64 * u + lane < i1 ? labels[i + 64 * u + lane] : ignore_index;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = i + 64 * u + lane;
+            const bool valid = is_valid(y[u]);
+            const unsigned long long set = __ballot(valid);
+            const int mine = pos + (int)__popcll(set & ((1ull << lane) - 1ull));
+            const bool keep = valid && mine < max_rows;
+            if (keep) perm[mine] = row;
+            if (!keep && loss && row < i1) {
+                loss[row] = 0.f;
+                lse[row] = 0.f;
+            }
+            pos += (int)__popcll(set);
         }
     }
     if (zero_row)
@@ -1118,21 +1142,19 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
 
     const int32_t* fwd_perm = cc ? cc->perm : (const int32_t*)nullptr;
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
-    if (!cc) {
-        drop_stale_hip_error();
-        hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, stream, status);
-    }
+    if (!cc) drop_stale_hip_error();
+    int32_t* clear = cc ? (int32_t*)nullptr : status;
     {
         ProfSpan span(CCE_KERNEL_LSE_PARTIAL, stream);
         if (fp8_in)
             hipLaunchKernelGGL((lse_partial_kernel<false, true>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm);
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
         else if (smooth)
             hipLaunchKernelGGL((lse_partial_kernel<true, false>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm);
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
         else
             hipLaunchKernelGGL((lse_partial_kernel<false, false>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm);
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
     }
     hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream,
                        (const uint16_t*)hidden, (const uint16_t*)weight, labels, partials, (const float*)sumz,
