@@ -135,6 +135,9 @@ struct BackwardModel {
     }
 };
 
+struct Schedule;
+static double schedule_us(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, bool* use);
+
 // budget_rows != 0 selects row skipping: the plan is made for N compact rows while the workspace
 // budget (1 % of the materialised logits) is that of the budget_rows original rows, and the
 // workspace also holds the compact-row bookkeeping (row map and per-row scalars).
@@ -257,27 +260,54 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
         const int64_t rounds = ((int64_t)p->TT * p->S + cus - 1) / cus;
         p->model_us = (p->split_acc ? cost_split : cost_f32) + (double)(rounds * ((p->VT + p->S - 1) / p->S)) * fm.t_tile();
     }
-    p->gemm_kind = best_kind;
-    p->Nb = (int64_t)best_a * 256;
-    p->Vc = (int64_t)best_b * 256;
+    auto lay_out = [&](Plan* q, int a, int b, int64_t spare) {
+        q->gemm_kind = best_kind;
+        q->Nb = (int64_t)a * 256;
+        q->Vc = (int64_t)b * 256;
+        q->off_status = 0;
+        q->off_partials = 256;
+        q->off_sumz = q->off_partials + md_bytes;
+        q->off_dhacc = q->off_partials + partial_bytes;
+        q->off_g = q->off_dhacc + (size_t)round_up(q->Nb * D * (q->split_acc ? 2 : 4), 256) + (size_t)spare;
+        q->total = q->off_g + (size_t)(q->Nb * q->Vc * 2);
+        q->rows_pad = Np;
+        q->off_count = q->off_perm = q->off_labels_c = q->off_fa_c = q->off_fb_c = q->off_zero_row = 0;
+        if (compact) {
+            q->off_count = round_up((int64_t)q->total, 256);
+            q->off_perm = q->off_count + 256;
+            q->off_labels_c = q->off_perm + scalar_bytes;
+            q->off_fa_c = q->off_labels_c + scalar_bytes;
+            q->off_fb_c = q->off_fa_c + scalar_bytes;
+            q->off_zero_row = q->off_fb_c + scalar_bytes;
+            q->total = q->off_zero_row + zero_row_bytes;
+        }
+    };
+    lay_out(p, best_a, best_b, 0);
     // the gradient chunk is addressed with 32-bit byte offsets (only a forced tiling can get here)
     if (p->Nb * p->Vc * 2 >= ((int64_t)1 << 32)) return false;
-    p->off_status = 0;
-    p->off_partials = 256;
-    p->off_sumz = p->off_partials + md_bytes;
-    p->off_dhacc = p->off_partials + partial_bytes;
-    p->off_g = p->off_dhacc + (size_t)round_up(p->Nb * D * (p->split_acc ? 2 : 4), 256);
-    p->total = p->off_g + (size_t)(p->Nb * p->Vc * 2);
-    p->rows_pad = Np;
-    p->off_count = p->off_perm = p->off_labels_c = p->off_fa_c = p->off_fb_c = p->off_zero_row = 0;
-    if (compact) {
-        p->off_count = round_up((int64_t)p->total, 256);
-        p->off_perm = p->off_count + 256;
-        p->off_labels_c = p->off_perm + scalar_bytes;
-        p->off_fa_c = p->off_labels_c + scalar_bytes;
-        p->off_fb_c = p->off_fa_c + scalar_bytes;
-        p->off_zero_row = p->off_fb_c + scalar_bytes;
-        p->total = p->off_zero_row + zero_row_bytes;
+    // All rows in one block and budget to spare: the plan itself has no use for more, but a schedule
+    // that cuts dH's serial reduction into parts wants room for their planes (up to 16 parts) beside a
+    // wide chunk.  That room is laid out, the chunk after it, if a schedule on it is rated 10 % faster,
+    // both for calls that overwrite dW and for calls that add to it.
+    const bool forced = knobs.row_tiles || knobs.vocab_tiles || knobs.gemm_cols || knobs.split_acc;
+    if (!forced && best_a == p->TT && p->TT <= 16) {
+        const int64_t slack = (int64_t)((double)budget - bytes_needed(best_a, best_b));
+        const int64_t tile = (int64_t)best_a * 131072, planes = 15 * (int64_t)round_up(N * D * 4, 256);
+        const int64_t room = best_b < p->VT ? slack / 2 : slack;
+        const int64_t spare = (planes < room ? planes : room) / 256 * 256;
+        if (spare >= planes / 15) {
+            int64_t wide = best_b + (slack - spare) / tile;
+            wide = wide < p->VT ? wide : p->VT;
+            Plan q = *p;
+            lay_out(&q, best_a, (int)wide, spare);
+            bool better = true, use = false;
+            for (int dw_free = 0; dw_free < 2 && better; ++dw_free) {
+                const double now = schedule_us(*p, N, D, V, compact, dw_free != 0, &use);
+                const double then = schedule_us(q, N, D, V, compact, dw_free != 0, &use);
+                better = use && then < 0.9 * now;
+            }
+            if (better) *p = q;
+        }
     }
     cache[cache_next] = {N, D, V, budget_rows, cus, knobs.row_tiles, knobs.vocab_tiles, knobs.gemm_cols, knobs.split_acc, *p, true};
     cache_next = (cache_next + 1) % kCached;
@@ -575,6 +605,14 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     *out = best;
     cache[cache_next] = {N, D, V, p.total, cus, forced, compact, dw_free, true, best};
     cache_next = (cache_next + 1) % kCached;
+}
+
+// Modelled time of a call's backward on this plan, and whether a schedule takes it over.
+static double schedule_us(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, bool* use) {
+    Schedule s;
+    make_schedule(p, N, D, V, compact, dw_free, &s);
+    *use = s.use;
+    return s.us;
 }
 
 }  // namespace cce
