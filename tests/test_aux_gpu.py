@@ -198,3 +198,11 @@ def test_adamw_argument_errors(B):
                             1e-3, 1.0, 0.999, 1e-8, 0.0, 1, None, None) == B.CCE_ERR_INVALID      # beta1 = 1
     assert L.cce_adamw_step(None, None, t.data_ptr(), t.data_ptr(), t.data_ptr(), 8,
                             1e-3, 0.9, 0.999, 1e-8, 0.0, 1, None, None) == B.CCE_ERR_INVALID
+
+
+@pytest.mark.parametrize("shape", [(517, 64), (70001, 64), (1, 128), (4111, 128), (2101, 192), (9000, 256), (9, 256)])
+def test_rmsnorm_narrow_rows(B, shape):
+    """D <= 256: several rows per wavefront (8, 16 or 32 lanes each), idle lanes at D = 192, a last
+    workgroup and a last trip that only some of the row groups take."""
+    test_rmsnorm_matches_oracle(B, shape)
+    test_rmsnorm_residual_form_matches_oracle(B, shape)
