@@ -33,7 +33,7 @@ namespace cce {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kGRowBytes = 256 * 2 + 16;     // LDS staging row of a G tile (256 bf16 + pad)
+template <class Cfg> constexpr int kGRowBytes = Cfg::BM * 2 + 16;     // LDS staging row of a G tile (bf16 + pad)
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
@@ -70,13 +70,12 @@ __device__ __forceinline__ int scale_byte(const void* scales, int groups, int ro
     return s[(((size_t)kb * groups + (row >> 7)) * 32 + (row & 31)) * 4 + ((row >> 5) & 3)];
 }
 
-template <bool SUMZ, bool FP8>
+template <bool SUMZ, bool FP8, class Cfg = TileBig>
 __global__ __launch_bounds__(kThreads) void lse_partial_kernel(
         const void* __restrict__ H, const void* __restrict__ W,
         int N, int D, int V, int TT, int VT, int S, float2* __restrict__ partials,
         float* __restrict__ partial_sumz, const Fp8Scales fp8, const int32_t* __restrict__ perm,
         int32_t* __restrict__ status) {
-    typedef TileBig Cfg;
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
 
@@ -117,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void lse_partial_kernel(
 
         OperandTile<true, Cfg::BM> Aop;
         Aop.init(W, ld, vt * Cfg::BM, V, ld);
-        if (FP8) {
+        if constexpr (FP8) {
             ScaleGroup SA;
             SA.init(fp8.wscale, fp8.wgroups, (vt * Cfg::BM + wm * (Cfg::TM * 32)) >> 7);
             gemm_mainloop_fp8<Cfg>(acc, Aop, Bop, SA, SB, (b_row0 >> 6) & 1, D, smem);
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict
 // contiguous) with full 512-byte rows.
 // Grid: one workgroup per tile of the [row block x chunk]; tile index -> (ti, vi).
 // ------------------------------------------------------------------------------------------
-template <bool FP8>
+template <bool FP8, class Cfg = TileBig>
 __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
         const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
         const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
@@ -392,7 +391,6 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
         int row0, int n_row_tiles, int v0, int n_v_tiles,
         uint16_t* __restrict__ G, int ldg, int v_off, int V_total, const Fp8Scales fp8,
         const int32_t* __restrict__ perm) {
-    typedef TileBig Cfg;
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
     const int l = threadIdx.x & 63;
@@ -437,7 +435,7 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
     const int ld = FP8 ? D / 2 : D;               // row length in 2-byte units
     Aop.init(W, ld, vt0, V, ld);
     Bop.init(H, ld, tok0, N, ld, perm);           // perm (row skipping): token t is row perm[t] of H
-    if (FP8) {
+    if constexpr (FP8) {
         ScaleGroup SA, SB;
         const int b_row0 = tok0 + wave_n<Cfg>() * (Cfg::TN * 32);
         SA.init(fp8.wscale, fp8.wgroups, (vt0 + wm * (Cfg::TM * 32)) >> 7);
@@ -466,7 +464,7 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
     const bool row_live = threadIdx.x < Cfg::BN && tok0 + (int)threadIdx.x < N &&
                           raw_row_y != ignore_index && raw_row_y >= 0 && raw_row_y < V_total;
 
-    CCE_LDS unsigned char* live_flags = (CCE_LDS unsigned char*)(smem + 256 * kGRowBytes);
+    CCE_LDS unsigned char* live_flags = (CCE_LDS unsigned char*)(smem + Cfg::BN * kGRowBytes<Cfg>);
     if (threadIdx.x < Cfg::BN) live_flags[threadIdx.x] = row_live ? 1 : 0;
 
     // Epilogue: softmax gradient, bf16, staged in LDS as [token][vocab] and stored with
@@ -474,7 +472,8 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
     // bn): the global stores of one phase drain while the next phase is computed, and the
     // barriers wait for LDS traffic only.
     const bool ragged = vt0 + Cfg::BM > V;                  // only the last vocabulary tile needs column masking
-    const int chunk = threadIdx.x & 31;
+    constexpr int kChunks = Cfg::BM / 8, kRowsPerPass = kThreads / kChunks;       // 16-byte chunks of a row
+    const int chunk = threadIdx.x % kChunks;
 #pragma unroll
     for (int bn = 0; bn < Cfg::TN; ++bn) {
         const int col = acc_col<Cfg>(bn);
@@ -506,20 +505,20 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
                 // (token rows with bit 3 set keep the two 8-byte halves of every 16-byte chunk swapped:
                 // with a row pitch that is a multiple of 16 bytes, rows c and c + 8 of the 16 lanes
                 // an 8-byte write serves per cycle would otherwise hit the same LDS banks)
-                *(CCE_LDS u32x2*)(smem + col * kGRowBytes + ((vrow * 2) ^ (col & 8))) = pk.u;
+                *(CCE_LDS u32x2*)(smem + col * kGRowBytes<Cfg> + ((vrow * 2) ^ (col & 8))) = pk.u;
             }
         }
         barrier_lds_only();
         // rows of this phase: tokens 64 * wn + 32 * bn + (0..31) for the WN wavefront columns;
-        // thread -> (row index t / 32 + 16 j, 16-byte chunk t % 32)
+        // thread -> (row index t / kChunks + kRowsPerPass j, 16-byte chunk t % kChunks)
 #pragma unroll
-        for (int j = 0; j < (Cfg::WN * 32) / 16; ++j) {
-            const int idx = (threadIdx.x >> 5) + 16 * j;
+        for (int j = 0; j < (Cfg::WN * 32) / kRowsPerPass; ++j) {
+            const int idx = (int)threadIdx.x / kChunks + kRowsPerPass * j;
             const int row = (idx >> 5) * (Cfg::TN * 32) + bn * 32 + (idx & 31);
             const bool live = live_flags[row] != 0;
             u32x4 v = {0u, 0u, 0u, 0u};
             if (live) {
-                v = *(const CCE_LDS u32x4*)(smem + row * kGRowBytes + chunk * 16);
+                v = *(const CCE_LDS u32x4*)(smem + row * kGRowBytes<Cfg> + chunk * 16);
                 if (row & 8) v = u32x4{v.z, v.w, v.x, v.y};           // undo the half swap of the staging writes
             }
             *(u32x4*)(G + (size_t)(ti * Cfg::BN + row) * ldg + (size_t)vi * Cfg::BM + chunk * 8) = v;
@@ -1008,7 +1007,11 @@ static bool allow_big_lds(K kernel, int bytes) {
     return hip_ok(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
 }
 
-constexpr int kGradTileLds = (256 * kGRowBytes + 256 > TileBig::kLdsBytes) ? 256 * kGRowBytes + 256 : TileBig::kLdsBytes;
+template <class Cfg> constexpr int grad_tile_lds() {
+    const int staging = Cfg::BN * kGRowBytes<Cfg> + Cfg::BN;
+    return staging > Cfg::kLdsBytes ? staging : Cfg::kLdsBytes;
+}
+constexpr int kGradTileLds = grad_tile_lds<TileBig>();
 
 // The MFMA kernels use more dynamic LDS than the default limit: raise it once per device
 // (not per call, so that the compute calls consist of kernel launches only).
@@ -1023,6 +1026,9 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(lse_partial_kernel<false, false>, TileBig::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<true, false>, TileBig::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, true>, TileBig::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_kernel<false, false, TileSmall>, TileSmall::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_kernel<true, false, TileSmall>, TileSmall::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_tile_kernel<false, TileSmall>, grad_tile_lds<TileSmall>())) return false;
     if (!allow_big_lds(grad_tile_kernel<false>, kGradTileLds)) return false;
     if (!allow_big_lds(grad_tile_kernel<true>, kGradTileLds)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 0>, kGemmLdsBig)) return false;
@@ -1037,6 +1043,22 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 3>, kGemmLdsNarrow + kRowTableBytes)) return false;
     done[dev] = true;
     return true;
+}
+
+// The bf16 gradient tiles of n_row_tiles x n_v_tiles tiles of 256 x 256.
+static void launch_grad_tiles(const void* H, const void* W, const int32_t* labels, const float* lse, const float* dloss,
+                              const float* mean_scale, int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
+                              int row0, int n_row_tiles, int v0, int n_v_tiles, uint16_t* G, int ldg, int v_off, int V_total,
+                              const int32_t* perm, hipStream_t stream) {
+    const Fp8Scales none = {nullptr, nullptr, 0, 0};
+    if (use_small_tiles(n_row_tiles, n_v_tiles))
+        hipLaunchKernelGGL((grad_tile_kernel<false, TileSmall>), dim3(4 * n_row_tiles * n_v_tiles), dim3(kThreads), grad_tile_lds<TileSmall>(),
+                           stream, H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
+                           2 * n_row_tiles, v0, 2 * n_v_tiles, G, ldg, v_off, V_total, none, perm);
+    else
+        hipLaunchKernelGGL(grad_tile_kernel<false>, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), kGradTileLds, stream,
+                           H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
+                           n_row_tiles, v0, n_v_tiles, G, ldg, v_off, V_total, none, perm);
 }
 
 // A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
@@ -1144,11 +1166,18 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
     if (!cc) drop_stale_hip_error();
     int32_t* clear = cc ? (int32_t*)nullptr : status;
+    const int S = p.small_tiles && !fp8_in ? p.fwd_vt() : p.S;         // vocabulary splits of this forward
     {
         ProfSpan span(CCE_KERNEL_LSE_PARTIAL, stream);
         if (fp8_in)
             hipLaunchKernelGGL((lse_partial_kernel<false, true>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
                                hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
+        else if (p.small_tiles && smooth)
+            hipLaunchKernelGGL((lse_partial_kernel<true, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
+                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear);
+        else if (p.small_tiles)
+            hipLaunchKernelGGL((lse_partial_kernel<false, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
+                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear);
         else if (smooth)
             hipLaunchKernelGGL((lse_partial_kernel<true, false>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
                                hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
@@ -1158,7 +1187,7 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
     }
     hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream,
                        (const uint16_t*)hidden, (const uint16_t*)weight, labels, partials, (const float*)sumz,
-                       (int)N, (int)D, (int)V, p.S, ignore_index, label_smoothing, z_loss, loss, lse, status,
+                       (int)N, (int)D, (int)V, S, ignore_index, label_smoothing, z_loss, loss, lse, status,
                        (int)v_off, (float4*)stats, fp8, fwd_perm);
     if (mean_loss && !stats)
         hipLaunchKernelGGL(mean_loss_kernel, dim3(1), dim3(1024), 0, stream,
@@ -1307,10 +1336,9 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
                                            ignore_index, label_smoothing, z_loss, (int)row0, row_tiles, (int)v0, v_tiles, G, ldg,
                                            (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
                     else
-                        hipLaunchKernelGGL(grad_tile_kernel<false>, grid, dim3(kThreads), kGradTileLds, stream,
-                                           (const void*)h_step, weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
-                                           (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
-                                           v_tiles, G, ldg, (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
+                        launch_grad_tiles((const void*)h_step, weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
+                                          (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
+                                          v_tiles, G, ldg, (int)v_off, (int)V_total, (const int32_t*)nullptr, stream);
                 }
                 // parts of the two reductions, in whole tiles of 256
                 const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
@@ -1470,11 +1498,9 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                                    (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, ldg, (int)v_off, (int)V_total, fp8,
                                    cc ? cc->perm : (const int32_t*)nullptr);
             else
-                hipLaunchKernelGGL(grad_tile_kernel<false>, dim3(st.row_tiles * st.v_tiles), dim3(kThreads), grad_lds, stream,
-                                   hidden, weight, labels, lse, dloss, (const float*)mean_scale,
-                                   n_rows_h, (int)D, (int)V, ignore_index, label_smoothing, z_loss,
-                                   (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, ldg, (int)v_off, (int)V_total, fp8,
-                                   cc ? cc->perm : (const int32_t*)nullptr);
+                launch_grad_tiles(hidden, weight, labels, lse, dloss, (const float*)mean_scale, n_rows_h, (int)D, (int)V, ignore_index,
+                                  label_smoothing, z_loss, (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, ldg, (int)v_off,
+                                  (int)V_total, cc ? cc->perm : (const int32_t*)nullptr, stream);
         }
         // 2. both contractions in one launch
         // dH block += G * W_chunk      (M = tokens, K = chunk columns, N = D)

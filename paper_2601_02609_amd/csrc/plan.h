@@ -33,12 +33,22 @@ static int device_cu_count() {
 }
 
 
+// Logit tiles of 128 x 128 instead of 256 x 256: where a launch has so few of the large ones that the
+// four times as many small ones still fit one round of compute units (256 on this part).
+static bool use_small_tiles(int64_t row_tiles, int64_t vocab_tiles) {
+    return row_tiles * vocab_tiles * 4 <= device_cu_count();
+}
+
 struct Plan {
     int TT, VT, S;              // forward: token tiles, vocabulary tiles, vocabulary splits
     int64_t Nb, Vc;             // backward: rows per row block, vocabulary columns per chunk (multiples of 256)
     int gemm_kind;              // backward: output tile of the contractions, 0 = 256 x 256, 1 = 256 x 128
     int split_acc;              // backward: dH running sum as two 16-bit planes (see GemmJob)
     double model_us;            // modelled time of forward + backward with this plan (ranking only)
+    bool small_tiles;           // forward: 128 x 128 tiles, one per workgroup (fwd_vt() splits; FP8 keeps 256 x 256)
+    int64_t rows, cols;         // N, V
+    int fwd_tt() const { return (int)((rows + 127) / 128); }
+    int fwd_vt() const { return (int)((cols + 127) / 128); }
     size_t off_status, off_partials, off_sumz, off_dhacc, off_g, total;
     // row skipping only (budget_rows != 0): compact-row bookkeeping
     int64_t rows_pad;           // compact rows rounded up to 256
@@ -175,7 +185,9 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
         }
         p->S = best_s;
     }
-    const int S = p->S;
+    p->rows = N; p->cols = V;
+    p->small_tiles = use_small_tiles(p->TT, p->VT);
+    const int S = p->small_tiles && p->fwd_vt() > p->S ? p->fwd_vt() : p->S;       // pairs per token that the workspace holds
 
     // per (token, split): (max, sum-exp) pair + the logit sum that label smoothing needs
     const size_t md_bytes = (size_t)round_up((int64_t)N * S * 8, 256);
