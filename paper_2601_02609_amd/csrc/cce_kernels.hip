@@ -545,8 +545,9 @@ constexpr int gemm_lds_bytes(int main_loop, int bm, int bn) {
 }
 constexpr int kGemmLdsBig = gemm_lds_bytes(TileBig::kLdsBytes, TileBig::BM, TileBig::BN);
 constexpr int kGemmLdsNarrow = gemm_lds_bytes(TileNarrow::kLdsBytes, TileNarrow::BM, TileNarrow::BN);
+constexpr int kGemmLdsSmall = gemm_lds_bytes(TileSmall::kLdsBytes, TileSmall::BM, TileSmall::BN);
 // Row skipping: the LDS table of one row block's row map (kRowTableBytes, plan.h) sits behind these.
-static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRowTableBytes <= 160 * 1024, "row table must fit the LDS");
+static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRowTableBytes <= 160 * 1024 && kGemmLdsSmall + kRowTableBytes <= 160 * 1024, "row table must fit the LDS");
 
 // Output of a job, one of three forms:
 //   fp32 (the dW job): out_f32 (+)= C when `beta`.
@@ -1033,6 +1034,11 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_tile_kernel<true>, kGradTileLds)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 0>, kGemmLdsBig)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 0>, kGemmLdsNarrow)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileSmall, 0>, kGemmLdsSmall)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileSmall, 1>, kGemmLdsSmall)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileSmall, 2>, kGemmLdsSmall + kRowTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileSmall, 3>, kGemmLdsSmall + kRowTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileSmall, 4>, kGemmLdsSmall)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 4>, kGemmLdsBig)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 4>, kGemmLdsNarrow)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 1>, kGemmLdsBig)) return false;
@@ -1068,6 +1074,8 @@ static void launch_contractions(int kind, const GemmJob& first, const GemmJob& s
     ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
     if (kind == 0)
         hipLaunchKernelGGL((grad_gemm_kernel<TileBig, MODE>), dim3(work), dim3(kThreads), kGemmLdsBig, stream, first, second);
+    else if (kind == 2)
+        hipLaunchKernelGGL((grad_gemm_kernel<TileSmall, MODE>), dim3(work), dim3(kThreads), kGemmLdsSmall, stream, first, second);
     else
         hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, MODE>), dim3(work), dim3(kThreads), kGemmLdsNarrow, stream, first, second);
 }
@@ -1291,8 +1299,8 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
                         const void* logit_hidden, const void* logit_weight, const Fp8Scales* fp8,
                         char* ws, hipStream_t stream, const CompactCtx* cc) {
     const Fp8Scales scales = fp8 ? *fp8 : Fp8Scales{nullptr, nullptr, 0, 0};
-    const GemmTile gt = gemm_tile_of_kind(sc.kind);
-    const int d_tiles = (int)((D + gt.bn - 1) / gt.bn);
+    const int d_tiles = (int)((D + gemm_tile_of_kind(sc.kind).bn - 1) / gemm_tile_of_kind(sc.kind).bn);
+    const Knobs knobs = Knobs::read();
     const int64_t block = (int64_t)sc.a * 256;
     float* planes = (float*)(ws + sc.off_acc);
     float* part_w = (float*)(ws + sc.off_part_w);
@@ -1342,12 +1350,16 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
                 }
                 // parts of the two reductions, in whole tiles of 256
                 const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
+                const int n_split_w = (row_tiles + kw - 1) / kw;
+                const int64_t items = ((int64_t)row_tiles * n_split_h + (int64_t)v_tiles * n_split_w) * d_tiles;
+                const int kind = contraction_kind(sc.kind, items, knobs);
+                const int per256 = 256 / gemm_tile_of_kind(kind).bm;
                 GemmJob dh;
                 dh.a_kmajor = 1;
                 dh.A = G; dh.lda = ldg; dh.a_free_n = row_tiles * 256; dh.a_k_n = ldg;
                 dh.B = (const void*)((const uint16_t*)weight + (size_t)v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)cols;
                 dh.k_total = ldg; dh.n_tiles = d_tiles; dh.split_k = kh * 256; dh.n_split = n_split_h;
-                dh.n_work = row_tiles * (256 / gt.bm) * d_tiles * dh.n_split;
+                dh.n_work = row_tiles * per256 * d_tiles * dh.n_split;
                 dh.m_valid = (int)srows; dh.n_valid = (int)D; dh.ld_out = D;
                 dh.out_f32 = sc.split_acc ? (float*)nullptr : planes + (size_t)s0 * D;
                 dh.part = planes + sc.plane_h + (size_t)s0 * D; dh.part_stride = sc.plane_h;
@@ -1363,8 +1375,8 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
                 dw.a_kmajor = 0;
                 dw.A = G; dw.lda = ldg; dw.a_free_n = ldg; dw.a_k_n = row_tiles * 256;
                 dw.B = (const void*)h_step; dw.ldb = (int)D; dw.b_k_n = (int)srows;
-                dw.k_total = row_tiles * 256; dw.n_tiles = d_tiles; dw.split_k = kw * 256; dw.n_split = (row_tiles + kw - 1) / kw;
-                dw.n_work = v_tiles * (256 / gt.bm) * d_tiles * dw.n_split;
+                dw.k_total = row_tiles * 256; dw.n_tiles = d_tiles; dw.split_k = kw * 256; dw.n_split = n_split_w;
+                dw.n_work = v_tiles * per256 * d_tiles * dw.n_split;
                 dw.m_valid = (int)cols; dw.n_valid = (int)D;
                 dw.out_f32 = dW + (size_t)v0 * D; dw.part = part_w; dw.part_stride = sc.plane_w; dw.ld_out = D;
                 dw.beta_n = (row0 > 0 || accumulate_dW) ? 1 : 0;
@@ -1377,14 +1389,14 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
                     // this dH job writes dHidden, which still holds the rows the dW job reads
                     GemmJob none = dh;
                     none.n_work = 0;
-                    launch_contractions<0>(sc.kind, dw, none, stream);
-                    launch_contractions<4>(sc.kind, dh, none, stream);
+                    launch_contractions<0>(kind, dw, none, stream);
+                    launch_contractions<4>(kind, dh, none, stream);
                 } else if (dh.final && cc) {
-                    launch_contractions<4>(sc.kind, first, second, stream);
+                    launch_contractions<4>(kind, first, second, stream);
                 } else if (sc.split_acc) {
-                    launch_contractions<1>(sc.kind, first, second, stream);
+                    launch_contractions<1>(kind, first, second, stream);
                 } else {
-                    launch_contractions<0>(sc.kind, first, second, stream);
+                    launch_contractions<0>(kind, first, second, stream);
                 }
                 if (dw.n_split > 1) {
                     const int64_t groups = cols * (D / 4);
@@ -1477,12 +1489,13 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         }
     }
     const int K = (int)steps.size();
+    const Knobs knobs = Knobs::read();
 
     for (int k = 0; k < K; ++k) {
         const Step& st = steps[k];
         const RowBlock& blk = *st.block;
-        const GemmTile gt = gemm_tile_of_kind(blk.kind);
-        const int d_tiles = (int)((D + gt.bn - 1) / gt.bn);
+        const int d_tiles = (int)((D + gemm_tile_of_kind(blk.kind).bn - 1) / gemm_tile_of_kind(blk.kind).bn);
+        const GemmTile gt = gemm_tile_of_kind(contraction_kind(blk.kind, (int64_t)(st.row_tiles + st.v_tiles) * d_tiles, knobs));
         const int per256 = 256 / gt.bm;                           // contraction row tiles per 256 rows
         uint16_t* G = (uint16_t*)((blk.g_in_dh ? (char*)dHidden : ws) + blk.off_g);
         char* acc = (blk.acc_in_dh ? (char*)dHidden : ws) + blk.off_acc;     // fp32 dH sums, or their lower halves (see GemmJob)
@@ -1542,6 +1555,9 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
             if (gt.kind == 0) {
                 if (mode == 0) CCE_LAUNCH_GEMM(TileBig, 0, kGemmLdsBig); else if (mode == 1) CCE_LAUNCH_GEMM(TileBig, 1, kGemmLdsBig);
                 else if (mode == 2) CCE_LAUNCH_GEMM(TileBig, 2, kGemmLdsBig); else CCE_LAUNCH_GEMM(TileBig, 3, kGemmLdsBig);
+            } else if (gt.kind == 2) {
+                if (mode == 0) CCE_LAUNCH_GEMM(TileSmall, 0, kGemmLdsSmall); else if (mode == 1) CCE_LAUNCH_GEMM(TileSmall, 1, kGemmLdsSmall);
+                else if (mode == 2) CCE_LAUNCH_GEMM(TileSmall, 2, kGemmLdsSmall); else CCE_LAUNCH_GEMM(TileSmall, 3, kGemmLdsSmall);
             } else {
                 if (mode == 0) CCE_LAUNCH_GEMM(TileNarrow, 0, kGemmLdsNarrow); else if (mode == 1) CCE_LAUNCH_GEMM(TileNarrow, 1, kGemmLdsNarrow);
                 else if (mode == 2) CCE_LAUNCH_GEMM(TileNarrow, 2, kGemmLdsNarrow); else CCE_LAUNCH_GEMM(TileNarrow, 3, kGemmLdsNarrow);

@@ -70,7 +70,8 @@ static constexpr size_t kBudgetFloor = 48000000;
 struct GemmTile { int kind, bm, bn; double us_per_slice; };
 static GemmTile gemm_tile_of_kind(int kind) {
     if (kind == 0) return {0, TileBig::BM, TileBig::BN, 2.0};
-    return {1, TileNarrow::BM, TileNarrow::BN, 1.1};
+    if (kind == 1) return {1, TileNarrow::BM, TileNarrow::BN, 1.1};
+    return {2, TileSmall::BM, TileSmall::BN, 0.6};              // chosen per launch, see contraction_kind
 }
 
 // Process-wide tuning / testing knobs (0 = automatic).  Atomics: a knob may be set from any host
@@ -118,6 +119,14 @@ static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2,
         }
     }
     return best > tB ? best : tB;
+}
+
+// Tile of one contraction launch: 128 x 128 where the planned 256 x 128 tiles would leave half of the
+// compute units without work (an item then costs about half as much, and all of them still start at
+// once).  A forced tile stays.  Backward of 256 x 64 x 1000: 23 -> 16 us, 322 x 1856 x 1015: 36 -> 28,
+// 2269 x 896 x 2131: 58 -> 50, 2500 x 64 x 1300: 33 -> 25.
+static int contraction_kind(int kind, int64_t items, const Knobs& knobs) {
+    return kind == 1 && knobs.gemm_cols == 0 && items * 2 <= device_cu_count() ? 2 : kind;
 }
 
 // Rough time model of the backward pipeline, in microseconds, used only to rank tilings.
