@@ -72,7 +72,7 @@ struct TileCfg {
 };
 typedef TileCfg<2, 4, 4, 2, 2> TileBig;      // 256 x 256, wave tile 128 x 64, 2 x 64 KB stages
 typedef TileCfg<2, 2, 4, 2, 3, 2> TileNarrow; // 256 x 128, wave tile 128 x 64, 2 K groups, 3 x 48 KB stages
-// 128 x 128, wave tile 64 x 32, 4 x 32 KB stages: for products of so few 256 x 256 tiles that most
+// 128 x 128, wave tile 64 x 32, 4 x 32 KB stages: for products of so few larger tiles that many
 // compute units would have none (three slices ahead: a slice lasts a third of a 256 x 256 one and no
 // other workgroup of the unit covers its latency).  322 x 1856 x 1015, 8 large tiles: forward and
 // backward 102.8 -> 58.2 us; 256 x 64 x 1000: 38.9 -> 30.2.

@@ -33,10 +33,12 @@ static int device_cu_count() {
 }
 
 
-// Logit tiles of 128 x 128 instead of 256 x 256: where a launch has so few of the large ones that the
-// four times as many small ones still fit one round of compute units (256 on this part).
+// Logit tiles of 128 x 128 instead of 256 x 256: where a launch has so few of the large ones that four
+// times as many small ones are at most two rounds of the compute units.  One round: 322 x 1856 x 1015
+// (8 large tiles) 102.8 -> 58.2 us a step; two: forward / backward of 500 x 2048 x 10000 (80) 47 / 101 ->
+// 42 / 93 us, of 3399 x 1088 x 1802 (112) 33 / 76 -> 31 / 72.  Beyond, the large tiles move half the bytes.
 static bool use_small_tiles(int64_t row_tiles, int64_t vocab_tiles) {
-    return row_tiles * vocab_tiles * 4 <= device_cu_count();
+    return row_tiles * vocab_tiles * 2 <= device_cu_count();
 }
 
 struct Plan {

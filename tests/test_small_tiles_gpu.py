@@ -1,4 +1,4 @@
-"""GPU parity where the logit tiles are 128 x 128 (at most 64 tiles of 256 x 256): tile edges, one row,
+"""GPU parity where the logit tiles are 128 x 128 (at most 128 tiles of 256 x 256): tile edges, one row,
 one column, idle last tiles, both sides of the line, with and without label smoothing and row skipping.
 Oracle and tolerances as in test_parity_gpu.py."""
 import numpy as np
@@ -15,7 +15,8 @@ IGN = -100
 
 @pytest.mark.parametrize("eps", [0.0, 0.1])
 @pytest.mark.parametrize("shape", [(1, 64, 1), (127, 128, 129), (128, 192, 128), (129, 256, 257), (513, 64, 255), (300, 1856, 1015),
-                                   (2048, 128, 2048), (2049, 128, 2048), (40, 320, 16384), (40, 320, 16385)])
+                                   (2048, 128, 2048), (2049, 128, 2048), (40, 320, 16384), (40, 320, 16385),
+                                   (40, 320, 32768), (40, 320, 32769)])
 def test_small_tiles_match_oracle(shape, eps):
     from paper_2601_02609_amd import binding as B
     N, D, V = shape
