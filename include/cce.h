@@ -139,8 +139,8 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
  *                                      at ignored rows are never used (may be NaN)
  *   dHidden  out bf16 [N, D]  device   fp32 accumulation, rounded to nearest even (used as
  *                                      scratch for partial sums while the call runs)
- *   dHidden, dW                        also serve as scratch until the call's work is done
- *   dW       out fp32 [V, D]  device   accumulate_dW == 0: overwritten;
+ *   dW       out fp32 [V, D]  device   accumulate_dW == 0: overwritten (rows not yet written
+ *                                      may hold gradient tiles while the call runs);
  *                                      accumulate_dW != 0: the gradient is added to it
  * The logit gradient tile is rounded to bf16 (nearest even) before the two
  * contractions, which accumulate in fp32.
@@ -198,8 +198,9 @@ int cce_backward_ex(const void* hidden, const void* weight, const int32_t* label
 int cce_set_backward_tiling(int row_tiles, int vocab_tiles);
 
 /* The tiling (in 256-wide tiles) the backward uses for this shape: the forced one, else the
- * automatic choice.  Host only; the two outputs are host ints.  Shapes whose contractions have few output tiles
- * may run in another order (chunks of several sizes, reductions cut into parts) while nothing is forced. */
+ * automatic choice.  Host only; the two outputs are host ints.  While nothing is forced, a shape
+ * may run in another order where that is rated faster (chunks of several sizes, row blocks from the
+ * last to the first, reductions cut into parts). */
 int cce_get_backward_tiling(int64_t N, int64_t D, int64_t V, int* row_tiles, int* vocab_tiles);
 
 /* Tuning / testing aid like cce_set_backward_tiling: force the output tile of the two gradient
