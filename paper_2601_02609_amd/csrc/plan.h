@@ -95,15 +95,15 @@ struct Knobs {
 };
 
 // Completion time of n1 jobs of length c1 followed by n2 jobs of length c2 <= c1, handed in that
-// order to `cus` units, each taking the next job when it becomes free.  The searches start where
-// no unit would ever be idle, which is where the answer usually is: a plan asks this thousands of
-// times, and counting up from the first job made the first call of a new shape wait up to 3 ms.
+// order to `cus` units, each taking the next job when it becomes free.  A plan asks this thousands of
+// times, so the searches start where no unit would be idle, which is a lower bound of every answer
+// behind the last long job; short jobs that all fit beside it are answered first.
 static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
     const int64_t full = n1 / cus, rem = n1 % cus;
     const double tA = (double)full * c1;                     // units without a long job in the last round
     const double tB = (double)(rem ? full + 1 : full) * c1;
-    if (n2 == 0) return tB;
     const int64_t nA = cus - rem, nB = rem;
+    if (n2 == 0 || nA * (int64_t)((tB - tA) / c2) >= n2) return tB;
     const double t0 = ((double)n2 * c2 + (double)nA * tA + (double)nB * tB) / (double)cus;
     auto first_k = [&](double from) { const int64_t k = (int64_t)((t0 - from) / c2) - 1; return k > 1 ? k : (int64_t)1; };
     // smallest t with nA * floor((t - tA) / c2) + nB * floor((t - tB) / c2) >= n2
@@ -120,7 +120,7 @@ static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2,
             if (nA * (int64_t)((t - tA) / c2) + nB * k >= n2) { best = t; break; }
         }
     }
-    return best > tB ? best : tB;
+    return best;
 }
 
 // Tile of one contraction launch: 128 x 128 where the planned 256 x 128 tiles would leave half of the

@@ -1,11 +1,15 @@
 // Host-only check of the backward's schedules (csrc/plan.h), built and run by tests/test_schedule_host.py
 // with AddressSanitizer and UndefinedBehaviorSanitizer on the host side: over seeded shapes every step
 // of a schedule covers the vocabulary once, keeps its gradient chunk inside the workspace or behind the
-// rows of dW that are written by then, and gives its K parts whole, non-empty ranges.
+// rows of dW that are written by then, and gives its K parts whole, non-empty ranges.  The time model's
+// makespan is compared with a hand-out of the jobs.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
+#include <functional>
+#include <queue>
+#include <vector>
 
 namespace cce { thread_local int g_last_hip_error = 0; }
 #include "../../paper_2601_02609_amd/csrc/plan.h"
@@ -96,8 +100,34 @@ static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
     return true;
 }
 
+// two_class_makespan against the hand-out itself: every job goes to the unit that is free first.
+// (Whole lengths: sums and quotients are exact.)
+static void check_makespan() {
+    for (int it = 0; it < 4000; ++it) {
+        const int cus = it % 3 ? 256 : (int)pick(1, 300);
+        const int64_t n1 = it % 2 ? pick(1, 40) : pick(1, 1200), n2 = it % 4 < 2 ? pick(0, 20) : pick(0, 1200);
+        const int64_t c2 = pick(1, 60), c1 = c2 + (it % 5 ? pick(0, 60) : pick(0, 3000));
+        std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
+        for (int u = 0; u < cus; ++u) free_at.push(0);
+        int64_t end = 0;
+        for (int64_t i = 0; i < n1 + n2; ++i) {
+            const int64_t t = free_at.top() + (i < n1 ? c1 : c2);
+            free_at.pop();
+            free_at.push(t);
+            end = end > t ? end : t;
+        }
+        const double got = two_class_makespan(cus, n1, (double)c1, n2, (double)c2);
+        if (got != (double)end) {
+            ++failures;
+            fprintf(stderr, "FAIL makespan of %lld x %lld, %lld x %lld on %d: %.0f instead of %lld\n", (long long)n1, (long long)c1,
+                    (long long)n2, (long long)c2, cus, got, (long long)end);
+        }
+    }
+}
+
 int main(int argc, char** argv) {
     const int iters = argc > 1 ? atoi(argv[1]) : 2000;
+    check_makespan();
     // shapes the schedules exist for: few rows against a full vocabulary; a small vocabulary
     bool dw_free = true; int64_t N = 509, D = 896, V = 151936, B = 0;
     CHECK(check(N, D, V, B, dw_free));
