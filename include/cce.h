@@ -81,9 +81,11 @@ const char* cce_strerror(int code);
 /* hipError_t (as int) of the last failed HIP call made by this thread, 0 if none. */
 int cce_last_hip_error(void);
 
-/* Bytes of device workspace needed by cce_forward / cce_backward for this shape.
- * Pure host function (queries the current device's CU count once); returns 0 for
- * invalid shapes. */
+/* Bytes of device workspace to give cce_forward / cce_backward for this shape: at most 1 % of the
+ * materialised logits or 48 MB.  A workspace of this size also serves every smaller N at the same D
+ * and V.  (A call accepts less where its tiling needs less; the backward of a few rows may then run in
+ * a slower order, whose fp32 sums are taken in another sequence.)  Pure host function (queries the
+ * current device's CU count once); returns 0 for invalid shapes. */
 size_t cce_workspace_bytes(int64_t N, int64_t D, int64_t V);
 
 /* Size N*V*4 of the logit tensor that is NOT materialised (the paper's memory

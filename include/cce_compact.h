@@ -48,9 +48,9 @@ int cce_get_compact_tiling(int64_t N, int64_t D, int64_t V, int64_t max_valid_ro
 /* Tuning / testing aid: 1 = never skip, 2 = skip whenever max_valid_rows < N, 0 = automatic. */
 int cce_set_row_skipping(int mode);
 
-/* Workspace bytes of the two calls below; within 1 % of the materialised logits of the N rows
- * (never below the 48 MB floor of cce_workspace_bytes).  0 for invalid
- * shapes.  Host only. */
+/* Workspace bytes to give the two calls below; at most 1 % of the materialised logits of the N rows
+ * or 48 MB.  A workspace of this size also serves every smaller N and every other max_valid_rows at
+ * the same D and V.  0 for invalid shapes.  Host only. */
 size_t cce_compact_workspace_bytes(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows);
 
 /* cce_forward over the valid rows only.  loss and lse are written for all N rows (0 for rows

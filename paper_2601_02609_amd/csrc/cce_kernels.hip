@@ -1105,7 +1105,7 @@ size_t cce_workspace_bytes(int64_t N, int64_t D, int64_t V) {
     Plan p;
     if (N <= 0 || D <= 0 || V <= 0 || D % 64 != 0) return 0;
     if (!make_plan(N, D, V, &p)) return 0;
-    return p.total;
+    return workspace_to_ask_for(p, N, D, V, false);
 }
 
 size_t cce_materialised_logit_bytes(int64_t N, int64_t V) {
@@ -1122,7 +1122,8 @@ struct CompactCtx {
     Plan plan;                  // made for the compact rows
     const int32_t* perm;        // device: original row of each compact row, -1 for padding
     const char* zero_row = nullptr;   // device: D bf16 zeros (backward only)
-    // backward only: the caller's rows and labels, for the zero rows of dHidden
+    // backward only: the order, and the caller's rows and labels for the zero rows of dHidden
+    Schedule order;
     int64_t all_rows = 0;
     const int32_t* all_labels = nullptr;
     const int32_t* count = nullptr;
@@ -1444,11 +1445,14 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
     if (((uintptr_t)dHidden | (uintptr_t)dW) & 15) return CCE_ERR_INVALID;
     if (!variant_ok(label_smoothing, z_loss)) return CCE_ERR_INVALID;
     if (v_off < 0 || V_total > (1 << 30) || v_off + V > V_total) return CCE_ERR_INVALID;
+    Schedule sc;
     if (cc) {
         p = cc->plan;
+        sc = cc->order;
     } else {
         int rc = check_common(hidden, weight, labels, N, D, V, workspace, workspace_bytes, &p);
         if (rc != CCE_OK) return rc;
+        plan_backward(&p, N, D, V, false, !accumulate_dW, workspace_bytes, &sc);
     }
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
     hipStream_t stream = (hipStream_t)stream_;
@@ -1461,8 +1465,6 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                            labels, (int)N, (int)V_total, ignore_index, grad_scale, mean_scale);
     const int grad_lds = kGradTileLds;
 
-    Schedule sc;
-    make_schedule(p, N, D, V, cc != nullptr, !accumulate_dW, &sc);
     if (sc.use)
         return run_schedule(sc, hidden, weight, labels, lse, dloss, mean_scale, N, D, V, v_off, V_total, ignore_index,
                             label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
@@ -1597,11 +1599,9 @@ static bool choose_compact_plan(int64_t N, int64_t D, int64_t V, int64_t max_val
     *p = plain;
     const int force = g_force_row_skipping.load(std::memory_order_relaxed);
     if (M >= N || force == 1 || !make_plan(M, D, V, &comp, N)) return true;
-    Schedule ps, cs;
-    make_schedule(plain, N, D, V, false, true, &ps);
-    make_schedule(comp, M, D, V, true, true, &cs);
     const ForwardCost fwd{device_cu_count(), D};
-    if (force == 2 || cs.us + fwd.us(comp) + 30.0 < 0.94 * (ps.us + fwd.us(plain))) {
+    if (force == 2 || backward_us(comp, M, D, V, true, true) + fwd.us(comp) + 30.0 <
+                          0.94 * (backward_us(plain, N, D, V, false, true) + fwd.us(plain))) {
         *use_compact = true;
         *p = comp;
     }
@@ -1658,7 +1658,7 @@ size_t cce_compact_workspace_bytes(int64_t N, int64_t D, int64_t V, int64_t max_
     bool use_compact = false;
     if (N <= 0 || D <= 0 || V <= 0 || D % 64 != 0 || max_valid_rows < 0) return 0;
     if (!choose_compact_plan(N, D, V, max_valid_rows, &p, &use_compact)) return 0;
-    return p.total;
+    return workspace_to_ask_for(p, N, D, V, true);
 }
 
 int cce_forward_compact_ex(const void* hidden, const void* weight, const int32_t* labels,
@@ -1724,8 +1724,9 @@ int cce_backward_compact_ex(const void* hidden, const void* weight, const int32_
         return backward_impl(hidden, weight, labels, lse, dloss, grad_scale, N, D, V, 0, V, ignore_index, label_smoothing, z_loss,
                              dHidden, dW, accumulate_dW, nullptr, nullptr, nullptr, workspace, workspace_bytes, stream_);
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
-    const Plan& p = cc.plan;
     const int64_t M = max_valid_rows < 1 ? 1 : (max_valid_rows < N ? max_valid_rows : N);
+    plan_backward(&cc.plan, M, D, V, true, !accumulate_dW, workspace_bytes, &cc.order);
+    const Plan& p = cc.plan;
     hipStream_t stream = (hipStream_t)stream_;
     char* ws = (char*)workspace;
     int32_t* status = (int32_t*)(ws + p.off_status);

@@ -52,6 +52,8 @@ struct Plan {
     int fwd_tt() const { return (int)((rows + 127) / 128); }
     int fwd_vt() const { return (int)((cols + 127) / 128); }
     size_t off_status, off_partials, off_sumz, off_dhacc, off_g, total;
+    size_t budget;              // what `total` may grow to (see room_for_planes)
+    bool forced;                // a knob was set: the layout and order are exactly those
     // row skipping only (budget_rows != 0): compact-row bookkeeping
     int64_t rows_pad;           // compact rows rounded up to 256
     size_t off_count, off_perm, off_labels_c, off_fa_c, off_fb_c;
@@ -155,9 +157,6 @@ struct BackwardModel {
         return ((a * b + cus - 1) / cus) * t_tile() + mk + bytes / 3.0e6 + 4.0;
     }
 };
-
-struct Schedule;
-static double schedule_us(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, bool* use);
 
 // budget_rows != 0 selects row skipping: the plan is made for N compact rows while the workspace
 // budget (1 % of the materialised logits) is that of the budget_rows original rows, and the
@@ -283,58 +282,75 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
         const int64_t rounds = ((int64_t)p->TT * p->S + cus - 1) / cus;
         p->model_us = (p->split_acc ? cost_split : cost_f32) + (double)(rounds * ((p->VT + p->S - 1) / p->S)) * fm.t_tile();
     }
-    auto lay_out = [&](Plan* q, int a, int b, int64_t spare) {
-        q->gemm_kind = best_kind;
-        q->Nb = (int64_t)a * 256;
-        q->Vc = (int64_t)b * 256;
-        q->off_status = 0;
-        q->off_partials = 256;
-        q->off_sumz = q->off_partials + md_bytes;
-        q->off_dhacc = q->off_partials + partial_bytes;
-        q->off_g = q->off_dhacc + (size_t)round_up(q->Nb * D * (q->split_acc ? 2 : 4), 256) + (size_t)spare;
-        q->total = q->off_g + (size_t)(q->Nb * q->Vc * 2);
-        q->rows_pad = Np;
-        q->off_count = q->off_perm = q->off_labels_c = q->off_fa_c = q->off_fb_c = q->off_zero_row = 0;
-        if (compact) {
-            q->off_count = round_up((int64_t)q->total, 256);
-            q->off_perm = q->off_count + 256;
-            q->off_labels_c = q->off_perm + scalar_bytes;
-            q->off_fa_c = q->off_labels_c + scalar_bytes;
-            q->off_fb_c = q->off_fa_c + scalar_bytes;
-            q->off_zero_row = q->off_fb_c + scalar_bytes;
-            q->total = q->off_zero_row + zero_row_bytes;
-        }
-    };
-    lay_out(p, best_a, best_b, 0);
+    p->gemm_kind = best_kind;
+    p->Nb = (int64_t)best_a * 256;
+    p->Vc = (int64_t)best_b * 256;
+    p->off_status = 0;
+    p->off_partials = 256;
+    p->off_sumz = p->off_partials + md_bytes;
+    p->off_dhacc = p->off_partials + partial_bytes;
+    p->off_g = p->off_dhacc + (size_t)round_up(p->Nb * D * acc_bytes, 256);
+    p->total = p->off_g + (size_t)(p->Nb * p->Vc * 2);
+    p->rows_pad = Np;
+    p->off_count = p->off_perm = p->off_labels_c = p->off_fa_c = p->off_fb_c = p->off_zero_row = 0;
+    if (compact) {
+        p->off_count = round_up((int64_t)p->total, 256);
+        p->off_perm = p->off_count + 256;
+        p->off_labels_c = p->off_perm + scalar_bytes;
+        p->off_fa_c = p->off_labels_c + scalar_bytes;
+        p->off_fb_c = p->off_fa_c + scalar_bytes;
+        p->off_zero_row = p->off_fb_c + scalar_bytes;
+        p->total = p->off_zero_row + zero_row_bytes;
+    }
+    p->budget = budget;
+    p->forced = knobs.row_tiles || knobs.vocab_tiles || knobs.gemm_cols || knobs.split_acc;
     // the gradient chunk is addressed with 32-bit byte offsets (only a forced tiling can get here)
     if (p->Nb * p->Vc * 2 >= ((int64_t)1 << 32)) return false;
-    // All rows in one block and budget to spare: the plan itself has no use for more, but a schedule
-    // that cuts dH's serial reduction into parts wants room for their planes (up to 16 parts) beside a
-    // wide chunk.  That room is laid out, the chunk after it, if a schedule on it is rated 10 % faster,
-    // both for calls that overwrite dW and for calls that add to it.
-    const bool forced = knobs.row_tiles || knobs.vocab_tiles || knobs.gemm_cols || knobs.split_acc;
-    if (!forced && best_a == p->TT && p->TT <= 16) {
-        const int64_t slack = (int64_t)((double)budget - bytes_needed(best_a, best_b));
-        const int64_t tile = (int64_t)best_a * 131072, planes = 15 * (int64_t)round_up(N * D * 4, 256);
-        const int64_t room = best_b < p->VT ? slack / 2 : slack;
-        const int64_t spare = (planes < room ? planes : room) / 256 * 256;
-        if (spare >= planes / 15) {
-            int64_t wide = best_b + (slack - spare) / tile;
-            wide = wide < p->VT ? wide : p->VT;
-            Plan q = *p;
-            lay_out(&q, best_a, (int)wide, spare);
-            bool better = true, use = false;
-            for (int dw_free = 0; dw_free < 2 && better; ++dw_free) {
-                const double now = schedule_us(*p, N, D, V, compact, dw_free != 0, &use);
-                const double then = schedule_us(q, N, D, V, compact, dw_free != 0, &use);
-                better = use && then < 0.9 * now;
-            }
-            if (better) *p = q;
-        }
-    }
     cache[cache_next] = {N, D, V, budget_rows, cus, knobs.row_tiles, knobs.vocab_tiles, knobs.gemm_cols, knobs.split_acc, *p, true};
     cache_next = (cache_next + 1) % kCached;
     return true;
+}
+
+// All rows in one block and budget to spare: the Plan itself has no use for more, but a schedule that cuts
+// dH's serial reduction into parts wants room for their planes (up to 16 parts) beside a wide chunk.  *q
+// is that layout.  A call takes it only where its workspace holds it, so what a call NEEDS stays p.total.
+static bool room_for_planes(const Plan& p, int64_t D, Plan* q) {
+    if (p.forced || p.Nb != (int64_t)p.TT * 256 || p.TT > 16) return false;
+    const int64_t slack = (int64_t)p.budget - (int64_t)p.total, b = p.Vc / 256;
+    const int64_t tile = (int64_t)p.TT * 131072, planes = 15 * (int64_t)round_up(p.rows * D * 4, 256);
+    const int64_t room = b < p.VT ? slack / 2 : slack;
+    const int64_t spare = (planes < room ? planes : room) / 256 * 256;
+    if (spare < planes / 15) return false;
+    int64_t wide = b + (slack - spare) / tile;
+    wide = wide < p.VT ? wide : p.VT;
+    const size_t more = (size_t)(spare + (wide - b) * tile);
+    *q = p;
+    q->Vc = wide * 256;
+    q->off_g += (size_t)spare;
+    q->total += more;
+    if (q->off_count) {
+        q->off_count += more; q->off_perm += more; q->off_labels_c += more;
+        q->off_fa_c += more; q->off_fb_c += more; q->off_zero_row += more;
+    }
+    return true;
+}
+
+// The workspace to ask for.  Every layout that a call with this many rows or fewer can want (same D and V;
+// row skipping: under any bound) fits it, whichever tiling each row count gets: the budget, or the most
+// that a layout for such a problem can hold where that is less.  (Sized by its own layout alone, 356 rows
+// at D = 2048, V = 4000 asked for 48 MB where 1024 rows asked for 17: a workspace made for the largest
+// batch did not serve the last, short one.)
+static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact) {
+    Plan roomy;
+    const size_t own = room_for_planes(p, D, &roomy) ? roomy.total : p.total;
+    if (p.forced) return own;
+    const int64_t TT = (N + 255) / 256, VT = (V + 255) / 256, a = TT < 64 ? TT : 64;
+    const double pairs = (double)N * 12.0 * (double)(2 * VT), sums = (double)a * 256.0 * (double)D * 4.0;
+    const double planes = 15.0 * (double)((N < 4096 ? N : 4096) * D * 4 + 256);
+    const double rows = compact ? 4.0 * (double)(TT * 256 * 4 + 256) + (double)(D * 2 + 512) : 0.0;
+    const double most = 256.0 + 512.0 + pairs + sums + planes + (double)(a * VT) * 131072.0 + rows;
+    const size_t serves = most < (double)p.budget ? (size_t)most : p.budget;
+    return own > serves ? own : serves;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -630,11 +646,21 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     cache_next = (cache_next + 1) % kCached;
 }
 
-// Modelled time of a call's backward on this plan, and whether a schedule takes it over.
-static double schedule_us(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, bool* use) {
+// The layout and order of a backward whose workspace has `workspace_bytes` (at least p->total): *p becomes
+// the layout with room for planes where the workspace holds it and a schedule on it is rated 10 % faster.
+static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc) {
+    make_schedule(*p, N, D, V, compact, dw_free, sc);
+    Plan roomy;
+    if (!room_for_planes(*p, D, &roomy) || roomy.total > workspace_bytes) return;
     Schedule s;
-    make_schedule(p, N, D, V, compact, dw_free, &s);
-    *use = s.use;
+    make_schedule(roomy, N, D, V, compact, dw_free, &s);
+    if (s.use && s.us < 0.9 * sc->us) { *p = roomy; *sc = s; }
+}
+
+// Modelled time of the backward that plan_backward would choose in a workspace of the size asked for.
+static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free) {
+    Schedule s;
+    plan_backward(&p, N, D, V, compact, dw_free, (size_t)-1, &s);
     return s.us;
 }
 

@@ -25,9 +25,8 @@ static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blo
 #define CHECK(cond) do { if (!(cond)) { ++failures; fprintf(stderr, "FAIL %d: %s | N=%lld D=%lld V=%lld B=%lld free=%d\n", __LINE__, #cond, \
     (long long)N, (long long)D, (long long)V, (long long)B, (int)dw_free); } } while (0)
 
-static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
-    Plan p; Schedule s;
-    if (!make_plan(N, D, V, &p, B)) return false;
+static bool check_layout(const Plan& p, int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
+    Schedule s;
     make_schedule(p, N, D, V, B != 0, dw_free, &s);
     if (s.n_blocks) {
         ++fronts;
@@ -98,6 +97,21 @@ static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
         if (s.split_acc) ++split_accs;
     }
     return true;
+}
+
+// The plan's own layout, and the one with room for planes that a call takes where its workspace holds it.
+static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
+    Plan p, roomy;
+    if (!make_plan(N, D, V, &p, B)) return false;
+    bool used = check_layout(p, N, D, V, B, dw_free);
+    const size_t ask = workspace_to_ask_for(p, B ? B : N, D, V, B != 0);
+    CHECK(p.total <= ask);
+    if (room_for_planes(p, D, &roomy)) {
+        CHECK(roomy.total <= ask && roomy.total > p.total && roomy.off_dhacc == p.off_dhacc);
+        CHECK((roomy.off_g & 255) == 0 && (roomy.off_perm & 255) == 0 && (!B || roomy.off_count - p.off_count == roomy.total - p.total));
+        used = check_layout(roomy, N, D, V, B, dw_free) || used;
+    }
+    return used;
 }
 
 // two_class_makespan against the hand-out itself: every job goes to the unit that is free first.

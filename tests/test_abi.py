@@ -63,6 +63,17 @@ def test_workspace_is_small_and_independent_of_NV(L):
         assert binding.workspace_bytes(n, d, v) <= 0.01 * binding.materialised_logit_bytes(n, v)
 
 
+def test_workspace_serves_fewer_rows(L):
+    """A workspace sized for the largest batch serves every smaller one, and any bound under row skipping."""
+    for d, v in [(2048, 4000), (64, 1000), (896, 151936), (512, 32000), (256, 128256)]:
+        rows = [1, 63, 100, 356, 500, 1024, 1500, 2048, 4096, 6000, 8192, 16384]
+        ask = [binding.workspace_bytes(n, d, v) for n in rows]
+        assert ask == sorted(ask), (d, v, ask)
+        compact = [[binding.compact_workspace_bytes(n, d, v, m) for m in (1, n // 2, n * 9 // 10, n)] for n in rows]
+        for small, large in zip(compact, compact[1:]):
+            assert max(small) <= min(large), (d, v, compact)
+
+
 def test_forced_tiling_is_bounded(L):
     """A forced tiling whose gradient chunk would need more than 32-bit byte offsets is refused."""
     try:

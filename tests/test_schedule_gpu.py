@@ -107,3 +107,22 @@ def test_schedule_matches_forced_tiling(shape, form):
     e = float((h0 - h1).norm() / h1.norm()), float((w0 - w1).norm() / w1.norm())
     print(f"[schedule] {form} N={N} D={D} V={V}: relF(dH)={e[0]:.2e} relF(dW)={e[1]:.2e}", flush=True)
     assert e[0] <= 2e-3 and e[1] <= 2e-5
+
+
+def test_workspace_of_the_largest_batch_serves_shorter_ones():
+    """One workspace for 1024 rows, then batches of fewer: accepted, and right whichever order fits it."""
+    from paper_2601_02609_amd import binding as B
+    D, V = 2048, 4000
+    ws = B.alloc_workspace(1024, D, V)
+    for N in (1024, 356, 100, 1):
+        print(f"[schedule] N={N} in the workspace of 1024 rows", flush=True)
+        w = I.make_workload(I.custom_spec(N, D, V, seed=78, ignore_frac=0.2 if N > 1 else 0.0))
+        H, W, y = dev_inputs(w)
+        loss, lse = B.cce_forward(H, W, y, IGN, workspace=ws)
+        dH, dW = B.cce_backward(H, W, y, lse, torch.from_numpy(w.dloss_var).cuda(), IGN, workspace=ws)
+        torch.cuda.synchronize()
+        assert B.read_status(ws) == 0
+        o_loss, _ = O.forward(w.hidden, w.weight, w.labels, IGN)
+        o_dH, o_dW = O.backward(w.hidden, w.weight, w.labels, w.dloss_var, IGN)
+        assert np.abs(loss.cpu().numpy() - o_loss).max() <= LOSS_ATOL
+        assert rel_fro(bf16_host(dH), o_dH) <= GRAD_RTOL and rel_fro(dW.cpu().numpy().astype(np.float64), o_dW) <= GRAD_RTOL
