@@ -7,10 +7,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <string.h>
 #include <atomic>
 
 #include "gemm_core.h"
 #include "host_util.h"
+
+#ifndef CCE_PLAN_PRICED
+#define CCE_PLAN_PRICED() ((void)0)     // a makespan was searched for: counted by the host tests
+#endif
 
 namespace cce {
 
@@ -101,6 +106,7 @@ struct Knobs {
 // times, so the searches start where no unit would be idle, which is a lower bound of every answer
 // behind the last long job; short jobs that all fit beside it are answered first.
 static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
+    CCE_PLAN_PRICED();
     const int64_t full = n1 / cus, rem = n1 % cus;
     const double tA = (double)full * c1;                     // units without a long job in the last round
     const double tB = (double)(rem ? full + 1 : full) * c1;
@@ -125,6 +131,19 @@ static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2,
     return best;
 }
 
+// The same of two jobs in either order, longer items first.
+static double makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
+    return c1 >= c2 ? two_class_makespan(cus, n1, c1, n2, c2) : two_class_makespan(cus, n2, c2, n1, c1);
+}
+// A bound that it never falls below, without the search: all work spread evenly, the rounds of the longer job.
+static double makespan_floor(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
+    const double even = ((double)n1 * c1 + (double)n2 * c2) / (double)cus;
+    const double rounds = c1 >= c2 ? (double)((n1 + cus - 1) / cus) * c1 : (double)((n2 + cus - 1) / cus) * c2;
+    return even > rounds ? even : rounds;
+}
+// Floors and times are sums in different orders: what lies above by less than this is not passed over.
+constexpr double kAbove = 1.0 + 1e-9;
+
 // Tile of one contraction launch: 128 x 128 where the planned 256 x 128 tiles would leave half of the
 // compute units without work (an item then costs about half as much, and all of them still start at
 // once).  A forced tile stays.  Backward of 256 x 64 x 1000: 23 -> 16 us, 322 x 1856 x 1015: 36 -> 28,
@@ -145,16 +164,35 @@ struct BackwardModel {
     int d_tiles() const { return (int)((D + tile.bn - 1) / tile.bn); }
 
     // One step = the gradient tiles, then the contractions, of an [a x b] block of 256 x 256
-    // tiles: two launches that follow each other on the caller's stream.
+    // tiles: two launches that follow each other on the caller's stream.  FLOOR: with makespan_floor.
+    template <bool FLOOR = false>
     double step(int a, int b, bool dw_beta) const {
         const int dt = d_tiles(), per256 = 256 / tile.bm;
         const int n_dh = a * per256 * dt, n_dw = b * per256 * dt;
         const double c_dh = t_gemm(b), c_dw = t_gemm(a);
-        const double mk = (c_dh >= c_dw) ? two_class_makespan(cus, n_dh, c_dh, n_dw, c_dw)
-                                          : two_class_makespan(cus, n_dw, c_dw, n_dh, c_dh);
+        const double mk = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
         // fp32 accumulator traffic of the step at ~3 TB/s
         const double bytes = (double)a * 256 * D * 8.0 + (dw_beta ? (double)b * 256 * D * 8.0 : (double)b * 256 * D * 4.0);
         return ((a * b + cus - 1) / cus) * t_tile() + mk + bytes / 3.0e6 + 4.0;
+    }
+    // All work of TT x VT tiles spread evenly, and a bound made of it for a backward in blocks of a x b.
+    double even(int TT, int VT) const {
+        return (double)TT * VT * (t_tile() + 8.0 * d_tiles() * (256 / tile.bm) * tile.us_per_slice) / cus;
+    }
+    double quick_floor(double even_us, int TT, int VT, int nblk, int nch) const {
+        return even_us + (double)(nblk * nch) * 4.0 + (double)(256 * D) / 3.0e6 * (8.0 * (double)TT * nch + (double)VT * (8.0 * nblk - 4.0));
+    }
+    // The whole backward of TT x VT tiles in blocks of a x b.
+    template <bool FLOOR = false>
+    double backward(int TT, int VT, int a, int b) const {
+        const int nblk = (TT + a - 1) / a, a_last = TT - (nblk - 1) * a;
+        const int nch = (VT + b - 1) / b, b_last = VT - (nch - 1) * b;
+        // the first row block overwrites dW, later ones add to it
+        auto block_cost = [&](int aa, bool beta) {
+            return (nch > 1 ? (nch - 1) * step<FLOOR>(aa, b, beta) : 0.0) + step<FLOOR>(aa, b_last, beta);
+        };
+        return nblk == 1 ? block_cost(a_last, false)
+                         : block_cost(a, false) + (nblk > 2 ? (nblk - 2) * block_cost(a, true) : 0.0) + block_cost(a_last, true);
     }
 };
 
@@ -168,7 +206,7 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
     // A row-skipping call asks for two plans (all rows, the valid ones) in its forward and again in its
     // backward, so the cache holds several; the oldest entry goes first.
     struct Key { int64_t N, D, V, B; int cus, fa, fb, fc, fs; Plan plan; bool valid; };
-    constexpr int kCached = 8;
+    constexpr int kCached = 32;
     static thread_local Key cache[kCached] = {};
     static thread_local int cache_next = 0;
     for (const Key& k : cache)
@@ -213,8 +251,11 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
     auto bytes_needed = [&](int64_t a, int64_t b) {
         return (double)fixed + (double)round_up(a * 256 * D * acc_bytes, 256) + (double)(a * 256) * (double)(b * 256) * 2.0;
     };
-    // Tiling for a given contraction tile: the (a, b) with the smallest modelled time.
-    auto plan_for_kind = [&](int kind, int* a_out, int* b_out) -> double {
+    // Tiling for a given contraction tile: the (a, b) with the smallest modelled time (the smallest of
+    // equal ones).  The widest blocks are tried first, they are usually the best, and a tiling whose floor
+    // is above the best so far is passed over: of 5504 makespans for 16000 x 64 x 2000 26 are left, of 31158
+    // for 30000 x 3584 x 151936 1866.  Where nothing is below `bound` the result is `bound` or more.
+    auto plan_for_kind = [&](int kind, double bound, int* a_out, int* b_out) -> double {
         BackwardModel model{cus, D, gemm_tile_of_kind(kind)};
         if (knobs.row_tiles > 0 && knobs.vocab_tiles > 0) {
             *a_out = knobs.row_tiles < p->TT ? knobs.row_tiles : p->TT;
@@ -222,26 +263,25 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
             *b_out = knobs.vocab_tiles < p->VT ? knobs.vocab_tiles : p->VT;
             return 0.0;
         }
-        double best_cost = 1e300;
+        double best_cost = bound;
+        const double even_us = model.even(p->TT, p->VT);
         // (row skipping: a row block's row map must fit its LDS table)
         const int a_cap = compact ? kCompactMaxRowTiles : 64;
         const int a_max = p->TT < a_cap ? p->TT : a_cap, b_max = p->VT < 128 ? p->VT : 128;
         *a_out = 1; *b_out = 1;
-        for (int a = 1; a <= a_max; ++a) {
-            for (int b = 1; b <= b_max; ++b) {
-                if (bytes_needed(a, b) > (double)budget && !(a == 1 && b == 1)) break;
-                const int nblk = (p->TT + a - 1) / a, a_last = p->TT - (nblk - 1) * a;
-                const int nch = (p->VT + b - 1) / b, b_last = p->VT - (nch - 1) * b;
-                // the first row block overwrites dW, later ones add to it
-                auto block_cost = [&](int aa, bool beta) {
-                    return (nch - 1) * model.step(aa, b, beta) + model.step(aa, b_last, beta);
-                };
-                double cost = (nblk == 1) ? block_cost(a_last, false)
-                                          : block_cost(a, false) + (nblk - 2) * block_cost(a, true) + block_cost(a_last, true);
+        for (int a = a_max; a >= 1; --a) {
+            const double left = (double)budget - bytes_needed(a, 0);
+            int b_fits = left < 0.0 ? 0 : left >= (double)a * 131072.0 * b_max ? b_max : (int)(left / ((double)a * 131072.0));
+            if (a == 1 && b_fits < 1) b_fits = 1;           // one tile is always allowed
+            for (int b = b_fits; b >= 1; --b) {
                 // measured per contraction launch: the split running sum costs 2 us, 9 us when its
                 // upper-half plane is also reached through the row map of the compact row space
-                if (acc_bytes == 2) cost += (double)nblk * nch * (compact ? 9.0 : 2.0);
-                if (cost < best_cost) { best_cost = cost; *a_out = a; *b_out = b; }
+                const int nblk = (p->TT + a - 1) / a, nch = (p->VT + b - 1) / b;
+                const double split_us = acc_bytes == 2 ? (double)nblk * nch * (compact ? 9.0 : 2.0) : 0.0;
+                if (model.quick_floor(even_us, p->TT, p->VT, nblk, nch) + split_us > best_cost * kAbove) continue;
+                if (model.backward<true>(p->TT, p->VT, a, b) + split_us > best_cost * kAbove) continue;
+                const double cost = model.backward(p->TT, p->VT, a, b) + split_us;
+                if (cost <= best_cost) { best_cost = cost; *a_out = a; *b_out = b; }
             }
         }
         return best_cost;
@@ -251,27 +291,27 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
     // of one tile shape well but is off by ~15 % between the shapes, so the shape is decided
     // by occupancy: measured, D = 1024 and 2048 gain 17 % with the narrow tile, D = 1536 with
     // 77 % occupancy loses 6 %.)
-    auto plan_for_acc = [&](int bytes, int* a_out, int* b_out, int* kind_out) -> double {
+    auto plan_for_acc = [&](int bytes, double bound, int* a_out, int* b_out, int* kind_out) -> double {
         acc_bytes = bytes;
         double cost = 0.0;
         *kind_out = 1;
         if (knobs.gemm_cols != 0) {
             *kind_out = knobs.gemm_cols == 256 ? 0 : 1;
-            if (*kind_out == 0) cost = plan_for_kind(0, a_out, b_out);
+            if (*kind_out == 0) cost = plan_for_kind(0, bound, a_out, b_out);
         } else if (D % 256 == 0) {
-            cost = plan_for_kind(0, a_out, b_out);
+            cost = plan_for_kind(0, 1e300, a_out, b_out);      // (the tile follows from its tiling, below the bound or not)
             const int64_t tiles = (int64_t)(*a_out + *b_out) * (D / 256);
             const int64_t rounds = (tiles + cus - 1) / cus;
             *kind_out = (double)tiles >= 0.7 * (double)(rounds * cus) ? 0 : 1;
         }
-        if (*kind_out == 1) cost = plan_for_kind(1, a_out, b_out);
+        if (*kind_out == 1) cost = plan_for_kind(1, bound, a_out, b_out);
         return cost;
     };
     // The dH running sum: plain fp32 unless the split form (half the workspace, a little slower
     // per launch) buys a tiling that the model rates at least 3 % faster.
     int best_a = 1, best_b = 1, best_kind = 1, sa = 1, sb = 1, skind = 1;
-    const double cost_f32 = plan_for_acc(4, &best_a, &best_b, &best_kind);
-    const double cost_split = plan_for_acc(2, &sa, &sb, &skind);
+    const double cost_f32 = plan_for_acc(4, 1e300, &best_a, &best_b, &best_kind);
+    const double cost_split = plan_for_acc(2, knobs.split_acc == 0 ? 0.97 * cost_f32 : 1e300, &sa, &sb, &skind);
     p->split_acc = 0;
     if (knobs.split_acc == 2 || (knobs.split_acc == 0 && cost_split < 0.97 * cost_f32)) {
         best_a = sa; best_b = sb; best_kind = skind; p->split_acc = 1;
@@ -378,10 +418,8 @@ struct RowBlock {
 };
 constexpr int kMaxRowBlocks = 48;
 
-struct Schedule {
+struct ScheduleSteps {
     bool use;                   // false: the Plan's row blocks and chunks, or blocks[]
-    int n_blocks;               // > 0: blocks[], in execution order
-    RowBlock blocks[kMaxRowBlocks];
     int kind;                   // contraction tile
     int a;                      // row tiles per block (all of them: one row block)
     int b;                      // vocabulary tiles per chunk, at most
@@ -395,11 +433,15 @@ struct Schedule {
     double us;                  // modelled time of the backward
     double plan_us;             // ... and of the Plan's order, same model
 };
+struct Schedule : ScheduleSteps {
+    int n_blocks;               // > 0: blocks[], in execution order
+    RowBlock blocks[kMaxRowBlocks];
+};
 
 // The chunk that starts `rest` columns before the end of the vocabulary: b tiles wide, in steps over
 // `rows` row tiles each.
 struct ScheduleChunk { int64_t b; int rows; bool in_tail; };
-static inline ScheduleChunk schedule_chunk(const Schedule& sc, int64_t D, int64_t rest) {
+static inline ScheduleChunk schedule_chunk(const ScheduleSteps& sc, int64_t D, int64_t rest) {
     const int64_t rest_tiles = (rest + 255) / 256;
     ScheduleChunk c = {0, 0, false};
     for (int parts = 1; ; parts = sc.row_parts) {
@@ -427,20 +469,45 @@ struct ScheduleModel {
     double slice() const { return tile.kind == 0 ? 1.58 : 0.79; }
     double item(int64_t slices, bool beta) const { return (double)slices * slice() + (tile.kind == 0 ? 13.0 : 9.0) + (beta ? 2.0 : 0.0); }
     int64_t d_tiles() const { return (D + tile.bn - 1) / tile.bn; }
-    // one step over a x b tiles
+    double logit_tile() const { return (double)(D / 64) * 1.55 + 7.0; }
+    // One step over a x b tiles.  FLOOR: with makespan_floor.
+    template <bool FLOOR = false>
     double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta) const {
         const int64_t dt = d_tiles();
         const int64_t kh = (b + split_h - 1) / split_h, kw = (a + split_w - 1) / split_w;       // K tiles per part
         const int64_t n_dh = a * dt * ((b + kh - 1) / kh), n_dw = b * dt * ((a + kw - 1) / kw);
         const double c_dh = item(kh * 4, dh_beta), c_dw = item(kw * 4, dw_beta) + (mapped ? (double)(kw * 4) * 0.11 * slice() : 0.0);
-        const double mk = c_dh >= c_dw ? two_class_makespan(cus, n_dh, c_dh, n_dw, c_dw) : two_class_makespan(cus, n_dw, c_dw, n_dh, c_dh);
+        const double mk = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
         const double g = (double)(a * b) * 131072.0, w = (double)b * 512.0 * (double)D;
-        const double tiles_us = (double)((a * b + cus - 1) / cus) * ((double)(D / 64) * 1.55 + 7.0);
+        const double tiles_us = (double)((a * b + cus - 1) / cus) * logit_tile();
         const double tiles_mem = (g + w) / 4.5e6;
         const double gemm_mem = (g * 2.0 + w * (dw_beta ? 5.0 : 3.0)) / 4.5e6;
         double t = (tiles_us > tiles_mem ? tiles_us : tiles_mem) + (mk > gemm_mem ? mk : gemm_mem) + 8.0;
         if (split_w > 1) t += 4.0 + w * 2.0 * (double)(split_w + 1) / 4.0e6;
         return t;
+    }
+    // A bound that no sequence of steps over `a` row tiles and `b` vocabulary tiles falls below, in chunks of
+    // at most `b_max`: all work spread evenly, the serial reduction of one item per step or all bytes at the rate
+    // of HBM, and what each step costs by itself.
+    double floor_us(int64_t a, int64_t b, int64_t b_max, int split_h, int split_w) const {
+        const double ab = (double)(a * b), dt = (double)d_tiles(), per_item = item(0, false);
+        const double steps = (double)((b + b_max - 1) / b_max);
+        const int64_t kh = (b + split_h - 1) / split_h, kw = (a + split_w - 1) / split_w;
+        double even = (8.0 * ab * dt * slice() + ((double)(b * ((a + kw - 1) / kw)) + (double)a * steps) * dt * per_item) / (double)cus;
+        const double dh_item = (double)(kh * 4) * slice() + steps * per_item, dw_item = steps * item(kw * 4, false);
+        if (dh_item > even) even = dh_item;
+        if (dw_item > even) even = dw_item;
+        const double tiles_us = ab * logit_tile() / (double)cus;
+        const double w = (double)b * 512.0 * (double)D;
+        const double tiles_mem = (ab * 131072.0 + w) / 4.5e6, gemm_mem = (ab * 262144.0 + w * 3.0) / 4.5e6;
+        return (tiles_us > tiles_mem ? tiles_us : tiles_mem) + (even > gemm_mem ? even : gemm_mem) + 8.0 * steps +
+               (split_w > 1 ? 4.0 * steps + w * 2.0 * (double)(split_w + 1) / 4.0e6 : 0.0);
+    }
+    // The part of it that grows with the width, per vocabulary tile.
+    double floor_per_tile(int64_t a, int64_t b_max) const {
+        const double dt = (double)d_tiles(), per_item = item(0, false), steps = 1.0 / (double)b_max;
+        return (double)a * logit_tile() / (double)cus + 8.0 * steps +
+               (8.0 * (double)a * dt * slice() + (1.0 + (double)a * steps) * dt * per_item) / (double)cus;
     }
 };
 
@@ -456,24 +523,42 @@ struct ForwardCost {
 // Row blocks from the last to the first with dHidden's front rows as scratch: the partition of the
 // row tiles with the least modelled time (f(R) = min over a of [block of rows R - a .. R] + f(R - a)).
 struct RowBlockPlanner {
-    const ScheduleModel m[2];
+    ScheduleModel m[2];
     int TT, VT; int64_t D; size_t region, off0; bool compact, dw_free;
-    struct State { double us; RowBlock block; bool known; };
+    // Rows 0 .. R: their least time and the last block of that order once `exact`, else it is `us` or more.
+    struct State { double us; RowBlock block; bool exact; };
     State states[1 + 256];
+    struct Priced { int b; bool beta; double us; };
+    Priced priced[1 + 64][2][2][3];
+    static constexpr double kNone = 1e300;
 
+    template <bool FLOOR = false>
     double block_us(const RowBlock& k, bool beta) const {
         const int64_t nch = (VT + k.b - 1) / k.b;
         const ScheduleModel& mm = m[k.kind];
-        double t = (double)(nch - 1) * mm.step(k.a, k.b, 1, 1, true, beta) + mm.step(k.a, VT - (nch - 1) * k.b, 1, 1, nch > 1, beta);
+        double t = nch > 1 ? (double)(nch - 1) * mm.template step<FLOOR>(k.a, k.b, 1, 1, true, beta) : 0.0;
+        t += mm.template step<FLOOR>(k.a, VT - (nch - 1) * k.b, 1, 1, nch > 1, beta);
         if (k.split_acc) t += (double)nch * (compact ? 9.0 : 2.0);
         return t;
     }
-    double best(int R) {
-        if (R == 0) return 0.0;
+    void prepare() {
+        for (int a = 0; a <= 64 && a <= TT; ++a)
+            for (int i = 0; i < 12; ++i) priced[a][i / 6][i / 3 % 2][i % 3].b = 0;
+        states[0].us = 0.0;
+        states[0].exact = true;
+        for (int R = 1; R <= TT; ++R) {
+            const double f0 = m[0].floor_us(R, VT, VT, 1, 1), f1 = m[1].floor_us(R, VT, VT, 1, 1);
+            states[R].us = f0 < f1 ? f0 : f1;
+            states[R].exact = false;
+        }
+    }
+    // The least time of the first R row tiles if it is below `bound`, else kNone.
+    double best(int R, double bound) {
         State& st = states[R];
-        if (st.known) return st.us;
-        st.known = true;
-        st.us = 1e300;
+        if (st.exact) return st.us;
+        if (st.us > bound * kAbove) return kNone;
+        double least = bound;
+        bool found = false;
         const int sizes[] = {R, (R + 1) / 2, (R + 2) / 3, 4, 6, 8, 10, 12, 14, 16, 20, 24, 32};
         for (int i = 0; i < 13; ++i) {
             const int a = sizes[i];
@@ -500,52 +585,62 @@ struct RowBlockPlanner {
                         if (j > 0 && bs[j] == bs[j - 1]) continue;
                         k.b = (int)bs[j];
                         if (k.b < 1 || k.b > cap) continue;
-                        const double t = block_us(k, R < TT || !dw_free) + best(R - a);
-                        if (t < st.us) { st.us = t; st.block = k; }
+                        const bool beta = R < TT || !dw_free;
+                        Priced& known = priced[a][split][kind][j];           // chunks in the workspace are alike for every R
+                        const bool hit = known.b == k.b && known.beta == beta;
+                        if (!hit && block_us<true>(k, beta) + states[R - a].us > least * kAbove) continue;
+                        const double us = hit ? known.us : block_us(k, beta);
+                        known = {k.b, beta, us};
+                        if (us + states[R - a].us > least * kAbove) continue;
+                        const double rest = best(R - a, kNone);
+                        if (us + rest < least) { least = us + rest; st.block = k; found = true; }
                     }
                 }
             }
         }
-        return st.us;
+        if (!found) { st.us = st.us > bound ? st.us : bound; return kNone; }
+        st.us = least;
+        st.exact = true;
+        return least;
     }
 };
 
 // The schedule of a backward over N rows (row skipping: the compact ones) for the workspace laid out
 // by `p`.  dw_free: dW is overwritten, so its unwritten rows may hold a gradient chunk.  Forced
-// tilings, tiles and accumulators keep the Plan's order.
-static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out) {
-    const Knobs knobs = Knobs::read();
+// tilings, tiles and accumulators keep the Plan's order.  Nothing that takes `limit` or longer is looked for.
+// A shape that is seen once pays for this search, so orders whose floor is not below the best so far
+// are passed over: of the thousands of orders a few hundred are priced, the one chosen stays the same.
+static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out, double limit = 1e300) {
     const int cus = device_cu_count();
-    struct Key { int64_t N, D, V; size_t total; int cus, forced; bool compact, dw_free, valid; Schedule s; };
-    constexpr int kCached = 8;
-    static thread_local Key cache[kCached] = {};
-    static thread_local int cache_next = 0;
-    const int forced = (knobs.row_tiles || knobs.vocab_tiles || knobs.gemm_cols || knobs.split_acc) ? 1 : 0;
-    for (const Key& k : cache)
-        if (k.valid && k.N == N && k.D == D && k.V == V && k.total == p.total && k.cus == cus && k.forced == forced &&
-            k.compact == compact && k.dw_free == dw_free) { *out = k.s; return; }
-
     Schedule best = {};
     const int TT = p.TT, VT = p.VT;
     const size_t region = (compact ? p.off_count : p.total) - p.off_dhacc;
     {   // the Plan's order under the same model
         const ScheduleModel m{cus, D, gemm_tile_of_kind(p.gemm_kind), compact};
-        const int64_t a = p.Nb / 256, b = p.Vc / 256;
-        for (int64_t r = 0; r < TT; r += a) {
-            const int64_t aa = TT - r < a ? TT - r : a;
-            const int64_t nch = (VT + b - 1) / b;
-            best.plan_us += (double)(nch - 1) * m.step(aa, b, 1, 1, true, r > 0) + m.step(aa, VT - (nch - 1) * b, 1, 1, nch > 1, r > 0);
-            if (p.split_acc) best.plan_us += (double)nch * (compact ? 9.0 : 2.0);
-        }
+        const int64_t a = p.Nb / 256, b = p.Vc / 256, nch = (VT + b - 1) / b;
+        auto block_us = [&](int64_t aa, bool later) {
+            return (nch > 1 ? (double)(nch - 1) * m.step(aa, b, 1, 1, true, later) : 0.0) + m.step(aa, VT - (nch - 1) * b, 1, 1, nch > 1, later);
+        };
+        const int64_t nblk = (TT + a - 1) / a;
+        best.plan_us = block_us(nblk > 1 ? a : TT, false);
+        if (nblk > 1) best.plan_us += (nblk > 2 ? (double)(nblk - 2) * block_us(a, true) : 0.0) + block_us(TT - (nblk - 1) * a, true);
+        if (p.split_acc) best.plan_us += (double)(nblk * nch) * (compact ? 9.0 : 2.0);
     }
     // A schedule has to be rated 10 % faster: the model is that far off between orders of much
     // different chunk sizes (6963 rows x 896 x 151936 was rated 8 % faster and measured 1 % slower).
     best.us = 0.90 * best.plan_us;
+    if (limit < best.us) best.us = limit;
     const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+    // What the steps of a chunk over all rows take, in 1 ... 4 row parts: many orders share such chunks
+    // (from eight row tiles on, where row parts are tried).
+    constexpr int kKnown = 64;
+    double chunk_us[2][2][2][4][kKnown];
+    const bool keep = TT >= 8;
+    if (keep) memset(chunk_us, 0, sizeof chunk_us);
     auto try_one = [&](int kind, int a, int bcap, int sh, int sw, int row_parts, int b_min, int split_acc) {
         const ScheduleModel m{cus, D, gemm_tile_of_kind(kind)};
-        Schedule sc = {};
+        ScheduleSteps sc = {};
         sc.kind = kind; sc.a = a; sc.split_h = sh; sc.split_w = sw;
         sc.b = bcap < VT ? bcap : VT;
         sc.tail = dw_free && a == TT;
@@ -556,6 +651,12 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         const int64_t cols_max = (int64_t)sc.b * 256 < V ? (int64_t)sc.b * 256 : V;
         sc.plane_h = (rows < N ? rows : N) * D;
         sc.plane_w = cols_max * D;
+        const int nblk = (TT + a - 1) / a;
+        // beside the steps: the sum of the planes, the gathered rows
+        const double sum_us = sh > 1 ? (double)nblk * (8.0 + (double)sh * (double)sc.plane_h * 4.0 / 4.0e6) : 0.0;
+        const double gather_us = compact ? (double)nblk * 5.0 + (double)N * (double)D * 4.0 / 4.0e6 : 0.0;
+        const double extra = sum_us + gather_us;
+        if (m.floor_us(TT, VT, sc.b, sh, sw) + (double)(nblk - 1) * 8.0 + extra > best.us * kAbove) return;
         auto lay_out = [&](int planes) {
             sc.off_acc = p.off_dhacc;
             sc.off_part_w = sc.off_acc + (size_t)round_up((int64_t)planes * sc.plane_h * (split_acc ? 2 : 4), 256);
@@ -569,6 +670,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         bool ok = sh == 1 && !split_acc && row_parts == 1 && lay_out(0) && schedule_chunk(sc, D, V).b == VT;
         if (!ok) ok = lay_out(sh) && (!one_chunk || schedule_chunk(sc, D, V).b == VT);
         if (!ok) return;
+        const double per_tile = m.floor_per_tile(a, sc.b);
         double block_us[2] = {0.0, 0.0};        // first row block, later ones (they add to dW)
         for (int later = 0; later < (one_chunk ? 2 : 1); ++later) {
             ScheduleChunk last = {-1, 0, false}; double last_us = 0.0;
@@ -576,9 +678,16 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                 const ScheduleChunk c = schedule_chunk(sc, D, V - v);
                 if (c.b < 1 || (int64_t)c.rows * c.b * 131072 >= ((int64_t)1 << 32)) return;
                 if (c.b != last.b || c.rows != last.rows) {
-                    last_us = 0.0;
-                    for (int r = 0; r < a; r += c.rows)
-                        last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free) + (split_acc ? 2.0 : 0.0);
+                    double* const known = keep && sh == 1 && sw == 1 && !one_chunk && c.b < kKnown
+                                              ? &chunk_us[kind][split_acc][v > 0][(a + c.rows - 1) / c.rows - 1][c.b] : nullptr;
+                    last_us = known ? *known : 0.0;
+                    const int64_t rest = VT - v / 256 - c.b;
+                    const double least = last_us > 0.0 ? last_us : (double)(a / c.rows) * m.template step<true>(c.rows, c.b, sh, sw, v > 0, later > 0 || !dw_free);
+                    if (block_us[later] + least + (double)rest * per_tile + extra > best.us * kAbove) return;
+                    if (last_us == 0.0)
+                        for (int r = 0; r < a; r += c.rows)
+                            last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free) + (split_acc ? 2.0 : 0.0);
+                    if (known) *known = last_us;
                     last = c;
                 }
                 block_us[later] += last_us;
@@ -586,25 +695,23 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                 v += c.b * 256;
             }
         }
-        const int nblk = (TT + a - 1) / a;
-        sc.us = block_us[0] + (double)(nblk - 1) * block_us[1];
-        if (sh > 1) sc.us += (double)nblk * (8.0 + (double)sh * (double)sc.plane_h * 4.0 / 4.0e6);
-        if (compact) sc.us += (double)nblk * 5.0 + (double)N * (double)D * 4.0 / 4.0e6;
+        sc.us = block_us[0] + (double)(nblk - 1) * block_us[1] + sum_us + gather_us;
         if (sc.us < best.us) {
-            const double plan_us = best.plan_us;
-            best = sc;
-            best.plan_us = plan_us;
-            best.use = true;
+            sc.use = true;
+            sc.plan_us = best.plan_us;
+            (ScheduleSteps&)best = sc;
         }
     };
-    if (!forced) {
+    if (!p.forced) {
         for (int kind = 0; kind < 2; ++kind) {
+            const ScheduleModel m{cus, D, gemm_tile_of_kind(kind)};
             const int64_t dt = (D + gemm_tile_of_kind(kind).bn - 1) / gemm_tile_of_kind(kind).bn;
             if (kind == 0 && dt * 256 * 7 > D * 8) continue;           // more than an eighth of the columns wasted
             for (int sh : splits) {
                 if (sh > 1 && (sh > VT || TT * dt * (sh / 2) > 2 * cus)) break;     // parts beyond two rounds of tiles
                 for (int sw : splits) {
                     if (sw > 1 && (sw > TT || VT * dt * (sw / 2) > 2 * cus)) break;
+                    if (m.floor_us(TT, VT, VT, sh, sw) > best.us * kAbove) continue;
                     int prev = 0;
                     for (int cap : caps) {
                         const int b = cap < VT ? cap : VT;
@@ -626,11 +733,17 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
             }
         }
     }
-    if (!forced && TT > 1 && TT <= 256) {
-        RowBlockPlanner rp = {{{cus, D, gemm_tile_of_kind(0), compact}, {cus, D, gemm_tile_of_kind(1), compact}}, TT, VT, D, region, p.off_dhacc, compact, dw_free, {}};
-        const double us = rp.best(TT);
+    if (!p.forced && TT > 1 && TT <= 256) {
         // 5 %: steps like the Plan's own, which the model ranks more closely than chunks of other widths
-        if (us < best.us || (!best.use && us < 0.95 * best.plan_us)) {
+        double bound = best.use ? best.us : 0.95 * best.plan_us;
+        if (limit < bound) bound = limit;
+        RowBlockPlanner rp;
+        rp.m[0] = {cus, D, gemm_tile_of_kind(0), compact};
+        rp.m[1] = {cus, D, gemm_tile_of_kind(1), compact};
+        rp.TT = TT; rp.VT = VT; rp.D = D; rp.region = region; rp.off0 = p.off_dhacc; rp.compact = compact; rp.dw_free = dw_free;
+        rp.prepare();
+        const double us = rp.best(TT, bound);
+        if (us < bound) {
             int n = 0, R = TT;
             bool front = false;
             for (; R > 0 && n < kMaxRowBlocks; R -= best.blocks[n++].a) {
@@ -642,19 +755,34 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     }
     if (!best.use && !best.n_blocks) best.us = best.plan_us;
     *out = best;
-    cache[cache_next] = {N, D, V, p.total, cus, forced, compact, dw_free, true, best};
-    cache_next = (cache_next + 1) % kCached;
 }
 
 // The layout and order of a backward whose workspace has `workspace_bytes` (at least p->total): *p becomes
 // the layout with room for planes where the workspace holds it and a schedule on it is rated 10 % faster.
+// Kept per thread for the last shapes, the oldest goes first.
 static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc) {
-    make_schedule(*p, N, D, V, compact, dw_free, sc);
     Plan roomy;
-    if (!room_for_planes(*p, D, &roomy) || roomy.total > workspace_bytes) return;
-    Schedule s;
-    make_schedule(roomy, N, D, V, compact, dw_free, &s);
-    if (s.use && s.us < 0.9 * sc->us) { *p = roomy; *sc = s; }
+    const bool room = room_for_planes(*p, D, &roomy) && roomy.total <= workspace_bytes;
+    const int cus = device_cu_count();
+    struct Key { int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, dw_free, room, valid; Plan plan; Schedule order; };
+    constexpr int kCached = 24;
+    static thread_local Key cache[kCached] = {};
+    static thread_local int cache_next = 0;
+    for (const Key& k : cache)
+        if (k.valid && k.N == N && k.D == D && k.V == V && k.total == p->total && k.budget == p->budget && k.cus == cus &&
+            k.forced == p->forced && k.compact == compact && k.dw_free == dw_free && k.room == room) { *p = k.plan; *sc = k.order; return; }
+    Key& k = cache[cache_next];
+    cache_next = (cache_next + 1) % kCached;
+    k.N = N; k.D = D; k.V = V; k.total = p->total; k.budget = p->budget; k.cus = cus;
+    k.forced = p->forced; k.compact = compact; k.dw_free = dw_free; k.room = room; k.valid = true;
+    k.plan = *p;
+    make_schedule(*p, N, D, V, compact, dw_free, &k.order);
+    if (room) {
+        make_schedule(roomy, N, D, V, compact, dw_free, sc, 0.9 * k.order.us);
+        if (sc->use) { k.plan = roomy; k.order = *sc; }
+    }
+    *p = k.plan;
+    *sc = k.order;
 }
 
 // Modelled time of the backward that plan_backward would choose in a workspace of the size asked for.

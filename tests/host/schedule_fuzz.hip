@@ -12,6 +12,8 @@
 #include <vector>
 
 namespace cce { thread_local int g_last_hip_error = 0; }
+static long priced = 0;
+#define CCE_PLAN_PRICED() ((void)++priced)
 #include "../../paper_2601_02609_amd/csrc/plan.h"
 
 using namespace cce;
@@ -139,9 +141,31 @@ static void check_makespan() {
     }
 }
 
+// What planning a backward for a shape seen once may cost: callers whose row count changes with every
+// batch pay it in front of their launches.  Counted in makespans searched for, which is what pricing an order
+// costs (the bounds that pass orders over are a few products each); limits a quarter above today's.
+static void check_planning_cost() {
+    const struct { int64_t N, D, V; long limit; } shapes[] = {
+        {256, 64, 1000, 10}, {900, 256, 12000, 310}, {2000, 512, 5000, 40}, {16000, 64, 2000, 220}, {30000, 64, 2000, 450},
+        {509, 896, 151936, 400}, {8192, 896, 151936, 3000}, {3001, 1024, 50257, 400}, {12000, 4096, 32000, 1100},
+        {30000, 3584, 151936, 4400}};
+    for (auto& s : shapes)
+        for (int dw_free = 0; dw_free < 2; ++dw_free) {
+            Plan p; Schedule sc;
+            const long before = priced;
+            const int64_t N = s.N + dw_free;                     // a shape of its own: nothing is kept from the other form
+            if (!make_plan(N, s.D, s.V, &p)) { ++failures; return; }
+            plan_backward(&p, N, s.D, s.V, false, dw_free != 0, workspace_to_ask_for(p, N, s.D, s.V, false), &sc);
+            printf("planning %lld x %lld x %lld, dW %s: %ld makespans\n", (long long)N, (long long)s.D, (long long)s.V,
+                   dw_free ? "overwritten" : "added to", priced - before);
+            if (priced - before > s.limit) { ++failures; fprintf(stderr, "FAIL planning: %ld makespans, limit %ld\n", priced - before, s.limit); }
+        }
+}
+
 int main(int argc, char** argv) {
     const int iters = argc > 1 ? atoi(argv[1]) : 2000;
     check_makespan();
+    check_planning_cost();
     // shapes the schedules exist for: few rows against a full vocabulary; a small vocabulary
     bool dw_free = true; int64_t N = 509, D = 896, V = 151936, B = 0;
     CHECK(check(N, D, V, B, dw_free));
