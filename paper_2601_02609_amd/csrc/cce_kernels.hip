@@ -1583,29 +1583,8 @@ int cce_backward_ex(const void* hidden, const void* weight, const int32_t* label
                          workspace, workspace_bytes, stream_);
 }
 
-// Row skipping pays when enough rows can be skipped: the compact row space costs a label scan and a
-// few small launches, its hidden rows are read through the row map, and its tiling may fit the launches
-// worse.  It is used when the schedules' model rates it at least 6 % faster (plus ~30 us for the small
-// kernels).  Measured, rated / skipping against all rows: 31130 of 32768 x 3584 x 151936 0.967 / 1.001,
-// 15565 of 16384 x 2048 x 151936 0.956 / 1.080, 6963 of 8192 x 896 x 151936 0.920 / 0.93,
-// 12288 of 16384 x 4096 x 32000 0.79 / 0.81.  Otherwise every row is processed, exactly as
-// cce_forward / cce_backward do.
 static bool choose_compact_plan(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows, Plan* p, bool* use_compact) {
-    Plan plain, comp;
-    int64_t M = max_valid_rows < N ? max_valid_rows : N;
-    if (M < 1) M = 1;
-    if (!make_plan(N, D, V, &plain)) return false;
-    *use_compact = false;
-    *p = plain;
-    const int force = g_force_row_skipping.load(std::memory_order_relaxed);
-    if (M >= N || force == 1 || !make_plan(M, D, V, &comp, N)) return true;
-    const ForwardCost fwd{device_cu_count(), D};
-    if (force == 2 || backward_us(comp, M, D, V, true, true) + fwd.us(comp) + 30.0 <
-                          0.94 * (backward_us(plain, N, D, V, false, true) + fwd.us(plain))) {
-        *use_compact = true;
-        *p = comp;
-    }
-    return true;
+    return plan_row_skipping(N, D, V, max_valid_rows, g_force_row_skipping.load(std::memory_order_relaxed), p, use_compact);
 }
 
 // Row skipping: shared argument checks and plan.
