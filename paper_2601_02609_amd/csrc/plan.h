@@ -511,10 +511,15 @@ struct ScheduleModel {
     }
 };
 
-// The forward under the same constants: rounds of workgroups that walk their vocabulary tiles.
+// The forward under the same constants: rounds of workgroups that walk their vocabulary tiles, or of one
+// small tile each (500 x 2048 x 10000, two rounds of 32 slices: 42 us).
 struct ForwardCost {
     int cus; int64_t D;
     double us(const Plan& p) const {
+        if (p.small_tiles) {
+            const int64_t tiles = (int64_t)p.fwd_tt() * p.fwd_vt();
+            return (double)((tiles + cus - 1) / cus) * ((double)(D / 64) * 0.55 + 4.0);
+        }
         const int64_t rounds = ((int64_t)p.TT * p.S + cus - 1) / cus;
         return (double)(rounds * ((p.VT + p.S - 1) / p.S)) * ((double)(D / 64) * 1.55 + 4.0);
     }
@@ -798,7 +803,7 @@ static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact,
 // schedules' model rates it 6 % faster, with 15 us for the small launches (500 x 256 x 3000 with 300 valid
 // rows: 29 -> 43 us, 1500 x 512 x 2000 with 900: 41 -> 53).  A forward and the workspace query do not know whether the
 // backward will overwrite dW or add to it, and the two run in different orders, so both forms count.
-// Over 130 drawn shapes with 5 ... 60 % of the rows ignored, both forms timed: 1.2 % above the better side
+// Over 130 drawn shapes with 5 ... 60 % of the rows ignored, both forms timed: 1.0 % above the better side
 // on average, one choice slower than all rows (1.02).  Rated on the overwriting form alone with 30 us it was 1.8 %,
 // and four of the calls lost 7 ... 13 % against skipping (1402 x 2432 x 112762 with 1191 valid: 3054 us for 3454).
 // At 4 % the model is wrong too often (16384 x 2048 x 151936 with 15565 valid, rated 0.956, takes 1.07).
