@@ -799,19 +799,25 @@ static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact,
 
 // Row skipping pays when enough rows can be skipped: the compact row space costs a label scan and a few
 // small launches, its hidden rows are read through the row map or gathered, and its tiling may fit the
-// launches worse.  `comp` is the plan for M compact rows, `plain` the one for all N.  Skipping is taken where the
-// schedules' model rates it 6 % faster, with 15 us for the small launches (500 x 256 x 3000 with 300 valid
-// rows: 29 -> 43 us, 1500 x 512 x 2000 with 900: 41 -> 53).  A forward and the workspace query do not know whether the
-// backward will overwrite dW or add to it, and the two run in different orders, so both forms count.
-// Over 130 drawn shapes with 5 ... 60 % of the rows ignored, both forms timed: 1.0 % above the better side
-// on average, one choice slower than all rows (1.02).  Rated on the overwriting form alone with 30 us it was 1.8 %,
-// and four of the calls lost 7 ... 13 % against skipping (1402 x 2432 x 112762 with 1191 valid: 3054 us for 3454).
-// At 4 % the model is wrong too often (16384 x 2048 x 151936 with 15565 valid, rated 0.956, takes 1.07).
+// launches worse.  `comp` is the plan for M compact rows, `plain` the one for all N.  15 us stand for the small
+// launches (500 x 256 x 3000 with 300 valid rows: 29 -> 43 us, 1500 x 512 x 2000 with 900: 41 -> 53).  The forward
+// and the workspace query do not know whether the backward will overwrite dW or add to it, and the two run in
+// different orders: skipping is taken where the schedules' model rates one of the two 6 % faster and the other
+// no slower.  Over 130 drawn shapes with 5 ... 60 % of the rows ignored, both forms timed, that is 0.8 % above the
+// better side on average, with one choice slower than all rows (1.02).  The overwriting form alone, with 30 us: 1.8 %,
+// and calls that lost 7 ... 13 % against skipping (1402 x 2432 x 112762 with 1191 valid: 3054 us for 3454); 6 % on the
+// sum of both: 1.0 %, but 4 ... 9 % lost where only one form gains (4974 x 384 x 124212 with 4477 valid).  At 4 % the
+// model is wrong too often (16384 x 2048 x 151936 with 15565 valid, rated 0.956, takes 1.07).
 static bool skipping_pays(const Plan& plain, const Plan& comp, int64_t N, int64_t M, int64_t D, int64_t V) {
     const ForwardCost fwd{device_cu_count(), D};
-    const double all = backward_us(plain, N, D, V, false, true) + backward_us(plain, N, D, V, false, false) + 2.0 * fwd.us(plain);
-    const double skipped = backward_us(comp, M, D, V, true, true) + backward_us(comp, M, D, V, true, false) + 2.0 * fwd.us(comp);
-    return skipped + 2.0 * 15.0 < 0.94 * all;
+    double least = 1e300, most = 0.0;
+    for (int dw_free = 0; dw_free < 2; ++dw_free) {
+        const double rated = (backward_us(comp, M, D, V, true, dw_free != 0) + fwd.us(comp) + 15.0) /
+                             (backward_us(plain, N, D, V, false, dw_free != 0) + fwd.us(plain));
+        least = rated < least ? rated : least;
+        most = rated > most ? rated : most;
+    }
+    return least < 0.94 && most < 1.0;
 }
 
 // Whether a call with at most M = max_valid_rows < N valid rows skips the others; mode as in

@@ -79,6 +79,8 @@ def test_workspace_serves_fewer_rows(L):
     ((500, 256, 3000, 300), False), ((8385, 192, 2434, 5031), False),
     # faster when skipped by 12 % in both forms of the backward, by 7 and 14 %
     ((1402, 2432, 112762, 1191), True), ((4800, 3008, 37936, 4080), True),
+    # only one form of the two gains much: overwriting 9 %, 8 % and 7 %, adding to dW 6 %, nothing and 4 %
+    ((4974, 384, 124212, 4477), True), ((6675, 256, 59907, 6341), True), ((1998, 1280, 122224, 1698), True),
     # 0.77 of the time when skipped: the forward of all rows is a round of small tiles longer
     ((2003, 2240, 2596, 1202), True)])
 def test_row_skipping_choice(L, shape, skips):
