@@ -1293,7 +1293,7 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
 // The backward in the order of a Schedule (plan.h); arguments as in backward_impl, checked there.
 // Row skipping: the hidden rows that take part are gathered first -- for one row block into dHidden,
 // which is as large and is not written before the last contraction; per row block into the workspace.
-static int run_schedule(const Schedule& sc, const void* hidden, const void* weight, const int32_t* labels,
+static void run_schedule(const Schedule& sc, const void* hidden, const void* weight, const int32_t* labels,
                         const float* lse, const float* dloss, const float* mean_scale,
                         int64_t N, int64_t D, int64_t V, int64_t v_off, int64_t V_total, int32_t ignore_index,
                         float label_smoothing, float z_loss, void* dHidden, float* dW, int accumulate_dW,
@@ -1415,10 +1415,6 @@ static int run_schedule(const Schedule& sc, const void* hidden, const void* weig
                                (uint16_t*)dHidden + (cc ? (size_t)0 : (size_t)r0 * D), cc ? cc->perm + r0 : (const int32_t*)nullptr);
         }
     }
-    // the gathered rows overwrote the zeros of dHidden's skipped rows
-    if (cc && one_block) cc->zero_skipped(stream, dHidden);
-    if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
-    return CCE_OK;
 }
 
 // Backward over the V rows of `weight`, which are the rows [v_off, v_off + V) of a matrix of
@@ -1465,10 +1461,14 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                            labels, (int)N, (int)V_total, ignore_index, grad_scale, mean_scale);
     const int grad_lds = kGradTileLds;
 
-    if (sc.use)
-        return run_schedule(sc, hidden, weight, labels, lse, dloss, mean_scale, N, D, V, v_off, V_total, ignore_index,
-                            label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
-                            ws, stream, cc);
+    if (sc.use) {
+        run_schedule(sc, hidden, weight, labels, lse, dloss, mean_scale, N, D, V, v_off, V_total, ignore_index,
+                     label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
+                     ws, stream, cc);
+        if (cc && order_uses_dhidden(p, sc)) cc->zero_skipped(stream, dHidden);
+        if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
+        return CCE_OK;
+    }
 
     // The [row block x vocabulary chunk] steps in execution order: the Plan's blocks from the first to
     // the last, or those of a schedule that keeps sums or chunks in dHidden, from the last to the first.
@@ -1479,11 +1479,9 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         for (int r = 0; r < p.TT; r += (int)(p.Nb / 256))
             blocks.push_back({r, (int)(p.Nb / 256), (int)(p.Vc / 256), p.gemm_kind, p.split_acc, false, false, p.off_dhacc, p.off_g});
     std::vector<Step> steps;
-    bool dh_scratch = false;
     for (const RowBlock& k : blocks) {
         const int64_t r0 = (int64_t)k.r0 * 256, block = (int64_t)k.a * 256, chunk = (int64_t)k.b * 256;
         const int64_t rows = (N - r0 < block) ? (N - r0) : block;
-        dh_scratch = dh_scratch || k.acc_in_dh || k.g_in_dh;
         for (int64_t v0 = 0; v0 < V; v0 += chunk) {
             const int64_t cols = (V - v0 < chunk) ? (V - v0) : chunk;
             steps.push_back({r0, rows, v0, cols, (int)((rows + 255) / 256), (int)((cols + 255) / 256), v0 == 0, v0 + cols >= V,
@@ -1567,7 +1565,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
 #undef CCE_LAUNCH_GEMM
         }
     }
-    if (cc && dh_scratch) cc->zero_skipped(stream, dHidden);      // scratch was kept in the zeros of the skipped rows
+    if (cc && order_uses_dhidden(p, sc)) cc->zero_skipped(stream, dHidden);
     if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
     return CCE_OK;
 }
@@ -1719,11 +1717,13 @@ int cce_backward_compact_ex(const void* hidden, const void* weight, const int32_
                        (int)(max_valid_rows < N ? max_valid_rows : N), rows_pad, perm, (int32_t*)(ws + p.off_count), status,
                        (float*)nullptr, (float*)nullptr, (uint16_t*)(ws + p.off_zero_row), (int)D);
     {
-        const unsigned g_gather = (unsigned)((rows_pad + 255) / 256), g_zero = (unsigned)((N + 3) / 4);
+        // (dHidden's rows that take no part become zeros here, or behind an order that uses dHidden)
+        uint16_t* zero = order_uses_dhidden(p, cc.order) ? (uint16_t*)nullptr : (uint16_t*)dHidden;
+        const unsigned g_gather = (unsigned)((rows_pad + 255) / 256), g_zero = zero ? (unsigned)((N + 3) / 4) : 0u;
         hipLaunchKernelGGL(compact_prepare_backward_kernel, dim3(g_gather > g_zero ? g_gather : g_zero), dim3(256), 0, stream,
                            (const int32_t*)perm, (const int32_t*)(ws + p.off_count), rows_pad,
                            labels, (int)N, (int)V, ignore_index, labels_c, lse, lse_c, dloss, dloss_c,
-                           (int)D, (uint16_t*)dHidden);
+                           (int)D, zero);
     }
     cc.perm = perm;
     cc.zero_row = ws + p.off_zero_row;

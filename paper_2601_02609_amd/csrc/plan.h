@@ -790,6 +790,15 @@ static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact
     *sc = k.order;
 }
 
+// Row skipping: the order keeps something in dHidden while it runs -- the gathered rows of a single row block,
+// or sums and chunks in front of a row block -- and zeroes the rows that take no part when it is done.
+static bool order_uses_dhidden(const Plan& p, const Schedule& sc) {
+    if (sc.use) return sc.a >= p.TT;
+    for (int i = 0; i < sc.n_blocks; ++i)
+        if (sc.blocks[i].acc_in_dh || sc.blocks[i].g_in_dh) return true;
+    return false;
+}
+
 // Modelled time of the backward that plan_backward would choose in a workspace of the size asked for.
 static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free) {
     Schedule s;
