@@ -50,6 +50,7 @@ static bool check_layout(const Plan& p, int64_t N, int64_t D, int64_t V, int64_t
         }
         CHECK(R == 0);
     }
+    if (B) CHECK(order_uses_dhidden(p, s) == (s.use ? (int64_t)s.a * 256 >= N : s.n_blocks > 0));
     if (!s.use) return false;
     ++used;
     const int64_t block = (int64_t)s.a * 256;
@@ -162,7 +163,41 @@ static void check_planning_cost() {
         }
 }
 
+// What a call runs, as one line of "word=number": rows N of which B = 0 (all) or M take part.
+static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free) {
+    Plan p; Schedule s;
+    const bool compact = M > 0;
+    const int64_t rows = compact ? M : N;
+    if (!make_plan(rows, D, V, &p, compact ? N : 0)) { printf("refused\n"); return; }
+    Plan asked = p;
+    if (compact && M < N) { bool skip; plan_row_skipping(N, D, V, M, 2, &asked, &skip); }
+    plan_backward(&p, rows, D, V, compact, dw_free, workspace_to_ask_for(asked, N, D, V, compact), &s);
+    int chunks = 0, in_dw = 0, part_steps = 0, least_h = 1 << 30, most_h = 0, most_w = 0, sums_dh = 0, chunks_dh = 0;
+    if (s.use) {
+        for (int64_t v = 0; v < V; ++chunks) {
+            const ScheduleChunk c = schedule_chunk(s, D, V - v);
+            const int kh = (int)((c.b + s.split_h - 1) / s.split_h), nh = (int)((c.b + kh - 1) / kh);
+            const int kw = (c.rows + s.split_w - 1) / s.split_w, nw = (c.rows + kw - 1) / kw;
+            least_h = nh < least_h ? nh : least_h; most_h = nh > most_h ? nh : most_h; most_w = nw > most_w ? nw : most_w;
+            in_dw += c.in_tail ? 1 : 0;
+            part_steps += c.rows < s.a ? 1 : 0;
+            v += c.b * 256;
+        }
+    } else {
+        least_h = most_h = most_w = 1;
+        for (int i = 0; i < s.n_blocks; ++i) { sums_dh += s.blocks[i].acc_in_dh; chunks_dh += s.blocks[i].g_in_dh; }
+    }
+    printf("schedule=%d chunks=%d in_dw=%d row_parts=%d parts_h=%d least_parts_h=%d parts_w=%d split_sums=%d row_blocks=%d "
+           "dhidden_blocks=%d sums_in_dhidden=%d chunks_in_dhidden=%d\n",
+           (int)s.use, chunks, in_dw, part_steps, most_h, least_h, most_w, s.use ? s.split_acc : 0, s.use ? (p.TT + s.a - 1) / s.a : 0,
+           s.n_blocks, sums_dh, chunks_dh);
+}
+
 int main(int argc, char** argv) {
+    if (argc > 2) {                          // N D V M dw_free, any number of times
+        for (int i = 1; i + 4 < argc; i += 5) print_form(atoll(argv[i]), atoll(argv[i + 1]), atoll(argv[i + 2]), atoll(argv[i + 3]), atoi(argv[i + 4]) != 0);
+        return 0;
+    }
     const int iters = argc > 1 ? atoi(argv[1]) : 2000;
     check_makespan();
     check_planning_cost();

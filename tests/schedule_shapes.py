@@ -1,0 +1,55 @@
+"""Shapes whose backward runs in an order of its own (csrc/plan.h), and what that order has to contain: read
+by test_schedule_gpu.py, which runs them, and by test_schedule_host.py, which asks the planner whether they
+still take those orders.  "rows": dW overwritten, "accumulate": added to, "compact": row skipping with the
+exact count of valid rows, one in five ignored (one in seven in AGAINST_FORCED).
+
+Words (least values): chunks of the vocabulary, in_dw of them in unwritten rows of dW, row_parts chunks taken in steps over
+part of the rows, parts_h / parts_w K parts of dH / dW, varied (a chunk with fewer dH parts than another),
+split_sums (dH sums in two planes), row_blocks, dhidden_blocks (row blocks from the last to the first) with
+sums_in_dhidden / chunks_in_dhidden."""
+
+# against the fp64 oracle
+AGAINST_ORACLE = {
+    (300, 64, 30011): dict(rows=dict(parts_h=8), accumulate=dict(parts_h=8), compact=dict(parts_h=8)),
+    (80, 512, 30000): dict(rows=dict(parts_h=8), accumulate=dict(parts_h=8), compact=dict(parts_h=8)),       # one row tile
+    (900, 1088, 9001): dict(rows=dict(parts_h=2), accumulate=dict(parts_h=2), compact=dict(parts_h=2)),      # D not a multiple of the tile
+    (3000, 64, 1100): dict(rows=dict(parts_w=2), accumulate=dict(parts_w=2), compact=dict(parts_w=2)),       # ragged last part
+    (9000, 64, 300): dict(rows=dict(parts_w=8), accumulate=dict(parts_w=8), compact=dict(parts_w=2, row_blocks=2)),
+    (5000, 128, 700): dict(rows=dict(parts_w=4), accumulate=dict(parts_w=4), compact=dict(parts_w=4)),
+    (2445, 256, 8265): dict(rows=dict(row_blocks=2, parts_h=2)),
+    (3712, 64, 28036): dict(rows=dict(chunks=3, parts_h=4, parts_w=2, varied=1)),
+    (323, 896, 54016): dict(rows=dict(chunks=2, in_dw=1, parts_h=2)),
+    (707, 384, 30095): dict(compact=dict(chunks=2, parts_h=4, varied=1)),
+}
+
+# against the same call with forced 16 x 16 tiles
+AGAINST_FORCED = {
+    (509, 896, 151936): dict(rows=dict(chunks=3, in_dw=2, parts_h=4), accumulate=dict(chunks=3, parts_h=4), compact=dict(chunks=3, in_dw=2, parts_h=4)),
+    (8001, 896, 150001): dict(rows=dict(chunks=10, in_dw=8, row_parts=2, split_sums=1), compact=dict(chunks=10, in_dw=8, row_parts=2)),
+    (7500, 640, 90001): dict(rows=dict(chunks=10, in_dw=8, row_parts=2, split_sums=1), compact=dict(chunks=10, in_dw=8, row_parts=2)),
+    (12001, 4096, 8001): dict(rows=dict(dhidden_blocks=2, sums_in_dhidden=1, chunks_in_dhidden=1),
+                              accumulate=dict(dhidden_blocks=2, sums_in_dhidden=1, chunks_in_dhidden=1),
+                              compact=dict(dhidden_blocks=2, sums_in_dhidden=1, chunks_in_dhidden=1)),
+}
+
+
+def n_ignored(N, against_forced=False):
+    return N // 7 if against_forced else int(round(0.2 * N))
+
+
+def drawn(case):
+    """One of the seeded calls of test_random_schedules: sizes at which the planner leaves its own tiling, the loss
+    variants, both forms of the backward; nothing forced."""
+    import numpy as np
+    rng = np.random.default_rng(6100 + case)
+    while True:
+        N, V = (int(np.exp(rng.uniform(np.log(lo), np.log(hi)))) for lo, hi in ((40, 9000), (300, 90000)))
+        D = 64 * int(rng.integers(1, 17))
+        if 2e8 <= N * D * V <= 1.6e10:
+            break
+    return dict(N=N, D=D, V=V, frac=float(rng.choice([0.0, 0.1, 0.4])), skip=bool(rng.integers(0, 2)), slack=int(rng.integers(0, 3)),
+                eps=float(rng.choice([0.0, 0.1])), lam=float(rng.choice([0.0, 1e-3])), mean=bool(rng.integers(0, 2)),
+                accumulate=bool(rng.integers(0, 2)))
+
+
+N_DRAWN = 24
