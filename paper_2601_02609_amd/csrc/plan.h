@@ -465,17 +465,22 @@ static inline ScheduleChunk schedule_chunk(const ScheduleSteps& sc, int64_t D, i
 // 896 x 151936 in steps of 16 x 16 tiles 7.47 ms modelled, 7.33 measured; of 32 x 32 6.3 and 6.45.)
 struct ScheduleModel {
     int cus; int64_t D; GemmTile tile;
-    bool mapped = false;        // the dW job reads hidden rows through the row map: 0.85 us a slice against 0.76
+    bool mapped;                // the dW job reads hidden rows through the row map: 0.85 us a slice against 0.76
+    int64_t dt;                 // output tiles across D
+    ScheduleModel() = default;
+    ScheduleModel(int cus_, int64_t D_, GemmTile tile_, bool mapped_ = false)
+        : cus(cus_), D(D_), tile(tile_), mapped(mapped_), dt((D_ + tile_.bn - 1) / tile_.bn) {}
+    // (32-bit divisions: a search makes tens of thousands of them, and 64-bit ones take twice as long)
+    static int64_t ceil_div(int64_t a, int64_t b) { return (int64_t)(((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b); }
     double slice() const { return tile.kind == 0 ? 1.58 : 0.79; }
     double item(int64_t slices, bool beta) const { return (double)slices * slice() + (tile.kind == 0 ? 13.0 : 9.0) + (beta ? 2.0 : 0.0); }
-    int64_t d_tiles() const { return (D + tile.bn - 1) / tile.bn; }
+    int64_t d_tiles() const { return dt; }
     double logit_tile() const { return (double)(D / 64) * 1.55 + 7.0; }
     // One step over a x b tiles.  FLOOR: with makespan_floor.
     template <bool FLOOR = false>
     double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta) const {
-        const int64_t dt = d_tiles();
-        const int64_t kh = (b + split_h - 1) / split_h, kw = (a + split_w - 1) / split_w;       // K tiles per part
-        const int64_t n_dh = a * dt * ((b + kh - 1) / kh), n_dw = b * dt * ((a + kw - 1) / kw);
+        const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);       // K tiles per part
+        const int64_t n_dh = a * dt * ceil_div(b, kh), n_dw = b * dt * ceil_div(a, kw);
         const double c_dh = item(kh * 4, dh_beta), c_dw = item(kw * 4, dw_beta) + (mapped ? (double)(kw * 4) * 0.11 * slice() : 0.0);
         const double mk = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
         const double g = (double)(a * b) * 131072.0, w = (double)b * 512.0 * (double)D;
@@ -490,10 +495,10 @@ struct ScheduleModel {
     // at most `b_max`: all work spread evenly, the serial reduction of one item per step or all bytes at the rate
     // of HBM, and what each step costs by itself.
     double floor_us(int64_t a, int64_t b, int64_t b_max, int split_h, int split_w) const {
-        const double ab = (double)(a * b), dt = (double)d_tiles(), per_item = item(0, false);
-        const double steps = (double)((b + b_max - 1) / b_max);
-        const int64_t kh = (b + split_h - 1) / split_h, kw = (a + split_w - 1) / split_w;
-        double even = (8.0 * ab * dt * slice() + ((double)(b * ((a + kw - 1) / kw)) + (double)a * steps) * dt * per_item) / (double)cus;
+        const double ab = (double)(a * b), per_item = item(0, false);
+        const double steps = (double)ceil_div(b, b_max);
+        const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);
+        double even = (8.0 * ab * (double)dt * slice() + ((double)(b * ceil_div(a, kw)) + (double)a * steps) * (double)dt * per_item) / (double)cus;
         const double dh_item = (double)(kh * 4) * slice() + steps * per_item, dw_item = steps * item(kw * 4, false);
         if (dh_item > even) even = dh_item;
         if (dw_item > even) even = dw_item;
@@ -505,9 +510,9 @@ struct ScheduleModel {
     }
     // The part of it that grows with the width, per vocabulary tile.
     double floor_per_tile(int64_t a, int64_t b_max) const {
-        const double dt = (double)d_tiles(), per_item = item(0, false), steps = 1.0 / (double)b_max;
+        const double per_item = item(0, false), steps = 1.0 / (double)b_max;
         return (double)a * logit_tile() / (double)cus + 8.0 * steps +
-               (8.0 * (double)a * dt * slice() + (1.0 + (double)a * steps) * dt * per_item) / (double)cus;
+               (8.0 * (double)a * (double)dt * slice() + (1.0 + (double)a * steps) * (double)dt * per_item) / (double)cus;
     }
 };
 
@@ -637,6 +642,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     if (limit < best.us) best.us = limit;
     const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+    const ScheduleModel models[2] = {{cus, D, gemm_tile_of_kind(0)}, {cus, D, gemm_tile_of_kind(1)}};
     // What the steps of a chunk over all rows take, in 1 ... 4 row parts: many orders share such chunks
     // (from eight row tiles on, where row parts are tried).
     constexpr int kKnown = 64;
@@ -644,7 +650,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     const bool keep = TT >= 8;
     if (keep) memset(chunk_us, 0, sizeof chunk_us);
     auto try_one = [&](int kind, int a, int bcap, int sh, int sw, int row_parts, int b_min, int split_acc) {
-        const ScheduleModel m{cus, D, gemm_tile_of_kind(kind)};
+        const ScheduleModel& m = models[kind];
         ScheduleSteps sc = {};
         sc.kind = kind; sc.a = a; sc.split_h = sh; sc.split_w = sw;
         sc.b = bcap < VT ? bcap : VT;
@@ -709,7 +715,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     };
     if (!p.forced) {
         for (int kind = 0; kind < 2; ++kind) {
-            const ScheduleModel m{cus, D, gemm_tile_of_kind(kind)};
+            const ScheduleModel& m = models[kind];
             const int64_t dt = (D + gemm_tile_of_kind(kind).bn - 1) / gemm_tile_of_kind(kind).bn;
             if (kind == 0 && dt * 256 * 7 > D * 8) continue;           // more than an eighth of the columns wasted
             for (int sh : splits) {
@@ -763,31 +769,56 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
 }
 
 // The layout and order of a backward whose workspace has `workspace_bytes` (at least p->total): *p becomes
-// the layout with room for planes where the workspace holds it and a schedule on it is rated 10 % faster.
+// the layout with room for planes where the workspace holds it and schedules on it are rated 10 % faster in
+// both forms of the backward.  (Where only one form is rated so the model is not sure enough: of 13 such
+// shapes added to dW, nine gained 5 ... 28 % on the larger layout and 40 x 2240 x 108256 and 58 x 1408 x 95496 lost 3 and 5.)
 // Kept per thread for the last shapes, the oldest goes first.
 static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc) {
     Plan roomy;
     const bool room = room_for_planes(*p, D, &roomy) && roomy.total <= workspace_bytes;
-    const int cus = device_cu_count();
-    struct Key { int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, dw_free, room, valid; Plan plan; Schedule order; };
-    constexpr int kCached = 24;
+    const int cus = device_cu_count(), f = dw_free ? 1 : 0;
+    // chosen: basic or roomy (or not decided); order[form] of the chosen layout, or of the basic one before that
+    enum Layout { kOpen, kBasic, kRoomy };
+    struct Key {
+        int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, room, valid;
+        Layout layout; bool have[2]; Schedule order[2];
+    };
+    constexpr int kCached = 16;
     static thread_local Key cache[kCached] = {};
     static thread_local int cache_next = 0;
-    for (const Key& k : cache)
-        if (k.valid && k.N == N && k.D == D && k.V == V && k.total == p->total && k.budget == p->budget && k.cus == cus &&
-            k.forced == p->forced && k.compact == compact && k.dw_free == dw_free && k.room == room) { *p = k.plan; *sc = k.order; return; }
-    Key& k = cache[cache_next];
-    cache_next = (cache_next + 1) % kCached;
-    k.N = N; k.D = D; k.V = V; k.total = p->total; k.budget = p->budget; k.cus = cus;
-    k.forced = p->forced; k.compact = compact; k.dw_free = dw_free; k.room = room; k.valid = true;
-    k.plan = *p;
-    make_schedule(*p, N, D, V, compact, dw_free, &k.order);
-    if (room) {
-        make_schedule(roomy, N, D, V, compact, dw_free, sc, 0.9 * k.order.us);
-        if (sc->use) { k.plan = roomy; k.order = *sc; }
+    Key* k = nullptr;
+    for (Key& c : cache)
+        if (c.valid && c.N == N && c.D == D && c.V == V && c.total == p->total && c.budget == p->budget && c.cus == cus &&
+            c.forced == p->forced && c.compact == compact && c.room == room) k = &c;
+    if (!k) {
+        k = &cache[cache_next];
+        cache_next = (cache_next + 1) % kCached;
+        k->N = N; k->D = D; k->V = V; k->total = p->total; k->budget = p->budget; k->cus = cus;
+        k->forced = p->forced; k->compact = compact; k->room = room; k->valid = true;
+        k->layout = room ? kOpen : kBasic;
+        k->have[0] = k->have[1] = false;
     }
-    *p = k.plan;
-    *sc = k.order;
+    auto basic = [&](int form) {
+        if (!k->have[form]) make_schedule(*p, N, D, V, compact, form != 0, &k->order[form]);
+        k->have[form] = true;
+    };
+    if (k->layout != kRoomy) basic(f);
+    if (k->layout == kOpen) {
+        Schedule own, other;
+        make_schedule(roomy, N, D, V, compact, f != 0, &own, 0.9 * k->order[f].us);
+        k->layout = kBasic;
+        if (own.use) {
+            basic(1 - f);
+            make_schedule(roomy, N, D, V, compact, f == 0, &other, 0.9 * k->order[1 - f].us);
+            if (other.use) {
+                k->layout = kRoomy;
+                k->order[f] = own;
+                k->order[1 - f] = other;
+            }
+        }
+    }
+    if (k->layout == kRoomy) *p = roomy;
+    *sc = k->order[f];
 }
 
 // Row skipping: the order keeps something in dHidden while it runs -- the gathered rows of a single row block,
@@ -820,7 +851,7 @@ static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact,
 static bool skipping_pays(const Plan& plain, const Plan& comp, int64_t N, int64_t M, int64_t D, int64_t V) {
     const ForwardCost fwd{device_cu_count(), D};
     double least = 1e300, most = 0.0;
-    for (int dw_free = 0; dw_free < 2; ++dw_free) {
+    for (int dw_free = 1; dw_free >= 0 && most < 1.0; --dw_free) {
         const double rated = (backward_us(comp, M, D, V, true, dw_free != 0) + fwd.us(comp) + 15.0) /
                              (backward_us(plain, N, D, V, false, dw_free != 0) + fwd.us(plain));
         least = rated < least ? rated : least;
