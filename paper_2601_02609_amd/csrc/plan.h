@@ -51,7 +51,6 @@ struct Plan {
     int64_t Nb, Vc;             // backward: rows per row block, vocabulary columns per chunk (multiples of 256)
     int gemm_kind;              // backward: output tile of the contractions, 0 = 256 x 256, 1 = 256 x 128
     int split_acc;              // backward: dH running sum as two 16-bit planes (see GemmJob)
-    double model_us;            // modelled time of forward + backward with this plan (ranking only)
     bool small_tiles;           // forward: 128 x 128 tiles, one per workgroup (fwd_vt() splits; FP8 keeps 256 x 256)
     int64_t rows, cols;         // N, V
     int fwd_tt() const { return (int)((rows + 127) / 128); }
@@ -317,11 +316,6 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
         best_a = sa; best_b = sb; best_kind = skind; p->split_acc = 1;
     }
     acc_bytes = p->split_acc ? 2 : 4;
-    {
-        BackwardModel fm{cus, D, gemm_tile_of_kind(0)};
-        const int64_t rounds = ((int64_t)p->TT * p->S + cus - 1) / cus;
-        p->model_us = (p->split_acc ? cost_split : cost_f32) + (double)(rounds * ((p->VT + p->S - 1) / p->S)) * fm.t_tile();
-    }
     p->gemm_kind = best_kind;
     p->Nb = (int64_t)best_a * 256;
     p->Vc = (int64_t)best_b * 256;

@@ -70,7 +70,6 @@ static void check_plan(int64_t N, int64_t D, int64_t V, int64_t budget_rows, boo
             CHECK((double)p.total <= budget + 1.0, "over budget: total=%zu budget=%.0f N=%lld D=%lld V=%lld B=%lld",
                   p.total, budget, (long long)N, (long long)D, (long long)V, (long long)budget_rows);
     }
-    CHECK(p.model_us >= 0.0, "model");
 }
 
 // Every workgroup id of a grid maps to a distinct item inside the grid (a repeated or out-of-range item
