@@ -354,8 +354,9 @@ def main() -> int:
                 "workspace_bytes": int(wso.numel()),
                 "workspace_pct_of_logits": round(100.0 * wso.numel() / B.materialised_logit_bytes(No, Vo), 3),
                 "entry_points": "cce_forward_compact + cce_backward_compact" if skip_o else "cce_forward + cce_backward",
-                "backward_tiling_256": list(B.get_compact_tiling(No, Do, Vo, nv) if skip_o else B.get_backward_tiling(No, Do, Vo)),
-                "backward_gemm_tile": list(B.get_backward_gemm_tile(nv if skip_o else No, Do, Vo)),
+                # the plan's; the backward may run an order of its own (cce_get_backward_tiling in cce.h)
+                "plan_tiling_256": list(B.get_compact_tiling(No, Do, Vo, nv) if skip_o else B.get_backward_tiling(No, Do, Vo)),
+                "plan_gemm_tile": list(B.get_backward_gemm_tile(nv if skip_o else No, Do, Vo)),
                 "steps": 3, "mean_loss": round(float(lo.sum().item()) / max(nv, 1), 5)}
             del wo, Ho, Wo, yo, dlo, wso, lo, so, dHo, dWo
             torch.cuda.empty_cache()
@@ -395,7 +396,7 @@ def main() -> int:
         "rows_computed": int(rows_run),
         "workspace_bytes": int(ws_used.numel()),
         "workspace_pct_of_logits": round(100.0 * ws_used.numel() / B.materialised_logit_bytes(N, V), 3),
-        "backward_tiling_256": list(B.get_compact_tiling(N, D, V, n_valid) if skipping else B.get_backward_tiling(N, D, V)),
+        "plan_tiling_256": list(B.get_compact_tiling(N, D, V, n_valid) if skipping else B.get_backward_tiling(N, D, V)),
         "mean_loss": round(mean_loss, 5),
         "roofline": roofline, "cpu_baseline": cpu, "other_configs": other_configs, "around_the_path_hbm": aux,
         "fp8_variant": fp8, "other_path": other_path, "mfma_peak": peak_info, "matmul_calibration": matmul_cal,

@@ -44,8 +44,9 @@
  *     O(N*D + tile): per-row partial (max, sum-exp, logit-sum) triples, the fp32
  *     dHidden sums of one row block (for large D only their lower halves: the upper
  *     halves then live in dHidden itself until the last vocabulary chunk rounds the
- *     sums to bf16 there) and one bf16 [row block x vocab chunk] gradient chunk; it
- *     never scales with N*V.  Contents are scratch: nothing
+ *     sums to bf16 there; several planes of them where the reduction is cut into
+ *     parts) and one bf16 [row block x vocab chunk] gradient chunk; it is at most 1 %
+ *     of the materialised logits or 48 MB.  Contents are scratch: nothing
  *     needs to survive between forward and backward except what the caller
  *     passes explicitly (lse).
  */
@@ -140,7 +141,8 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
  *                                      (1/N_valid everywhere for a mean loss); entries
  *                                      at ignored rows are never used (may be NaN)
  *   dHidden  out bf16 [N, D]  device   fp32 accumulation, rounded to nearest even (used as
- *                                      scratch for partial sums while the call runs)
+ *                                      scratch while the call runs: partial sums, gradient tiles,
+ *                                      with row skipping a copy of the hidden rows that take part)
  *   dW       out fp32 [V, D]  device   accumulate_dW == 0: overwritten (rows not yet written
  *                                      may hold gradient tiles while the call runs);
  *                                      accumulate_dW != 0: the gradient is added to it
@@ -217,12 +219,15 @@ int cce_set_backward_gemm_tile(int tile_cols);
  * launch); 0 restores the automatic choice (2 only where it buys a better tiling, i.e. large D).
  * Results are bit-identical between the two for the same tiling.  Host state only. */
 int cce_set_backward_accumulator(int mode);
-/* The form (1 or 2) used for this shape.  Host only. */
+/* The form (1 or 2) of this shape's plan; another order of the backward (see cce_get_backward_tiling) has its
+ * own.  Host only. */
 int cce_get_backward_accumulator(int64_t N, int64_t D, int64_t V, int* mode);
 
-/* Rows x columns of the output tile the two gradient contractions use for this shape (256 x 256
- * or 256 x 128; chosen with the tiling, by the same cost model: the narrow tile when a chunk's
+/* Rows x columns of the output tile the two gradient contractions are planned with for this shape
+ * (256 x 256 or 256 x 128; chosen with the tiling, by the same cost model: the narrow tile when a chunk's
  * outputs would otherwise be too few tiles to fill the GPU, or when D is not a multiple of 256).
+ * While nothing is forced, launches of so few 256 x 128 tiles that half of the compute units would have
+ * none use 128 x 128, and another order of the backward has its own tile.
  * Host only; the two outputs are host ints. */
 int cce_get_backward_gemm_tile(int64_t N, int64_t D, int64_t V, int* tile_rows, int* tile_cols);
 

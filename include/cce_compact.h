@@ -9,7 +9,8 @@
  * synchronisation.  A training loop usually has the labels on the host as well (the data loader
  * produced them): given the count of valid rows -- or any upper bound -- these entry points
  * number the valid rows, in order (one label scan), and run the same kernels in that compact
- * row space: the operand loaders reach the hidden rows through the row map (nothing is copied),
+ * row space: the forward's loaders reach the hidden rows through the row map; the backward does the
+ * same or copies them, in order, into dHidden or the workspace first, whichever its order of steps asks for.
  * loss / lse / dHidden go to the original rows.  With a fraction f of ignored rows the MFMA work
  * drops by f; the results are those of cce_forward / cce_backward up to fp32 summation order
  * (the tiling differs), and exactly equal for ignored rows (zeros).
@@ -38,11 +39,12 @@ extern "C" {
 /* Whether the two calls below skip rows for this shape and bound (1) or process all rows like
  * cce_forward / cce_backward (0): skipping costs a label scan and a few small launches, and the
  * smaller row count may tile the launches worse, so it is used only where a time model rates it
- * faster (few ignored rows do not pay).  Host only. */
+ * faster (few ignored rows do not pay).  One answer for backwards that overwrite dW and that add to
+ * it.  Host only. */
 int cce_get_row_skipping(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows, int* skipping);
-/* The backward tiling cce_backward_compact runs for this shape and bound, in 256-wide tiles per
- * gradient chunk like cce_get_backward_tiling (which it equals where rows are not skipped).
- * Host only. */
+/* The tiling cce_backward_compact is planned with for this shape and bound, in 256-wide tiles per
+ * gradient chunk like cce_get_backward_tiling (which it equals where rows are not skipped); as there, the
+ * call may run in another order where that is rated faster.  Host only. */
 int cce_get_compact_tiling(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows,
                            int* row_tiles, int* vocab_tiles);
 /* Tuning / testing aid: 1 = never skip, 2 = skip whenever max_valid_rows < N, 0 = automatic. */
