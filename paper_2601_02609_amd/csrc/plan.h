@@ -369,24 +369,6 @@ static bool room_for_planes(const Plan& p, int64_t D, Plan* q) {
     return true;
 }
 
-// The workspace to ask for.  Every layout that a call with this many rows or fewer can want (same D and V;
-// row skipping: under any bound) fits it, whichever tiling each row count gets: the budget, or the most
-// that a layout for such a problem can hold where that is less.  (Sized by its own layout alone, 356 rows
-// at D = 2048, V = 4000 asked for 48 MB where 1024 rows asked for 17: a workspace made for the largest
-// batch did not serve the last, short one.)
-static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact) {
-    Plan roomy;
-    const size_t own = room_for_planes(p, D, &roomy) ? roomy.total : p.total;
-    if (p.forced) return own;
-    const int64_t TT = (N + 255) / 256, VT = (V + 255) / 256, a = TT < 64 ? TT : 64;
-    const double pairs = (double)N * 12.0 * (double)(2 * VT), sums = (double)a * 256.0 * (double)D * 4.0;
-    const double planes = 15.0 * (double)((N < 4096 ? N : 4096) * D * 4 + 256);
-    const double rows = compact ? 4.0 * (double)(TT * 256 * 4 + 256) + (double)(D * 2 + 512) : 0.0;
-    const double most = 256.0 + 512.0 + pairs + sums + planes + (double)(a * VT) * 131072.0 + rows;
-    const size_t serves = most < (double)p.budget ? (size_t)most : p.budget;
-    return own > serves ? own : serves;
-}
-
 // ------------------------------------------------------------------------------------------
 // Schedules of the backward.  A Plan walks [row block x vocabulary chunk] steps whose gradient
 // chunk and dH sums share 1 % of the logits' size.  Two things make other orders faster where they
@@ -650,6 +632,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         sc.b = bcap < VT ? bcap : VT;
         sc.tail = dw_free && a == TT;
         sc.row_parts = row_parts; sc.b_min = b_min; sc.split_acc = split_acc;
+        if (VT > 4096 * sc.b) return;           // thousands of launches (vocabularies of millions)
         const bool one_chunk = a < TT;          // row blocks: the whole vocabulary in one chunk, no running sums
         if (one_chunk && bcap < VT) return;
         const int64_t rows = (int64_t)a * 256;
@@ -813,6 +796,31 @@ static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact
     }
     if (k->layout == kRoomy) *p = roomy;
     *sc = k->order[f];
+}
+
+// The workspace to ask for.  What a call with this many rows or fewer needs (same D and V; row skipping: under
+// any bound) fits it, whichever tiling each row count gets: the budget, or the most that a plan's layout for such a
+// problem can hold where that is less.  So does, up to the budget's floor, the layout with room for planes; beyond the
+// floor only this call's own is counted, if it would be taken.  (Sized by its own layout alone, 356 rows at
+// D = 2048, V = 4000 asked for 48 MB where 1024 rows asked for 17: a workspace made for the largest batch did not
+// serve the last, short one.)  `p` is the plan for N rows, or with `compact` the one for some of N rows.
+static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact) {
+    if (p.forced) return p.total;
+    Plan roomy, taken = p;
+    Schedule order;
+    const bool room = room_for_planes(p, D, &roomy);
+    if (room && roomy.total > kBudgetFloor) plan_backward(&taken, p.rows, D, V, compact, false, roomy.total, &order);
+    else if (room) taken = roomy;
+    const int64_t TT = (N + 255) / 256, VT = (V + 255) / 256, a = TT < 64 ? TT : 64, b = VT < 128 ? VT : 128;
+    const int64_t splits = 2 * VT < 2 * device_cu_count() ? 2 * VT : 2 * device_cu_count();
+    const double rows = compact ? 4.0 * (double)(TT * 256 * 4 + 256) + (double)(D * 2 + 512) : 0.0;
+    const double sums = 256.0 + 512.0 + (double)N * 12.0 * (double)splits + (double)a * 256.0 * (double)D * 4.0 + rows;
+    const double planes = 15.0 * ((double)(N < 4096 ? N : 4096) * (double)D * 4.0 + 256.0);
+    const double plan_most = sums + (double)(a * b) * 131072.0, room_most = sums + planes + (double)(a * VT) * 131072.0;
+    const size_t plans = plan_most < (double)p.budget ? (size_t)plan_most : p.budget;
+    const size_t rooms = room_most < (double)kBudgetFloor ? (size_t)room_most : kBudgetFloor;
+    const size_t serves = plans > rooms ? plans : rooms;
+    return taken.total > serves ? taken.total : serves;
 }
 
 // Row skipping: the order keeps something in dHidden while it runs -- the gathered rows of a single row block,

@@ -109,8 +109,15 @@ static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
     bool used = check_layout(p, N, D, V, B, dw_free);
     const size_t ask = workspace_to_ask_for(p, B ? B : N, D, V, B != 0);
     CHECK(p.total <= ask);
+    for (int i = 0; i < 3; ++i) {            // any smaller call's own layout fits, and up to the floor its room for planes
+        const int64_t b = B ? pick(1, B) : 0, n = pick(1, B ? b : N);
+        Plan less, less_roomy;
+        CHECK(make_plan(n, D, V, &less, b) && less.total <= ask);
+        if (room_for_planes(less, D, &less_roomy)) CHECK(less_roomy.total <= ask || less_roomy.total > kBudgetFloor);
+    }
     if (room_for_planes(p, D, &roomy)) {
-        CHECK(roomy.total <= ask && roomy.total > p.total && roomy.off_dhacc == p.off_dhacc);
+        CHECK(roomy.total <= ask || roomy.total > kBudgetFloor);
+        CHECK(roomy.total > p.total && roomy.off_dhacc == p.off_dhacc);
         CHECK((roomy.off_g & 255) == 0 && (roomy.off_perm & 255) == 0 && (!B || roomy.off_count - p.off_count == roomy.total - p.total));
         used = check_layout(roomy, N, D, V, B, dw_free) || used;
     }

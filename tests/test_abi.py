@@ -74,6 +74,14 @@ def test_workspace_serves_fewer_rows(L):
             assert max(small) <= min(large), (d, v, compact)
 
 
+def test_workspace_stays_near_what_layouts_hold(L):
+    """1 % of the logits is a bound and not the answer where no layout comes near it: a chunk has at most 64 x 128
+    tiles (1.07 GB) in a plan's layout, whatever the vocabulary."""
+    assert binding.workspace_bytes(5000, 64, 30_000_000) < 0.4e9          # 1 %: 6.0 GB
+    assert binding.workspace_bytes(30000, 64, 1 << 24) < 1.4e9            # 1 %: 20 GB
+    assert binding.workspace_bytes(4096, 64, 33_000_000) < 0.4e9          # at most 16 row tiles: no room for planes is taken here
+
+
 @pytest.mark.parametrize("shape,skips", [
     ((8192, 896, 151936, 6963), True), ((16384, 4096, 32000, 12288), True), ((16384, 2048, 151936, 15565), False),
     ((500, 256, 3000, 300), False), ((8385, 192, 2434, 5031), False),
