@@ -71,7 +71,7 @@ __device__ __forceinline__ int scale_byte(const void* scales, int groups, int ro
 }
 
 template <bool SUMZ, bool FP8, class Cfg = TileBig>
-__global__ __launch_bounds__(kThreads) void lse_partial_kernel(
+__global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_kernel(
         const void* __restrict__ H, const void* __restrict__ W,
         int N, int D, int V, int TT, int VT, int S, float2* __restrict__ partials,
         float* __restrict__ partial_sumz, const Fp8Scales fp8, const int32_t* __restrict__ perm,
@@ -87,15 +87,15 @@ __global__ __launch_bounds__(kThreads) void lse_partial_kernel(
     // Work index -> (token tile, vocabulary split).  The 32 workgroups that share an XCD (and
     // its 4 MB L2) take a panel of 4 token tiles x all splits: per K slice they touch 4 H
     // tiles + S W tiles instead of 32 + 1, which is what keeps most operand fetches in L2.
-    const int lin = xcd_round_id(blockIdx.x, gridDim.x, 256);
+    const int lin = xcd_round_id(blockIdx.x, gridDim.x, 2048 / Cfg::NW);
     int tt, s;
-    group_map(lin, TT, S, 4, tt, s);
+    group_map(lin, TT, S, 32 / Cfg::NW, tt, s);
     const int vt0 = (int)((int64_t)s * VT / S), vt1 = (int)((int64_t)(s + 1) * VT / S);
     const int l = threadIdx.x & 63;
     const int wm = wave_m<Cfg>();
 
     const int ld = FP8 ? D / 2 : D;               // row length in 2-byte units
-    OperandTile<true, Cfg::BN> Bop;
+    OperandTile<true, Cfg::BN, false, Cfg::NW, Cfg::BK> Bop;
     Bop.init(H, ld, tt * Cfg::BN, N, ld, perm);       // perm: token t of the tile space is row perm[t] of H
     ScaleGroup SB;
     const int b_row0 = tt * Cfg::BN + wave_n<Cfg>() * (Cfg::TN * 32);      // this wavefront's first token
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kThreads) void lse_partial_kernel(
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[bm][bn][r] = 0.f;
 
-        OperandTile<true, Cfg::BM> Aop;
+        OperandTile<true, Cfg::BM, false, Cfg::NW, Cfg::BK> Aop;
         Aop.init(W, ld, vt * Cfg::BM, V, ld);
         if constexpr (FP8) {
             ScaleGroup SA;
@@ -379,26 +379,25 @@ __global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict
 // W may be a vocabulary shard: its V rows are the rows [v_off, v_off + V) of a V_total-row
 // matrix, labels index the full one (v_off = 0, V_total = V without sharding).
 // Same orientation as the forward (lane owns a token column).  The tile is staged in LDS as
-// [token][vocab] and written to the scratch chunk G (row-major [rows_pad][ldg], vocab
-// contiguous) with full 512-byte rows.
+// [token][vocab] and written to the scratch chunk G in panels of 1 << panel_shift vocabulary columns (see PanelTile).
 // Grid: one workgroup per tile of the [row block x chunk]; tile index -> (ti, vi).
 // ------------------------------------------------------------------------------------------
 template <bool FP8, class Cfg = TileBig>
-__global__ __launch_bounds__(kThreads) void grad_tile_kernel(
+__global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
         const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
         const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
         int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
         int row0, int n_row_tiles, int v0, int n_v_tiles,
-        uint16_t* __restrict__ G, int ldg, int v_off, int V_total, const Fp8Scales fp8,
+        uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total, const Fp8Scales fp8,
         const int32_t* __restrict__ perm) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
     const int l = threadIdx.x & 63;
     const int wm = wave_m<Cfg>();
 
-    const int lin = xcd_round_id(blockIdx.x, gridDim.x, 256);
+    const int lin = xcd_round_id(blockIdx.x, gridDim.x, 2048 / Cfg::NW);
     int ti, vi;
-    group_map(lin, n_row_tiles, n_v_tiles, 4, ti, vi);          // an XCD works on ~4 x 8 tiles
+    group_map(lin, n_row_tiles, n_v_tiles, 32 / Cfg::NW, ti, vi);          // an XCD works on ~4 x 8 tiles
     const int tok0 = row0 + ti * Cfg::BN;        // first token of the tile (global index)
     const int vt0 = v0 + vi * Cfg::BM;           // first vocabulary row of the tile (global index)
 
@@ -430,8 +429,8 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
         raw_row_y = labels[tok < N ? tok : N - 1];
     }
 
-    OperandTile<true, Cfg::BM> Aop;
-    OperandTile<true, Cfg::BN> Bop;
+    OperandTile<true, Cfg::BM, false, Cfg::NW, Cfg::BK> Aop;
+    OperandTile<true, Cfg::BN, false, Cfg::NW, Cfg::BK> Bop;
     const int ld = FP8 ? D / 2 : D;               // row length in 2-byte units
     Aop.init(W, ld, vt0, V, ld);
     Bop.init(H, ld, tok0, N, ld, perm);           // perm (row skipping): token t is row perm[t] of H
@@ -468,11 +467,11 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
     if (threadIdx.x < Cfg::BN) live_flags[threadIdx.x] = row_live ? 1 : 0;
 
     // Epilogue: softmax gradient, bf16, staged in LDS as [token][vocab] and stored with
-    // full 512-byte rows.  Done in TN phases (the 32 token columns per wavefront of block
+    // whole 128-byte lines of the panels.  Done in TN phases (the 32 token columns per wavefront of block
     // bn): the global stores of one phase drain while the next phase is computed, and the
     // barriers wait for LDS traffic only.
     const bool ragged = vt0 + Cfg::BM > V;                  // only the last vocabulary tile needs column masking
-    constexpr int kChunks = Cfg::BM / 8, kRowsPerPass = kThreads / kChunks;       // 16-byte chunks of a row
+    constexpr int kChunks = Cfg::BM / 8, kRowsPerPass = Cfg::kThreads / kChunks;       // 16-byte chunks of a row
     const int chunk = threadIdx.x % kChunks;
 #pragma unroll
     for (int bn = 0; bn < Cfg::TN; ++bn) {
@@ -521,7 +520,8 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
                 v = *(const CCE_LDS u32x4*)(smem + row * kGRowBytes<Cfg> + chunk * 16);
                 if (row & 8) v = u32x4{v.z, v.w, v.x, v.y};           // undo the half swap of the staging writes
             }
-            *(u32x4*)(G + (size_t)(ti * Cfg::BN + row) * ldg + (size_t)vi * Cfg::BM + chunk * 8) = v;
+            *(u32x4*)(G + (size_t)((vi * Cfg::BM + chunk * 8) >> panel_shift) * panel + ((size_t)(ti * Cfg::BN + row) << panel_shift) +
+              ((chunk * 8) & ((1 << panel_shift) - 1))) = v;
         }
     }
 }
@@ -537,15 +537,8 @@ __global__ __launch_bounds__(kThreads) void grad_tile_kernel(
 // dropped.  The host puts the job with the longer reduction first; xcd_two_job_map deals the items
 // of both jobs to the workgroup ids so that every XCD starts with its share of the long ones.
 // ------------------------------------------------------------------------------------------
-// LDS of grad_gemm_kernel: the main loop's stages or the epilogue staging, whichever is larger.
-constexpr int gemm_lds_bytes(int main_loop, int bm, int bn) {
-    const int one_pass = bm * (bn + 8) * 4;
-    const int staging = one_pass <= 150 * 1024 ? one_pass : 64 * (bn + 8) * 4;
-    return staging > main_loop ? staging : main_loop;
-}
-constexpr int kGemmLdsBig = gemm_lds_bytes(TileBig::kLdsBytes, TileBig::BM, TileBig::BN);
-constexpr int kGemmLdsNarrow = gemm_lds_bytes(TileNarrow::kLdsBytes, TileNarrow::BM, TileNarrow::BN);
-constexpr int kGemmLdsSmall = gemm_lds_bytes(TileSmall::kLdsBytes, TileSmall::BM, TileSmall::BN);
+// LDS of grad_gemm_kernel: the main loop's stages (the exchange between K groups fits them).
+constexpr int kGemmLdsBig = TileBig::kLdsBytes, kGemmLdsNarrow = TileNarrow::kLdsBytes, kGemmLdsSmall = TileSmall::kLdsBytes;
 // Row skipping: the LDS table of one row block's row map (kRowTableBytes, plan.h) sits behind these.
 static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRowTableBytes <= 160 * 1024 && kGemmLdsSmall + kRowTableBytes <= 160 * 1024, "row table must fit the LDS");
 
@@ -570,7 +563,7 @@ static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRo
 // GPU anyway a split only adds plane traffic: the planner (plan.h) prices both.
 struct GemmJob {
     int a_kmajor;               // 1: A is K-major (the dH job), 0: A is K-slow (the dW job)
-    const uint16_t* A; int lda; int a_free_n; int a_k_n;
+    const uint16_t* A; uint32_t panel;           // the gradient chunk, see PanelTile
     const void* B; int ldb; int b_k_n; int k_total;
     int n_tiles; int n_work; int m_valid; int n_valid;
     int n_split; int split_k; float* part; int64_t part_stride;
@@ -585,6 +578,158 @@ struct GemmJob {
 // MODE 4: only the bf16 rows go through row_map (row skipping on a gathered copy of the hidden
 // rows).  Launch-wide constants, compiled as separate kernels so that the plain form carries none
 // of their code.  K split exists in modes 0 and 4.
+// Result of a work item, straight from the accumulators.  A lane holds one column of a 32 x 32 block and, per
+// register, two rows of it lie in a wavefront: a dword store is two full 128-byte segments, so nothing is staged
+// through LDS and only the K groups' exchange needs a barrier.  The 16-bit forms exchange values between neighbouring
+// lanes first (even lanes keep the first of two rows, odd lanes the second), so that a lane again moves one dword:
+// two neighbouring columns of a row.  Bound by the burst of stores and old values that all work items of a round make
+// at once (256 of 256 x 128: 33 MB, 6 us at the rate of HBM) and by the latency of the first of them.  Measured against
+// the tile staged through LDS for 16-byte row accesses, us per launch: 16 x 16 tiles at D = 896 60.2 -> 57.0, at
+// D = 1024 64.2 -> 61.9, 12 x 20 at D = 1024 70.4 -> 65.8, 256 x 256 tiles of 16 x 16 at D = 1024 87.9 -> 85.2; only the
+// planes of the split running sum lose (64-byte segments: items of 96 slices 101.1 -> 101.8).
+template <class Cfg, bool A_KMAJOR, int MODE>
+__device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], const GemmJob& j, float* out, bool beta, int mi, int ni,
+                                             CCE_LDS char* smem) {
+    constexpr bool SPLIT = A_KMAJOR && (MODE & 1) != 0, ROWMAP = A_KMAJOR && (MODE & 6) != 0;
+    constexpr int KG = Cfg::KG, NB = Cfg::TM / KG;              // 32-row bands that a wavefront stores
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), l = threadIdx.x & 63;
+    const int kg = wave / (Cfg::WM * Cfg::WN), wm = wave % (Cfg::WM * Cfg::WN) / Cfg::WN, wn = wave % Cfg::WN;
+    const int row0 = mi * Cfg::BM + wm * (Cfg::TM * 32), col0 = ni * Cfg::BN + wn * (Cfg::TN * 32);
+    const bool inside = col0 < j.n_valid;                       // all columns of a wavefront or none (n_valid is a multiple of 64)
+    const uint32_t ld = (uint32_t)j.ld_out;
+    // fp32 form: this lane's column, its four-row half; 16-bit forms: its pair of columns, its row of the pair
+    const uint32_t lane_off = (uint32_t)(4 * (l >> 5)) * ld + (uint32_t)(l & 31);
+    const int pair_row = 4 * (l >> 5) + (l & 1), pair_col = l & 30;
+    auto block_row = [](int r) { return 8 * (r >> 2) + (r & 3); };         // of register r, without the lane's half
+
+    auto run = [&](auto first, auto full) {
+        constexpr int B0 = decltype(first)::value;
+        constexpr bool FULL = decltype(full)::value;
+        float old[2][Cfg::TN][16];                              // split form: 8 words of upper halves, 8 of lower halves
+        int orow[2][8];                                         // split form: out_hi row of each register pair
+        auto fetch = [&](int set, int bm) {
+            const int brow = row0 + bm * 32;
+            if constexpr (SPLIT) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int row = brow + block_row(2 * i) + pair_row;
+                    orow[set][i] = row < j.m_valid ? (ROWMAP ? j.row_map[row] : row) : -1;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < (SPLIT ? 8 : 16) * Cfg::TN; ++i) {
+                const int r = SPLIT ? i % 8 : i / Cfg::TN, bn = SPLIT ? i / 8 : i % Cfg::TN;
+                if constexpr (SPLIT) {
+                    const int row = brow + block_row(2 * r) + pair_row, col = col0 + bn * 32 + pair_col;
+                    const bool ok = row < j.m_valid && beta;
+                    old[set][bn][r] = ok && orow[set][r] >= 0 ? *(const float*)(j.out_hi + (size_t)orow[set][r] * ld + col) : 0.f;
+                    old[set][bn][8 + r] = ok ? *(const float*)(j.out_lo + (size_t)row * ld + col) : 0.f;
+                } else {
+                    const float* p = out + (size_t)(brow + block_row(r)) * ld + col0 + bn * 32;
+                    old[set][bn][r] = FULL || brow + block_row(r) + 4 * (l >> 5) < j.m_valid ? p[lane_off] : 0.f;
+                }
+            }
+        };
+        if (inside && (beta || SPLIT)) fetch(0, B0);
+        if constexpr (KG == 2) {
+            // the two K groups hold partial sums of the same positions: each hands the blocks that it does not store to
+            // its partner, a lane's registers to the same lane
+            constexpr int O0 = B0 == 0 ? NB : 0;
+            CCE_LDS char* mine = smem + (size_t)(wave * 16384 + l * 16);
+#pragma unroll
+            for (int b = 0; b < NB * Cfg::TN; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x16& v = acc[O0 + b / Cfg::TN][b % Cfg::TN];
+                    *(CCE_LDS f32x4*)(mine + (b * 4 + q) * 1024) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+                }
+            if (inside && (beta || SPLIT)) fetch(1, B0 + 1);                // (NB = 2; the blocks handed over are free)
+            barrier_lds_only();
+        }
+        if (!inside) return;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int bm = B0 + b, brow = row0 + bm * 32;
+            __builtin_amdgcn_sched_barrier(0);                  // keeps the next band's registers out of this one
+            if (KG == 1 && (beta || SPLIT) && b + 1 < NB) fetch((b + 1) & 1, bm + 1);
+            // the blocks beside each other at once: a longer run of every row (one by one with the planes, whose old values
+            // take the registers)
+            constexpr int STEP = SPLIT ? 1 : Cfg::TN;
+#pragma unroll
+            for (int bn0 = 0; bn0 < Cfg::TN; bn0 += STEP) {
+                float v[Cfg::TN][16];
+#pragma unroll
+                for (int bn = bn0; bn < bn0 + STEP; ++bn) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) v[bn][r] = acc[bm][bn][r];
+                    if constexpr (KG == 2) {
+                        const CCE_LDS char* theirs = smem + (size_t)((wave ^ (Cfg::WM * Cfg::WN)) * 16384 + l * 16);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const f32x4 t = *(const CCE_LDS f32x4*)(theirs + ((b * Cfg::TN + bn) * 4 + q) * 1024);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[bn][4 * q + e] += t[e];
+                        }
+                    }
+                    if (!SPLIT && beta) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) v[bn][r] += old[b & 1][bn][r];
+                    }
+                }
+                if (!SPLIT && !(A_KMAJOR && j.final)) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+#pragma unroll
+                        for (int bn = bn0; bn < bn0 + STEP; ++bn) {
+                            float* p = out + (size_t)(brow + block_row(r)) * ld + col0 + bn * 32;
+                            if (FULL || brow + block_row(r) + 4 * (l >> 5) < j.m_valid) p[lane_off] = v[bn][r];
+                        }
+                    continue;
+                }
+                if constexpr (A_KMAJOR) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int row = brow + block_row(2 * i) + pair_row;
+                        int to;
+                        if constexpr (SPLIT) to = orow[b & 1][i];
+                        else to = row < j.m_valid ? (ROWMAP ? j.row_map[row] : row) : -1;
+#pragma unroll
+                        for (int bn = bn0; bn < bn0 + STEP; ++bn) {
+                            const int col = col0 + bn * 32 + pair_col;
+                            // even lanes: (own, neighbour's) of register 2i; odd lanes: (neighbour's, own) of register 2i + 1
+                            const float give = (l & 1) ? v[bn][2 * i] : v[bn][2 * i + 1];
+                            const float got = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give), 0xB1, 0xF, 0xF, true));
+                            float x = (l & 1) ? got : v[bn][2 * i], y = (l & 1) ? v[bn][2 * i + 1] : got;
+                            if constexpr (SPLIT) {
+                                const uint32_t hi = __builtin_bit_cast(uint32_t, old[b & 1][bn][i]), lo = __builtin_bit_cast(uint32_t, old[b & 1][bn][8 + i]);
+                                x += __builtin_bit_cast(float, (hi << 16) | (lo & 0xffffu));
+                                y += __builtin_bit_cast(float, (hi & 0xffff0000u) | (lo >> 16));
+                            }
+                            if (j.final) {
+                                union { __bf16 h[2]; uint32_t u; } cv;
+                                cv.h[0] = (__bf16)x;
+                                cv.h[1] = (__bf16)y;
+                                if (to >= 0) *(uint32_t*)(j.out_hi + (size_t)to * ld + col) = cv.u;
+                            } else {
+                                const uint32_t bx = __builtin_bit_cast(uint32_t, x), by = __builtin_bit_cast(uint32_t, y);
+                                if (to >= 0) *(uint32_t*)(j.out_hi + (size_t)to * ld + col) = (by & 0xffff0000u) | (bx >> 16);
+                                if (row < j.m_valid) *(uint32_t*)(j.out_lo + (size_t)row * ld + col) = (by << 16) | (bx & 0xffffu);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+    };
+    const bool full = row0 + Cfg::TM * 32 <= j.m_valid;
+    auto with_rows = [&](auto first) {
+        if (full) run(first, std::true_type{});
+        else run(first, std::false_type{});
+    };
+    if (KG == 1 || kg == 0) with_rows(std::integral_constant<int, 0>{});
+    else with_rows(std::integral_constant<int, Cfg::TM / 2>{});
+}
+
 template <class Cfg, bool A_KMAJOR, int MODE>
 __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS char* smem) {
     constexpr bool KSPLIT = (MODE & 3) == 0;
@@ -609,161 +754,31 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
             for (int r = 0; r < 16; ++r) acc[bm][bn][r] = 0.f;
 
     constexpr bool kMappedB = (MODE & 2) != 0 && !A_KMAJOR;        // row skipping, dW job
-    OperandTile<A_KMAJOR, Cfg::BM> Aop;
-    OperandTile<false, Cfg::BN, kMappedB> Bop;
-    Aop.init(j.A + (A_KMAJOR ? (size_t)k0 : (size_t)k0 * j.lda), j.lda, mi * Cfg::BM, j.a_free_n, j.a_k_n - k0);
+    PanelTile<A_KMAJOR, Cfg::BM, Cfg::NW, Cfg::BK> Aop;
+    OperandTile<false, Cfg::BN, kMappedB, Cfg::NW, Cfg::BK> Bop;
+    Aop.init(j.A, j.panel, mi * Cfg::BM, k0);
     Bop.init((const uint16_t*)j.B + (size_t)k0 * j.ldb, j.ldb, ni * Cfg::BN, j.n_valid, j.b_k_n - k0);
     if constexpr ((MODE & 2) != 0 && !A_KMAJOR) {
         // row skipping, dW job: the reduction runs over the compact rows of the block, whose hidden
         // rows are scattered over the original tensor.  The block's row map is copied into LDS
         // (behind everything the kernel otherwise uses) and the operand loader looks each of its
         // k-rows up there.  (The host gives every row-skipping launch its row map.)
-        CCE_LDS int32_t* tab = (CCE_LDS int32_t*)(smem + gemm_lds_bytes(Cfg::kLdsBytes, Cfg::BM, Cfg::BN));
-        for (int i = threadIdx.x; i < j.b_k_n; i += kThreads) tab[i] = j.row_map[i];
+        CCE_LDS int32_t* tab = (CCE_LDS int32_t*)(smem + Cfg::kLdsBytes);
+        for (int i = threadIdx.x; i < j.b_k_n; i += Cfg::kThreads) tab[i] = j.row_map[i];
         __syncthreads();
         Bop.kmap = tab;
         Bop.kzero = j.zero_row;
     }
+    // Whatever the compiler loaded so far has to be there: it cannot see the main loop's loads, and a register still
+    // waited for inside the loop (a field of the job, say) becomes a wait for all of them in every slice.
+    __builtin_amdgcn_s_waitcnt(0x0f70);                          // vmcnt(0)
     gemm_mainloop<Cfg, A_KMAJOR, false, true>(acc, Aop, Bop, k_len, smem);
 
-    // Epilogue through LDS so that global memory sees 16-byte accesses along full rows:
-    // the fp32 tile is staged [rows][BN + 8 floats] (the padding keeps the two 128-byte
-    // row segments a wavefront writes per instruction in different halves of the banks),
-    // 64 rows at a time when the whole tile does not fit (which also keeps the number of
-    // chunks a thread holds per pass, and with it the register pressure, small).
-    constexpr int kPasses = (Cfg::BM * (Cfg::BN + 8) * 4 <= 150 * 1024) ? 1 : Cfg::BM / 64;
-    constexpr int kRowsPerPass = Cfg::BM / kPasses;
-    constexpr int kRowBytes = (Cfg::BN + 8) * 4;
-    constexpr int kChunksPerRow = Cfg::BN / 4;                 // 16-byte chunks
-    constexpr int kRowsPerIter = kThreads / kChunksPerRow;
-    constexpr int kIters = kRowsPerPass / kRowsPerIter;        // chunks per thread and pass
-    static_assert(kThreads % kChunksPerRow == 0 && kRowsPerPass % kRowsPerIter == 0, "whole rows per iteration");
-    static_assert(kRowsPerPass * kRowBytes <= 160 * 1024, "epilogue staging must fit the LDS");
-    static_assert(Cfg::KG == 1 || kPasses == 1, "K-group reduction shares the one-pass staging");
-    const int wave_row0 = wave_m<Cfg>() * (Cfg::TM * 32);
-    // this thread's chunks of a pass: rows it * kRowsPerIter + threadIdx.x / kChunksPerRow
-    const int my_chunk = threadIdx.x % kChunksPerRow, my_row = threadIdx.x / kChunksPerRow;
-    const int col = ni * Cfg::BN + my_chunk * 4;
-    const bool col_ok = col < j.n_valid;                       // n_valid is a multiple of 8: whole chunks
-
-    // When the tile is added to what the output already holds, those values are fetched
-    // as early as possible -- all chunks of a pass at once, right after the main loop /
-    // the previous pass -- so that their latency hides under the staging through LDS
-    // (whose barriers wait for LDS traffic only).
-    // (split form: words 0-1 of old[] hold the upper-half plane, words 2-3 the lower-half plane)
-    constexpr bool SPLIT = (MODE & 1) != 0, ROWMAP = (MODE & 6) != 0;
-    const bool split = SPLIT && j.out_lo != nullptr;
-    // row of out_hi that tile row `row` goes to (-1: a padding row of the compact row space)
-    auto hi_row = [&](int row) { return ROWMAP && j.row_map ? j.row_map[row] : row; };
-    f32x4 old[kIters];
-    auto fetch_old = [&](int pr0) {
-#pragma unroll
-        for (int it = 0; it < kIters; ++it) {
-            const int row = mi * Cfg::BM + pr0 + it * kRowsPerIter + my_row;
-            old[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (beta && col_ok && row < j.m_valid) {
-                if (split) {
-                    const int orow = hi_row(row);
-                    const u32x2 hi = orow >= 0 ? *(const u32x2*)(j.out_hi + (size_t)orow * j.ld_out + col) : u32x2{0u, 0u};
-                    const u32x2 lo = *(const u32x2*)(j.out_lo + (size_t)row * j.ld_out + col);
-                    old[it] = __builtin_bit_cast(f32x4, u32x4{hi.x, hi.y, lo.x, lo.y});
-                } else {
-                    old[it] = *(const f32x4*)(out_f32 + (size_t)row * j.ld_out + col);
-                }
-            }
-        }
-    };
-    // the four fp32 values of a chunk from its two planes
-    auto join_planes = [](const f32x4 planes) {
-        const u32x4 w = __builtin_bit_cast(u32x4, planes);
-        const u32x4 bits = {(w.x << 16) | (w.z & 0xffffu), (w.x & 0xffff0000u) | (w.z >> 16),
-                            (w.y << 16) | (w.w & 0xffffu), (w.y & 0xffff0000u) | (w.w >> 16)};
-        return __builtin_bit_cast(f32x4, bits);
-    };
-    fetch_old(0);
-
-    if (Cfg::KG == 2) {
-        // The two K groups hold partial sums of the same positions.  Each wavefront finalises half
-        // of its blocks (K group g the blocks bm with bm / (TM / 2) == g): it hands the other half
-        // to its partner through the staging area, at the positions the sums end up in, then adds
-        // what the partner left at its own positions and puts the sums there, in place (a lane
-        // reads and rewrites its own words only).  All eight wavefronts work in both steps; a + b
-        // is the same value whichever group adds.
-        static_assert(Cfg::KG == 1 || Cfg::TM % 2 == 0, "blocks split evenly between the K groups");
-        const int kg = wave_kg<Cfg>();
-#pragma unroll
-        for (int bm = 0; bm < Cfg::TM; ++bm) {
-            if (bm / (Cfg::TM / 2) == kg) continue;
-#pragma unroll
-            for (int bn = 0; bn < Cfg::TN; ++bn)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    *(CCE_LDS float*)(smem + acc_row<Cfg>(bm, r) * kRowBytes + acc_col<Cfg>(bn) * 4) = acc[bm][bn][r];
-        }
-        barrier_lds_only();
-#pragma unroll
-        for (int bm = 0; bm < Cfg::TM; ++bm) {
-            if (bm / (Cfg::TM / 2) != kg) continue;
-#pragma unroll
-            for (int bn = 0; bn < Cfg::TN; ++bn)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    CCE_LDS float* pos = (CCE_LDS float*)(smem + acc_row<Cfg>(bm, r) * kRowBytes + acc_col<Cfg>(bn) * 4);
-                    *pos = acc[bm][bn][r] + *pos;
-                }
-        }
-    }
-#pragma unroll
-    for (int pass = 0; pass < kPasses; ++pass) {
-        const int pr0 = pass * kRowsPerPass;
-        if (Cfg::KG == 1) {
-#pragma unroll
-            for (int bm = 0; bm < Cfg::TM; ++bm) {
-                const int brow = wave_row0 + bm * 32;           // the 32-row block lies in one pass
-                if (brow < pr0 || brow >= pr0 + kRowsPerPass) continue;
-#pragma unroll
-                for (int bn = 0; bn < Cfg::TN; ++bn)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        *(CCE_LDS float*)(smem + (acc_row<Cfg>(bm, r) - pr0) * kRowBytes + acc_col<Cfg>(bn) * 4) = acc[bm][bn][r];
-            }
-        }
-        barrier_lds_only();
-        f32x4 v[kIters];
-#pragma unroll
-        for (int it = 0; it < kIters; ++it)
-            v[it] = *(const CCE_LDS f32x4*)(smem + (it * kRowsPerIter + my_row) * kRowBytes + my_chunk * 16) +
-                    (split ? join_planes(old[it]) : old[it]);
-#pragma unroll
-        for (int it = 0; it < kIters; ++it) {
-            const int row = mi * Cfg::BM + pr0 + it * kRowsPerIter + my_row;
-            if (!col_ok || row >= j.m_valid) continue;
-            if (j.final) {
-                union { __bf16 h[4]; u32x2 u; } cv;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) cv.h[e] = (__bf16)v[it][e];
-                const int orow = hi_row(row);
-                if (orow >= 0) *(u32x2*)(j.out_hi + (size_t)orow * j.ld_out + col) = cv.u;
-            } else if (!split) {
-                *(f32x4*)(out_f32 + (size_t)row * j.ld_out + col) = v[it];
-            } else {
-                const u32x4 b = __builtin_bit_cast(u32x4, v[it]);
-                const u32x2 hi = {(b.y & 0xffff0000u) | (b.x >> 16), (b.w & 0xffff0000u) | (b.z >> 16)};
-                const u32x2 lo = {(b.y << 16) | (b.x & 0xffffu), (b.w << 16) | (b.z & 0xffffu)};
-                const int orow = hi_row(row);
-                if (orow >= 0) *(u32x2*)(j.out_hi + (size_t)orow * j.ld_out + col) = hi;
-                *(u32x2*)(j.out_lo + (size_t)row * j.ld_out + col) = lo;
-            }
-        }
-        if (pass + 1 < kPasses) {
-            fetch_old(pr0 + kRowsPerPass);
-            barrier_lds_only();                               // staging is free for the next pass
-        }
-    }
+    store_result<Cfg, A_KMAJOR, MODE>(acc, j, out_f32, beta, mi, ni, smem);
 }
 
 template <class Cfg, int MODE>
-__global__ __launch_bounds__(kThreads) void grad_gemm_kernel(const GemmJob first, const GemmJob second) {
+__global__ __launch_bounds__(Cfg::kThreads, 2) void grad_gemm_kernel(const GemmJob first, const GemmJob second) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
     bool in_first;
@@ -771,7 +786,7 @@ __global__ __launch_bounds__(kThreads) void grad_gemm_kernel(const GemmJob first
     if (first.n_work >= 8 && second.n_work >= 8) {
         xcd_two_job_map(blockIdx.x, first.n_work, second.n_work, in_first, item);
     } else {
-        const int lin = xcd_round_id(blockIdx.x, gridDim.x, 256);
+        const int lin = xcd_round_id(blockIdx.x, gridDim.x, 2048 / Cfg::NW);
         in_first = lin < first.n_work;
         item = in_first ? lin : lin - first.n_work;
     }
@@ -1054,17 +1069,17 @@ static bool ensure_kernel_attributes() {
 // The bf16 gradient tiles of n_row_tiles x n_v_tiles tiles of 256 x 256.
 static void launch_grad_tiles(const void* H, const void* W, const int32_t* labels, const float* lse, const float* dloss,
                               const float* mean_scale, int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
-                              int row0, int n_row_tiles, int v0, int n_v_tiles, uint16_t* G, int ldg, int v_off, int V_total,
+                              int row0, int n_row_tiles, int v0, int n_v_tiles, uint16_t* G, uint32_t panel, int panel_shift, int v_off, int V_total,
                               const int32_t* perm, hipStream_t stream) {
     const Fp8Scales none = {nullptr, nullptr, 0, 0};
     if (use_small_tiles(n_row_tiles, n_v_tiles))
         hipLaunchKernelGGL((grad_tile_kernel<false, TileSmall>), dim3(4 * n_row_tiles * n_v_tiles), dim3(kThreads), grad_tile_lds<TileSmall>(),
                            stream, H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           2 * n_row_tiles, v0, 2 * n_v_tiles, G, ldg, v_off, V_total, none, perm);
+                           2 * n_row_tiles, v0, 2 * n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm);
     else
         hipLaunchKernelGGL(grad_tile_kernel<false>, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), kGradTileLds, stream,
                            H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           n_row_tiles, v0, n_v_tiles, G, ldg, v_off, V_total, none, perm);
+                           n_row_tiles, v0, n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm);
 }
 
 // A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
@@ -1333,6 +1348,13 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 const int64_t row0 = r0 + s0;
                 const uint16_t* h_step = h_rows + (size_t)s0 * D;
                 const size_t g_bytes = (size_t)row_tiles * 256 * (size_t)ldg * 2;
+                // parts of the two reductions, in whole tiles of 256
+                const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
+                const int n_split_w = (row_tiles + kw - 1) / kw;
+                const int64_t items = ((int64_t)row_tiles * n_split_h + (int64_t)v_tiles * n_split_w) * d_tiles;
+                const int kind = contraction_kind(sc.kind, items, knobs);
+                const int panel_shift = 6;                // log2 of the K slice of the contractions' tiles
+                const uint32_t panel = (uint32_t)(row_tiles * 256) << panel_shift;
                 uint16_t* G = ch.in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
                                          : (uint16_t*)(ws + sc.off_g);
                 {
@@ -1342,22 +1364,17 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                     if (fp8)
                         hipLaunchKernelGGL(grad_tile_kernel<true>, grid, dim3(kThreads), kGradTileLds, stream,
                                            logit_hidden, logit_weight, labels, lse, dloss, mean_scale, (int)N, (int)D, (int)V,
-                                           ignore_index, label_smoothing, z_loss, (int)row0, row_tiles, (int)v0, v_tiles, G, ldg,
+                                           ignore_index, label_smoothing, z_loss, (int)row0, row_tiles, (int)v0, v_tiles, G, panel, panel_shift,
                                            (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
                     else
                         launch_grad_tiles((const void*)h_step, weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
                                           (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
-                                          v_tiles, G, ldg, (int)v_off, (int)V_total, (const int32_t*)nullptr, stream);
+                                          v_tiles, G, panel, panel_shift, (int)v_off, (int)V_total, (const int32_t*)nullptr, stream);
                 }
-                // parts of the two reductions, in whole tiles of 256
-                const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
-                const int n_split_w = (row_tiles + kw - 1) / kw;
-                const int64_t items = ((int64_t)row_tiles * n_split_h + (int64_t)v_tiles * n_split_w) * d_tiles;
-                const int kind = contraction_kind(sc.kind, items, knobs);
                 const int per256 = 256 / gemm_tile_of_kind(kind).bm;
                 GemmJob dh;
                 dh.a_kmajor = 1;
-                dh.A = G; dh.lda = ldg; dh.a_free_n = row_tiles * 256; dh.a_k_n = ldg;
+                dh.A = G; dh.panel = panel;
                 dh.B = (const void*)((const uint16_t*)weight + (size_t)v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)cols;
                 dh.k_total = ldg; dh.n_tiles = d_tiles; dh.split_k = kh * 256; dh.n_split = n_split_h;
                 dh.n_work = row_tiles * per256 * d_tiles * dh.n_split;
@@ -1374,7 +1391,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 dh.zero_row = nullptr;
                 GemmJob dw;
                 dw.a_kmajor = 0;
-                dw.A = G; dw.lda = ldg; dw.a_free_n = ldg; dw.a_k_n = row_tiles * 256;
+                dw.A = G; dw.panel = panel;
                 dw.B = (const void*)h_step; dw.ldb = (int)D; dw.b_k_n = (int)srows;
                 dw.k_total = row_tiles * 256; dw.n_tiles = d_tiles; dw.split_k = kw * 256; dw.n_split = n_split_w;
                 dw.n_work = v_tiles * per256 * d_tiles * dw.n_split;
@@ -1500,6 +1517,8 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         uint16_t* G = (uint16_t*)((blk.g_in_dh ? (char*)dHidden : ws) + blk.off_g);
         char* acc = (blk.acc_in_dh ? (char*)dHidden : ws) + blk.off_acc;     // fp32 dH sums, or their lower halves (see GemmJob)
         const int ldg = st.v_tiles * 256;                       // the chunk is stored densely padded
+        const int panel_shift = 6;            // log2 of the K slice of the contractions' tiles
+        const uint32_t panel = (uint32_t)(st.row_tiles * 256) << panel_shift;
         const int n_rows_h = (int)N;
         // 1. gradient tiles of this [row block x chunk]
         {
@@ -1508,18 +1527,18 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                 hipLaunchKernelGGL(grad_tile_kernel<true>, dim3(st.row_tiles * st.v_tiles), dim3(kThreads), grad_lds, stream,
                                    logit_hidden, logit_weight, labels, lse, dloss, (const float*)mean_scale,
                                    (int)N, (int)D, (int)V, ignore_index, label_smoothing, z_loss,
-                                   (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, ldg, (int)v_off, (int)V_total, fp8,
+                                   (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, panel, panel_shift, (int)v_off, (int)V_total, fp8,
                                    cc ? cc->perm : (const int32_t*)nullptr);
             else
                 launch_grad_tiles(hidden, weight, labels, lse, dloss, (const float*)mean_scale, n_rows_h, (int)D, (int)V, ignore_index,
-                                  label_smoothing, z_loss, (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, ldg, (int)v_off,
+                                  label_smoothing, z_loss, (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, panel, panel_shift, (int)v_off,
                                   (int)V_total, cc ? cc->perm : (const int32_t*)nullptr, stream);
         }
         // 2. both contractions in one launch
         // dH block += G * W_chunk      (M = tokens, K = chunk columns, N = D)
         GemmJob dh;
         dh.a_kmajor = 1;
-        dh.A = G; dh.lda = ldg; dh.a_free_n = st.row_tiles * 256; dh.a_k_n = ldg;
+        dh.A = G; dh.panel = panel;
         dh.B = (const void*)((const uint16_t*)weight + (size_t)st.v0 * D); dh.ldb = (int)D; dh.b_k_n = (int)st.cols;
         dh.k_total = ldg; dh.n_tiles = d_tiles; dh.n_work = st.row_tiles * per256 * d_tiles;
         dh.m_valid = (int)st.rows; dh.n_valid = (int)D;
@@ -1532,7 +1551,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         // dW chunk (+)= G^T * H_block   (M = chunk columns, K = rows, N = D)
         GemmJob dw;
         dw.a_kmajor = 0;
-        dw.A = G; dw.lda = ldg; dw.a_free_n = ldg; dw.a_k_n = st.row_tiles * 256;
+        dw.A = G; dw.panel = panel;
         // (row skipping: hidden is the caller's tensor and the block's rows are reached through the row map)
         dw.B = cc ? hidden : (const void*)((const uint16_t*)hidden + (size_t)st.r0 * D); dw.ldb = (int)D; dw.b_k_n = (int)st.rows;
         dw.k_total = st.row_tiles * 256; dw.n_tiles = d_tiles; dw.n_work = st.v_tiles * per256 * d_tiles;

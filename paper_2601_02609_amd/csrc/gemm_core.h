@@ -55,19 +55,23 @@ constexpr int kThreads = 512;     // 8 wavefronts
 // on the same output positions (their accumulators are summed once, after the loop): a
 // 256 x 128 tile then keeps the 128 x 64 wavefront tile of the 256 x 256 one, i.e. 0.75
 // instead of 1 LDS fragment read per MFMA and 8 instead of 4 independent accumulators.
-template <int WM_, int WN_, int TM_, int TN_, int STAGES_, int KG_ = 1>
+template <int WM_, int WN_, int TM_, int TN_, int STAGES_, int KG_ = 1, int BK_ = 64>
 struct TileCfg {
-    static_assert(WM_ * WN_ * KG_ == 8, "eight wavefronts per workgroup");
+    static constexpr int NW = WM_ * WN_ * KG_;                  // wavefronts per workgroup
+    static constexpr int kThreads = NW * 64;
+    static constexpr int BK = BK_;                              // K slice
+    static_assert(NW == 8 || NW == 4, "eight or four wavefronts per workgroup");
+    static_assert(BK_ == 64 || BK_ == 32, "128 or 64 bytes per row of a K-major stage");
     static_assert(KG_ == 1 || KG_ == 2, "one or two K groups");
     static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, STAGES = STAGES_, KG = KG_;
-    static constexpr int kSteps = 4 / KG_;                      // k16 steps per slice and wavefront
+    static constexpr int kSteps = BK_ / 16 / KG_;                      // k16 steps per slice and wavefront
     static constexpr int BM = WM_ * TM_ * 32;
     static constexpr int BN = WN_ * TN_ * 32;
-    static constexpr int kAStage = BM * kBK * 2;
-    static constexpr int kBStage = BN * kBK * 2;
+    static constexpr int kAStage = BM * BK * 2;
+    static constexpr int kBStage = BN * BK * 2;
     static constexpr int kStage = kAStage + kBStage;
     static constexpr int kLdsBytes = STAGES_ * kStage;
-    static constexpr int kLoadsPerSlice = BM / 64 + BN / 64;   // 16-byte loads per thread
+    static constexpr int kLoadsPerSlice = (BM + BN) * BK / 8 / kThreads;   // 16-byte loads per thread
     static_assert(kLdsBytes <= 160 * 1024, "stages must fit the 160 KB LDS");
 };
 typedef TileCfg<2, 4, 4, 2, 2> TileBig;      // 256 x 256, wave tile 128 x 64, 2 x 64 KB stages
@@ -108,10 +112,10 @@ __device__ __forceinline__ void load16_to_lds_sbase(const char* uniform_base, ui
 
 // One operand (R = 128 or 256 free indices) of one workgroup tile: global -> LDS.
 // MAPPED (K-slow only): the k-rows are reached through a row map (kmap, kzero).
-template <bool KMAJOR, int R, bool MAPPED = false>
+template <bool KMAJOR, int R, bool MAPPED = false, int NW = 8, int BK = 64>
 struct OperandTile {
     static_assert(!(KMAJOR && MAPPED), "only a K-slow operand carries a k-row map");
-    static constexpr int NL = R / 64;   // 16-byte loads per thread and K slice
+    static constexpr int NL = R * BK / 512 / NW;   // 16-byte loads per thread and K slice
     const char* base;       // matrix base address
     uint32_t ld_bytes;      // leading dimension in bytes
     uint32_t off[NL];       // K-major: clamped row offset + swizzled chunk; K-slow: clamped column offset
@@ -134,11 +138,13 @@ struct OperandTile {
         kzero = nullptr;
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         if (KMAJOR) {
-            const int sw = ((lane >> 4) & 3) | ((wave & 1) << 2);
-            const int c = (lane & 7) ^ sw;
+            constexpr int CPR = BK / 8, RPL = 64 / CPR;      // 16-byte chunks per row, rows per wavefront load
+            const int r0 = RPL * wave + lane / CPR;          // row inside the tile of load 0
+            const int sw = BK == 64 ? (r0 >> 1) & 7 : (r0 >> 2) & 3;
+            const int c = (lane % CPR) ^ sw;
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
-                int row = free0 + 64 * i + 8 * wave + (lane >> 3);
+                int row = free0 + RPL * NW * i + r0;
                 row = row < free_n ? row : free_n - 1;
                 if (row_map) {
                     const int mapped = row_map[row];
@@ -159,7 +165,7 @@ struct OperandTile {
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
                 off[i] = (uint32_t)col * 2u;
-                krow[i] = (wave + 8 * i) * RPL + sub;
+                krow[i] = (wave + NW * i) * RPL + sub;
                 slow_off[i] = (uint32_t)krow[i] * ld_bytes + off[i];
             }
         }
@@ -167,7 +173,7 @@ struct OperandTile {
 
     // K slices [0, full_slices()) lie entirely inside the operand's valid K extent (every slice of a
     // K-major operand does: its extent is padded to the slice).
-    __device__ __forceinline__ int full_slices() const { return KMAJOR ? 0x7fffffff : (k_last + 1) / kBK; }
+    __device__ __forceinline__ int full_slices() const { return KMAJOR ? 0x7fffffff : (k_last + 1) / BK; }
 
     // Issue this thread's loads of the K slice starting at k0 into `stage` (LDS).  FULL (compile time):
     // the caller knows that the slice is one of full_slices().
@@ -179,15 +185,15 @@ struct OperandTile {
             // uniform base = matrix base + this slice's K offset; lane offsets are those of init()
             const char* sb = base + (size_t)((uint32_t)k0 * 2u);
 #pragma unroll
-            for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, off[i], lds0 + (uint32_t)i * 8192u);
+            for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, off[i], lds0 + (uint32_t)i * (NW * 1024u));
             return;
         }
-        if (!MAPPED && (FULL || k0 + 63 <= k_last)) {
+        if (!MAPPED && (FULL || k0 + BK - 1 <= k_last)) {
             // a full slice of a K-slow operand: uniform base = row k0, lane offset = its k-row inside
             // the slice times the row pitch plus its column offset
             const char* sb = base + (size_t)k0 * ld_bytes;
 #pragma unroll
-            for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, slow_off[i], lds0 + (uint32_t)i * 8192u);
+            for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, slow_off[i], lds0 + (uint32_t)i * (NW * 1024u));
             return;
         }
         if constexpr (MAPPED) {
@@ -207,7 +213,7 @@ struct OperandTile {
             if (__builtin_amdgcn_ballot_w64(any < 0) == 0) {
 #pragma unroll
                 for (int i = 0; i < NL; ++i)
-                    load16_to_lds_sbase(base, (uint32_t)m[i] * ld_bytes + off[i], lds0 + (uint32_t)i * 8192u);
+                    load16_to_lds_sbase(base, (uint32_t)m[i] * ld_bytes + off[i], lds0 + (uint32_t)i * (NW * 1024u));
                 return;
             }
         }
@@ -227,14 +233,57 @@ struct OperandTile {
                     g = mapped < 0 ? kzero + off[i] : base + (size_t)((uint32_t)mapped * ld_bytes + off[i]);
                 }
             }
-            load16_to_lds(g, stage + (wave + 8 * i) * 1024);
+            load16_to_lds(g, stage + (wave + NW * i) * 1024);
         }
+    }
+};
+
+// The gradient chunk G as the A operand of the contractions.  It is kept in panels as wide as the K slice of the
+// tiles that read it, element (row, col) at (col / BK) * panel + row * BK + col % BK: a K slice of the dH product
+// (K = columns) is then one contiguous run, and one of the dW product (K = rows) whole 128-byte lines.  Rows and
+// columns are padded to whole tiles: nothing is clamped.
+template <bool KMAJOR, int R, int NW, int BK>
+struct PanelTile {
+    static constexpr int NL = R * BK / 512 / NW;
+    static constexpr int CPP = BK / 8;          // 16-byte chunks across a panel
+    const char* base;
+    uint32_t panel;         // bytes from one panel to the next
+    uint32_t off[NL];
+    __device__ __forceinline__ void init(const uint16_t* chunk, uint32_t panel_elements, int free0, int k0) {
+        panel = panel_elements * 2u;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        if (KMAJOR) {
+            base = (const char*)chunk + (size_t)(k0 / BK) * panel;
+            constexpr int RPL = 64 / CPP;
+            const int r0 = RPL * wave + lane / CPP;
+            const int sw = BK == 64 ? (r0 >> 1) & 7 : (r0 >> 2) & 3;
+            const int c = (lane % CPP) ^ sw;
+#pragma unroll
+            for (int i = 0; i < NL; ++i) off[i] = (uint32_t)(free0 + RPL * NW * i + r0) * (BK * 2u) + (uint32_t)c * 16u;
+        } else {
+            base = (const char*)chunk + (size_t)k0 * (BK * 2u);
+            constexpr int CR = R / 8, RPL = 512 / R;
+            const int sub = lane / CR, k3 = (RPL * wave + sub) & 3;
+            const int c = (lane % CR) ^ (k3 << 2);
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                off[i] = (uint32_t)((wave + NW * i) * RPL + sub) * (BK * 2u) + (uint32_t)(free0 / BK + c / CPP) * panel + (uint32_t)(c % CPP) * 16u;
+        }
+    }
+    __device__ __forceinline__ int full_slices() const { return 0x7fffffff; }
+    template <bool FULL = false>
+    __device__ __forceinline__ void issue(CCE_LDS char* stage, int k0) const {
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const uint32_t lds0 = (uint32_t)(uintptr_t)stage + (uint32_t)wave * 1024u;
+        const char* sb = base + (KMAJOR ? (size_t)(k0 / BK) * panel : (size_t)k0 * (BK * 2u));
+#pragma unroll
+        for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, off[i], lds0 + (uint32_t)i * (NW * 1024u));
     }
 };
 
 // Per-lane LDS byte offsets of the MFMA fragments of one operand, relative to its stage.
 // A wavefront of K group kg reads the k16 steps kk = j * KG + kg, j = 0 .. STEPS - 1.
-template <bool KMAJOR, int R, int NB, int STEPS, int KG>
+template <bool KMAJOR, int R, int NB, int STEPS, int KG, int BK = 64>
 struct FragAddr {
     uint32_t a[KMAJOR ? STEPS : NB];   // K-major: one per step j; K-slow: one per 32-wide block
 
@@ -243,11 +292,11 @@ struct FragAddr {
         const int l = threadIdx.x & 63;
         if (KMAJOR) {
             const int row = tile_off + (l & 31);
-            const int s = ((l & 31) >> 1) & 7;
+            const int s = BK == 64 ? ((l & 31) >> 1) & 7 : ((l & 31) >> 2) & 3;
 #pragma unroll
             for (int j = 0; j < STEPS; ++j) {
                 const int kk = j * KG + kg;
-                a[j] = (uint32_t)(row * 128 + (((2 * kk + (l >> 5)) ^ s) << 4));
+                a[j] = (uint32_t)(row * (BK * 2) + (((2 * kk + (l >> 5)) ^ s) << 4));
             }
         } else {
             const int q = l >> 4, jj = l & 15;
@@ -266,7 +315,7 @@ struct FragAddr {
     // lane l gets elements (free = block base + l % 32, k = 16 kk + 8 (l / 32) + 0..7).
     __device__ __forceinline__ bf16x8 load(const CCE_LDS char* op, int b, int j) const {
         if (KMAJOR) {
-            return *(const CCE_LDS bf16x8*)(op + a[j] + b * (32 * 128));
+            return *(const CCE_LDS bf16x8*)(op + a[j] + b * (32 * BK * 2));
         } else {
             const CCE_LDS char* p = op + a[b] + j * (KG * 16 * 2 * R);
             s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CCE_LDS s16x4*)p);
@@ -324,20 +373,20 @@ __device__ __forceinline__ void barrier_lds_only() {
 template <class Cfg, bool A_KMAJOR, bool B_KMAJOR, bool PEEL = false, class OpA, class OpB>
 __device__ __forceinline__ void gemm_mainloop(f32x16 (&acc)[Cfg::TM][Cfg::TN], const OpA& A, const OpB& B,
                                                int k_total, CCE_LDS char* smem) {
-    constexpr int S = Cfg::STAGES;
+    constexpr int S = Cfg::STAGES, BK = Cfg::BK;
     constexpr int kAhead = (S - 2) * Cfg::kLoadsPerSlice;    // loads that may stay in flight
     constexpr int SPS = Cfg::kSteps;
-    FragAddr<A_KMAJOR, Cfg::BM, Cfg::TM, SPS, Cfg::KG> fa;
-    FragAddr<B_KMAJOR, Cfg::BN, Cfg::TN, SPS, Cfg::KG> fb;
+    FragAddr<A_KMAJOR, Cfg::BM, Cfg::TM, SPS, Cfg::KG, Cfg::BK> fa;
+    FragAddr<B_KMAJOR, Cfg::BN, Cfg::TN, SPS, Cfg::KG, Cfg::BK> fb;
     fa.init(wave_m<Cfg>() * (Cfg::TM * 32), wave_kg<Cfg>());
     fb.init(wave_n<Cfg>() * (Cfg::TN * 32), wave_kg<Cfg>());
 
-    const int KT = (k_total + kBK - 1) / kBK;
+    const int KT = (k_total + BK - 1) / BK;
 #pragma unroll
     for (int s = 0; s < S - 1; ++s) {
         if (s < KT) {
-            A.issue(smem + s * Cfg::kStage, s * kBK);
-            B.issue(smem + s * Cfg::kStage + Cfg::kAStage, s * kBK);
+            A.issue(smem + s * Cfg::kStage, s * BK);
+            B.issue(smem + s * Cfg::kStage + Cfg::kAStage, s * BK);
         }
     }
     if (KT >= S - 1) barrier_pending_loads<kAhead>();
@@ -360,8 +409,8 @@ __device__ __forceinline__ void gemm_mainloop(f32x16 (&acc)[Cfg::TM][Cfg::TN], c
         CCE_LDS char* nxt = smem + nxt_s * Cfg::kStage;
         const int ld_s = (cur_s == 0) ? S - 1 : cur_s - 1;       // stage of slice kt - 1, free again
         if (MORE) {
-            A.template issue<FULL>(smem + ld_s * Cfg::kStage, (kt + S - 1) * kBK);
-            B.template issue<FULL>(smem + ld_s * Cfg::kStage + Cfg::kAStage, (kt + S - 1) * kBK);
+            A.template issue<FULL>(smem + ld_s * Cfg::kStage, (kt + S - 1) * BK);
+            B.template issue<FULL>(smem + ld_s * Cfg::kStage + Cfg::kAStage, (kt + S - 1) * BK);
         }
 #pragma unroll
         for (int kk = 0; kk < SPS; ++kk) {
