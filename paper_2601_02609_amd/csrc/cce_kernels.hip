@@ -539,6 +539,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
 // ------------------------------------------------------------------------------------------
 // LDS of grad_gemm_kernel: the main loop's stages (the exchange between K groups fits them).
 constexpr int kGemmLdsBig = TileBig::kLdsBytes, kGemmLdsNarrow = TileNarrow::kLdsBytes, kGemmLdsSmall = TileSmall::kLdsBytes;
+constexpr int kGemmLdsDuo = TileDuo::kLdsBytes;
 // Row skipping: the LDS table of one row block's row map (kRowTableBytes, plan.h) sits behind these.
 static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRowTableBytes <= 160 * 1024 && kGemmLdsSmall + kRowTableBytes <= 160 * 1024, "row table must fit the LDS");
 
@@ -1062,6 +1063,9 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 2>, kGemmLdsNarrow + kRowTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 3>, kGemmLdsBig + kRowTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 3>, kGemmLdsNarrow + kRowTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileDuo, 0>, kGemmLdsDuo)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileDuo, 1>, kGemmLdsDuo)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileDuo, 4>, kGemmLdsDuo)) return false;
     done[dev] = true;
     return true;
 }
@@ -1087,7 +1091,9 @@ template <int MODE>
 static void launch_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
     const int work = first.n_work + second.n_work;
     ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
-    if (kind == 0)
+    if (kind == 3)
+        hipLaunchKernelGGL((grad_gemm_kernel<TileDuo, MODE>), dim3(work), dim3(256), kGemmLdsDuo, stream, first, second);
+    else if (kind == 0)
         hipLaunchKernelGGL((grad_gemm_kernel<TileBig, MODE>), dim3(work), dim3(kThreads), kGemmLdsBig, stream, first, second);
     else if (kind == 2)
         hipLaunchKernelGGL((grad_gemm_kernel<TileSmall, MODE>), dim3(work), dim3(kThreads), kGemmLdsSmall, stream, first, second);
@@ -1351,9 +1357,10 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 // parts of the two reductions, in whole tiles of 256
                 const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
                 const int n_split_w = (row_tiles + kw - 1) / kw;
-                const int64_t items = ((int64_t)row_tiles * n_split_h + (int64_t)v_tiles * n_split_w) * d_tiles;
-                const int kind = contraction_kind(sc.kind, items, knobs);
-                const int panel_shift = 6;                // log2 of the K slice of the contractions' tiles
+                const bool dw_beta = row0 > 0 || accumulate_dW;
+                const int kind = contraction_kind(sc.kind, D, (int64_t)row_tiles * n_split_h * d_tiles, kh * 4, planes_written > 0, sc.split_acc != 0,
+                                                  (int64_t)v_tiles * n_split_w * d_tiles, kw * 4, dw_beta, false, knobs);
+                const int panel_shift = kind == 3 ? 5 : 6;                // log2 of the K slice of the contractions' tiles
                 const uint32_t panel = (uint32_t)(row_tiles * 256) << panel_shift;
                 uint16_t* G = ch.in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
                                          : (uint16_t*)(ws + sc.off_g);
@@ -1397,7 +1404,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 dw.n_work = v_tiles * per256 * d_tiles * dw.n_split;
                 dw.m_valid = (int)cols; dw.n_valid = (int)D;
                 dw.out_f32 = dW + (size_t)v0 * D; dw.part = part_w; dw.part_stride = sc.plane_w; dw.ld_out = D;
-                dw.beta_n = (row0 > 0 || accumulate_dW) ? 1 : 0;
+                dw.beta_n = dw_beta ? 1 : 0;
                 dw.final = 0; dw.out_hi = nullptr; dw.out_lo = nullptr; dw.row_map = nullptr; dw.zero_row = nullptr;
 
                 const bool dh_first = kh >= kw;                          // longer items first
@@ -1512,12 +1519,14 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         const Step& st = steps[k];
         const RowBlock& blk = *st.block;
         const int d_tiles = (int)((D + gemm_tile_of_kind(blk.kind).bn - 1) / gemm_tile_of_kind(blk.kind).bn);
-        const GemmTile gt = gemm_tile_of_kind(contraction_kind(blk.kind, (int64_t)(st.row_tiles + st.v_tiles) * d_tiles, knobs));
+        const GemmTile gt = gemm_tile_of_kind(contraction_kind(blk.kind, D, (int64_t)st.row_tiles * d_tiles, st.v_tiles * 4,
+                                               !st.first_chunk, blk.split_acc != 0, (int64_t)st.v_tiles * d_tiles, st.row_tiles * 4,
+                                               !st.first_block || accumulate_dW, cc != nullptr, knobs));
         const int per256 = 256 / gt.bm;                           // contraction row tiles per 256 rows
         uint16_t* G = (uint16_t*)((blk.g_in_dh ? (char*)dHidden : ws) + blk.off_g);
         char* acc = (blk.acc_in_dh ? (char*)dHidden : ws) + blk.off_acc;     // fp32 dH sums, or their lower halves (see GemmJob)
         const int ldg = st.v_tiles * 256;                       // the chunk is stored densely padded
-        const int panel_shift = 6;            // log2 of the K slice of the contractions' tiles
+        const int panel_shift = gt.kind == 3 ? 5 : 6;            // log2 of the K slice of the contractions' tiles
         const uint32_t panel = (uint32_t)(st.row_tiles * 256) << panel_shift;
         const int n_rows_h = (int)N;
         // 1. gradient tiles of this [row block x chunk]
@@ -1571,7 +1580,10 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
             const int mode = (blk.split_acc ? 1 : 0) | (cc ? 2 : 0);
 #define CCE_LAUNCH_GEMM(CFG, MODE, LDS) \
     hipLaunchKernelGGL((grad_gemm_kernel<CFG, MODE>), dim3(work), dim3(kThreads), (LDS) + ((MODE) >= 2 ? kRowTableBytes : 0), stream, first, second)
-            if (gt.kind == 0) {
+            if (gt.kind == 3) {
+                if (mode == 0) hipLaunchKernelGGL((grad_gemm_kernel<TileDuo, 0>), dim3(work), dim3(TileDuo::kThreads), kGemmLdsDuo, stream, first, second);
+                else hipLaunchKernelGGL((grad_gemm_kernel<TileDuo, 1>), dim3(work), dim3(TileDuo::kThreads), kGemmLdsDuo, stream, first, second);
+            } else if (gt.kind == 0) {
                 if (mode == 0) CCE_LAUNCH_GEMM(TileBig, 0, kGemmLdsBig); else if (mode == 1) CCE_LAUNCH_GEMM(TileBig, 1, kGemmLdsBig);
                 else if (mode == 2) CCE_LAUNCH_GEMM(TileBig, 2, kGemmLdsBig); else CCE_LAUNCH_GEMM(TileBig, 3, kGemmLdsBig);
             } else if (gt.kind == 2) {

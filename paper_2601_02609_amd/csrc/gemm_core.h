@@ -81,6 +81,13 @@ typedef TileCfg<2, 2, 4, 2, 3, 2> TileNarrow; // 256 x 128, wave tile 128 x 64, 
 // other workgroup of the unit covers its latency).  322 x 1856 x 1015, 8 large tiles: forward and
 // backward 102.8 -> 58.2 us; 256 x 64 x 1000: 38.9 -> 30.2.
 typedef TileCfg<2, 4, 2, 1, 4> TileSmall;
+// 256 x 128 by four wavefronts, K slices of 32 in 3 x 24 KB stages: two workgroups to a compute unit, each with half
+// of its LDS and registers, so that one's first slice and epilogue run beside the other's main loop.  For contractions
+// of many items (see contraction_kind).  Rounds of 256 items, dW: 8 slices of 64 15.3 -> 13.7 us, 32 37.6 -> 33.2,
+// 96 94.2 -> 90.3; alone on its unit an item is slower than TileNarrow's (252 items of 48 slices: 51 -> 60 us).
+// Not for the logit products: their K-major operands would come in 64-byte rows (forward at D = 896 1.9 -> 2.3 ms).
+typedef TileCfg<2, 2, 4, 2, 3, 1, 32> TileDuo;
+
 
 // Wavefront coordinates inside the workgroup: K group, then position along M and N.
 template <class Cfg> __device__ __forceinline__ int wave_kg() { return (threadIdx.x >> 6) / (Cfg::WM * Cfg::WN); }
@@ -240,8 +247,10 @@ struct OperandTile {
 
 // The gradient chunk G as the A operand of the contractions.  It is kept in panels as wide as the K slice of the
 // tiles that read it, element (row, col) at (col / BK) * panel + row * BK + col % BK: a K slice of the dH product
-// (K = columns) is then one contiguous run, and one of the dW product (K = rows) whole 128-byte lines.  Rows and
-// columns are padded to whole tiles: nothing is clamped.
+// (K = columns) is then one contiguous run, and one of the dW product (K = rows) whole 128-byte lines.  (With rows
+// as long as the chunk, K slices of 32 took half of every line: 96 slices of a dH item 104 us, in panels 92; K slices of
+// 64 from panels of 32: the 128 x 128 dW items of 16 x 16 tiles at D = 512 34 -> 50 us.)  Rows and columns are padded to
+// whole tiles: nothing is clamped.
 template <bool KMAJOR, int R, int NW, int BK>
 struct PanelTile {
     static constexpr int NL = R * BK / 512 / NW;

@@ -79,7 +79,8 @@ struct GemmTile { int kind, bm, bn; double us_per_slice; };
 static GemmTile gemm_tile_of_kind(int kind) {
     if (kind == 0) return {0, TileBig::BM, TileBig::BN, 2.0};
     if (kind == 1) return {1, TileNarrow::BM, TileNarrow::BN, 1.1};
-    return {2, TileSmall::BM, TileSmall::BN, 0.6};              // chosen per launch, see contraction_kind
+    if (kind == 2) return {2, TileSmall::BM, TileSmall::BN, 0.6};              // chosen per launch, see contraction_kind
+    return {3, TileDuo::BM, TileDuo::BN, 1.1};                  // likewise
 }
 
 // Process-wide tuning / testing knobs (0 = automatic).  Atomics: a knob may be set from any host
@@ -143,12 +144,35 @@ static double makespan_floor(int64_t cus, int64_t n1, double c1, int64_t n2, dou
 // Floors and times are sums in different orders: what lies above by less than this is not passed over.
 constexpr double kAbove = 1.0 + 1e-9;
 
+// Time of a launch of 256 x 128 tiles two to a compute unit (TileDuo), microseconds: n1 items that take c1 beside
+// another one of their unit, n2 that take c2.  An item alone on its unit takes 0.6 of that time (96 slices: 181 us
+// beside another, 100 alone), so what counts beside the even share of the work is when the slots run empty and how
+// many of them the last items keep.  FLOOR: a bound it never falls below.
+template <bool FLOOR = false>
+static double duo_makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
+    if (c2 > c1) { const int64_t n = n1; n1 = n2; n2 = n; const double c = c1; c1 = c2; c2 = c; }
+    if (n1 == 0) { n1 = n2; c1 = c2; n2 = 0; }
+    const int64_t units = 2 * cus, rounds = (n1 + units - 1) / units;
+    const double even = ((double)n1 * c1 + (double)n2 * c2) / (double)units, last = (double)rounds * c1;
+    if (n1 + n2 <= cus) return 0.6 * c1 + 1.0;
+    const double spread = even + 0.5 * (n2 ? c2 : c1);
+    if (FLOOR) return even > 0.6 * last ? even : 0.6 * last;
+    if (spread >= last || n2 == 0) {
+        const double end = spread > last ? spread : last, start = 2.0 * even - end;      // slots run empty one by one
+        return start > 0.0 ? start + 0.75 * (end - start) : 0.75 * end;
+    }
+    const double f = (double)(n1 - (rounds - 1) * units) / (double)units;                 // the long items' share of the slots
+    const double start = f < 1.0 ? (even - last * f) / (1.0 - f) : 0.0;
+    const double alone = f <= 0.5 ? 0.6 : 0.2 + 0.8 * f;
+    return start > 0.0 ? start + alone * (last - start) : alone * last;
+}
+
 // Tile of one contraction launch: 128 x 128 where the planned 256 x 128 tiles would leave half of the
 // compute units without work (an item then costs about half as much, and all of them still start at
 // once).  A forced tile stays.  Backward of 256 x 64 x 1000: 23 -> 16 us, 322 x 1856 x 1015: 36 -> 28,
 // 2269 x 896 x 2131: 58 -> 50, 2500 x 64 x 1300: 33 -> 25.
-static int contraction_kind(int kind, int64_t items, const Knobs& knobs) {
-    return kind == 1 && knobs.gemm_cols == 0 && items * 2 <= device_cu_count() ? 2 : kind;
+static bool small_contractions(int kind, int64_t items, const Knobs& knobs) {
+    return kind == 1 && knobs.gemm_cols == 0 && items * 2 <= device_cu_count();
 }
 
 // Rough time model of the backward pipeline, in microseconds, used only to rank tilings.
@@ -443,6 +467,8 @@ struct ScheduleModel {
     int cus; int64_t D; GemmTile tile;
     bool mapped;                // the dW job reads hidden rows through the row map: 0.85 us a slice against 0.76
     int64_t dt;                 // output tiles across D
+    bool one_to_unit = false;   // 256 x 128 tiles: not two to a compute unit
+    bool duo() const { return tile.kind == 1 && !mapped && !one_to_unit; }
     ScheduleModel() = default;
     ScheduleModel(int cus_, int64_t D_, GemmTile tile_, bool mapped_ = false)
         : cus(cus_), D(D_), tile(tile_), mapped(mapped_), dt((D_ + tile_.bn - 1) / tile_.bn) {}
@@ -450,15 +476,34 @@ struct ScheduleModel {
     static int64_t ceil_div(int64_t a, int64_t b) { return (int64_t)(((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b); }
     double slice() const { return tile.kind == 0 ? 1.58 : 0.79; }
     double item(int64_t slices, bool beta) const { return (double)slices * slice() + (tile.kind == 0 ? 13.0 : 9.0) + (beta ? 2.0 : 0.0); }
+    double duo_item(int64_t slices, bool beta, bool split) const { return (double)slices * 1.53 + 10.0 + (beta ? 6.0 : 0.0) + (split ? 8.0 : 0.0); }
     int64_t d_tiles() const { return dt; }
+    // What an item costs at least, of either form.
+    double least_slice() const { return duo() ? 0.765 : slice(); }
+    double least_item() const { return duo() ? 5.0 : item(0, false); }
+    // Both contractions of a step; *kind becomes the tile they take.  (Narrow tiles are searched for only where they could win.)
+    template <bool FLOOR = false>
+    double contractions(int64_t n_dh, int64_t s_dh, bool dh_beta, bool split, int64_t n_dw, int64_t s_dw, bool dw_beta, int* kind = nullptr) const {
+        const double c_dh = item(s_dh, dh_beta), c_dw = item(s_dw, dw_beta) + (mapped ? (double)s_dw * 0.11 * slice() : 0.0);
+        const double least = makespan_floor(cus, n_dh, c_dh, n_dw, c_dw);
+        double duo_us = 1e300;
+        if (duo()) {
+            duo_us = duo_makespan<FLOOR>(cus, n_dh, duo_item(s_dh, dh_beta, split), n_dw, duo_item(s_dw, dw_beta, false));
+            if (kind) *kind = 3;
+            if (duo_us <= least) return duo_us;
+        }
+        const double us = FLOOR ? least : makespan(cus, n_dh, c_dh, n_dw, c_dw);
+        if (duo_us < us) return duo_us;
+        if (kind) *kind = tile.kind;
+        return us;
+    }
     double logit_tile() const { return (double)(D / 64) * 1.55 + 7.0; }
     // One step over a x b tiles.  FLOOR: with makespan_floor.
     template <bool FLOOR = false>
-    double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta) const {
+    double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta, bool split = false) const {
         const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);       // K tiles per part
         const int64_t n_dh = a * dt * ceil_div(b, kh), n_dw = b * dt * ceil_div(a, kw);
-        const double c_dh = item(kh * 4, dh_beta), c_dw = item(kw * 4, dw_beta) + (mapped ? (double)(kw * 4) * 0.11 * slice() : 0.0);
-        const double mk = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
+        const double mk = contractions<FLOOR>(n_dh, kh * 4, dh_beta, split, n_dw, kw * 4, dw_beta);
         const double g = (double)(a * b) * 131072.0, w = (double)b * 512.0 * (double)D;
         const double tiles_us = (double)((a * b + cus - 1) / cus) * logit_tile();
         const double tiles_mem = (g + w) / 4.5e6;
@@ -471,11 +516,11 @@ struct ScheduleModel {
     // at most `b_max`: all work spread evenly, the serial reduction of one item per step or all bytes at the rate
     // of HBM, and what each step costs by itself.
     double floor_us(int64_t a, int64_t b, int64_t b_max, int split_h, int split_w) const {
-        const double ab = (double)(a * b), per_item = item(0, false);
+        const double ab = (double)(a * b), per_item = least_item();
         const double steps = (double)ceil_div(b, b_max);
         const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);
-        double even = (8.0 * ab * (double)dt * slice() + ((double)(b * ceil_div(a, kw)) + (double)a * steps) * (double)dt * per_item) / (double)cus;
-        const double dh_item = (double)(kh * 4) * slice() + steps * per_item, dw_item = steps * item(kw * 4, false);
+        double even = (8.0 * ab * (double)dt * least_slice() + ((double)(b * ceil_div(a, kw)) + (double)a * steps) * (double)dt * per_item) / (double)cus;
+        const double dh_item = (double)(kh * 4) * slice() + steps * per_item, dw_item = steps * ((double)(kw * 4) * slice() + per_item);
         if (dh_item > even) even = dh_item;
         if (dw_item > even) even = dw_item;
         const double tiles_us = ab * logit_tile() / (double)cus;
@@ -486,11 +531,22 @@ struct ScheduleModel {
     }
     // The part of it that grows with the width, per vocabulary tile.
     double floor_per_tile(int64_t a, int64_t b_max) const {
-        const double per_item = item(0, false), steps = 1.0 / (double)b_max;
+        const double per_item = least_item(), steps = 1.0 / (double)b_max;
         return (double)a * logit_tile() / (double)cus + 8.0 * steps +
-               (8.0 * (double)a * (double)dt * slice() + (1.0 + (double)a * steps) * (double)dt * per_item) / (double)cus;
+               (8.0 * (double)a * (double)dt * least_slice() + (1.0 + (double)a * steps) * (double)dt * per_item) / (double)cus;
     }
 };
+
+// Tile of one launch of n_dh and n_dw work items of `kind` with reductions of s_dh and s_dw slices: the forms that a
+// plan or schedule leaves open.  row_map: the dW job reads its rows through a map (256 x 128 tiles one to a unit).
+static int contraction_kind(int kind, int64_t D, int64_t n_dh, int64_t s_dh, bool dh_beta, bool split, int64_t n_dw, int64_t s_dw,
+                            bool dw_beta, bool row_map, const Knobs& knobs) {
+    if (small_contractions(kind, n_dh + n_dw, knobs)) return 2;
+    if (kind != 1 || knobs.gemm_cols != 0 || row_map) return kind;
+    const ScheduleModel m{device_cu_count(), D, gemm_tile_of_kind(kind)};
+    m.contractions(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta, &kind);
+    return kind;
+}
 
 // The forward under the same constants: rounds of workgroups that walk their vocabulary tiles, or of one
 // small tile each (500 x 2048 x 10000, two rounds of 32 slices: 42 us).
@@ -522,8 +578,8 @@ struct RowBlockPlanner {
     double block_us(const RowBlock& k, bool beta) const {
         const int64_t nch = (VT + k.b - 1) / k.b;
         const ScheduleModel& mm = m[k.kind];
-        double t = nch > 1 ? (double)(nch - 1) * mm.template step<FLOOR>(k.a, k.b, 1, 1, true, beta) : 0.0;
-        t += mm.template step<FLOOR>(k.a, VT - (nch - 1) * k.b, 1, 1, nch > 1, beta);
+        double t = nch > 1 ? (double)(nch - 1) * mm.template step<FLOOR>(k.a, k.b, 1, 1, true, beta, k.split_acc != 0) : 0.0;
+        t += mm.template step<FLOOR>(k.a, VT - (nch - 1) * k.b, 1, 1, nch > 1, beta, k.split_acc != 0);
         if (k.split_acc) t += (double)nch * (compact ? 9.0 : 2.0);
         return t;
     }
@@ -605,7 +661,8 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         const ScheduleModel m{cus, D, gemm_tile_of_kind(p.gemm_kind), compact};
         const int64_t a = p.Nb / 256, b = p.Vc / 256, nch = (VT + b - 1) / b;
         auto block_us = [&](int64_t aa, bool later) {
-            return (nch > 1 ? (double)(nch - 1) * m.step(aa, b, 1, 1, true, later) : 0.0) + m.step(aa, VT - (nch - 1) * b, 1, 1, nch > 1, later);
+            return (nch > 1 ? (double)(nch - 1) * m.step(aa, b, 1, 1, true, later, p.split_acc != 0) : 0.0) +
+                   m.step(aa, VT - (nch - 1) * b, 1, 1, nch > 1, later, p.split_acc != 0);
         };
         const int64_t nblk = (TT + a - 1) / a;
         best.plan_us = block_us(nblk > 1 ? a : TT, false);
@@ -619,6 +676,9 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
     const ScheduleModel models[2] = {{cus, D, gemm_tile_of_kind(0)}, {cus, D, gemm_tile_of_kind(1)}};
+    // (row blocks add to dW with every block: the orders with dHidden's front rows are rated with the same items)
+    ScheduleModel block_models[2] = {models[0], models[1]};
+    block_models[1].one_to_unit = true;
     // What the steps of a chunk over all rows take, in 1 ... 4 row parts: many orders share such chunks
     // (from eight row tiles on, where row parts are tried).
     constexpr int kKnown = 64;
@@ -626,7 +686,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     const bool keep = TT >= 8;
     if (keep) memset(chunk_us, 0, sizeof chunk_us);
     auto try_one = [&](int kind, int a, int bcap, int sh, int sw, int row_parts, int b_min, int split_acc) {
-        const ScheduleModel& m = models[kind];
+        const ScheduleModel& m = a < TT ? block_models[kind] : models[kind];
         ScheduleSteps sc = {};
         sc.kind = kind; sc.a = a; sc.split_h = sh; sc.split_w = sw;
         sc.b = bcap < VT ? bcap : VT;
@@ -674,7 +734,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                     if (block_us[later] + least + (double)rest * per_tile + extra > best.us * kAbove) return;
                     if (last_us == 0.0)
                         for (int r = 0; r < a; r += c.rows)
-                            last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free) + (split_acc ? 2.0 : 0.0);
+                            last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free, split_acc != 0) + (split_acc ? 2.0 : 0.0);
                     if (known) *known = last_us;
                     last = c;
                 }
