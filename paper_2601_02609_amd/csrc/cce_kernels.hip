@@ -75,7 +75,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_kernel(
         const void* __restrict__ H, const void* __restrict__ W,
         int N, int D, int V, int TT, int VT, int S, float2* __restrict__ partials,
         float* __restrict__ partial_sumz, const Fp8Scales fp8, const int32_t* __restrict__ perm,
-        int32_t* __restrict__ status) {
+        int32_t* __restrict__ status, const int32_t* __restrict__ rows_splits) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
 
@@ -84,10 +84,20 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_kernel(
     // (it took 1.4 us and a launch boundary of about 2 at the smallest shapes).
     if (status && blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;
 
+    // The rows that take part and the splits that fit them, where only the device knows (see row_scan_kernel); the
+    // workgroups beyond are not needed.
+    if (rows_splits) {
+        N = rows_splits[0];
+        S = rows_splits[1];
+        TT = (N + Cfg::BN - 1) / Cfg::BN;
+    }
+    const int n_work = rows_splits ? TT * S : (int)gridDim.x;
+    if ((int)blockIdx.x >= n_work) return;
+
     // Work index -> (token tile, vocabulary split).  The 32 workgroups that share an XCD (and
     // its 4 MB L2) take a panel of 4 token tiles x all splits: per K slice they touch 4 H
     // tiles + S W tiles instead of 32 + 1, which is what keeps most operand fetches in L2.
-    const int lin = xcd_round_id(blockIdx.x, gridDim.x, 2048 / Cfg::NW);
+    const int lin = xcd_round_id(blockIdx.x, n_work, 2048 / Cfg::NW);
     int tt, s;
     group_map(lin, TT, S, 32 / Cfg::NW, tt, s);
     const int vt0 = (int)((int64_t)s * VT / S), vt1 = (int)((int64_t)(s + 1) * VT / S);
@@ -208,7 +218,9 @@ __global__ __launch_bounds__(256) void finalize_kernel(
         const float2* __restrict__ partials, const float* __restrict__ partial_sumz,
         int N, int D, int V, int S, int32_t ignore_index, float label_smoothing, float z_loss,
         float* __restrict__ loss, float* __restrict__ lse, int32_t* __restrict__ status,
-        int v_off, float4* __restrict__ stats, const Fp8Scales fp8, const int32_t* __restrict__ perm) {
+        int v_off, float4* __restrict__ stats, const Fp8Scales fp8, const int32_t* __restrict__ perm,
+        const int32_t* __restrict__ rows_splits) {
+    if (rows_splits) S = rows_splits[1];
     const int l = threadIdx.x & 63;
     const int ctok = blockIdx.x * 4 + (threadIdx.x >> 6);     // token of the (compact) tile space
     if (ctok >= N) return;
@@ -832,6 +844,11 @@ __global__ __launch_bounds__(256) void dw_planes_kernel(float* __restrict__ dw, 
 // order, into a compact row space in which the unchanged kernels run; results are scattered
 // back.  perm[r] = original row of compact row r, -1 for the padding behind the last valid one.
 // ------------------------------------------------------------------------------------------
+// rows_splits (optional): the forward of a call that does not know its number of valid rows takes it from here,
+// rows_splits[0], and with it the vocabulary splits that fit so many rows, rows_splits[1]: the rule of make_plan over the
+// s <= s_max whose workgroups the launch has.  One thread per s.
+struct SplitRule { int32_t* rows_splits; int vocab_tiles, cus, s_max, workgroups; };
+
 // One workgroup of 1024 threads: stable compaction of the valid rows (label in [0, V) and not
 // ignore_index).  At most max_rows are kept (more: CCE_STATUS_ROW_BOUND, the rest is dropped).
 // loss / lse of the rows that are not valid, and of valid rows that were dropped, are set to zero
@@ -846,7 +863,8 @@ __global__ __launch_bounds__(256) void dw_planes_kernel(float* __restrict__ dw, 
 __global__ __launch_bounds__(1024) void row_scan_kernel(
         const int32_t* __restrict__ labels, int N, int V, int32_t ignore_index, int max_rows, int rows_pad,
         int32_t* __restrict__ perm, int32_t* __restrict__ count_out, int32_t* __restrict__ status,
-        float* __restrict__ loss, float* __restrict__ lse, uint16_t* __restrict__ zero_row, int zero_row_len) {
+        float* __restrict__ loss, float* __restrict__ lse, uint16_t* __restrict__ zero_row, int zero_row_len, const SplitRule rule) {
+    __shared__ unsigned long long wave_best[16];
     __shared__ int wave_total[16];
     __shared__ int wave_bad[16];
     constexpr int U = 8;                              // 64-row groups a wavefront has in flight
@@ -856,10 +874,15 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
     auto is_valid = [&](int32_t y) { return y != ignore_index && y >= 0 && y < V; };
     int c = 0;
     bool bad = false;
+    int32_t y0[U];                                    // the first labels are kept: 8192 rows are not read twice
     for (int i = i0; i < i1; i += 64 * U) {
         int32_t y[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) y[u] = i + 64 * u + lane < i1 ? labels[i + 64 * u + lane] : ignore_index;
+        if (i == i0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) y0[u] = y[u];
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             c += __popcll(__ballot(is_valid(y[u])));  // the same in every lane
@@ -880,8 +903,13 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
     int pos = before;                                 // valid rows in front of the group
     for (int i = i0; i < i1; i += 64 * U) {
         int32_t y[U];
+        if (i == i0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) y[u] = i + 64 * u + lane < i1 ? labels[i + 64 * u + lane] : ignore_index;
+            for (int u = 0; u < U; ++u) y[u] = y0[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) y[u] = i + 64 * u + lane < i1 ? labels[i + 64 * u + lane] : ignore_index;
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int row = i + 64 * u + lane;
@@ -904,6 +932,28 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
     if (tid == 0) {
         count_out[0] = kept;
         status[0] = (any_bad ? CCE_STATUS_BAD_LABEL : 0) | (total > max_rows ? CCE_STATUS_ROW_BOUND : 0);
+    }
+    if (rule.rows_splits) {
+        const int tiles = (kept + 255) / 256, s = tid + 1;
+        unsigned long long best = ~0ull;
+        if (s <= rule.s_max && (s == 1 || tiles * s <= rule.workgroups)) {
+            const unsigned rounds = (unsigned)(tiles * s + rule.cus - 1) / (unsigned)rule.cus;
+            const unsigned per = (unsigned)(rule.vocab_tiles + s - 1) / (unsigned)s;
+            best = ((unsigned long long)rounds * (4ull * per + 1ull) << 10) | (unsigned long long)tid;      // the smallest s of equal ones
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            const unsigned long long other = __shfl_xor(best, o);
+            best = other < best ? other : best;
+        }
+        if (lane == 0) wave_best[wave] = best;
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int w = 0; w < 16; ++w) best = wave_best[w] < best ? wave_best[w] : best;
+            rule.rows_splits[0] = kept;
+            rule.rows_splits[1] = (int)(best & 1023ull) + 1;
+        }
     }
 }
 
@@ -1166,8 +1216,9 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
                         float* loss, float* lse, float* mean_loss,
                         int64_t v_off, float* stats, bool want_sumz, const Fp8Scales* fp8_in,
                         void* workspace, size_t workspace_bytes, void* stream_, const CompactCtx* cc = nullptr,
-                        int32_t* status_word = nullptr) {
+                        int32_t* status_word = nullptr, size_t scratch_bytes = 0) {
     Plan p;
+    if (!scratch_bytes) scratch_bytes = workspace_bytes;        // (cce_forward_static: less than it claims)
     Fp8Scales fp8 = {nullptr, nullptr, 0, 0};
     if (fp8_in) {
         fp8 = *fp8_in;
@@ -1196,32 +1247,49 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
     if (!cc) drop_stale_hip_error();
     int32_t* clear = cc ? (int32_t*)nullptr : status;
+    const int32_t* rows_splits = nullptr;
+    int grid = p.TT * p.S;
+    // All rows, ignored ones among them perhaps: large forwards leave those out without being told how many there are.
+    const ForwardSkip skip = cc || stats || fp8_in ? ForwardSkip{} : forward_skip(p, D, scratch_bytes);
+    if (skip.use) {
+        int32_t* const perm = (int32_t*)(ws + skip.off_perm);
+        int32_t* const found = (int32_t*)(ws + skip.off_found);
+        partials = (float2*)(ws + skip.off_partials);
+        if (smooth) sumz = (float*)(ws + skip.off_sumz);
+        grid = skip.workgroups;
+        hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, labels, (int)N, (int)V, ignore_index, (int)N, p.TT * 256,
+                           perm, found + 2, status, loss, lse, (uint16_t*)nullptr, 0,
+                           SplitRule{found, p.VT, device_cu_count(), skip.s_max, skip.workgroups});
+        fwd_perm = perm;
+        rows_splits = found;
+        clear = nullptr;                                         // the scan writes the status word
+    }
     const int S = p.small_tiles && !fp8_in ? p.fwd_vt() : p.S;         // vocabulary splits of this forward
     {
         ProfSpan span(CCE_KERNEL_LSE_PARTIAL, stream);
         if (fp8_in)
             hipLaunchKernelGGL((lse_partial_kernel<false, true>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
         else if (p.small_tiles && smooth)
             hipLaunchKernelGGL((lse_partial_kernel<true, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear);
+                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
         else if (p.small_tiles)
             hipLaunchKernelGGL((lse_partial_kernel<false, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear);
+                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
         else if (smooth)
-            hipLaunchKernelGGL((lse_partial_kernel<true, false>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
+            hipLaunchKernelGGL((lse_partial_kernel<true, false>), dim3(grid), dim3(kThreads), TileBig::kLdsBytes, stream,
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
         else
-            hipLaunchKernelGGL((lse_partial_kernel<false, false>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear);
+            hipLaunchKernelGGL((lse_partial_kernel<false, false>), dim3(grid), dim3(kThreads), TileBig::kLdsBytes, stream,
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
     }
     hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream,
                        (const uint16_t*)hidden, (const uint16_t*)weight, labels, partials, (const float*)sumz,
                        (int)N, (int)D, (int)V, S, ignore_index, label_smoothing, z_loss, loss, lse, status,
-                       (int)v_off, (float4*)stats, fp8, fwd_perm);
+                       (int)v_off, (float4*)stats, fp8, fwd_perm, rows_splits);
     if (mean_loss && !stats)
         hipLaunchKernelGGL(mean_loss_kernel, dim3(1), dim3(1024), 0, stream,
-                           (const float*)loss, labels, (int)N, (int)V, ignore_index, mean_loss, (const int32_t*)nullptr);
+                           (const float*)loss, labels, (int)N, (int)V, ignore_index, mean_loss, rows_splits);
     if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
     return CCE_OK;
 }
@@ -1308,7 +1376,7 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
     // forward_impl checks a workspace against the whole plan (forward + backward); only the part
     // in front of off_dhacc exists here and only that part is addressed by the forward kernels
     return forward_impl(hidden, weight, labels, N, D, V, ignore_index, 0.f, 0.f, loss, lse, nullptr,
-                        0, nullptr, false, nullptr, ws, p.total, stream_, nullptr, status);
+                        0, nullptr, false, nullptr, ws, p.total, stream_, nullptr, status, (size_t)CCE_STATIC_SCRATCH_BYTES);
 }
 
 // The backward in the order of a Schedule (plan.h); arguments as in backward_impl, checked there.
@@ -1695,7 +1763,7 @@ int cce_forward_compact_ex(const void* hidden, const void* weight, const int32_t
     // (the scan writes the status word: no clearing launch)
     hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, labels, (int)N, (int)V, ignore_index,
                        (int)(max_valid_rows < N ? max_valid_rows : N), rows_pad, perm, (int32_t*)(ws + p.off_count), status, loss, lse,
-                       (uint16_t*)nullptr, 0);
+                       (uint16_t*)nullptr, 0, SplitRule{});
     // the kernels fetch hidden rows through perm and write loss / lse to the original rows
     cc.perm = perm;
     rc = forward_impl(hidden, weight, labels, M, D, V, ignore_index, label_smoothing, z_loss, loss, lse, nullptr,
@@ -1746,7 +1814,7 @@ int cce_backward_compact_ex(const void* hidden, const void* weight, const int32_
     drop_stale_hip_error();
     hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, labels, (int)N, (int)V, ignore_index,
                        (int)(max_valid_rows < N ? max_valid_rows : N), rows_pad, perm, (int32_t*)(ws + p.off_count), status,
-                       (float*)nullptr, (float*)nullptr, (uint16_t*)(ws + p.off_zero_row), (int)D);
+                       (float*)nullptr, (float*)nullptr, (uint16_t*)(ws + p.off_zero_row), (int)D, SplitRule{});
     {
         // (dHidden's rows that take no part become zeros here, or behind an order that uses dHidden)
         uint16_t* zero = order_uses_dhidden(p, cc.order) ? (uint16_t*)nullptr : (uint16_t*)dHidden;
