@@ -90,6 +90,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_kernel(
         N = rows_splits[0];
         S = rows_splits[1];
         TT = (N + Cfg::BN - 1) / Cfg::BN;
+        if (rows_splits[3]) perm = nullptr;           // every row takes part
     }
     const int n_work = rows_splits ? TT * S : (int)gridDim.x;
     if ((int)blockIdx.x >= n_work) return;
@@ -382,6 +383,13 @@ __global__ __launch_bounds__(1024) void mean_loss_kernel(const float* __restrict
 }
 
 // ------------------------------------------------------------------------------------------
+// Rows of `rows` planned ones that take part when the first is number `first` of those that do (count[0] in all).
+__device__ __forceinline__ int rows_left(const int32_t* count, int first, int rows) {
+    const int left = count[0] - first;
+    return left < 0 ? 0 : (left < rows ? left : rows);
+}
+
+// ------------------------------------------------------------------------------------------
 // Backward, step 1: recompute one logit tile and store the bf16 gradient tile
 //   G[i, v] = dloss_i * ((1 + 2 lambda lse_i) exp(z_iv - lse_i) - (1 - eps) [v == y_i] - eps / V),
 //   0 where the row is ignored / beyond N or the column is beyond V.  eps = lambda = 0 is the
@@ -401,13 +409,23 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
         int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
         int row0, int n_row_tiles, int v0, int n_v_tiles,
         uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total, const Fp8Scales fp8,
-        const int32_t* __restrict__ perm) {
+        const int32_t* __restrict__ perm, const int32_t* __restrict__ count, int first_row) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
     const int l = threadIdx.x & 63;
     const int wm = wave_m<Cfg>();
 
-    const int lin = xcd_round_id(blockIdx.x, gridDim.x, 2048 / Cfg::NW);
+    // (count: the rows that take part, where only the device knows; this launch's begin at first_row of them)
+    if (count) {
+        N = rows_left(count, first_row, N);
+        n_row_tiles = (N + 255) / 256 * (256 / Cfg::BN);        // whole 256-row tiles: the contractions read them
+        if (count[1]) {                               // every row takes part: no lookup in front of the first slice
+            H = (const char*)H + (size_t)first_row * (size_t)D * (FP8 ? 1 : 2);
+            perm = nullptr;
+        }
+    }
+    if ((int)blockIdx.x >= n_row_tiles * n_v_tiles) return;
+    const int lin = xcd_round_id(blockIdx.x, n_row_tiles * n_v_tiles, 2048 / Cfg::NW);
     int ti, vi;
     group_map(lin, n_row_tiles, n_v_tiles, 32 / Cfg::NW, ti, vi);          // an XCD works on ~4 x 8 tiles
     const int tok0 = row0 + ti * Cfg::BN;        // first token of the tile (global index)
@@ -448,7 +466,7 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
     Bop.init(H, ld, tok0, N, ld, perm);           // perm (row skipping): token t is row perm[t] of H
     if constexpr (FP8) {
         ScaleGroup SA, SB;
-        const int b_row0 = tok0 + wave_n<Cfg>() * (Cfg::TN * 32);
+        const int b_row0 = first_row + tok0 + wave_n<Cfg>() * (Cfg::TN * 32);       // (counted rows: scales in their order)
         SA.init(fp8.wscale, fp8.wgroups, (vt0 + wm * (Cfg::TM * 32)) >> 7);
         SB.init(fp8.hscale, fp8.hgroups, b_row0 >> 7);
         gemm_mainloop_fp8<Cfg>(acc, Aop, Bop, SA, SB, (b_row0 >> 6) & 1, D, smem);
@@ -584,12 +602,15 @@ struct GemmJob {
     uint16_t* out_hi; uint16_t* out_lo; int final;
     const int32_t* row_map;     // row skipping: out_hi row of tile row r is row_map[r] (-1: none); else nullptr
     const char* zero_row;       // row skipping: a row of zeros, read by the dW job for k-rows that map to no row
+    const int32_t* count; int first_row, rows;  // counted rows (MODE 9): see rows_left
 };
 
 // MODE bit 0: the launch's dH job uses the split running sum; bit 1: its bf16 rows go through
 // row_map and the dW job reads hidden rows through it (row skipping in the caller's tensors);
 // MODE 4: only the bf16 rows go through row_map (row skipping on a gathered copy of the hidden
-// rows).  Launch-wide constants, compiled as separate kernels so that the plain form carries none
+// rows); MODE 9: the number of rows that take part is found on the device (count), the dW job reads hidden rows through
+// row_map as 16-bit entries, the dH job's planes lie in compact rows and its bf16 result replaces the lower halves, from
+// where scatter_rows_kernel takes it.  Launch-wide constants, compiled as separate kernels so that the plain form carries none
 // of their code.  K split exists in modes 0 and 4.
 // Result of a work item, straight from the accumulators.  A lane holds one column of a 32 x 32 block and, per
 // register, two rows of it lie in a wavefront: a dword store is two full 128-byte segments, so nothing is staged
@@ -602,7 +623,7 @@ struct GemmJob {
 // planes of the split running sum lose (64-byte segments: items of 96 slices 101.1 -> 101.8).
 template <class Cfg, bool A_KMAJOR, int MODE>
 __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], const GemmJob& j, float* out, bool beta, int mi, int ni,
-                                             CCE_LDS char* smem) {
+                                             int m_valid, CCE_LDS char* smem) {
     constexpr bool SPLIT = A_KMAJOR && (MODE & 1) != 0, ROWMAP = A_KMAJOR && (MODE & 6) != 0;
     constexpr int KG = Cfg::KG, NB = Cfg::TM / KG;              // 32-row bands that a wavefront stores
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), l = threadIdx.x & 63;
@@ -626,7 +647,7 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     const int row = brow + block_row(2 * i) + pair_row;
-                    orow[set][i] = row < j.m_valid ? (ROWMAP ? j.row_map[row] : row) : -1;
+                    orow[set][i] = row < m_valid ? (ROWMAP ? j.row_map[row] : row) : -1;
                 }
             }
 #pragma unroll
@@ -634,12 +655,12 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
                 const int r = SPLIT ? i % 8 : i / Cfg::TN, bn = SPLIT ? i / 8 : i % Cfg::TN;
                 if constexpr (SPLIT) {
                     const int row = brow + block_row(2 * r) + pair_row, col = col0 + bn * 32 + pair_col;
-                    const bool ok = row < j.m_valid && beta;
+                    const bool ok = row < m_valid && beta;
                     old[set][bn][r] = ok && orow[set][r] >= 0 ? *(const float*)(j.out_hi + (size_t)orow[set][r] * ld + col) : 0.f;
                     old[set][bn][8 + r] = ok ? *(const float*)(j.out_lo + (size_t)row * ld + col) : 0.f;
                 } else {
                     const float* p = out + (size_t)(brow + block_row(r)) * ld + col0 + bn * 32;
-                    old[set][bn][r] = FULL || brow + block_row(r) + 4 * (l >> 5) < j.m_valid ? p[lane_off] : 0.f;
+                    old[set][bn][r] = FULL || brow + block_row(r) + 4 * (l >> 5) < m_valid ? p[lane_off] : 0.f;
                 }
             }
         };
@@ -695,7 +716,7 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
 #pragma unroll
                         for (int bn = bn0; bn < bn0 + STEP; ++bn) {
                             float* p = out + (size_t)(brow + block_row(r)) * ld + col0 + bn * 32;
-                            if (FULL || brow + block_row(r) + 4 * (l >> 5) < j.m_valid) p[lane_off] = v[bn][r];
+                            if (FULL || brow + block_row(r) + 4 * (l >> 5) < m_valid) p[lane_off] = v[bn][r];
                         }
                     continue;
                 }
@@ -705,7 +726,7 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
                         const int row = brow + block_row(2 * i) + pair_row;
                         int to;
                         if constexpr (SPLIT) to = orow[b & 1][i];
-                        else to = row < j.m_valid ? (ROWMAP ? j.row_map[row] : row) : -1;
+                        else to = row < m_valid ? (ROWMAP ? j.row_map[row] : row) : -1;
 #pragma unroll
                         for (int bn = bn0; bn < bn0 + STEP; ++bn) {
                             const int col = col0 + bn * 32 + pair_col;
@@ -722,11 +743,12 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
                                 union { __bf16 h[2]; uint32_t u; } cv;
                                 cv.h[0] = (__bf16)x;
                                 cv.h[1] = (__bf16)y;
-                                if (to >= 0) *(uint32_t*)(j.out_hi + (size_t)to * ld + col) = cv.u;
+                                uint16_t* const result = MODE == 9 ? j.out_lo : j.out_hi;
+                                if (to >= 0) *(uint32_t*)(result + (size_t)to * ld + col) = cv.u;
                             } else {
                                 const uint32_t bx = __builtin_bit_cast(uint32_t, x), by = __builtin_bit_cast(uint32_t, y);
                                 if (to >= 0) *(uint32_t*)(j.out_hi + (size_t)to * ld + col) = (by & 0xffff0000u) | (bx >> 16);
-                                if (row < j.m_valid) *(uint32_t*)(j.out_lo + (size_t)row * ld + col) = (by << 16) | (bx & 0xffffu);
+                                if (row < m_valid) *(uint32_t*)(j.out_lo + (size_t)row * ld + col) = (by << 16) | (bx & 0xffffu);
                             }
                         }
                     }
@@ -734,7 +756,7 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
             }
         }
     };
-    const bool full = row0 + Cfg::TM * 32 <= j.m_valid;
+    const bool full = row0 + Cfg::TM * 32 <= m_valid;
     auto with_rows = [&](auto first) {
         if (full) run(first, std::true_type{});
         else run(first, std::false_type{});
@@ -744,8 +766,8 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
 }
 
 template <class Cfg, bool A_KMAJOR, int MODE>
-__device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS char* smem) {
-    constexpr bool KSPLIT = (MODE & 3) == 0;
+__device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, int rows, CCE_LDS char* smem) {
+    constexpr bool COUNTED = (MODE & 8) != 0, KSPLIT = (MODE & 3) == 0 && !COUNTED;
     int part = 0;
     if (KSPLIT && j.n_split > 1) {
         const int per = j.n_work / j.n_split;
@@ -753,7 +775,7 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
         item -= part * per;
     }
     const int k0 = KSPLIT ? part * j.split_k : 0;
-    const int k_len = !KSPLIT ? j.k_total : (j.k_total - k0 < j.split_k ? j.k_total - k0 : j.split_k);
+    const int k_len = COUNTED && !A_KMAJOR ? (rows + 255) / 256 * 256 : !KSPLIT ? j.k_total : (j.k_total - k0 < j.split_k ? j.k_total - k0 : j.split_k);
     float* const out_f32 = part == 0 ? j.out_f32 : j.part + (size_t)(part - 1) * j.part_stride;
     const bool beta = part < j.beta_n;
     const int mi = item / j.n_tiles, ni = item % j.n_tiles;    // consecutive items share the A band
@@ -766,12 +788,20 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[bm][bn][r] = 0.f;
 
-    constexpr bool kMappedB = (MODE & 2) != 0 && !A_KMAJOR;        // row skipping, dW job
+    constexpr int kMapB = A_KMAJOR ? 0 : COUNTED ? 2 : (MODE & 2) != 0 ? 1 : 0;        // row skipping, dW job
     PanelTile<A_KMAJOR, Cfg::BM, Cfg::NW, Cfg::BK> Aop;
-    OperandTile<false, Cfg::BN, kMappedB, Cfg::NW, Cfg::BK> Bop;
+    OperandTile<false, Cfg::BN, kMapB, Cfg::NW, Cfg::BK> Bop;
     Aop.init(j.A, j.panel, mi * Cfg::BM, k0);
     Bop.init((const uint16_t*)j.B + (size_t)k0 * j.ldb, j.ldb, ni * Cfg::BN, j.n_valid, j.b_k_n - k0);
-    if constexpr ((MODE & 2) != 0 && !A_KMAJOR) {
+    if constexpr (kMapB == 2) {
+        // the rows that take part, in 16 bits (at most 65536 rows); behind the last one that row again, whose products
+        // meet the chunk's zero rows
+        CCE_LDS uint16_t* tab = (CCE_LDS uint16_t*)(smem + Cfg::kLdsBytes);
+        for (int i = threadIdx.x; i < k_len; i += Cfg::kThreads) tab[i] = (uint16_t)j.row_map[i < rows ? i : rows - 1];
+        __syncthreads();
+        Bop.kmap16 = tab;
+    }
+    if constexpr (kMapB == 1) {
         // row skipping, dW job: the reduction runs over the compact rows of the block, whose hidden
         // rows are scattered over the original tensor.  The block's row map is copied into LDS
         // (behind everything the kernel otherwise uses) and the operand loader looks each of its
@@ -787,25 +817,75 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, CCE_LDS
     __builtin_amdgcn_s_waitcnt(0x0f70);                          // vmcnt(0)
     gemm_mainloop<Cfg, A_KMAJOR, false, true>(acc, Aop, Bop, k_len, smem);
 
-    store_result<Cfg, A_KMAJOR, MODE>(acc, j, out_f32, beta, mi, ni, smem);
+    store_result<Cfg, A_KMAJOR, MODE>(acc, j, out_f32, beta, mi, ni, COUNTED && A_KMAJOR ? rows : j.m_valid, smem);
 }
 
 template <class Cfg, int MODE>
 __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_gemm_kernel(const GemmJob first, const GemmJob second) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
+    constexpr bool COUNTED = (MODE & 8) != 0;
+    int rows = 0, n1 = first.n_work, n2 = second.n_work;
+    bool swapped = false;
+    if constexpr (COUNTED) {
+        // Items and reductions of the rows that take part: the dH job's items follow them, the dW job's reduction.
+        rows = rows_left(first.count, first.first_row, first.rows);
+        const int tiles = (rows + 255) / 256;
+        auto items = [&](const GemmJob& j) { return j.a_kmajor ? tiles * (256 / Cfg::BM) * j.n_tiles : (tiles == 0 && j.beta_n ? 0 : j.n_work); };
+        auto length = [&](const GemmJob& j) { return j.a_kmajor ? j.k_total : tiles * 256; };
+        swapped = length(first) < length(second);               // longer reduction first
+        n1 = items(swapped ? second : first);
+        n2 = items(swapped ? first : second);
+        if ((int)blockIdx.x >= n1 + n2) return;
+    }
     bool in_first;
     int item;
-    if (first.n_work >= 8 && second.n_work >= 8) {
-        xcd_two_job_map(blockIdx.x, first.n_work, second.n_work, in_first, item);
+    if (n1 >= 8 && n2 >= 8) {
+        xcd_two_job_map(blockIdx.x, n1, n2, in_first, item);
     } else {
-        const int lin = xcd_round_id(blockIdx.x, gridDim.x, 2048 / Cfg::NW);
-        in_first = lin < first.n_work;
-        item = in_first ? lin : lin - first.n_work;
+        const int lin = xcd_round_id(blockIdx.x, n1 + n2, 2048 / Cfg::NW);
+        in_first = lin < n1;
+        item = in_first ? lin : lin - n1;
     }
-    const GemmJob& j = in_first ? first : second;
-    if (j.a_kmajor) run_gemm_job<Cfg, true, MODE>(j, item, smem);
-    else run_gemm_job<Cfg, false, (MODE & 2)>(j, item, smem);
+    const GemmJob& j = in_first != swapped ? first : second;
+    if (j.a_kmajor) run_gemm_job<Cfg, true, MODE>(j, item, rows, smem);
+    else run_gemm_job<Cfg, false, (MODE & 10)>(j, item, rows, smem);
+}
+
+// E4M3 scale bytes of the rows that take part, in their order and the grouped layout (see ScaleGroup); one dword, i.e.
+// four rows of one 128-column block, per thread.  Rows that stand for none get scale 1.
+__global__ __launch_bounds__(256) void compact_scales_kernel(const void* __restrict__ scales, int groups, const int32_t* __restrict__ perm,
+                                                             int groups_c, int blocks, uint32_t* __restrict__ out) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= blocks * groups_c * 32) return;
+    const int kb = i / (groups_c * 32), g = (i >> 5) % groups_c;
+    uint32_t word = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = perm[g * 128 + q * 32 + (i & 31)];
+        word |= (uint32_t)(row < 0 ? 127 : scale_byte(scales, groups, row, kb)) << (8 * q);
+    }
+    out[i] = word;
+}
+
+// Split running sum of counted rows: dHidden row perm[r] = compact row r of the result; zero rows where the label takes
+// no part.  One wavefront per row of either kind.
+__global__ __launch_bounds__(256) void scatter_rows_kernel(const uint16_t* __restrict__ rows, const int32_t* __restrict__ perm,
+                                                           const int32_t* __restrict__ count, const int32_t* __restrict__ labels, int N, int V,
+                                                           int32_t ignore_index, int D, uint16_t* __restrict__ dhidden) {
+    const int l = threadIdx.x & 63;
+    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= N) return;
+    const int32_t y = labels[r];
+    if (y == ignore_index || y < 0 || y >= V) {
+        u32x4* zero = (u32x4*)(dhidden + (size_t)r * D);
+        for (int c = l; c < (D >> 3); c += 64) zero[c] = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (r < count[0]) {
+        const u32x4* from = (const u32x4*)(rows + (size_t)r * D);
+        u32x4* to = (u32x4*)(dhidden + (size_t)perm[r] * D);
+        for (int c = l; c < (D >> 3); c += 64) to[c] = from[c];
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -931,6 +1011,7 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
     for (int r = kept + tid; r < rows_pad; r += 1024) perm[r] = -1;
     if (tid == 0) {
         count_out[0] = kept;
+        count_out[1] = kept == N ? 1 : 0;             // the row map is the identity
         status[0] = (any_bad ? CCE_STATUS_BAD_LABEL : 0) | (total > max_rows ? CCE_STATUS_ROW_BOUND : 0);
     }
     if (rule.rows_splits) {
@@ -1116,6 +1197,8 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 0>, kGemmLdsDuo)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 1>, kGemmLdsDuo)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 4>, kGemmLdsDuo)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileBig, 9>, kGemmLdsBig + kRowTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 9>, kGemmLdsNarrow + kRowTableBytes)) return false;
     done[dev] = true;
     return true;
 }
@@ -1124,19 +1207,29 @@ static bool ensure_kernel_attributes() {
 static void launch_grad_tiles(const void* H, const void* W, const int32_t* labels, const float* lse, const float* dloss,
                               const float* mean_scale, int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
                               int row0, int n_row_tiles, int v0, int n_v_tiles, uint16_t* G, uint32_t panel, int panel_shift, int v_off, int V_total,
-                              const int32_t* perm, hipStream_t stream) {
+                              const int32_t* perm, hipStream_t stream, const int32_t* count = nullptr, int first_row = 0) {
     const Fp8Scales none = {nullptr, nullptr, 0, 0};
     if (use_small_tiles(n_row_tiles, n_v_tiles))
         hipLaunchKernelGGL((grad_tile_kernel<false, TileSmall>), dim3(4 * n_row_tiles * n_v_tiles), dim3(kThreads), grad_tile_lds<TileSmall>(),
                            stream, H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           2 * n_row_tiles, v0, 2 * n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm);
+                           2 * n_row_tiles, v0, 2 * n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
     else
         hipLaunchKernelGGL(grad_tile_kernel<false>, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), kGradTileLds, stream,
                            H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           n_row_tiles, v0, n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm);
+                           n_row_tiles, v0, n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
 }
 
 // A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
+// Counted rows (mode 9): 256 x 256 or 256 x 128 tiles, the row table behind their stages.
+static void launch_counted_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+    const int work = first.n_work + second.n_work;
+    ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
+    if (kind == 0)
+        hipLaunchKernelGGL((grad_gemm_kernel<TileBig, 9>), dim3(work), dim3(kThreads), kGemmLdsBig + kRowTableBytes, stream, first, second);
+    else
+        hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, 9>), dim3(work), dim3(kThreads), kGemmLdsNarrow + kRowTableBytes, stream, first, second);
+}
+
 template <int MODE>
 static void launch_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
     const int work = first.n_work + second.n_work;
@@ -1207,6 +1300,9 @@ struct CompactCtx {
     }
 };
 
+// A backward over all rows that leaves the ignored ones out by a count found on the device.
+struct CountedRows { const int32_t* perm; const int32_t* count; };
+
 // Forward over the V rows of `weight`, which are the rows [v_off, v_off + V) of the full
 // matrix.  With `stats` the per-token shard statistics are written instead of loss / lse
 // (`smooth` then says whether the logit sums are wanted).
@@ -1250,7 +1346,8 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
     const int32_t* rows_splits = nullptr;
     int grid = p.TT * p.S;
     // All rows, ignored ones among them perhaps: large forwards leave those out without being told how many there are.
-    const ForwardSkip skip = cc || stats || fp8_in ? ForwardSkip{} : forward_skip(p, D, scratch_bytes);
+    const ForwardSkip skip = cc || stats ? ForwardSkip{} : forward_skip(p, D, fp8_in != nullptr, scratch_bytes);
+    Fp8Scales tile_fp8 = fp8;                                   // (the label logit keeps the caller's scales)
     if (skip.use) {
         int32_t* const perm = (int32_t*)(ws + skip.off_perm);
         int32_t* const found = (int32_t*)(ws + skip.off_found);
@@ -1260,6 +1357,13 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
         hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, labels, (int)N, (int)V, ignore_index, (int)N, p.TT * 256,
                            perm, found + 2, status, loss, lse, (uint16_t*)nullptr, 0,
                            SplitRule{found, p.VT, device_cu_count(), skip.s_max, skip.workgroups});
+        if (fp8_in) {
+            const int groups = p.TT * 2, words = (int)(D / 128) * groups * 32;
+            hipLaunchKernelGGL(compact_scales_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, fp8.hscale, fp8.hgroups,
+                               (const int32_t*)perm, groups, (int)(D / 128), (uint32_t*)(ws + skip.off_scales));
+            tile_fp8.hscale = ws + skip.off_scales;
+            tile_fp8.hgroups = groups;
+        }
         fwd_perm = perm;
         rows_splits = found;
         clear = nullptr;                                         // the scan writes the status word
@@ -1268,8 +1372,8 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
     {
         ProfSpan span(CCE_KERNEL_LSE_PARTIAL, stream);
         if (fp8_in)
-            hipLaunchKernelGGL((lse_partial_kernel<false, true>), dim3(p.TT * p.S), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
+            hipLaunchKernelGGL((lse_partial_kernel<false, true>), dim3(grid), dim3(kThreads), TileBig::kLdsBytes, stream,
+                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, tile_fp8, fwd_perm, clear, rows_splits);
         else if (p.small_tiles && smooth)
             hipLaunchKernelGGL((lse_partial_kernel<true, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
                                hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
@@ -1387,7 +1491,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                         int64_t N, int64_t D, int64_t V, int64_t v_off, int64_t V_total, int32_t ignore_index,
                         float label_smoothing, float z_loss, void* dHidden, float* dW, int accumulate_dW,
                         const void* logit_hidden, const void* logit_weight, const Fp8Scales* fp8,
-                        char* ws, hipStream_t stream, const CompactCtx* cc) {
+                        char* ws, hipStream_t stream, const CompactCtx* cc, const CountedRows* counted) {
     const Fp8Scales scales = fp8 ? *fp8 : Fp8Scales{nullptr, nullptr, 0, 0};
     const int d_tiles = (int)((D + gemm_tile_of_kind(sc.kind).bn - 1) / gemm_tile_of_kind(sc.kind).bn);
     const Knobs knobs = Knobs::read();
@@ -1426,8 +1530,9 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
                 const int n_split_w = (row_tiles + kw - 1) / kw;
                 const bool dw_beta = row0 > 0 || accumulate_dW;
-                const int kind = contraction_kind(sc.kind, D, (int64_t)row_tiles * n_split_h * d_tiles, kh * 4, planes_written > 0, sc.split_acc != 0,
-                                                  (int64_t)v_tiles * n_split_w * d_tiles, kw * 4, dw_beta, false, knobs);
+                const int kind = counted ? sc.kind
+                                         : contraction_kind(sc.kind, D, (int64_t)row_tiles * n_split_h * d_tiles, kh * 4, planes_written > 0, sc.split_acc != 0,
+                                                            (int64_t)v_tiles * n_split_w * d_tiles, kw * 4, dw_beta, false, knobs);
                 const int panel_shift = kind == 3 ? 5 : 6;                // log2 of the K slice of the contractions' tiles
                 const uint32_t panel = (uint32_t)(row_tiles * 256) << panel_shift;
                 uint16_t* G = ch.in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
@@ -1436,11 +1541,21 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                     // tokens are counted inside the step: its rows and per-row scalars are contiguous
                     ProfSpan span(CCE_KERNEL_GRAD_TILE, stream);
                     const dim3 grid((unsigned)(row_tiles * v_tiles));
-                    if (fp8)
+                    if (fp8 && counted)
+                        hipLaunchKernelGGL(grad_tile_kernel<true>, grid, dim3(kThreads), kGradTileLds, stream,
+                                           logit_hidden, logit_weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
+                                           (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0, v_tiles,
+                                           G, panel, panel_shift, (int)v_off, (int)V_total, scales, counted->perm + row0, counted->count, (int)row0);
+                    else if (fp8)
                         hipLaunchKernelGGL(grad_tile_kernel<true>, grid, dim3(kThreads), kGradTileLds, stream,
                                            logit_hidden, logit_weight, labels, lse, dloss, mean_scale, (int)N, (int)D, (int)V,
                                            ignore_index, label_smoothing, z_loss, (int)row0, row_tiles, (int)v0, v_tiles, G, panel, panel_shift,
-                                           (int)v_off, (int)V_total, scales, (const int32_t*)nullptr);
+                                           (int)v_off, (int)V_total, scales, (const int32_t*)nullptr, (const int32_t*)nullptr, 0);
+                    else if (counted)
+                        launch_grad_tiles(hidden, weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
+                                          (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
+                                          v_tiles, G, panel, panel_shift, (int)v_off, (int)V_total, counted->perm + row0, stream,
+                                          counted->count, (int)row0);
                     else
                         launch_grad_tiles((const void*)h_step, weight, labels + row0, lse + row0, dloss ? dloss + row0 : dloss, mean_scale,
                                           (int)srows, (int)D, (int)V, ignore_index, label_smoothing, z_loss, 0, row_tiles, (int)v0,
@@ -1475,6 +1590,17 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 dw.beta_n = dw_beta ? 1 : 0;
                 dw.final = 0; dw.out_hi = nullptr; dw.out_lo = nullptr; dw.row_map = nullptr; dw.zero_row = nullptr;
 
+                dh.count = dw.count = nullptr;
+                dh.first_row = dw.first_row = 0;
+                dh.rows = dw.rows = (int)srows;
+                if (counted) {
+                    dh.count = dw.count = counted->count;
+                    dh.first_row = dw.first_row = (int)row0;
+                    dw.B = hidden;
+                    dh.row_map = dw.row_map = counted->perm + row0;
+                    launch_counted_contractions(kind, dh, dw, stream);
+                    continue;
+                }
                 const bool dh_first = kh >= kw;                          // longer items first
                 const GemmJob& first = dh_first ? dh : dw;
                 const GemmJob& second = dh_first ? dw : dh;
@@ -1553,10 +1679,39 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                            labels, (int)N, (int)V_total, ignore_index, grad_scale, mean_scale);
     const int grad_lds = kGradTileLds;
 
+    const BackwardSkip skip = cc || V_total != V ? BackwardSkip{} : backward_skip(p, sc, D, fp8_in != nullptr);
+    if (skip.use) {
+        int32_t* const perm = (int32_t*)(ws + skip.off_perm);
+        int32_t* const labels_c = (int32_t*)(ws + skip.off_labels);
+        float* const lse_c = (float*)(ws + skip.off_lse);
+        float* const dloss_c = (float*)(ws + skip.off_dloss);
+        int32_t* const count = (int32_t*)(ws + skip.off_count);
+        const int rows_pad = p.TT * 256;
+        hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, labels, (int)N, (int)V, ignore_index, (int)N, rows_pad, perm, count,
+                           (int32_t*)(ws + p.off_status), (float*)nullptr, (float*)nullptr, (uint16_t*)nullptr, 0, SplitRule{});
+        hipLaunchKernelGGL(compact_prepare_backward_kernel, dim3((unsigned)(rows_pad / 256)), dim3(256), 0, stream,
+                           (const int32_t*)perm, (const int32_t*)count, rows_pad, labels, (int)N, (int)V, ignore_index, labels_c,
+                           lse, lse_c, dloss, dloss_c, (int)D, (uint16_t*)nullptr);
+        if (fp8_in) {
+            const int groups = p.TT * 2, words = (int)(D / 128) * groups * 32;
+            hipLaunchKernelGGL(compact_scales_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, fp8.hscale, fp8.hgroups,
+                               (const int32_t*)perm, groups, (int)(D / 128), (uint32_t*)(ws + skip.off_scales));
+            fp8.hscale = ws + skip.off_scales;
+            fp8.hgroups = groups;
+        }
+        const CountedRows counted = {perm, count};
+        run_schedule(sc, hidden, weight, labels_c, lse_c, dloss ? dloss_c : (const float*)nullptr, mean_scale, N, D, V, v_off, V_total, ignore_index,
+                     label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
+                     ws, stream, nullptr, &counted);
+        hipLaunchKernelGGL(scatter_rows_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream, (const uint16_t*)(ws + sc.off_acc),
+                           (const int32_t*)perm, (const int32_t*)count, labels, (int)N, (int)V, ignore_index, (int)D, (uint16_t*)dHidden);
+        if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
+        return CCE_OK;
+    }
     if (sc.use) {
         run_schedule(sc, hidden, weight, labels, lse, dloss, mean_scale, N, D, V, v_off, V_total, ignore_index,
                      label_smoothing, z_loss, dHidden, dW, accumulate_dW, logit_hidden, logit_weight, fp8_in ? &fp8 : nullptr,
-                     ws, stream, cc);
+                     ws, stream, cc, nullptr);
         if (cc && order_uses_dhidden(p, sc)) cc->zero_skipped(stream, dHidden);
         if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
         return CCE_OK;
@@ -1605,7 +1760,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
                                    logit_hidden, logit_weight, labels, lse, dloss, (const float*)mean_scale,
                                    (int)N, (int)D, (int)V, ignore_index, label_smoothing, z_loss,
                                    (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, panel, panel_shift, (int)v_off, (int)V_total, fp8,
-                                   cc ? cc->perm : (const int32_t*)nullptr);
+                                   cc ? cc->perm : (const int32_t*)nullptr, (const int32_t*)nullptr, 0);
             else
                 launch_grad_tiles(hidden, weight, labels, lse, dloss, (const float*)mean_scale, n_rows_h, (int)D, (int)V, ignore_index,
                                   label_smoothing, z_loss, (int)st.r0, st.row_tiles, (int)st.v0, st.v_tiles, G, panel, panel_shift, (int)v_off,
@@ -1638,6 +1793,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         dw.row_map = cc ? cc->perm + st.r0 : (const int32_t*)nullptr;
         dw.zero_row = cc ? cc->zero_row : (const char*)nullptr;
         dw.n_split = 1; dw.split_k = dw.k_total; dw.part = nullptr; dw.part_stride = 0;
+        dh.count = dw.count = nullptr; dh.first_row = dw.first_row = 0; dh.rows = dw.rows = (int)st.rows;
         const bool dh_first = dh.k_total >= dw.k_total;          // longer reduction first
         const GemmJob& first = dh_first ? dh : dw;
         const GemmJob& second = dh_first ? dw : dh;

@@ -118,10 +118,12 @@ __device__ __forceinline__ void load16_to_lds_sbase(const char* uniform_base, ui
 }
 
 // One operand (R = 128 or 256 free indices) of one workgroup tile: global -> LDS.
-// MAPPED (K-slow only): the k-rows are reached through a row map (kmap, kzero).
-template <bool KMAJOR, int R, bool MAPPED = false, int NW = 8, int BK = 64>
+// MAP (K-slow only): 1, the k-rows are reached through a row map (kmap, kzero); 2, through one of 16 bits whose
+// entries are all rows (kmap16): a load then costs one LDS read and one multiply-add.
+template <bool KMAJOR, int R, int MAP = 0, int NW = 8, int BK = 64>
 struct OperandTile {
-    static_assert(!(KMAJOR && MAPPED), "only a K-slow operand carries a k-row map");
+    static constexpr bool MAPPED = MAP == 1;
+    static_assert(!(KMAJOR && MAP), "only a K-slow operand carries a k-row map");
     static constexpr int NL = R * BK / 512 / NW;   // 16-byte loads per thread and K slice
     const char* base;       // matrix base address
     uint32_t ld_bytes;      // leading dimension in bytes
@@ -131,6 +133,7 @@ struct OperandTile {
     int k_last;             // K-slow: last valid k (rows beyond are clamped to it)
     const CCE_LDS int32_t* kmap;   // K-slow, optional: k-row k is matrix row kmap[k]; where it holds -1 the
     const char* kzero;             // row is read from kzero instead: a row of zeros as long as a matrix row
+    const CCE_LDS uint16_t* kmap16;
 
     // free0: first free index of the tile; free_n: number of valid free indices in the matrix
     // (a multiple of 8, at least 8, for a K-slow operand); k_n: valid K extent.
@@ -143,6 +146,7 @@ struct OperandTile {
         k_last = k_n - 1;
         kmap = nullptr;
         kzero = nullptr;
+        kmap16 = nullptr;
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         if (KMAJOR) {
             constexpr int CPR = BK / 8, RPL = 64 / CPR;      // 16-byte chunks per row, rows per wavefront load
@@ -180,7 +184,7 @@ struct OperandTile {
 
     // K slices [0, full_slices()) lie entirely inside the operand's valid K extent (every slice of a
     // K-major operand does: its extent is padded to the slice).
-    __device__ __forceinline__ int full_slices() const { return KMAJOR ? 0x7fffffff : (k_last + 1) / BK; }
+    __device__ __forceinline__ int full_slices() const { return KMAJOR || MAP == 2 ? 0x7fffffff : (k_last + 1) / BK; }
 
     // Issue this thread's loads of the K slice starting at k0 into `stage` (LDS).  FULL (compile time):
     // the caller knows that the slice is one of full_slices().
@@ -193,6 +197,12 @@ struct OperandTile {
             const char* sb = base + (size_t)((uint32_t)k0 * 2u);
 #pragma unroll
             for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, off[i], lds0 + (uint32_t)i * (NW * 1024u));
+            return;
+        }
+        if constexpr (MAP == 2) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                load16_to_lds_sbase(base, __umul24((uint32_t)kmap16[k0 + krow[i]], ld_bytes) + off[i], lds0 + (uint32_t)i * (NW * 1024u));
             return;
         }
         if (!MAPPED && (FULL || k0 + BK - 1 <= k_last)) {

@@ -649,14 +649,14 @@ struct RowBlockPlanner {
 
 // A forward over all rows that leaves the ignored ones out: their number is found on the device, so the launch has the
 // workgroups of all rows and those beyond the rows that take part return at once; what is laid out behind the plan's
-// partials (the forward uses nothing there) is the row map, the counts and partials for more splits than the plan's.
+// partials (the forward uses nothing there) is the row map, the counts, FP8 scales in the order of those rows, and partials for more splits than the plan's.
 // The label scan and its launch take 9 us at 8192 rows.  Taken from about 1 ms of forward on (1.15 PFLOP/s): at most 1 %
 // where nothing is ignored; 8192 x 896 x 151936 with 15 % ignored 1.89 -> 1.64 ms, 4099 x 2048 x 128256 with 5 % 1.78 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.60 -> 1.24, none ignored 1.600 -> 1.606.
 // Below, and for few row tiles, a launch of one round hardly gets shorter by the rows that real padding leaves out.
-struct ForwardSkip { bool use; int s_max, workgroups; size_t off_perm, off_found, off_partials, off_sumz; };
-static ForwardSkip forward_skip(const Plan& p, int64_t D, size_t bytes) {
+struct ForwardSkip { bool use; int s_max, workgroups; size_t off_perm, off_found, off_scales, off_partials, off_sumz; };
+static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8, size_t bytes) {
     ForwardSkip f = {};
-    if (p.small_tiles || p.TT < 8 || g_force_row_skipping.load(std::memory_order_relaxed) != 0) return f;
+    if ((p.small_tiles && !fp8) || p.TT < 8 || g_force_row_skipping.load(std::memory_order_relaxed) != 0) return f;
     if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return f;
     const int cus = device_cu_count(), most = 2 * p.S + 8;
     f.s_max = most < p.VT ? most : p.VT;
@@ -665,7 +665,8 @@ static ForwardSkip forward_skip(const Plan& p, int64_t D, size_t bytes) {
     f.workgroups = (p.TT * p.S + cus - 1) / cus * cus;
     f.off_perm = p.off_dhacc;
     f.off_found = f.off_perm + (size_t)round_up((int64_t)p.TT * 1024, 256);
-    f.off_partials = f.off_found + 256;
+    f.off_scales = f.off_found + 256;                          // FP8: the scale bytes of the rows that take part
+    f.off_partials = f.off_scales + (fp8 ? (size_t)round_up(D / 128 * p.TT * 256, 256) : (size_t)0);
     f.off_sumz = f.off_partials + (size_t)round_up(p.rows * f.s_max * 8, 256);
     f.use = f.off_sumz + (size_t)p.rows * f.s_max * 4 <= bytes;
     return f;
@@ -905,6 +906,29 @@ static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t 
     const size_t rooms = room_most < (double)kBudgetFloor ? (size_t)room_most : kBudgetFloor;
     const size_t serves = plans > rooms ? plans : rooms;
     return taken.total > serves ? taken.total : serves;
+}
+
+// The same of a backward: one whose schedule has all rows in one block, no K parts and its dH sums in two planes (large
+// ones have), and whose row map fits the contraction's LDS table in 16 bits.  The order stays.  Step of 8192 x 896 x 151936
+// with 15 % ignored 8.10 -> 7.69 ms (40 %: 6.25), with FP8 logits 7.13 -> 6.56, 6000 x 1536 x 65001 4.47 -> 3.96.  Without
+// ignored rows it costs the scan, the gather of the per-row scalars and the scatter of dHidden's rows: 8.61 -> 8.63, FP8
+// 7.18 -> 7.25; at most 1.1 %, where launches would have taken tiles two to a unit (6000 x 1536 x 65001 4.58 -> 4.63).
+// The bookkeeping lies where the forward's partials were.
+struct BackwardSkip { bool use; size_t off_perm, off_labels, off_lse, off_dloss, off_count, off_scales; };
+static BackwardSkip backward_skip(const Plan& p, const Schedule& sc, int64_t D, bool fp8) {
+    BackwardSkip b = {};
+    if (!sc.use || !sc.split_acc || sc.a < p.TT || sc.split_h != 1 || sc.split_w != 1 || p.TT < 8 || p.TT > kRowTableBytes / 512) return b;
+    if (g_force_row_skipping.load(std::memory_order_relaxed) != 0 || p.forced) return b;
+    if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return b;
+    const size_t each = (size_t)p.TT * 1024;
+    b.off_perm = p.off_partials;
+    b.off_labels = b.off_perm + each;
+    b.off_lse = b.off_labels + each;
+    b.off_dloss = b.off_lse + each;
+    b.off_count = b.off_dloss + each;
+    b.off_scales = b.off_count + 256;
+    b.use = b.off_scales + (fp8 ? (size_t)(D / 128 * p.TT * 256) : (size_t)0) <= p.off_dhacc;
+    return b;
 }
 
 // Row skipping: the order keeps something in dHidden while it runs -- the gathered rows of a single row block,
