@@ -601,8 +601,9 @@ struct GemmJob {
     float* out_f32; int64_t ld_out; int beta_n;
     uint16_t* out_hi; uint16_t* out_lo; int final;
     const int32_t* row_map;     // row skipping: out_hi row of tile row r is row_map[r] (-1: none); else nullptr
-    const char* zero_row;       // row skipping: a row of zeros, read by the dW job for k-rows that map to no row
-    const int32_t* count; int first_row, rows;  // counted rows (MODE 9): see rows_left
+    const char* zero_row;       // row skipping: a row of zeros, read by the dW job where no row takes part
+    int first_row;              // row_map's first entry is that of this compact row
+    const int32_t* count; int rows;             // counted rows (MODE 9): see rows_left
 };
 
 // MODE bit 0: the launch's dH job uses the split running sum; bit 1: its bf16 rows go through
@@ -802,15 +803,20 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, int row
         Bop.kmap16 = tab;
     }
     if constexpr (kMapB == 1) {
-        // row skipping, dW job: the reduction runs over the compact rows of the block, whose hidden
-        // rows are scattered over the original tensor.  The block's row map is copied into LDS
-        // (behind everything the kernel otherwise uses) and the operand loader looks each of its
-        // k-rows up there.  (The host gives every row-skipping launch its row map.)
-        CCE_LDS int32_t* tab = (CCE_LDS int32_t*)(smem + Cfg::kLdsBytes);
-        for (int i = threadIdx.x; i < j.b_k_n; i += Cfg::kThreads) tab[i] = j.row_map[i];
+        // row skipping, dW job: the reduction runs over the compact rows of the block, whose hidden rows are scattered over
+        // the original tensor.  Their byte offsets are put into LDS, behind everything the kernel otherwise uses.
+        // Compact rows that stand for none take the first valid row, whose products meet the chunk's zero rows;
+        // where there is no valid row at all, a row of zeros (whatever a skipped row holds -- NaN included -- would
+        // meet the other operand's zero in the MFMA).
+        CCE_LDS uint32_t* tab = (CCE_LDS uint32_t*)(smem + Cfg::kLdsBytes);
+        const int32_t some = __builtin_amdgcn_readfirstlane(j.row_map[-j.first_row]);
+        for (int i = threadIdx.x; i < j.k_total; i += Cfg::kThreads) {
+            const int32_t row = i < j.b_k_n ? j.row_map[i] : -1;
+            tab[i] = some < 0 ? 0u : (uint32_t)(row < 0 ? some : row) * (uint32_t)(j.ldb * 2);
+        }
         __syncthreads();
         Bop.kmap = tab;
-        Bop.kzero = j.zero_row;
+        if (some < 0) Bop.base = j.zero_row;
     }
     // Whatever the compiler loaded so far has to be there: it cannot see the main loop's loads, and a register still
     // waited for inside the loop (a field of the job, say) becomes a wait for all of them in every slice.
@@ -1793,7 +1799,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         dw.row_map = cc ? cc->perm + st.r0 : (const int32_t*)nullptr;
         dw.zero_row = cc ? cc->zero_row : (const char*)nullptr;
         dw.n_split = 1; dw.split_k = dw.k_total; dw.part = nullptr; dw.part_stride = 0;
-        dh.count = dw.count = nullptr; dh.first_row = dw.first_row = 0; dh.rows = dw.rows = (int)st.rows;
+        dh.count = dw.count = nullptr; dh.first_row = dw.first_row = (int)st.r0; dh.rows = dw.rows = (int)st.rows;
         const bool dh_first = dh.k_total >= dw.k_total;          // longer reduction first
         const GemmJob& first = dh_first ? dh : dw;
         const GemmJob& second = dh_first ? dw : dh;

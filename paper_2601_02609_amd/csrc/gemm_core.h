@@ -118,11 +118,12 @@ __device__ __forceinline__ void load16_to_lds_sbase(const char* uniform_base, ui
 }
 
 // One operand (R = 128 or 256 free indices) of one workgroup tile: global -> LDS.
-// MAP (K-slow only): 1, the k-rows are reached through a row map (kmap, kzero); 2, through one of 16 bits whose
-// entries are all rows (kmap16): a load then costs one LDS read and one multiply-add.
+// MAP (K-slow only): the k-rows are reached through a table in LDS with an entry for every k of whole slices, 1: byte
+// offsets of matrix rows (kmap), 2: row numbers in 16 bits (kmap16).  A load then costs one LDS read and one add or
+// multiply-add.  (With bounds, rows that map to none and the multiplication in the loop: contractions of 8400 of 12000 rows x
+// 1024 x 40000 1.79 ms, now 1.71; of 12288 of 16384 x 2048 x 50000 5.27, now 5.17.)
 template <bool KMAJOR, int R, int MAP = 0, int NW = 8, int BK = 64>
 struct OperandTile {
-    static constexpr bool MAPPED = MAP == 1;
     static_assert(!(KMAJOR && MAP), "only a K-slow operand carries a k-row map");
     static constexpr int NL = R * BK / 512 / NW;   // 16-byte loads per thread and K slice
     const char* base;       // matrix base address
@@ -131,8 +132,7 @@ struct OperandTile {
     int krow[NL];           // K-slow: k-row inside a slice handled by load i
     uint32_t slow_off[NL];  // K-slow: krow[i] * row pitch + off[i] (full slices are loaded from a uniform base)
     int k_last;             // K-slow: last valid k (rows beyond are clamped to it)
-    const CCE_LDS int32_t* kmap;   // K-slow, optional: k-row k is matrix row kmap[k]; where it holds -1 the
-    const char* kzero;             // row is read from kzero instead: a row of zeros as long as a matrix row
+    const CCE_LDS uint32_t* kmap;
     const CCE_LDS uint16_t* kmap16;
 
     // free0: first free index of the tile; free_n: number of valid free indices in the matrix
@@ -145,7 +145,6 @@ struct OperandTile {
         ld_bytes = (uint32_t)(ld * 2);
         k_last = k_n - 1;
         kmap = nullptr;
-        kzero = nullptr;
         kmap16 = nullptr;
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         if (KMAJOR) {
@@ -184,7 +183,7 @@ struct OperandTile {
 
     // K slices [0, full_slices()) lie entirely inside the operand's valid K extent (every slice of a
     // K-major operand does: its extent is padded to the slice).
-    __device__ __forceinline__ int full_slices() const { return KMAJOR || MAP == 2 ? 0x7fffffff : (k_last + 1) / BK; }
+    __device__ __forceinline__ int full_slices() const { return KMAJOR || MAP ? 0x7fffffff : (k_last + 1) / BK; }
 
     // Issue this thread's loads of the K slice starting at k0 into `stage` (LDS).  FULL (compile time):
     // the caller knows that the slice is one of full_slices().
@@ -199,40 +198,24 @@ struct OperandTile {
             for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, off[i], lds0 + (uint32_t)i * (NW * 1024u));
             return;
         }
+        if constexpr (MAP == 1) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) load16_to_lds_sbase(base, kmap[k0 + krow[i]] + off[i], lds0 + (uint32_t)i * (NW * 1024u));
+            return;
+        }
         if constexpr (MAP == 2) {
 #pragma unroll
             for (int i = 0; i < NL; ++i)
                 load16_to_lds_sbase(base, __umul24((uint32_t)kmap16[k0 + krow[i]], ld_bytes) + off[i], lds0 + (uint32_t)i * (NW * 1024u));
             return;
         }
-        if (!MAPPED && (FULL || k0 + BK - 1 <= k_last)) {
+        if (FULL || k0 + BK - 1 <= k_last) {
             // a full slice of a K-slow operand: uniform base = row k0, lane offset = its k-row inside
             // the slice times the row pitch plus its column offset
             const char* sb = base + (size_t)k0 * ld_bytes;
 #pragma unroll
             for (int i = 0; i < NL; ++i) load16_to_lds_sbase(sb, slow_off[i], lds0 + (uint32_t)i * (NW * 1024u));
             return;
-        }
-        if constexpr (MAPPED) {
-            // mapped k-rows: lane offset = mapped row times the row pitch plus the
-            // column offset, from the matrix base -- unless some lane of the wavefront has a k-row that
-            // maps to no row (only behind the last valid row of the whole problem), which takes the
-            // per-lane form below
-            int m[NL];
-            int any = 0;
-#pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                int k = k0 + krow[i];
-                k = k < k_last ? k : k_last;
-                m[i] = kmap[k];
-                any |= m[i];
-            }
-            if (__builtin_amdgcn_ballot_w64(any < 0) == 0) {
-#pragma unroll
-                for (int i = 0; i < NL; ++i)
-                    load16_to_lds_sbase(base, (uint32_t)m[i] * ld_bytes + off[i], lds0 + (uint32_t)i * (NW * 1024u));
-                return;
-            }
         }
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
@@ -243,12 +226,6 @@ struct OperandTile {
                 int k = k0 + krow[i];
                 k = k < k_last ? k : k_last;
                 g = base + (size_t)((uint32_t)k * ld_bytes + off[i]);
-                if constexpr (MAPPED) {
-                    // a k-row that stands for no matrix row must not fetch one: whatever that row
-                    // holds (NaN included) would meet the other operand's zero in the MFMA
-                    const int mapped = kmap[k];
-                    g = mapped < 0 ? kzero + off[i] : base + (size_t)((uint32_t)mapped * ld_bytes + off[i]);
-                }
             }
             load16_to_lds(g, stage + (wave + NW * i) * 1024);
         }
