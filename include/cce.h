@@ -102,7 +102,8 @@ size_t cce_materialised_logit_bytes(int64_t N, int64_t V);
  *   loss    out fp32 [N]       device   loss_i = lse_i - h_i . W_{y_i}; 0 for ignored rows
  *   lse     out fp32 [N]       device   log-sum-exp of row i's logits; 0 for ignored rows
  * Logit tiles are accumulated in fp32 and consumed unrounded; the label logit is an
- * fp32 dot product of the bf16 inputs.
+ * fp32 dot product of the bf16 inputs.  Large calls (from about 1 ms on) scan the labels first and leave
+ * ignored rows out of the logit products; hidden rows must be finite all the same.
  */
 int cce_forward(const void* hidden, const void* weight, const int32_t* labels,
                 int64_t N, int64_t D, int64_t V, int32_t ignore_index,
@@ -112,8 +113,9 @@ int cce_forward(const void* hidden, const void* weight, const int32_t* labels,
 /*
  * cce_forward without a workspace argument and without any allocation -- for callers that cannot
  * allocate device memory or size a workspace where they call it: code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same results (bit for bit)
- * as cce_forward; the scratch the forward needs (status word and the per-vocabulary-split
+ * tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same results (bit for bit; in
+ * the last bits of fp32 sums where rows are ignored and the array is too small for the row map, from
+ * a third of the limit below) as cce_forward; the scratch the forward needs (status word and the per-vocabulary-split
  * (max, sum-exp) pairs, 12 bytes x N x splits) lives in a static device array of
  * CCE_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds until
  * the process ends.

@@ -4,9 +4,10 @@
  *
  * A row whose label is ignore_index contributes nothing to the loss or to either gradient (the
  * forward kernel of the paper stores 0 and returns for it), so none of the path's four products
- * needs to see it.  cce_forward / cce_backward process every row because how many rows are valid
- * is only known on the device and the tiling of the work is decided on the host, without a
- * synchronisation.  A training loop usually has the labels on the host as well (the data loader
+ * needs to see it.  How many rows are valid is only known on the device, and the tiling of the work is
+ * decided on the host, without a synchronisation: cce_forward / cce_backward process every row, or, where a call is
+ * large enough for a label scan in front, plan for every row and leave those out that the scan finds.
+ * A training loop usually has the labels on the host as well (the data loader
  * produced them): given the count of valid rows -- or any upper bound -- these entry points
  * number the valid rows, in order (one label scan), and run the same kernels in that compact
  * row space: the forward's loaders reach the hidden rows through the row map; the backward does the
@@ -21,7 +22,7 @@
  * contribution to dW), CCE_STATUS_ROW_BOUND is set in the workspace status word and the results
  * are those of the kept rows only -- check cce_read_status where the bound is not certain.
  * The hidden row of a row that is not valid is never loaded by these calls, so it may hold
- * anything, NaN and Inf included (cce_forward / cce_backward ask for finite values there).  (Where the calls
+ * anything, NaN and Inf included (cce_forward / cce_backward ask for finite values there: small calls compute every row).  (Where the calls
  * decide not to skip rows, see cce_get_row_skipping, every row is processed and nothing is
  * dropped or flagged.)  max_valid_rows >= N
  * is allowed (nothing is skipped then).
