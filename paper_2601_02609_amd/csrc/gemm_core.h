@@ -2,7 +2,7 @@
 // (logit tile of the chunked forward algorithm, its recomputation in the backward
 // algorithm, and the two gradient products dH = G W and dW = G^T H).
 //
-// One workgroup = 512 threads = 8 wavefronts arranged WM x WN, computing a BM x BN fp32 tile
+// One workgroup = 512 threads = 8 wavefronts (256 = 4 for TileDuo) arranged WM x WN, computing a BM x BN fp32 tile
 // C[m, n] = sum_k A(m, k) * B(n, k) with v_mfma_f32_32x32x16_bf16.  Each wavefront owns
 // TM x TN blocks of 32 x 32 (16 accumulator registers per block and lane).
 //
@@ -13,7 +13,9 @@
 //             in dW; fragments are then fetched with the LDS transpose read
 //             (ds_read_b64_tr_b16), so no transposed copy of any tensor is ever made.
 //
-// K is walked in slices of 64.  A slice of both operands is brought straight from global
+// The gradient chunk G lies in panels (PanelTile) and is read in either way.
+//
+// K is walked in slices of 64 (32 for TileDuo).  A slice of both operands is brought straight from global
 // memory into LDS (global_load_lds_dwordx4: 16 B per lane, a wavefront fills 1 KB of
 // consecutive LDS), double buffered: the loads of slice t+1 are issued before the MFMAs of
 // slice t.  Because the LDS side of such a load is fixed (lane * 16 B), the
