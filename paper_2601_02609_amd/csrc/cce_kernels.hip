@@ -940,8 +940,9 @@ struct SplitRule { int32_t* rows_splits; int vocab_tiles, cus, s_max, workgroups
 // loss / lse of the rows that are not valid, and of valid rows that were dropped, are set to zero
 // when the pointers are given (a caller that does not poll the status word then sees a zero
 // contribution from a dropped row, not stale memory).  zero_row (optional): zero_row_len bf16 zeros
-// are written there.  The status word is WRITTEN here (bad label / bound bits or 0): the scan is the
-// first launch of a row-skipping call and needs no clearing launch in front of it.
+// are written there.  The status word (optional) is WRITTEN here (bad label / bound bits or 0): the scan is
+// the first launch of a forward or row-skipping call and needs no clearing launch in front of it.  A
+// backward over all rows gives none: it says nothing about its labels, whichever way it runs.
 // Each wavefront owns a contiguous run of rows and takes 64 at a time, coalesced, positions from the
 // ballot; the sixteen wavefront totals go through LDS: one barrier.  Eight label loads are in flight per
 // lane.  One workgroup against the latency of its loads is all that bounds it: with a run of rows per
@@ -1018,7 +1019,7 @@ __global__ __launch_bounds__(1024) void row_scan_kernel(
     if (tid == 0) {
         count_out[0] = kept;
         count_out[1] = kept == N ? 1 : 0;             // the row map is the identity
-        status[0] = (any_bad ? CCE_STATUS_BAD_LABEL : 0) | (total > max_rows ? CCE_STATUS_ROW_BOUND : 0);
+        if (status) status[0] = (any_bad ? CCE_STATUS_BAD_LABEL : 0) | (total > max_rows ? CCE_STATUS_ROW_BOUND : 0);
     }
     if (rule.rows_splits) {
         const int tiles = (kept + 255) / 256, s = tid + 1;
@@ -1694,7 +1695,7 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         int32_t* const count = (int32_t*)(ws + skip.off_count);
         const int rows_pad = p.TT * 256;
         hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(1024), 0, stream, labels, (int)N, (int)V, ignore_index, (int)N, rows_pad, perm, count,
-                           (int32_t*)(ws + p.off_status), (float*)nullptr, (float*)nullptr, (uint16_t*)nullptr, 0, SplitRule{});
+                           (int32_t*)nullptr, (float*)nullptr, (float*)nullptr, (uint16_t*)nullptr, 0, SplitRule{});
         hipLaunchKernelGGL(compact_prepare_backward_kernel, dim3((unsigned)(rows_pad / 256)), dim3(256), 0, stream,
                            (const int32_t*)perm, (const int32_t*)count, rows_pad, labels, (int)N, (int)V, ignore_index, labels_c,
                            lse, lse_c, dloss, dloss_c, (int)D, (uint16_t*)nullptr);

@@ -95,3 +95,23 @@ def test_fp8_without_known_count():
         for a, b, tol in zip(got[0], got[1], (1e-6, 1e-6, 1e-3, 1e-5)):       # fp32 sums over the vocabulary in other splits
             assert (a - b).norm() <= tol * b.norm()
         assert torch.all(got[0][0][~valid] == 0) and torch.all(got[0][2][~valid] == 0)
+
+
+def test_status_word_is_the_forwards():
+    """A backward over all rows leaves the status word as it is, also where it scans the labels."""
+    from paper_2601_02609_amd import binding as B
+    N, D, V = 6000, 640, 150001
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    H = torch.randn(N, D, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, D, device="cuda", generator=g) * (2.5 / D ** 0.5)).bfloat16()
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    dl = torch.rand(N, device="cuda", generator=g) / N
+    ws = B.alloc_workspace(N, D, V)
+    bad = y.clone()
+    bad[5] = V
+    for first, then, want in ((bad, y, 1), (y, bad, 0)):        # 1: CCE_STATUS_BAD_LABEL
+        print(f"[status] {want}", flush=True)
+        _, lse = B.cce_forward(H, W, first, IGN, workspace=ws)
+        B.cce_backward(H, W, then, lse, dl, IGN, workspace=ws)
+        assert B.read_status(ws) == want
