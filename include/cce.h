@@ -113,9 +113,8 @@ int cce_forward(const void* hidden, const void* weight, const int32_t* labels,
 /*
  * cce_forward without a workspace argument and without any allocation -- for callers that cannot
  * allocate device memory or size a workspace where they call it: code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same results (bit for bit; in
- * the last bits of fp32 sums where rows are ignored and the array is too small for the row map, from
- * a third of the limit below) as cce_forward; the scratch the forward needs (status word and the per-vocabulary-split
+ * tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same results (bit for bit)
+ * as cce_forward; the scratch the forward needs (status word and the per-vocabulary-split
  * (max, sum-exp) pairs, 12 bytes x N x splits) lives in a static device array of
  * CCE_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds until
  * the process ends.

@@ -1319,9 +1319,8 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
                         float* loss, float* lse, float* mean_loss,
                         int64_t v_off, float* stats, bool want_sumz, const Fp8Scales* fp8_in,
                         void* workspace, size_t workspace_bytes, void* stream_, const CompactCtx* cc = nullptr,
-                        int32_t* status_word = nullptr, size_t scratch_bytes = 0) {
+                        int32_t* status_word = nullptr) {
     Plan p;
-    if (!scratch_bytes) scratch_bytes = workspace_bytes;        // (cce_forward_static: less than it claims)
     Fp8Scales fp8 = {nullptr, nullptr, 0, 0};
     if (fp8_in) {
         fp8 = *fp8_in;
@@ -1353,7 +1352,7 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
     const int32_t* rows_splits = nullptr;
     int grid = p.TT * p.S;
     // All rows, ignored ones among them perhaps: large forwards leave those out without being told how many there are.
-    const ForwardSkip skip = cc || stats ? ForwardSkip{} : forward_skip(p, D, fp8_in != nullptr, scratch_bytes);
+    const ForwardSkip skip = cc || stats ? ForwardSkip{} : forward_skip(p, D, fp8_in != nullptr);
     Fp8Scales tile_fp8 = fp8;                                   // (the label logit keeps the caller's scales)
     if (skip.use) {
         int32_t* const perm = (int32_t*)(ws + skip.off_perm);
@@ -1480,14 +1479,15 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
     if (D % 64 != 0) return CCE_ERR_UNSUPPORTED;
     Plan p;
     if (!make_plan(N, D, V, &p)) return CCE_ERR_INVALID;
-    // the forward touches the workspace up to the end of the partial results only
+    // the forward touches the workspace up to the end of the partial results only, or to the end of forward_skip's
+    // layout, which is taken where it fits the array
     if (p.off_dhacc > (size_t)CCE_STATIC_SCRATCH_BYTES) return CCE_ERR_TOO_LARGE;
     void* ws = static_scratch_address();
     if (!ws) return CCE_ERR_HIP;
-    // forward_impl checks a workspace against the whole plan (forward + backward); only the part
-    // in front of off_dhacc exists here and only that part is addressed by the forward kernels
+    // forward_impl checks a workspace against the whole plan (forward + backward); only the array's
+    // bytes exist here and only those are addressed by the forward kernels
     return forward_impl(hidden, weight, labels, N, D, V, ignore_index, 0.f, 0.f, loss, lse, nullptr,
-                        0, nullptr, false, nullptr, ws, p.total, stream_, nullptr, status, (size_t)CCE_STATIC_SCRATCH_BYTES);
+                        0, nullptr, false, nullptr, ws, p.total, stream_, nullptr, status);
 }
 
 // The backward in the order of a Schedule (plan.h); arguments as in backward_impl, checked there.

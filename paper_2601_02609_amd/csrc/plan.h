@@ -10,6 +10,7 @@
 #include <string.h>
 #include <atomic>
 
+#include "../../include/cce.h"
 #include "gemm_core.h"
 #include "host_util.h"
 
@@ -648,13 +649,15 @@ struct RowBlockPlanner {
 };
 
 // A forward over all rows that leaves the ignored ones out: their number is found on the device, so the launch has the
-// workgroups of all rows and those beyond the rows that take part return at once; what is laid out behind the plan's
-// partials (the forward uses nothing there) is the row map, the counts, FP8 scales in the order of those rows, and partials for more splits than the plan's.
+// workgroups of all rows and those beyond the rows that take part return at once; from the plan's partials on (the plan's own
+// are not needed then) lie the row map, the counts, FP8 scales in the order of those rows, and the partials: 256 per workgroup.
 // The label scan and its launch take 9 us at 8192 rows.  Taken from about 1 ms of forward on (1.15 PFLOP/s): at most 1 %
 // where nothing is ignored; 8192 x 896 x 151936 with 15 % ignored 1.89 -> 1.64 ms, 4099 x 2048 x 128256 with 5 % 1.78 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.60 -> 1.24, none ignored 1.600 -> 1.606.
 // Below, and for few row tiles, a launch of one round hardly gets shorter by the rows that real padding leaves out.
-struct ForwardSkip { bool use; int s_max, workgroups; size_t off_perm, off_found, off_scales, off_partials, off_sumz; };
-static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8, size_t bytes) {
+// Whether it is taken decides the order of the fp32 sums, so it follows from the shape alone and not from the workspace of a
+// call: the layout has to fit the smallest one that the shape's calls accept, the static array's included.
+struct ForwardSkip { bool use; int s_max, workgroups; size_t off_perm, off_found, off_scales, off_partials, off_sumz, end; };
+static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8) {
     ForwardSkip f = {};
     if ((p.small_tiles && !fp8) || p.TT < 8 || g_force_row_skipping.load(std::memory_order_relaxed) != 0) return f;
     if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return f;
@@ -663,12 +666,14 @@ static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8, size_t bytes
     if (f.s_max > 1024) f.s_max = 1024;
     if (f.s_max < p.S) return f;
     f.workgroups = (p.TT * p.S + cus - 1) / cus * cus;
-    f.off_perm = p.off_dhacc;
-    f.off_found = f.off_perm + (size_t)round_up((int64_t)p.TT * 1024, 256);
+    f.off_perm = p.off_partials;
+    f.off_found = f.off_perm + (size_t)p.TT * 1024;
     f.off_scales = f.off_found + 256;                          // FP8: the scale bytes of the rows that take part
     f.off_partials = f.off_scales + (fp8 ? (size_t)round_up(D / 128 * p.TT * 256, 256) : (size_t)0);
-    f.off_sumz = f.off_partials + (size_t)round_up(p.rows * f.s_max * 8, 256);
-    f.use = f.off_sumz + (size_t)p.rows * f.s_max * 4 <= bytes;
+    f.off_sumz = f.off_partials + (size_t)f.workgroups * 2048;
+    f.end = f.off_sumz + (size_t)f.workgroups * 1024;
+    const size_t array = CCE_STATIC_SCRATCH_BYTES;
+    f.use = f.end <= (p.off_dhacc <= array && array < p.total ? array : p.total);
     return f;
 }
 

@@ -23,7 +23,7 @@ static int64_t pick(int64_t lo, int64_t hi) {
     state ^= state << 13; state ^= state >> 7; state ^= state << 17;
     return lo + (int64_t)(state % (uint64_t)(hi - lo + 1));
 }
-static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0, fronts = 0;
+static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0, fronts = 0, fwd_skips = 0;
 #define CHECK(cond) do { if (!(cond)) { ++failures; fprintf(stderr, "FAIL %d: %s | N=%lld D=%lld V=%lld B=%lld free=%d\n", __LINE__, #cond, \
     (long long)N, (long long)D, (long long)V, (long long)B, (int)dw_free); } } while (0)
 
@@ -102,11 +102,35 @@ static bool check_layout(const Plan& p, int64_t N, int64_t D, int64_t V, int64_t
     return true;
 }
 
+// A forward that leaves ignored rows out: its layout fits every workspace that the shape's calls accept, the static array
+// included where cce_forward_static takes the shape, and holds the partials of any number of rows.
+static void check_forward_skip(const Plan& p, int64_t N, int64_t D, int64_t V) {
+    const int64_t B = 0; const bool dw_free = false;
+    for (int fp8 = 0; fp8 < (D % 128 ? 1 : 2); ++fp8) {
+        const ForwardSkip f = forward_skip(p, D, fp8 != 0);
+        if (!f.use) continue;
+        ++fwd_skips;
+        CHECK(f.end <= p.total && (p.off_dhacc > CCE_STATIC_SCRATCH_BYTES || f.end <= CCE_STATIC_SCRATCH_BYTES));
+        CHECK(f.off_perm >= p.off_partials && f.off_found - f.off_perm >= (size_t)p.TT * 256 * 4 && f.off_scales - f.off_found >= 16);
+        CHECK(f.off_partials - f.off_scales >= (fp8 ? (size_t)(D / 128 * p.TT * 256) : (size_t)0));
+        CHECK(((f.off_perm | f.off_found | f.off_scales | f.off_partials | f.off_sumz) & 255) == 0);
+        CHECK(p.S <= f.s_max && f.s_max <= p.VT && p.TT * p.S <= f.workgroups);
+        for (int tiles = 1; tiles <= p.TT; ++tiles) {
+            int s = f.workgroups / tiles;                        // as many splits as the label scan may take
+            s = s < f.s_max ? s : f.s_max;
+            CHECK(s >= 1 && tiles <= f.workgroups);
+            const size_t pairs = (size_t)(tiles * 256 < N ? tiles * 256 : N) * s;
+            CHECK(f.off_sumz - f.off_partials >= pairs * 8 && f.end - f.off_sumz >= pairs * 4);
+        }
+    }
+}
+
 // The plan's own layout, and the one with room for planes that a call takes where its workspace holds it.
 static bool check(int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
     Plan p, roomy;
     if (!make_plan(N, D, V, &p, B)) return false;
     bool used = check_layout(p, N, D, V, B, dw_free);
+    if (!B) check_forward_skip(p, N, D, V);
     const size_t ask = workspace_to_ask_for(p, B ? B : N, D, V, B != 0);
     CHECK(p.total <= ask);
     for (int i = 0; i < 3; ++i) {            // any smaller call's own layout fits, and up to the floor its room for planes
@@ -221,8 +245,8 @@ int main(int argc, char** argv) {
         check(n, d, v, 0, false);
         check(pick(1, n), d, v, n, it % 5 != 0);
     }
-    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d, orders with dHidden %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs, fronts);
-    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs || !fronts) { fprintf(stderr, "a form was never taken\n"); return 1; }
+    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d, orders with dHidden %d, forwards that skip %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs, fronts, fwd_skips);
+    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs || !fronts || !fwd_skips) { fprintf(stderr, "a form was never taken\n"); return 1; }
     if (failures) { fprintf(stderr, "%d failures\n", failures); return 1; }
     printf("schedule_fuzz: %d iterations ok\n", iters);
     return 0;

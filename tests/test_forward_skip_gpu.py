@@ -73,3 +73,28 @@ def test_bad_label_is_flagged_and_ignored(operands):
     assert B.read_status(ws) != 0
     ok = (y >= 0) & (y < V)
     assert torch.all(loss[~ok] == 0) and (loss.double() - (lse_ref - zy))[ok].abs().max() <= LOSS_ATOL
+
+
+@pytest.mark.parametrize("N,D,V", [(26694, 960, 28747), (28063, 128, 167142), (2100, 4096, 70001)])
+def test_static_forward_has_the_bits_of_the_forward(N, D, V):
+    """Also where ignored rows are left out, and whatever the workspace holds beyond what the call needs."""
+    from paper_2601_02609_amd import binding as B
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    H = torch.randn(N, D, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, D, device="cuda", generator=g) * (2.5 / D ** 0.5)).bfloat16()
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    y[torch.randperm(N, device="cuda", generator=g)[:N * 3 // 10]] = IGN
+    y[7] = V
+    ws = B.alloc_workspace(N, D, V)
+    more = torch.empty(2 * ws.numel(), dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    out = [(torch.empty(N, device="cuda"), torch.empty(N, device="cuda")) for _ in range(3)]
+    print(f"[static] {N}x{D}x{V}", flush=True)
+    B.cce_forward_static(H, W, y, IGN, *out[0], status)
+    B.cce_forward(H, W, y, IGN, workspace=ws, loss=out[1][0], lse=out[1][1])
+    B.cce_forward(H, W, y, IGN, workspace=more, loss=out[2][0], lse=out[2][1])
+    torch.cuda.synchronize()
+    assert int(status) == 1 == B.read_status(ws)
+    for loss, lse in out[1:]:
+        assert torch.equal(loss, out[0][0]) and torch.equal(lse, out[0][1])
