@@ -1204,7 +1204,6 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 0>, kGemmLdsDuo)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 1>, kGemmLdsDuo)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 4>, kGemmLdsDuo)) return false;
-    if (!allow_big_lds(grad_gemm_kernel<TileBig, 9>, kGemmLdsBig + kRowTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 9>, kGemmLdsNarrow + kRowTableBytes)) return false;
     done[dev] = true;
     return true;
@@ -1226,17 +1225,14 @@ static void launch_grad_tiles(const void* H, const void* W, const int32_t* label
                            n_row_tiles, v0, n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
 }
 
-// A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
-// Counted rows (mode 9): 256 x 256 or 256 x 128 tiles, the row table behind their stages.
-static void launch_counted_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+// Both contractions of counted rows (mode 9): 256 x 128 tiles, the row table behind their stages.
+static void launch_counted_contractions(const GemmJob& first, const GemmJob& second, hipStream_t stream) {
     const int work = first.n_work + second.n_work;
     ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
-    if (kind == 0)
-        hipLaunchKernelGGL((grad_gemm_kernel<TileBig, 9>), dim3(work), dim3(kThreads), kGemmLdsBig + kRowTableBytes, stream, first, second);
-    else
-        hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, 9>), dim3(work), dim3(kThreads), kGemmLdsNarrow + kRowTableBytes, stream, first, second);
+    hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, 9>), dim3(work), dim3(kThreads), kGemmLdsNarrow + kRowTableBytes, stream, first, second);
 }
 
+// A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
 template <int MODE>
 static void launch_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
     const int work = first.n_work + second.n_work;
@@ -1605,7 +1601,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                     dh.first_row = dw.first_row = (int)row0;
                     dw.B = hidden;
                     dh.row_map = dw.row_map = counted->perm + row0;
-                    launch_counted_contractions(kind, dh, dw, stream);
+                    launch_counted_contractions(dh, dw, stream);
                     continue;
                 }
                 const bool dh_first = kh >= kw;                          // longer items first

@@ -922,7 +922,8 @@ static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t 
 struct BackwardSkip { bool use; size_t off_perm, off_labels, off_lse, off_dloss, off_count, off_scales; };
 static BackwardSkip backward_skip(const Plan& p, const Schedule& sc, int64_t D, bool fp8) {
     BackwardSkip b = {};
-    if (!sc.use || !sc.split_acc || sc.a < p.TT || sc.split_h != 1 || sc.split_w != 1 || p.TT < 8 || p.TT > kRowTableBytes / 512) return b;
+    // (256 x 128 tiles: no order with the planes was ever planned with 256 x 256 ones)
+    if (!sc.use || sc.kind != 1 || !sc.split_acc || sc.a < p.TT || sc.split_h != 1 || sc.split_w != 1 || p.TT < 8 || p.TT > kRowTableBytes / 512) return b;
     if (g_force_row_skipping.load(std::memory_order_relaxed) != 0 || p.forced) return b;
     if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return b;
     const size_t each = (size_t)p.TT * 1024;

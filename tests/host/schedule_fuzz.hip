@@ -23,9 +23,26 @@ static int64_t pick(int64_t lo, int64_t hi) {
     state ^= state << 13; state ^= state >> 7; state ^= state << 17;
     return lo + (int64_t)(state % (uint64_t)(hi - lo + 1));
 }
-static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0, fronts = 0, fwd_skips = 0;
+static int failures = 0, used = 0, in_tails = 0, split_hs = 0, split_ws = 0, blocks = 0, parts = 0, split_accs = 0, fronts = 0, fwd_skips = 0, bwd_skips = 0;
 #define CHECK(cond) do { if (!(cond)) { ++failures; fprintf(stderr, "FAIL %d: %s | N=%lld D=%lld V=%lld B=%lld free=%d\n", __LINE__, #cond, \
     (long long)N, (long long)D, (long long)V, (long long)B, (int)dw_free); } } while (0)
+
+// A backward that leaves ignored rows out: its bookkeeping lies in the partials' area, its row map fits the table.
+static void check_backward_skip(const Plan& p, const Schedule& s, int64_t N, int64_t D, int64_t V, bool dw_free) {
+    const int64_t B = 0;
+    for (int fp8 = 0; fp8 < (D % 128 ? 1 : 2); ++fp8) {
+        const BackwardSkip b = backward_skip(p, s, D, fp8 != 0);
+        if (!b.use) continue;
+        ++bwd_skips;
+        const size_t each = (size_t)p.TT * 256 * 4;
+        CHECK(s.use && s.kind == 1 && s.a == p.TT && s.split_acc && s.split_h == 1 && s.split_w == 1);
+        CHECK(p.TT * 256 * 2 <= kRowTableBytes && N <= 65536);
+        CHECK(b.off_perm >= p.off_partials && b.off_labels - b.off_perm >= each && b.off_lse - b.off_labels >= each);
+        CHECK(b.off_dloss - b.off_lse >= each && b.off_count - b.off_dloss >= each && b.off_scales - b.off_count >= 8);
+        CHECK(b.off_scales + (fp8 ? (size_t)(D / 128 * p.TT * 256) : (size_t)0) <= p.off_dhacc && p.off_dhacc <= s.off_acc);
+        CHECK(((b.off_perm | b.off_labels | b.off_lse | b.off_dloss | b.off_count | b.off_scales) & 255) == 0);
+    }
+}
 
 static bool check_layout(const Plan& p, int64_t N, int64_t D, int64_t V, int64_t B, bool dw_free) {
     Schedule s;
@@ -51,6 +68,7 @@ static bool check_layout(const Plan& p, int64_t N, int64_t D, int64_t V, int64_t
         CHECK(R == 0);
     }
     if (B) CHECK(order_uses_dhidden(p, s) == (s.use ? (int64_t)s.a * 256 >= N : s.n_blocks > 0));
+    if (!B) check_backward_skip(p, s, N, D, V, dw_free);
     if (!s.use) return false;
     ++used;
     const int64_t block = (int64_t)s.a * 256;
@@ -245,8 +263,8 @@ int main(int argc, char** argv) {
         check(n, d, v, 0, false);
         check(pick(1, n), d, v, n, it % 5 != 0);
     }
-    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d, orders with dHidden %d, forwards that skip %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs, fronts, fwd_skips);
-    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs || !fronts || !fwd_skips) { fprintf(stderr, "a form was never taken\n"); return 1; }
+    printf("used %d, chunks in dW %d, split dH %d, split dW %d, row blocks %d, row parts %d, split sums %d, orders with dHidden %d, forwards that skip %d, backwards %d\n", used, in_tails, split_hs, split_ws, blocks, parts, split_accs, fronts, fwd_skips, bwd_skips);
+    if (!in_tails || !split_hs || !split_ws || !parts || !split_accs || !fronts || !fwd_skips || !bwd_skips) { fprintf(stderr, "a form was never taken\n"); return 1; }
     if (failures) { fprintf(stderr, "%d failures\n", failures); return 1; }
     printf("schedule_fuzz: %d iterations ok\n", iters);
     return 0;
