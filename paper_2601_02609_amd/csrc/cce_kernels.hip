@@ -570,6 +570,9 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
 // LDS of grad_gemm_kernel: the main loop's stages (the exchange between K groups fits them).
 constexpr int kGemmLdsBig = TileBig::kLdsBytes, kGemmLdsNarrow = TileNarrow::kLdsBytes, kGemmLdsSmall = TileSmall::kLdsBytes;
 constexpr int kGemmLdsDuo = TileDuo::kLdsBytes;
+// Counted rows (mode 9): bytes of the row map's 16-bit entries, whole or as many as leave room for two workgroups to a unit.
+template <class Cfg> constexpr int counted_table_bytes() { return Cfg::NW == 4 ? 80 * 1024 - Cfg::kLdsBytes : kRowTableBytes; }
+static_assert(counted_table_bytes<TileDuo>() % 512 == 0 && counted_table_bytes<TileDuo>() > 0, "whole row tiles");
 // Row skipping: the LDS table of one row block's row map (kRowTableBytes, plan.h) sits behind these.
 static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRowTableBytes <= 160 * 1024 && kGemmLdsSmall + kRowTableBytes <= 160 * 1024, "row table must fit the LDS");
 
@@ -794,14 +797,6 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, int row
     OperandTile<false, Cfg::BN, kMapB, Cfg::NW, Cfg::BK> Bop;
     Aop.init(j.A, j.panel, mi * Cfg::BM, k0);
     Bop.init((const uint16_t*)j.B + (size_t)k0 * j.ldb, j.ldb, ni * Cfg::BN, j.n_valid, j.b_k_n - k0);
-    if constexpr (kMapB == 2) {
-        // the rows that take part, in 16 bits (at most 65536 rows); behind the last one that row again, whose products
-        // meet the chunk's zero rows
-        CCE_LDS uint16_t* tab = (CCE_LDS uint16_t*)(smem + Cfg::kLdsBytes);
-        for (int i = threadIdx.x; i < k_len; i += Cfg::kThreads) tab[i] = (uint16_t)j.row_map[i < rows ? i : rows - 1];
-        __syncthreads();
-        Bop.kmap16 = tab;
-    }
     if constexpr (kMapB == 1) {
         // row skipping, dW job: the reduction runs over the compact rows of the block, whose hidden rows are scattered over
         // the original tensor.  Their byte offsets are put into LDS, behind everything the kernel otherwise uses.
@@ -818,10 +813,26 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, int row
         Bop.kmap = tab;
         if (some < 0) Bop.base = j.zero_row;
     }
-    // Whatever the compiler loaded so far has to be there: it cannot see the main loop's loads, and a register still
-    // waited for inside the loop (a field of the job, say) becomes a wait for all of them in every slice.
-    __builtin_amdgcn_s_waitcnt(0x0f70);                          // vmcnt(0)
-    gemm_mainloop<Cfg, A_KMAJOR, false, true>(acc, Aop, Bop, k_len, smem);
+    constexpr int kMapRows = counted_table_bytes<Cfg>() / 2;
+    constexpr bool kPieces = kMapB == 2 && kMapRows < kRowTableBytes / 2;
+    for (int k1 = 0;;) {                                         // one pass, but for counted rows that exceed the table
+        const int k_now = kPieces && k_len - k1 > kMapRows ? kMapRows : k_len - k1;
+        if constexpr (kMapB == 2) {
+            // the rows that take part, in 16 bits (at most 65536 rows); behind the last one that row again, whose products
+            // meet the chunk's zero rows
+            CCE_LDS uint16_t* tab = (CCE_LDS uint16_t*)(smem + Cfg::kLdsBytes);
+            for (int i = threadIdx.x; i < k_now; i += Cfg::kThreads) tab[i] = (uint16_t)j.row_map[k1 + i < rows ? k1 + i : rows - 1];
+            __syncthreads();
+            Bop.kmap16 = tab;
+        }
+        // Whatever the compiler loaded so far has to be there: it cannot see the main loop's loads, and a register still
+        // waited for inside the loop (a field of the job, say) becomes a wait for all of them in every slice.
+        __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0)
+        gemm_mainloop<Cfg, A_KMAJOR, false, true>(acc, Aop, Bop, k_now, smem);           // ends with a barrier
+        k1 += k_now;
+        if (!kPieces || k1 >= k_len) break;
+        Aop.init(j.A, j.panel, mi * Cfg::BM, k1);
+    }
 
     store_result<Cfg, A_KMAJOR, MODE>(acc, j, out_f32, beta, mi, ni, COUNTED && A_KMAJOR ? rows : j.m_valid, smem);
 }
@@ -1205,6 +1216,8 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 1>, kGemmLdsDuo)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 4>, kGemmLdsDuo)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 9>, kGemmLdsNarrow + kRowTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileSmall, 9>, kGemmLdsSmall + kRowTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TileDuo, 9>, kGemmLdsDuo + counted_table_bytes<TileDuo>())) return false;
     done[dev] = true;
     return true;
 }
@@ -1225,11 +1238,19 @@ static void launch_grad_tiles(const void* H, const void* W, const int32_t* label
                            n_row_tiles, v0, n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
 }
 
-// Both contractions of counted rows (mode 9): 256 x 128 tiles, the row table behind their stages.
-static void launch_counted_contractions(const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+// Both contractions of counted rows (mode 9), the row table behind the stages; tile: counted_contraction_kind.  (All of them
+// 256 x 128 one to a unit, backwards without ignored rows were 2.3 % behind those that do not look for them at
+// 5200 x 2048 x 65001, 4.5 % at 8192 x 512 x 140000, 5.8 % at 2527 x 3584 x 68330: 0.9, 0.8 and 0.4 so.)
+static void launch_counted_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
     const int work = first.n_work + second.n_work;
     ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
-    hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, 9>), dim3(work), dim3(kThreads), kGemmLdsNarrow + kRowTableBytes, stream, first, second);
+    if (kind == 3)
+        hipLaunchKernelGGL((grad_gemm_kernel<TileDuo, 9>), dim3(work), dim3(TileDuo::kThreads), kGemmLdsDuo + counted_table_bytes<TileDuo>(), stream,
+                           first, second);
+    else if (kind == 2)
+        hipLaunchKernelGGL((grad_gemm_kernel<TileSmall, 9>), dim3(work), dim3(kThreads), kGemmLdsSmall + kRowTableBytes, stream, first, second);
+    else
+        hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, 9>), dim3(work), dim3(kThreads), kGemmLdsNarrow + kRowTableBytes, stream, first, second);
 }
 
 // A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
@@ -1533,7 +1554,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
                 const int n_split_w = (row_tiles + kw - 1) / kw;
                 const bool dw_beta = row0 > 0 || accumulate_dW;
-                const int kind = counted ? sc.kind
+                const int kind = counted ? counted_contraction_kind(sc.kind, D, row_tiles, v_tiles, d_tiles, planes_written > 0, dw_beta, knobs)
                                          : contraction_kind(sc.kind, D, (int64_t)row_tiles * n_split_h * d_tiles, kh * 4, planes_written > 0, sc.split_acc != 0,
                                                             (int64_t)v_tiles * n_split_w * d_tiles, kw * 4, dw_beta, false, knobs);
                 const int panel_shift = kind == 3 ? 5 : 6;                // log2 of the K slice of the contractions' tiles
@@ -1601,7 +1622,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                     dh.first_row = dw.first_row = (int)row0;
                     dw.B = hidden;
                     dh.row_map = dw.row_map = counted->perm + row0;
-                    launch_counted_contractions(dh, dw, stream);
+                    launch_counted_contractions(kind, dh, dw, stream);
                     continue;
                 }
                 const bool dh_first = kh >= kw;                          // longer items first

@@ -549,6 +549,28 @@ static int contraction_kind(int kind, int64_t D, int64_t n_dh, int64_t s_dh, boo
     return kind;
 }
 
+// The same of a launch whose rows are counted on the device (a x b tiles, no K parts, dH sums in planes): the tile that it takes
+// over all rows, so that a call without ignored rows has the sums and the time of one that does not look for them -- but tiles two
+// to a unit only where they are rated no slower over launches with one to four eighths of the rows left out, and at none of them a
+// sixth slower: dH's long items, on units that they share, bound what is left of a launch (without that, 3000 x 2048 x 151936 with
+// 40 % ignored 3.74 -> 4.02 ms, 7000 x 640 x 151936 with 25 % 3.87 -> 3.96, 8001 x 576 x 150001 with 40 % 3.66 -> 3.71).
+static int counted_contraction_kind(int kind, int64_t D, int64_t a, int64_t b, int64_t d_tiles, bool dh_beta, bool dw_beta, const Knobs& knobs) {
+    const int taken = contraction_kind(kind, D, a * d_tiles, b * 4, dh_beta, true, b * d_tiles, a * 4, dw_beta, false, knobs);
+    if (taken != 3) return taken;
+    ScheduleModel m{device_cu_count(), D, gemm_tile_of_kind(kind)};
+    m.one_to_unit = true;
+    double paired = 0.0, single = 0.0;
+    for (int64_t eighths = 7; eighths >= 4; --eighths) {
+        const int64_t left = (eighths * a + 4) / 8;
+        const double two = duo_makespan(m.cus, left * d_tiles, m.duo_item(b * 4, dh_beta, true), b * d_tiles, m.duo_item(left * 4, dw_beta, false));
+        const double one = m.contractions(left * d_tiles, b * 4, dh_beta, true, b * d_tiles, left * 4, dw_beta);
+        if (6.0 * two > 7.0 * one) return kind;
+        paired += two;
+        single += one;
+    }
+    return paired <= single ? 3 : kind;
+}
+
 // The forward under the same constants: rounds of workgroups that walk their vocabulary tiles, or of one
 // small tile each (500 x 2048 x 10000, two rounds of 32 slices: 42 us).
 struct ForwardCost {
@@ -917,7 +939,8 @@ static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t 
 // ones have), and whose row map fits the contraction's LDS table in 16 bits.  The order stays.  Step of 8192 x 896 x 151936
 // with 15 % ignored 8.10 -> 7.69 ms (40 %: 6.25), with FP8 logits 7.13 -> 6.56, 6000 x 1536 x 65001 4.47 -> 3.96.  Without
 // ignored rows it costs the scan, the gather of the per-row scalars and the scatter of dHidden's rows: 8.61 -> 8.63, FP8
-// 7.18 -> 7.25; at most 1.1 %, where launches would have taken tiles two to a unit (6000 x 1536 x 65001 4.58 -> 4.63).
+// 7.18 -> 7.25; about 1 %, and up to 4.5 where launches over all rows take tiles two to a unit that counted ones do not
+// (3000 x 2048 x 151936).
 // The bookkeeping lies where the forward's partials were.
 struct BackwardSkip { bool use; size_t off_perm, off_labels, off_lse, off_dloss, off_count, off_scales; };
 static BackwardSkip backward_skip(const Plan& p, const Schedule& sc, int64_t D, bool fp8) {

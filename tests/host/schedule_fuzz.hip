@@ -221,7 +221,8 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
     Plan asked = p;
     if (compact && M < N) { bool skip; plan_row_skipping(N, D, V, M, 2, &asked, &skip); }
     plan_backward(&p, rows, D, V, compact, dw_free, workspace_to_ask_for(asked, N, D, V, compact), &s);
-    int chunks = 0, in_dw = 0, part_steps = 0, least_h = 1 << 30, most_h = 0, most_w = 0, sums_dh = 0, chunks_dh = 0;
+    int chunks = 0, in_dw = 0, part_steps = 0, least_h = 1 << 30, most_h = 0, most_w = 0, sums_dh = 0, chunks_dh = 0, small = 0, steps = 0, same_tiles = 0, paired = 0, most_rows = 0;
+    const int64_t dt = (D + gemm_tile_of_kind(s.kind).bn - 1) / gemm_tile_of_kind(s.kind).bn;
     if (s.use) {
         for (int64_t v = 0; v < V; ++chunks) {
             const ScheduleChunk c = schedule_chunk(s, D, V - v);
@@ -230,6 +231,18 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
             least_h = nh < least_h ? nh : least_h; most_h = nh > most_h ? nh : most_h; most_w = nw > most_w ? nw : most_w;
             in_dw += c.in_tail ? 1 : 0;
             part_steps += c.rows < s.a ? 1 : 0;
+            for (int64_t r = 0; r < p.TT; r += c.rows) {            // (steps of the first block's sizes)
+                const int64_t t = p.TT - r < c.rows ? p.TT - r : c.rows, tw = (t + s.split_w - 1) / s.split_w;
+                const int plain = contraction_kind(s.kind, D, t * nh * dt, kh * 4, v > 0, s.split_acc != 0, c.b * ((t + tw - 1) / tw) * dt, tw * 4,
+                                                   r > 0 || !dw_free, false, Knobs::read());
+                const int kind = counted_contraction_kind(s.kind, D, t, c.b, dt, v > 0, r > 0 || !dw_free, Knobs::read());
+                small += kind == 2;
+                same_tiles += kind == plain;
+                ++steps;
+                if (kind != 3) continue;
+                ++paired;
+                most_rows = (int)t > most_rows ? (int)t : most_rows;
+            }
             v += c.b * 256;
         }
     } else {
@@ -237,9 +250,12 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
         for (int i = 0; i < s.n_blocks; ++i) { sums_dh += s.blocks[i].acc_in_dh; chunks_dh += s.blocks[i].g_in_dh; }
     }
     printf("schedule=%d chunks=%d in_dw=%d row_parts=%d parts_h=%d least_parts_h=%d parts_w=%d split_sums=%d row_blocks=%d "
-           "dhidden_blocks=%d sums_in_dhidden=%d chunks_in_dhidden=%d\n",
+           "dhidden_blocks=%d sums_in_dhidden=%d chunks_in_dhidden=%d small_tiles=%d paired=%d paired_row_tiles=%d forward_skip=%d forward_skip_fp8=%d "
+           "backward_skip=%d backward_skip_fp8=%d same_tiles=%d\n",
            (int)s.use, chunks, in_dw, part_steps, most_h, least_h, most_w, s.use ? s.split_acc : 0, s.use ? (p.TT + s.a - 1) / s.a : 0,
-           s.n_blocks, sums_dh, chunks_dh);
+           s.n_blocks, sums_dh, chunks_dh, small, paired, most_rows, (int)forward_skip(p, D, false).use, (int)(D % 128 == 0 && forward_skip(p, D, true).use),
+           (int)(!compact && backward_skip(p, s, D, false).use), (int)(!compact && D % 128 == 0 && backward_skip(p, s, D, true).use),
+           (int)(steps > 0 && same_tiles == steps));
 }
 
 int main(int argc, char** argv) {

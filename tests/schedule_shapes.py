@@ -32,6 +32,25 @@ AGAINST_FORCED = {
                               compact=dict(dhidden_blocks=2, sums_in_dhidden=1, chunks_in_dhidden=1)),
 }
 
+# all-rows calls that find their ignored rows on the device: forward_skip, backward_skip (with _fp8: on E4M3 operands), small_tiles /
+# paired contraction launches of 128 x 128 tiles / 256 x 128 ones two to a unit, paired_row_tiles of the longest of those, same_tiles:
+# every launch has the tile of the call that computes all rows.
+# "forward": the forward alone is tested (test_forward_skip_gpu.py)
+COUNTED = {
+    (8001, 512, 150001): dict(rows=dict(forward_skip=1, backward_skip=1, small_tiles=1, row_parts=1, same_tiles=1)),
+    (6001, 2048, 52001): dict(rows=dict(forward_skip=1, backward_skip=1, paired=1, paired_row_tiles=17, row_parts=1, same_tiles=1)),
+    (5000, 1536, 110001): dict(accumulate=dict(backward_skip=1, paired=1, paired_row_tiles=17, same_tiles=1)),
+    (5130, 1536, 80001): dict(accumulate=dict(backward_skip=1, row_parts=1)),
+    (2527, 3584, 68330): dict(rows=dict(backward_skip=1, paired=1, in_dw=1, same_tiles=1), accumulate=dict(backward_skip=1, paired=1, same_tiles=1)),
+    (4500, 896, 150001): dict(rows=dict(forward_skip=1, backward_skip=1), fp8=dict(forward_skip_fp8=1, backward_skip_fp8=1)),
+    (6000, 640, 150001): dict(rows=dict(forward_skip=1, backward_skip=1, row_parts=1)),
+    (5001, 960, 121003): dict(rows=dict(forward_skip=1, backward_skip=1)),
+    (2100, 4096, 67001): dict(forward=dict(forward_skip=1)),
+    (26694, 960, 28747): dict(forward=dict(forward_skip=1)),
+    (28063, 128, 167142): dict(forward=dict(forward_skip=1)),
+    (2100, 4096, 70001): dict(forward=dict(forward_skip=1)),
+}
+
 
 def n_ignored(N, against_forced=False):
     return N // 7 if against_forced else int(round(0.2 * N))

@@ -60,6 +60,13 @@ def test_gpu_shapes_take_the_orders_they_are_listed_for(fuzz, against_forced):
         assert not short, (call, form, short, got)
 
 
+def test_counted_shapes_take_the_routes_they_are_listed_for(fuzz):
+    calls, wanted = zip(*[((*shape, 0, form != "accumulate"), (form, want)) for shape, forms in S.COUNTED.items() for form, want in forms.items()])
+    for call, (form, want), got in zip(calls, wanted, orders(fuzz, calls)):
+        short = {k: (got[k], v) for k, v in want.items() if got[k] < v}
+        assert not short, (call, form, short, got)
+
+
 def test_drawn_calls_meet_the_orders(fuzz):
     """More than half of the calls of test_random_schedules leave the plan's own tiling, and every kind of order is among them."""
     calls = []
