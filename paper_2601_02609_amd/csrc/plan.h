@@ -935,12 +935,13 @@ static size_t workspace_to_ask_for(const Plan& p, int64_t N, int64_t D, int64_t 
     return taken.total > serves ? taken.total : serves;
 }
 
-// The same of a backward: one whose schedule has all rows in one block, no K parts and its dH sums in two planes (large
-// ones have), and whose row map fits the contraction's LDS table in 16 bits.  The order stays.  Step of 8192 x 896 x 151936
-// with 15 % ignored 8.10 -> 7.69 ms (40 %: 6.25), with FP8 logits 7.13 -> 6.56, 6000 x 1536 x 65001 4.47 -> 3.96.  Without
-// ignored rows it costs the scan, the gather of the per-row scalars and the scatter of dHidden's rows: 8.61 -> 8.63, FP8
-// 7.18 -> 7.25; about 1 %, and up to 4.5 where launches over all rows take tiles two to a unit that counted ones do not
-// (3000 x 2048 x 151936).
+// A backward over all rows that leaves the ignored ones out likewise (see ForwardSkip): one whose schedule has all rows in one block,
+// no K parts and its dH sums in two planes (large ones have), and whose row map fits the contraction's LDS table in 16 bits.  The
+// order stays.  Backwards that compute every row against this, one box: 8192 x 896 x 151936 with 15 % ignored 6.42 -> 5.96 ms, with
+// FP8 logits 5.82 -> 5.35, 5200 x 2048 x 65001 with 15 % 3.91 -> 3.47.  Without ignored rows it costs the scan, the gather of the
+// per-row scalars and the scatter of dHidden's rows, 0.1 to 0.6 %: 6.46 -> 6.47, FP8 5.85 -> 5.87, 3.91 -> 3.93; more only where
+// launches keep one tile to a unit that would run two of them (see counted_contraction_kind): 3000 x 2048 x 151936 5.14 -> 5.37,
+// for 5.14 -> 4.70 with 15 %.
 // The bookkeeping lies where the forward's partials were.
 struct BackwardSkip { bool use; size_t off_perm, off_labels, off_lse, off_dloss, off_count, off_scales; };
 static BackwardSkip backward_skip(const Plan& p, const Schedule& sc, int64_t D, bool fp8) {
