@@ -102,8 +102,9 @@ size_t cce_materialised_logit_bytes(int64_t N, int64_t V);
  *   loss    out fp32 [N]       device   loss_i = lse_i - h_i . W_{y_i}; 0 for ignored rows
  *   lse     out fp32 [N]       device   log-sum-exp of row i's logits; 0 for ignored rows
  * Logit tiles are accumulated in fp32 and consumed unrounded; the label logit is an
- * fp32 dot product of the bf16 inputs.  Large calls (from about 1 ms on) scan the labels first and leave
- * ignored rows out of the logit products; hidden rows must be finite all the same.
+ * fp32 dot product of the bf16 inputs.  Large calls (from about 1 ms on, unless the scan would take more than a
+ * fiftieth of them) scan the labels first and leave ignored rows out of the logit products; hidden rows must be
+ * finite all the same.
  */
 int cce_forward(const void* hidden, const void* weight, const int32_t* labels,
                 int64_t N, int64_t D, int64_t V, int32_t ignore_index,

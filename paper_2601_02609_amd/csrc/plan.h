@@ -673,9 +673,13 @@ struct RowBlockPlanner {
 // A forward over all rows that leaves the ignored ones out: their number is found on the device, so the launch has the
 // workgroups of all rows and those beyond the rows that take part return at once; from the plan's partials on (the plan's own
 // are not needed then) lie the row map, the counts, FP8 scales in the order of those rows, and the partials: 256 per workgroup.
-// The label scan and its launch take 9 us at 8192 rows.  Taken from about 1 ms of forward on (1.15 PFLOP/s): at most 1 %
-// where nothing is ignored; 8192 x 896 x 151936 with 15 % ignored 1.89 -> 1.64 ms, 4099 x 2048 x 128256 with 5 % 1.78 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.60 -> 1.24, none ignored 1.600 -> 1.606.
-// Below, and for few row tiles, a launch of one round hardly gets shorter by the rows that real padding leaves out.
+// Taken from about 1 ms of forward on (1.15 PFLOP/s): 8192 x 896 x 151936 with 15 % ignored 1.89 -> 1.64 ms, 4099 x 2048 x 128256
+// with 5 % 1.78 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.60 -> 1.24, none ignored 1.600 -> 1.606.
+// The label scan is one workgroup: 4 us and 0.4 ns a row (131072 rows 55 us, a million 406), paid also where nothing is ignored.
+// It may take a fiftieth of the forward, whose products run at a rate that falls with D (2 N V (0.75 D + 72) fs: 131072 x 64 x 70000
+// 2.19 ms, 8192 x 896 x 80000 0.94), up to twice that with FP8 logits: 0.2 to 1.2 % on 8192 to 65536 rows without ignored ones;
+// calls that it leaves out lost 2.5 % (131072 x 256 x 32000) to 16 % (1000000 x 64 x 9100) there.
+// Below 1 ms, and for few row tiles, a launch of one round hardly gets shorter by the rows that real padding leaves out.
 // Whether it is taken decides the order of the fp32 sums, so it follows from the shape alone and not from the workspace of a
 // call: the layout has to fit the smallest one that the shape's calls accept, the static array's included.
 struct ForwardSkip { bool use; int s_max, workgroups; size_t off_perm, off_found, off_scales, off_partials, off_sumz, end; };
@@ -683,6 +687,8 @@ static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8) {
     ForwardSkip f = {};
     if ((p.small_tiles && !fp8) || p.TT < 8 || g_force_row_skipping.load(std::memory_order_relaxed) != 0) return f;
     if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return f;
+    const double scan_ns = 4000.0 + 0.4 * (double)p.rows, forward_ns = 2e-6 * (double)p.rows * (double)p.cols * (0.75 * (double)D + 72.0);
+    if (50.0 * scan_ns > forward_ns) return f;
     const int cus = device_cu_count(), most = 2 * p.S + 8;
     f.s_max = most < p.VT ? most : p.VT;
     if (f.s_max > 1024) f.s_max = 1024;

@@ -258,6 +258,19 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
            (int)(steps > 0 && same_tiles == steps));
 }
 
+// The label scan in front of a forward that leaves ignored rows out is one workgroup, 0.4 ns a row: it has to be small beside the forward.
+static void check_scan_is_priced() {
+    const struct { int64_t N, D, V; bool use; } shapes[] = {
+        {8192, 896, 151936, true}, {16384, 512, 70001, true}, {32768, 128, 140001, true}, {32768, 4096, 4400, true}, {131072, 896, 151936, true},
+        {131072, 256, 32000, false}, {131072, 64, 70000, false}, {262144, 64, 35000, false}, {1000000, 64, 9100, false}, {2000000, 64, 5000, false}};
+    for (auto& s : shapes) {
+        Plan p;
+        if (make_plan(s.N, s.D, s.V, &p) && forward_skip(p, s.D, false).use == s.use) continue;
+        ++failures;
+        fprintf(stderr, "FAIL scan in front of %lld x %lld x %lld\n", (long long)s.N, (long long)s.D, (long long)s.V);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc > 2) {                          // N D V M dw_free, any number of times
         for (int i = 1; i + 4 < argc; i += 5) print_form(atoll(argv[i]), atoll(argv[i + 1]), atoll(argv[i + 2]), atoll(argv[i + 3]), atoi(argv[i + 4]) != 0);
@@ -266,6 +279,7 @@ int main(int argc, char** argv) {
     const int iters = argc > 1 ? atoi(argv[1]) : 2000;
     check_makespan();
     check_planning_cost();
+    check_scan_is_priced();
     // shapes the schedules exist for: few rows against a full vocabulary; a small vocabulary
     bool dw_free = true; int64_t N = 509, D = 896, V = 151936, B = 0;
     CHECK(check(N, D, V, B, dw_free));
