@@ -48,7 +48,9 @@ int cce_get_row_skipping(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows
  * call may run in another order where that is rated faster.  Host only. */
 int cce_get_compact_tiling(int64_t N, int64_t D, int64_t V, int64_t max_valid_rows,
                            int* row_tiles, int* vocab_tiles);
-/* Tuning / testing aid: 1 = never skip, 2 = skip whenever max_valid_rows < N, 0 = automatic. */
+/* Tuning / testing aid: 1 = never skip, large all-rows calls (cce.h, cce_fp8.h) that find ignored rows by
+ * themselves included; 2 = the calls below skip whenever max_valid_rows < N, all-rows calls as with 0;
+ * 0 = automatic. */
 int cce_set_row_skipping(int mode);
 
 /* Workspace bytes to give the two calls below; at most 1 % of the materialised logits of the N rows

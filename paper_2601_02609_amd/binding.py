@@ -785,7 +785,7 @@ def compact_workspace_bytes(N: int, D: int, V: int, max_valid_rows: int) -> int:
 
 
 def set_row_skipping(mode: int = 0) -> None:
-    """1 = never skip rows, 2 = skip whenever the bound is below N, 0 = automatic."""
+    """1 = never skip rows (large all-rows calls included), 2 = skip whenever the bound is below N, 0 = automatic."""
     _rc(lib().cce_set_row_skipping(mode), "cce_set_row_skipping")
 
 

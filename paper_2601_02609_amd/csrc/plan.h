@@ -92,7 +92,7 @@ static GemmTile gemm_tile_of_kind(int kind) {
 static std::atomic<int> g_force_tiling{0};           // cce_set_backward_tiling: (row_tiles << 16) | vocab_tiles
 static std::atomic<int> g_force_gemm_cols{0};        // cce_set_backward_gemm_tile: 128 or 256
 static std::atomic<int> g_force_split_acc{0};        // cce_set_backward_accumulator: 1 = fp32, 2 = split
-static std::atomic<int> g_force_row_skipping{0};     // cce_set_row_skipping: 1 = never, 2 = whenever rows can be skipped
+static std::atomic<int> g_force_row_skipping{0};     // cce_set_row_skipping: 1 = never, 2 = whenever a bound on the valid rows is below N
 struct Knobs {
     int row_tiles, vocab_tiles, gemm_cols, split_acc;
     static Knobs read() {
@@ -685,7 +685,7 @@ struct RowBlockPlanner {
 struct ForwardSkip { bool use; int s_max, workgroups; size_t off_perm, off_found, off_scales, off_partials, off_sumz, end; };
 static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8) {
     ForwardSkip f = {};
-    if ((p.small_tiles && !fp8) || p.TT < 8 || g_force_row_skipping.load(std::memory_order_relaxed) != 0) return f;
+    if ((p.small_tiles && !fp8) || p.TT < 8 || g_force_row_skipping.load(std::memory_order_relaxed) == 1) return f;
     if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return f;
     const double scan_ns = 4000.0 + 0.4 * (double)p.rows, forward_ns = 2e-6 * (double)p.rows * (double)p.cols * (0.75 * (double)D + 72.0);
     if (50.0 * scan_ns > forward_ns) return f;
@@ -954,7 +954,7 @@ static BackwardSkip backward_skip(const Plan& p, const Schedule& sc, int64_t D, 
     BackwardSkip b = {};
     // (256 x 128 tiles: no order with the planes was ever planned with 256 x 256 ones)
     if (!sc.use || sc.kind != 1 || !sc.split_acc || sc.a < p.TT || sc.split_h != 1 || sc.split_w != 1 || p.TT < 8 || p.TT > kRowTableBytes / 512) return b;
-    if (g_force_row_skipping.load(std::memory_order_relaxed) != 0 || p.forced) return b;
+    if (g_force_row_skipping.load(std::memory_order_relaxed) == 1 || p.forced) return b;
     if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return b;
     const size_t each = (size_t)p.TT * 1024;
     b.off_perm = p.off_partials;

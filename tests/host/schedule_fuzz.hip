@@ -271,6 +271,21 @@ static void check_scan_is_priced() {
     }
 }
 
+// cce_set_row_skipping: 1 switches every route that leaves rows out off, 2 none.
+static void check_row_skipping_modes() {
+    for (int mode = 0; mode < 3; ++mode) {
+        const int64_t N = 8192, D = 896, V = 151936;
+        Plan p; Schedule s;
+        g_force_row_skipping.store(mode);
+        if (make_plan(N, D, V, &p)) plan_backward(&p, N, D, V, false, true, workspace_to_ask_for(p, N, D, V, false), &s);
+        if (forward_skip(p, D, false).use != (mode != 1) || backward_skip(p, s, D, false).use != (mode != 1)) {
+            ++failures;
+            fprintf(stderr, "FAIL row skipping, mode %d\n", mode);
+        }
+    }
+    g_force_row_skipping.store(0);
+}
+
 int main(int argc, char** argv) {
     if (argc > 2) {                          // N D V M dw_free, any number of times
         for (int i = 1; i + 4 < argc; i += 5) print_form(atoll(argv[i]), atoll(argv[i + 1]), atoll(argv[i + 2]), atoll(argv[i + 3]), atoi(argv[i + 4]) != 0);
@@ -280,6 +295,7 @@ int main(int argc, char** argv) {
     check_makespan();
     check_planning_cost();
     check_scan_is_priced();
+    check_row_skipping_modes();
     // shapes the schedules exist for: few rows against a full vocabulary; a small vocabulary
     bool dw_free = true; int64_t N = 509, D = 896, V = 151936, B = 0;
     CHECK(check(N, D, V, B, dw_free));
