@@ -609,13 +609,6 @@ struct GemmJob {
     const int32_t* count; int rows;             // counted rows (MODE 9): see rows_left
 };
 
-// MODE bit 0: the launch's dH job uses the split running sum; bit 1: its bf16 rows go through
-// row_map and the dW job reads hidden rows through it (row skipping in the caller's tensors);
-// MODE 4: only the bf16 rows go through row_map (row skipping on a gathered copy of the hidden
-// rows); MODE 9: the number of rows that take part is found on the device (count), the dW job reads hidden rows through
-// row_map as 16-bit entries, the dH job's planes lie in compact rows and its bf16 result replaces the lower halves, from
-// where scatter_rows_kernel takes it.  Launch-wide constants, compiled as separate kernels so that the plain form carries none
-// of their code.  K split exists in modes 0 and 4.
 // Result of a work item, straight from the accumulators.  A lane holds one column of a 32 x 32 block and, per
 // register, two rows of it lie in a wavefront: a dword store is two full 128-byte segments, so nothing is staged
 // through LDS and only the K groups' exchange needs a barrier.  The 16-bit forms exchange values between neighbouring
@@ -769,6 +762,13 @@ __device__ __forceinline__ void store_result(f32x16 (&acc)[Cfg::TM][Cfg::TN], co
     else with_rows(std::integral_constant<int, Cfg::TM / 2>{});
 }
 
+// MODE bit 0: the launch's dH job uses the split running sum; bit 1: its bf16 rows go through
+// row_map and the dW job reads hidden rows through it (row skipping in the caller's tensors);
+// MODE 4: only the bf16 rows go through row_map (row skipping on a gathered copy of the hidden
+// rows); MODE 9: the number of rows that take part is found on the device (count), the dW job reads hidden rows through
+// row_map as 16-bit entries, the dH job's planes lie in compact rows and its bf16 result replaces the lower halves, from
+// where scatter_rows_kernel takes it.  Launch-wide constants, compiled as separate kernels so that the plain form carries none
+// of their code.  K split exists in modes 0 and 4.
 template <class Cfg, bool A_KMAJOR, int MODE>
 __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, int rows, CCE_LDS char* smem) {
     constexpr bool COUNTED = (MODE & 8) != 0, KSPLIT = (MODE & 3) == 0 && !COUNTED;

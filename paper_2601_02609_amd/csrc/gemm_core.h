@@ -221,15 +221,9 @@ struct OperandTile {
         }
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-            const char* g;
-            if (KMAJOR) {
-                g = base + (size_t)(off[i] + (uint32_t)k0 * 2u);
-            } else {
-                int k = k0 + krow[i];
-                k = k < k_last ? k : k_last;
-                g = base + (size_t)((uint32_t)k * ld_bytes + off[i]);
-            }
-            load16_to_lds(g, stage + (wave + NW * i) * 1024);
+            int k = k0 + krow[i];                                 // a ragged slice of a K-slow operand
+            k = k < k_last ? k : k_last;
+            load16_to_lds(base + (size_t)((uint32_t)k * ld_bytes + off[i]), stage + (wave + NW * i) * 1024);
         }
     }
 };

@@ -466,7 +466,8 @@ static inline ScheduleChunk schedule_chunk(const ScheduleSteps& sc, int64_t D, i
 // 896 x 151936 in steps of 16 x 16 tiles 7.47 ms modelled, 7.33 measured; of 32 x 32 6.3 and 6.45.)
 struct ScheduleModel {
     int cus; int64_t D; GemmTile tile;
-    bool mapped;                // the dW job reads hidden rows through the row map: 0.85 us a slice against 0.76
+    bool mapped;                // the dW job reads hidden rows through the row map: priced at 0.11 of a slice more, what the lookup
+                                // took with its bounds checks (0.85 us against 0.76); byte offsets take less, see OperandTile
     int64_t dt;                 // output tiles across D
     bool one_to_unit = false;   // 256 x 128 tiles: not two to a compute unit
     bool duo() const { return tile.kind == 1 && !mapped && !one_to_unit; }
@@ -734,7 +735,8 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
     const ScheduleModel models[2] = {{cus, D, gemm_tile_of_kind(0)}, {cus, D, gemm_tile_of_kind(1)}};
-    // (row blocks add to dW with every block: the orders with dHidden's front rows are rated with the same items)
+    // (row blocks add to dW with every block, as do the orders with dHidden's front rows, and both are rated with the same
+    // items: one to a unit, though a launch of theirs may take two, so that the choice among them stays the one that was measured)
     ScheduleModel block_models[2] = {models[0], models[1]};
     block_models[1].one_to_unit = true;
     // What the steps of a chunk over all rows take, in 1 ... 4 row parts: many orders share such chunks
