@@ -674,8 +674,8 @@ struct RowBlockPlanner {
 // A forward over all rows that leaves the ignored ones out: their number is found on the device, so the launch has the
 // workgroups of all rows and those beyond the rows that take part return at once; from the plan's partials on (the plan's own
 // are not needed then) lie the row map, the counts, FP8 scales in the order of those rows, and the partials: 256 per workgroup.
-// Taken from about 1 ms of forward on (1.15 PFLOP/s): 8192 x 896 x 151936 with 15 % ignored 1.89 -> 1.64 ms, 4099 x 2048 x 128256
-// with 5 % 1.78 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.60 -> 1.24, none ignored 1.600 -> 1.606.
+// Taken from about 1 ms of forward on (1.15 PFLOP/s): 8192 x 896 x 151936 with 15 % ignored 1.87 -> 1.63 ms, 4099 x 2048 x 128256
+// with 5 % 1.76 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.59 -> 1.23, none ignored 1.591 -> 1.599.
 // The label scan is one workgroup: 4 us and 0.4 ns a row (131072 rows 55 us, a million 406), paid also where nothing is ignored.
 // It may take a fiftieth of the forward, whose products run at a rate that falls with D (2 N V (0.75 D + 72) fs: 131072 x 64 x 70000
 // 2.19 ms, 8192 x 896 x 80000 0.94), up to twice that with FP8 logits: 0.2 to 1.2 % on 8192 to 65536 rows without ignored ones;
