@@ -37,11 +37,13 @@ AGAINST_FORCED = {
 # every launch has the tile of the call that computes all rows.
 # "forward": the forward alone is tested (test_forward_skip_gpu.py)
 COUNTED = {
-    (8001, 512, 150001): dict(rows=dict(forward_skip=1, backward_skip=1, small_tiles=1, row_parts=1, same_tiles=1)),
+    (8001, 512, 150001): dict(rows=dict(forward_skip=1, backward_skip=1, small_tiles=1, row_parts=1, same_tiles=1),
+                              fp8=dict(forward_skip_fp8=1, backward_skip_fp8=1, small_tiles=1, row_parts=1, same_tiles=1)),
     (6001, 2048, 52001): dict(rows=dict(forward_skip=1, backward_skip=1, paired=1, paired_row_tiles=17, row_parts=1, same_tiles=1)),
     (5000, 1536, 110001): dict(accumulate=dict(backward_skip=1, paired=1, paired_row_tiles=17, same_tiles=1)),
     (5130, 1536, 80001): dict(accumulate=dict(backward_skip=1, row_parts=1)),
-    (2527, 3584, 68330): dict(rows=dict(backward_skip=1, paired=1, in_dw=1, same_tiles=1), accumulate=dict(backward_skip=1, paired=1, same_tiles=1)),
+    (2527, 3584, 68330): dict(rows=dict(backward_skip=1, paired=1, in_dw=1, same_tiles=1), accumulate=dict(backward_skip=1, paired=1, same_tiles=1),
+                              fp8=dict(forward_skip_fp8=1, backward_skip_fp8=1, paired=1, same_tiles=1)),
     (4500, 896, 150001): dict(rows=dict(forward_skip=1, backward_skip=1), fp8=dict(forward_skip_fp8=1, backward_skip_fp8=1)),
     (6000, 640, 150001): dict(rows=dict(forward_skip=1, backward_skip=1, row_parts=1)),
     (5001, 960, 121003): dict(rows=dict(forward_skip=1, backward_skip=1)),
