@@ -207,6 +207,165 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_kernel(
     }
 }
 
+// The same on tiles of two groups of wavefronts (see PingTile), bf16 operands.  The vocabulary split is cut at multiples of half
+// a tile's rows (a last half tile costs half), and a workgroup's slices follow each other without a gap: the first slice of a
+// vocabulary tile is requested in front of the last products of the one before and lands under its epilogue.  A token column lies in
+// four lane groups: each keeps the (max, sum) of a quarter of the columns.
+template <bool SUMZ, class Cfg>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_ping_kernel(
+        const void* __restrict__ H, const void* __restrict__ W,
+        int N, int D, int V, int TT, int S, float2* __restrict__ partials, float* __restrict__ partial_sumz,
+        const int32_t* __restrict__ perm, int32_t* __restrict__ status, const int32_t* __restrict__ rows_splits) {
+    extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
+    CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;        // (see lse_partial_kernel)
+    if (rows_splits) {
+        N = rows_splits[0];
+        S = rows_splits[1];
+        TT = (N + Cfg::BN - 1) / Cfg::BN;
+        if (rows_splits[3]) perm = nullptr;           // every row takes part
+    }
+    const int n_work = rows_splits ? TT * S : (int)gridDim.x;
+    if ((int)blockIdx.x >= n_work) return;
+    const int lin = xcd_round_id(blockIdx.x, n_work, 256);
+    int tt, s;
+    group_map(lin, TT, S, 4, tt, s);                  // (an XCD's workgroups: 4 token tiles x all splits, see lse_partial_kernel)
+    constexpr int kUnit = Cfg::BM / 2;
+    const int units = (V + kUnit - 1) / kUnit;
+    const int v_begin = (int)((int64_t)s * units / S) * kUnit;
+    int v_end = (int)((int64_t)(s + 1) * units / S) * kUnit;
+    v_end = v_end < V ? v_end : V;
+
+    const uint32_t ld = (uint32_t)D * 2u;
+    const int KT = D / Cfg::BK;
+    PingPong<Cfg, ARows::kHalves> pp;
+    PingLoads<Cfg, ARows::kHalves> loads;
+    pp.init(smem);
+    loads.init(smem, ld);
+#pragma unroll
+    for (int i = 0; i < Cfg::kBLoads; ++i) {
+        int row = tt * Cfg::BN + loads.row(i);
+        row = row < N ? row : N - 1;
+        if (perm) {
+            const int mapped = perm[row];             // token t of the tile space is row perm[t] of H
+            row = mapped < 0 ? 0 : mapped;
+        }
+        loads.set_b_row(i, row, ld);
+    }
+    auto request = [&](int stage, int half) {
+        if (loads.on) loads.issue(stage, half);
+    };
+    auto tile_rows = [&](int v) { return v_end - v < Cfg::BM ? v_end - v : Cfg::BM; };
+
+    float run_m[Cfg::NB / 4], run_d[Cfg::NB / 4], run_z[Cfg::NB / 4];        // of column 4 q + lane group
+#pragma unroll
+    for (int q = 0; q < Cfg::NB / 4; ++q) { run_m[q] = -INFINITY; run_d[q] = 0.f; run_z[q] = 0.f; }
+    const int g = (threadIdx.x & 63) >> 4;
+
+    loads.on = true;
+    loads.tile((const char*)W + (size_t)v_begin * ld, tile_rows(v_begin), (const char*)H, ld);
+    // (what the compiler has loaded so far has to be there: it cannot see the loads of the slices)
+    __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0)
+    loads.issue(0, 0);
+    loads.issue(0, 1);
+    pp.start();
+    for (int v = v_begin; v < v_end; v += Cfg::BM) {
+        f32x4 acc[Cfg::NA][Cfg::NB];
+        const int rows = tile_rows(v), parts = rows > kUnit ? 2 : 1;
+        auto next_slice = [&](int kt) {               // what slice kt's turns request
+            if (kt + 1 < KT) {
+                loads.a += 2 * Cfg::BK;
+                loads.b += 2 * Cfg::BK;
+            } else if (v + Cfg::BM < v_end) {
+                loads.tile((const char*)W + (size_t)(v + Cfg::BM) * ld, tile_rows(v + Cfg::BM), (const char*)H, ld);
+            } else {
+                loads.on = false;
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+            for (int j = 0; j < Cfg::NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+        for (int kt = 0;;) {
+            next_slice(kt);
+            pp.slice(acc, parts, request);
+            if (++kt == KT) break;
+            pp.barrier();
+        }
+        pp.tile_done();
+        if (rows < Cfg::BM) {                         // rows that are not this split's
+#pragma unroll
+            for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool dead = pp.row(i, r) >= rows;
+#pragma unroll
+                    for (int j = 0; j < Cfg::NB; ++j) acc[i][j][r] = dead ? -INFINITY : acc[i][j][r];
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < Cfg::NB; ++j) {
+            float tmax = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+            const float m = tmax * kLog2e, ms = (m == -INFINITY) ? 0.f : m;
+            float sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum += fast_exp2(fmaf(acc[i][j][r], kLog2e, -ms));
+            sum += __shfl_xor(sum, 16);
+            sum += __shfl_xor(sum, 32);
+            float nm = run_m[j >> 2], nd = run_d[j >> 2];
+            md_merge(nm, nd, m, sum);
+            run_m[j >> 2] = g == (j & 3) ? nm : run_m[j >> 2];
+            run_d[j >> 2] = g == (j & 3) ? nd : run_d[j >> 2];
+            if (SUMZ) {
+                float sz = 0.f;
+#pragma unroll
+                for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sz += (acc[i][j][r] == -INFINITY) ? 0.f : acc[i][j][r];
+                sz += __shfl_xor(sz, 16);
+                sz += __shfl_xor(sz, 32);
+                run_z[j >> 2] += g == (j & 3) ? sz : 0.f;
+            }
+        }
+        pp.tile_end();
+    }
+    pp.finish();
+
+    // the WM wavefronts stacked along the vocabulary share token columns: merge via LDS
+    CCE_LDS f32x2* red = (CCE_LDS f32x2*)smem;        // [WM][BN]
+    CCE_LDS float* redz = (CCE_LDS float*)(smem + Cfg::WM * Cfg::BN * 8);   // [WM][BN]
+#pragma unroll
+    for (int q = 0; q < Cfg::NB / 4; ++q) {
+        const int col = pp.wn * Cfg::TNR + (4 * q + g) * 16 + (int)(threadIdx.x & 15);
+        red[pp.wm * Cfg::BN + col] = f32x2{run_m[q], run_d[q]};
+        if (SUMZ) redz[pp.wm * Cfg::BN + col] = run_z[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < Cfg::BN) {
+        const int tok = tt * Cfg::BN + threadIdx.x;
+        float m = -INFINITY, d = 0.f, z = 0.f;
+#pragma unroll
+        for (int w = 0; w < Cfg::WM; ++w) {
+            const f32x2 p = red[w * Cfg::BN + threadIdx.x];
+            md_merge(m, d, p.x, p.y);
+            if (SUMZ) z += redz[w * Cfg::BN + threadIdx.x];
+        }
+        if (tok < N) {
+            partials[(size_t)tok * S + s] = make_float2(m, d);
+            if (SUMZ) partial_sumz[(size_t)tok * S + s] = z;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Forward finalisation: one wavefront per token.
 // ------------------------------------------------------------------------------------------
@@ -554,6 +713,141 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
               ((chunk * 8) & ((1 << panel_shift) - 1))) = v;
         }
     }
+}
+
+// The same on tiles of two groups of wavefronts (see PingTile), bf16 operands; n_v_tiles of them cover the chunk's v_cols
+// columns.  A lane holds eight consecutive columns of a token: the bf16 results go from the registers to the chunk, 16 bytes per
+// lane and whole 64-byte pieces of a panel's rows, without staging or barriers.  The tokens' labels, lse and upstream gradients are
+// brought into the LDS stage that the last slice leaves free.
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_ping_kernel(
+        const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
+        const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
+        int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
+        int row0, int n_row_tiles, int v0, int v_cols, int n_v_tiles,
+        uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total,
+        const int32_t* __restrict__ perm, const int32_t* __restrict__ count, int first_row) {
+    extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
+    CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
+    const uint32_t ld = (uint32_t)D * 2u;
+    if (count) {                                      // (see grad_tile_kernel)
+        N = rows_left(count, first_row, N);
+        n_row_tiles = (N + Cfg::BN - 1) / Cfg::BN;
+        if (count[1]) {
+            H = (const char*)H + (size_t)first_row * ld;
+            perm = nullptr;
+        }
+    }
+    if ((int)blockIdx.x >= n_row_tiles * n_v_tiles) return;
+    const int lin = xcd_round_id(blockIdx.x, n_row_tiles * n_v_tiles, 256);
+    int ti, vi;
+    group_map(lin, n_row_tiles, n_v_tiles, 4, ti, vi);
+    const int tok0 = row0 + ti * Cfg::BN;             // first token of the tile (global index)
+    const int vt0 = v0 + vi * Cfg::BM;                // first vocabulary row of the tile (global index)
+    const float uniform_dl = dloss ? 0.f : mean_scale[0];
+
+    PingPong<Cfg, ARows::kPairs> pp;
+    PingLoads<Cfg, ARows::kPairs> loads;
+    pp.init(smem);
+    loads.init(smem, ld);
+#pragma unroll
+    for (int i = 0; i < Cfg::kBLoads; ++i) {
+        int row = tok0 + loads.row(i);
+        row = row < N ? row : N - 1;
+        if (perm) {
+            const int mapped = perm[row];             // (row skipping: token t is row perm[t] of H)
+            row = mapped < 0 ? 0 : mapped;
+        }
+        loads.set_b_row(i, row, ld);
+    }
+    const int w_row = vt0 < V ? vt0 : V - 1;          // (the last tile of a chunk may lie behind the matrix: zeros)
+    loads.tile((const char*)W + (size_t)w_row * ld, V - w_row < Cfg::BM ? V - w_row : Cfg::BM, (const char*)H, ld);
+    __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): see lse_partial_ping_kernel
+    loads.issue(0, 0);
+    loads.issue(0, 1);
+
+    const int KT = D / Cfg::BK;
+    f32x4 acc[Cfg::NA][Cfg::NB];
+#pragma unroll
+    for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+        for (int j = 0; j < Cfg::NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    loads.on = true;
+    auto request = [&](int stage, int half) {
+        if (loads.on) {
+            loads.issue(stage, half);
+        } else if (half == 0) {
+            // the last slice: the tokens' scalars, 256 of each, labels and lse by the wavefronts of group 0, dloss by those of group 1
+            const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), part = wave & 3;
+            int tok = tok0 + part * 64 + (int)(threadIdx.x & 63);
+            tok = tok < N ? tok : N - 1;
+            const uint32_t to = (uint32_t)(uintptr_t)smem + (uint32_t)stage * Cfg::kStage + (uint32_t)part * 256u;
+            if (wave < 4) {
+                load4_to_lds_sbase(labels, (uint32_t)tok * 4u, to);
+                load4_to_lds_sbase(lse, (uint32_t)tok * 4u, to + 1024u);
+            } else if (dloss) {
+                load4_to_lds_sbase(dloss, (uint32_t)tok * 4u, to + 2048u);
+            }
+        }
+    };
+    static_assert(Cfg::BN == 256, "four wavefronts of tokens");
+    pp.start();
+#pragma nounroll
+    for (int kt = 0;;) {
+        loads.a += 2 * Cfg::BK;
+        loads.b += 2 * Cfg::BK;
+        loads.on = kt + 1 < KT;
+        pp.slice(acc, 2, request);
+        if (++kt == KT) break;
+        pp.barrier();
+    }
+    pp.tile_done();
+    const CCE_LDS int32_t* const raw_y = (const CCE_LDS int32_t*)(smem + pp.cur * Cfg::kStage);
+    const CCE_LDS float* const raw_ls = (const CCE_LDS float*)(raw_y + 256);
+    const CCE_LDS float* const raw_dl = raw_ls + 256;
+
+    const float eps_over_v = label_smoothing / (float)V_total;
+    const bool ragged = vt0 + Cfg::BM > V;            // only the last vocabulary tile needs column masking
+    const int g = (threadIdx.x & 63) >> 4;
+    const int wave_col = vi * Cfg::BM + pp.wm * Cfg::TMR;         // first column of this wavefront in the chunk
+#pragma unroll
+    for (int j = 0; j < Cfg::NB; ++j) {
+        const int t = pp.col(j);
+        const int32_t label = raw_y[t];
+        const bool live = tok0 + t < N && label != ignore_index && label >= 0 && label < V_total;
+        const float ls = raw_ls[t], dl = dloss ? raw_dl[t] : uniform_dl;
+        const float sp = dl * fmaf(2.f * z_loss, ls, 1.f);        // factor of the softmax term
+        const float ch = dl * (1.f - label_smoothing);            // subtracted at the label
+        const float ncs = -dl * eps_over_v;                       // added everywhere
+        const float nl2 = -ls * kLog2e;
+        // label as a column relative to this lane's first one (W holds the rows [v_off, v_off + V) of V_total)
+        const int64_t y_local = (int64_t)label - v_off;
+        const int yrel = y_local >= 0 && y_local < V ? (int)y_local - v0 - wave_col - 8 * g : -1;
+#pragma unroll
+        for (int q = 0; q < Cfg::NA / 2; ++q) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = fmaf(fast_exp2(fmaf(acc[2 * q + e / 4][j][e % 4], kLog2e, nl2)), sp, ncs);
+            const int hit = yrel - 32 * q;
+            if (hit >= 0 && hit < 8) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] -= e == hit ? ch : 0.f;
+            }
+            const int c = wave_col + 32 * q + 8 * g;              // column in the chunk
+            if (ragged) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = v0 + c + e < V ? x[e] : 0.f;
+            }
+            union { __bf16 h[8]; u32x4 u; } pk;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pk.h[e] = (__bf16)x[e];
+            if (!live) pk.u = u32x4{0u, 0u, 0u, 0u};
+            if (wave_col + 32 * q < v_cols)
+                *(u32x4*)(G + (size_t)(c >> panel_shift) * panel + ((size_t)(ti * Cfg::BN + t) << panel_shift) + (c & ((1 << panel_shift) - 1))) = pk.u;
+        }
+    }
+    pp.tile_end();
+    pp.finish();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1194,7 +1488,7 @@ template <class Cfg> constexpr int grad_tile_lds() {
     const int staging = Cfg::BN * kGRowBytes<Cfg> + Cfg::BN;
     return staging > Cfg::kLdsBytes ? staging : Cfg::kLdsBytes;
 }
-constexpr int kGradTileLds = grad_tile_lds<TileBig>();
+constexpr int kGradTileLds = grad_tile_lds<TileBig>();       // (FP8 logits)
 
 // The MFMA kernels use more dynamic LDS than the default limit: raise it once per device
 // (not per call, so that the compute calls consist of kernel launches only).
@@ -1206,13 +1500,16 @@ static bool ensure_kernel_attributes() {
     if (dev < 0 || dev >= 64) return false;
     std::lock_guard<std::mutex> lock(mu);
     if (done[dev]) return true;
-    if (!allow_big_lds(lse_partial_kernel<false, false>, TileBig::kLdsBytes)) return false;
-    if (!allow_big_lds(lse_partial_kernel<true, false>, TileBig::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_ping_kernel<false, TileTall>, TileTall::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_ping_kernel<true, TileTall>, TileTall::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_ping_kernel<false, TileSquare>, TileSquare::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_ping_kernel<true, TileSquare>, TileSquare::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_tile_ping_kernel<TileTall>, TileTall::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_tile_ping_kernel<TileSquare>, TileSquare::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, true>, TileBig::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, false, TileSmall>, TileSmall::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<true, false, TileSmall>, TileSmall::kLdsBytes)) return false;
     if (!allow_big_lds(grad_tile_kernel<false, TileSmall>, grad_tile_lds<TileSmall>())) return false;
-    if (!allow_big_lds(grad_tile_kernel<false>, kGradTileLds)) return false;
     if (!allow_big_lds(grad_tile_kernel<true>, kGradTileLds)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileBig, 0>, kGemmLdsBig)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 0>, kGemmLdsNarrow)) return false;
@@ -1249,10 +1546,15 @@ static void launch_grad_tiles(const void* H, const void* W, const int32_t* label
         hipLaunchKernelGGL((grad_tile_kernel<false, TileSmall>), dim3(4 * n_row_tiles * n_v_tiles), dim3(kThreads), grad_tile_lds<TileSmall>(),
                            stream, H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
                            2 * n_row_tiles, v0, 2 * n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
-    else
-        hipLaunchKernelGGL(grad_tile_kernel<false>, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), kGradTileLds, stream,
+    else if (tall_grad_tiles(n_row_tiles, n_v_tiles, D)) {
+        const int tiles = (n_v_tiles * 256 + TileTall::BM - 1) / TileTall::BM;
+        hipLaunchKernelGGL(grad_tile_ping_kernel<TileTall>, dim3(n_row_tiles * tiles), dim3(kThreads), TileTall::kLdsBytes, stream,
                            H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           n_row_tiles, v0, n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
+                           n_row_tiles, v0, n_v_tiles * 256, tiles, G, panel, panel_shift, v_off, V_total, perm, count, first_row);
+    } else
+        hipLaunchKernelGGL(grad_tile_ping_kernel<TileSquare>, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), TileSquare::kLdsBytes, stream,
+                           H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
+                           n_row_tiles, v0, n_v_tiles * 256, n_v_tiles, G, panel, panel_shift, v_off, V_total, perm, count, first_row);
 }
 
 // Both contractions of counted rows (mode 9), the row table behind the stages; tile: counted_contraction_kind.  (All of them
@@ -1420,12 +1722,17 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
         else if (p.small_tiles)
             hipLaunchKernelGGL((lse_partial_kernel<false, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
                                hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
-        else if (smooth)
-            hipLaunchKernelGGL((lse_partial_kernel<true, false>), dim3(grid), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
-        else
-            hipLaunchKernelGGL((lse_partial_kernel<false, false>), dim3(grid), dim3(kThreads), TileBig::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
+        else {
+#define CCE_LAUNCH_FORWARD(SUMZ, CFG) \
+    hipLaunchKernelGGL((lse_partial_ping_kernel<SUMZ, CFG>), dim3(grid), dim3(kThreads), CFG::kLdsBytes, stream, \
+                       hidden, weight, (int)N, (int)D, (int)V, p.TT, p.S, partials, sumz, fwd_perm, clear, rows_splits)
+            const bool tall = tall_forward_tiles(V, p.S);
+            if (smooth && tall) CCE_LAUNCH_FORWARD(true, TileTall);
+            else if (smooth) CCE_LAUNCH_FORWARD(true, TileSquare);
+            else if (tall) CCE_LAUNCH_FORWARD(false, TileTall);
+            else CCE_LAUNCH_FORWARD(false, TileSquare);
+#undef CCE_LAUNCH_FORWARD
+        }
     }
     hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream,
                        (const uint16_t*)hidden, (const uint16_t*)weight, labels, partials, (const float*)sumz,

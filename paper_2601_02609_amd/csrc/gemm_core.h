@@ -119,6 +119,12 @@ __device__ __forceinline__ void load16_to_lds_sbase(const char* uniform_base, ui
                  :: "v"(lane_offset), "s"(uniform_base), "s"(m0_value) : "memory", "m0");
 }
 
+// 4 bytes per lane.
+__device__ __forceinline__ void load4_to_lds_sbase(const void* uniform_base, uint32_t lane_offset, uint32_t m0_value) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :: "v"(lane_offset), "s"(uniform_base), "s"(m0_value) : "memory", "m0");
+}
+
 // One operand (R = 128 or 256 free indices) of one workgroup tile: global -> LDS.
 // MAP (K-slow only): the k-rows are reached through a table in LDS with an entry for every k of whole slices, 1: byte
 // offsets of matrix rows (kmap), 2: row numbers in 16 bits (kmap16).  A load then costs one LDS read and one add or
@@ -599,6 +605,191 @@ __device__ __forceinline__ void gemm_mainloop_fp8(f32x16 (&acc)[Cfg::TM][Cfg::TN
     }
     barrier_pending_loads<0>();
 }
+
+// ------------------------------------------------------------------------------------------
+// Tiles of eight wavefronts in two groups of four, one of each group to a SIMD, that take turns: while one group
+// multiplies, the other reads its next fragments from LDS and requests the next slice, a barrier at every turn.  A
+// wavefront owns NA x NB blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16: lane l holds column l % 16, rows 4 (l / 16) + 0 .. 3),
+// 4 x 2 wavefronts a tile of 64 NA x 32 NB.  Fragments need no second buffer (the other group's products hide their
+// latency), which leaves the registers for 384 x 256 outputs: a sixth fewer operand bytes per product than 256 x 256 from
+// L2, a fifth fewer from LDS, and the 16 x 16 form draws less power than the 32 x 32 one, whose smaller number of
+// instructions the turns make up for.  What bounds it is power: 18432 x 8192 x 4096 in one launch after the other, random /
+// constant operands, TFLOP/s: TileBig's loop 1 400 / 1 920; these turns with 32 x 32 x 16 at 256 x 256 1 425 / 2 015, at
+// 384 x 256 1 475 / 2 195; with 16 x 16 x 32 at 256 x 256 1 530 / 1 930, at 384 x 256 1 645 / 2 155 (K = 896: TileBig's
+// 1 350 / 1 755, 384 x 256 1 540 / 1 915).
+template <int NA_, int NB_>
+struct PingTile {
+    static constexpr int NA = NA_, NB = NB_, WM = 4, WN = 2;
+    static constexpr int kThreads = 512, BK = 64;
+    static constexpr int TMR = 16 * NA, TNR = 16 * NB;          // rows and columns of a wavefront
+    static constexpr int BM = WM * TMR, BN = WN * TNR;
+    static constexpr int kAStage = BM * BK * 2, kStage = (BM + BN) * BK * 2;
+    static constexpr int kLdsBytes = 2 * kStage;
+    static constexpr int kALoads = BM / 64, kBLoads = BN / 64;  // 16-byte loads per thread and slice
+    static constexpr int kParts = 2, QA = NA / kParts;          // a step's products in two turns, over half of the A blocks each
+    static_assert(NA % kParts == 0 && BN % 64 == 0 && kLdsBytes <= 160 * 1024, "whole parts and loads; two stages");
+};
+typedef PingTile<6, 8> TileTall;        // 384 x 256, wave tile 96 x 128
+typedef PingTile<4, 8> TileSquare;      // 256 x 256, wave tile 64 x 128: where the taller tiles leave compute units idle
+
+// Rows of the A stage that a wavefront's blocks stand for.  Halves: block i of part p covers rows p BM / 2 + 16 (QA wave + i),
+// so that a tile of BM / 2 rows is its first part alone.  Pairs: blocks 2 j and 2 j + 1 share rows 32 j ... 32 j + 31 of the
+// wavefront, lane group g holding rows 8 g .. 8 g + 7 of them, four in each block: 16 bytes of bf16 results in a row.
+enum class ARows { kHalves, kPairs };
+
+template <class Cfg, ARows ROWS>
+struct PingPong {
+    CCE_LDS char* smem;
+    int group, wm, wn;           // wave-uniform
+    uint32_t fa, fb;             // fragment addresses of the first step; the second is 64 bytes away, either side
+    int cur;                     // stage of the current slice
+
+    static __device__ __forceinline__ int a_swizzle(int row) {
+        // a lane's 16 bytes go to physical chunk c ^ swizzle of its 128-byte row: the 16 rows of a fragment differ in it
+        return ROWS == ARows::kHalves ? (row >> 1) & 7 : ((row >> 1) & 1) | (((row >> 3) & 3) << 1);
+    }
+    __device__ __forceinline__ void init(CCE_LDS char* smem_) {
+        smem = smem_;
+        cur = 0;
+        const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        group = wave >> 2;
+        wm = wave / Cfg::WN;
+        wn = wave % Cfg::WN;
+        const int r = l & 15, h = l >> 4;
+        const int arow = ROWS == ARows::kHalves ? wm * (16 * Cfg::QA) + r : wm * Cfg::TMR + 8 * (r >> 2) + (r & 3);
+        const int brow = wn * Cfg::TNR + r;
+        fa = (uint32_t)(arow * 128 + ((h ^ a_swizzle(arow)) << 4));
+        fb = (uint32_t)(Cfg::kAStage + brow * 128 + ((h ^ ((brow >> 1) & 7)) << 4));
+    }
+    static constexpr int a_offset(int i) {
+        return ROWS == ARows::kHalves ? (i / Cfg::QA * (Cfg::BM / 2) + i % Cfg::QA * 16) * 128 : (i / 2 * 32 + i % 2 * 4) * 128;
+    }
+    // Row of the tile of accumulator element r of block i, and column of block j, of the calling lane.
+    __device__ __forceinline__ int row(int i, int r) const {
+        const int g = (threadIdx.x & 63) >> 4;
+        return ROWS == ARows::kHalves ? i / Cfg::QA * (Cfg::BM / 2) + (wm * Cfg::QA + i % Cfg::QA) * 16 + 4 * g + r
+                                      : wm * Cfg::TMR + i / 2 * 32 + 8 * g + i % 2 * 4 + r;
+    }
+    __device__ __forceinline__ int col(int j) const { return wn * Cfg::TNR + j * 16 + (int)(threadIdx.x & 15); }
+
+    static __device__ __forceinline__ void barrier() { asm volatile("s_barrier" ::: "memory"); }
+    // In front of the first slice, whose loads have been requested into stage 0.
+    __device__ __forceinline__ void start() {
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        if (group) barrier();
+    }
+    // Behind the last slice of a tile and behind its epilogue: group 1 passes its barrier there, so that the groups' epilogues run
+    // beside each other.
+    __device__ __forceinline__ void tile_done() {
+        if (!group) barrier();
+    }
+    __device__ __forceinline__ void tile_end() {
+        if (group) barrier();
+    }
+    // Behind the last tile: both groups have passed the same barriers.
+    __device__ __forceinline__ void finish() {
+        if (!group) barrier();
+    }
+
+    // One slice of 64, a barrier() to follow (or tile_done()).  PARTS: 1 leaves out the second half of the A rows.  request(stage, half): issues one half of the loads of the slice behind this one, where there is one.
+    //
+    // Turns: group 0 reads in turn 2 i and multiplies in 2 i + 1, group 1 one turn later.  The loads of slice t + 1 are issued in the
+    // first reading turns of slice t, when every wavefront has its fragments of slice t - 1 (lgkmcnt(0) in front of the barriers), and
+    // each wavefront waits for its own (vmcnt(0)) in its last reading turn of slice t, which is in front of the barrier that precedes
+    // group 0's first reading turn of slice t + 1.
+    template <class Request>
+    __device__ __forceinline__ void slice(f32x4 (&acc)[Cfg::NA][Cfg::NB], int parts, Request request) {
+        CCE_LDS char* const st = smem + cur * Cfg::kStage;
+        const int next = cur ^ 1;
+        bf16x8 a[Cfg::QA], b[Cfg::NB];
+        auto turn = [&](auto step, auto part) {
+            constexpr int s = decltype(step)::value, p = decltype(part)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if (p == 0) {
+#pragma unroll
+                for (int j = 0; j < Cfg::NB; ++j) b[j] = *(const CCE_LDS bf16x8*)(st + (fb ^ (uint32_t)(s * 64)) + j * 2048);
+            }
+#pragma unroll
+            for (int i = 0; i < Cfg::QA; ++i) a[i] = *(const CCE_LDS bf16x8*)(st + (fa ^ (uint32_t)(s * 64)) + a_offset(p * Cfg::QA + i));
+            if (s == 0) {
+                request(next, p);
+                if (p == 0 && parts == 1) request(next, 1);
+            }
+            if (s == 1 && p == 0 && parts == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (s == 1 && p == 1) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < Cfg::QA; ++i)
+#pragma unroll
+                for (int jj = 0; jj < Cfg::NB; ++jj) {
+                    const int j = i & 1 ? Cfg::NB - 1 - jj : jj;          // (back and forth: the B operand of the last product stays: 1 %)
+                    f32x4& c = acc[p * Cfg::QA + i][j];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], c, 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        using Zero = std::integral_constant<int, 0>;
+        using One = std::integral_constant<int, 1>;
+        turn(Zero{}, Zero{});
+        barrier();
+        if (parts == 2) {
+            turn(Zero{}, One{});
+            barrier();
+        }
+        turn(One{}, Zero{});
+        if (parts == 2) {
+            barrier();
+            turn(One{}, One{});
+        }
+        cur = next;
+    }
+};
+
+// Global -> LDS loads of two K-major operands for these tiles.  Load i of a thread brings 16 bytes of row 64 i + 8 wave +
+// lane / 8 of the stage, A rows in front of B rows.  A rows are relative to the tile's first one, those behind the last valid
+// one read that again; B rows lie at any offsets (a row map).
+template <class Cfg, ARows ROWS>
+struct PingLoads {
+    const char* a;               // next slice: A's first row of the tile and B, both at the slice's K offset (uniform)
+    const char* b;
+    uint32_t a_off, a_last, a_step;
+    uint32_t b_off[Cfg::kBLoads];
+    uint32_t chunk, lds0;
+    bool on;
+    __device__ __forceinline__ int row(int i) const { return 64 * i + 8 * (int)(threadIdx.x >> 6) + (int)((threadIdx.x & 63) >> 3); }
+    __device__ __forceinline__ void init(CCE_LDS char* smem, uint32_t ld_bytes) {
+        chunk = (uint32_t)((threadIdx.x & 7) ^ PingPong<Cfg, ROWS>::a_swizzle(row(0))) * 16u;
+        a_off = (uint32_t)row(0) * ld_bytes + chunk;
+        a_step = 64u * ld_bytes;
+        lds0 = (uint32_t)(uintptr_t)smem + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * 1024u;
+    }
+    // B row i of this thread is row `r` of its matrix.
+    __device__ __forceinline__ void set_b_row(int i, int r, uint32_t ld_bytes) {
+        b_off[i] = (uint32_t)r * ld_bytes + (uint32_t)((threadIdx.x & 7) ^ ((row(0) >> 1) & 7)) * 16u;
+    }
+    __device__ __forceinline__ void tile(const char* a_tile, int a_rows, const char* b_matrix, uint32_t ld_bytes) {
+        a = a_tile;
+        b = b_matrix;
+        a_last = (uint32_t)(a_rows - 1) * ld_bytes + chunk;
+    }
+    __device__ __forceinline__ void issue(int stage, int half) const {
+        constexpr int NL = Cfg::kALoads + Cfg::kBLoads;
+        const uint32_t to = lds0 + (uint32_t)stage * Cfg::kStage;
+        uint32_t first = a_off;
+        asm volatile("" : "+v"(first));                 // (the sums below stay here: kept over the loop they cost registers)
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            if ((i < NL / 2) != (half == 0)) continue;
+            if (i < Cfg::kALoads) {
+                const uint32_t o = first + (uint32_t)i * a_step;
+                load16_to_lds_sbase(a, o < a_last ? o : a_last, to + (uint32_t)i * 8192u);
+            } else {
+                load16_to_lds_sbase(b, b_off[i - Cfg::kALoads], to + (uint32_t)i * 8192u);
+            }
+        }
+    }
+};
 
 // Tile coordinates of accumulator element acc[bm][bn][r] of the calling lane.
 template <class Cfg>
