@@ -720,24 +720,16 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_kernel(
 // lane and whole 64-byte pieces of a panel's rows, without staging or barriers.  The tokens' labels, lse and upstream gradients are
 // brought into the LDS stage that the last slice leaves free.
 template <class Cfg>
-__global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_ping_kernel(
+__device__ __forceinline__ void grad_tile_ping(
         const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
         const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
         int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
         int row0, int n_row_tiles, int v0, int v_cols, int n_v_tiles,
         uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total,
-        const int32_t* __restrict__ perm, const int32_t* __restrict__ count, int first_row) {
+        const int32_t* __restrict__ perm) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
     const uint32_t ld = (uint32_t)D * 2u;
-    if (count) {                                      // (see grad_tile_kernel)
-        N = rows_left(count, first_row, N);
-        n_row_tiles = (N + Cfg::BN - 1) / Cfg::BN;
-        if (count[1]) {
-            H = (const char*)H + (size_t)first_row * ld;
-            perm = nullptr;
-        }
-    }
     if ((int)blockIdx.x >= n_row_tiles * n_v_tiles) return;
     const int lin = xcd_round_id(blockIdx.x, n_row_tiles * n_v_tiles, 256);
     int ti, vi;
@@ -848,6 +840,40 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_ping_kernel(
     }
     pp.tile_end();
     pp.finish();
+}
+
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_ping_kernel(
+        const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
+        const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
+        int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss,
+        int row0, int n_row_tiles, int v0, int v_cols, int n_v_tiles,
+        uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total, const int32_t* __restrict__ perm) {
+    grad_tile_ping<Cfg>(H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0, n_row_tiles, v0, v_cols,
+                        n_v_tiles, G, panel, panel_shift, v_off, V_total, perm);
+}
+
+// Counted rows (see grad_tile_kernel): the taller or the square tiles, whichever take less time for the row tiles that are left
+// (tall_grad_tiles).  28 of 32 row tiles x 40 at D = 896: 1120 square ones are five rounds of 256 compute units, 756 tall ones three.
+__global__ __launch_bounds__(TileTall::kThreads, 2) void grad_tile_counted_kernel(
+        const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
+        const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
+        int N, int D, int V, int32_t ignore_index, float label_smoothing, float z_loss, int v0, int n_v_tiles,
+        uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total,
+        const int32_t* __restrict__ perm, const int32_t* __restrict__ count, int first_row, int cus) {
+    N = rows_left(count, first_row, N);
+    const int n_row_tiles = (N + 255) / 256;
+    if (count[1]) {                                   // every row takes part: no lookup in front of the first slice
+        H = (const char*)H + (size_t)first_row * ((size_t)D * 2);
+        perm = nullptr;
+    }
+    const int n_tall = (n_v_tiles * 256 + TileTall::BM - 1) / TileTall::BM;
+    if (tall_grad_tiles(n_row_tiles, n_v_tiles, D, cus))
+        grad_tile_ping<TileTall>(H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, 0, n_row_tiles, v0,
+                                 n_v_tiles * 256, n_tall, G, panel, panel_shift, v_off, V_total, perm);
+    else
+        grad_tile_ping<TileSquare>(H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, 0, n_row_tiles, v0,
+                                   n_v_tiles * 256, n_v_tiles, G, panel, panel_shift, v_off, V_total, perm);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1506,6 +1532,7 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(lse_partial_ping_kernel<true, TileSquare>, TileSquare::kLdsBytes)) return false;
     if (!allow_big_lds(grad_tile_ping_kernel<TileTall>, TileTall::kLdsBytes)) return false;
     if (!allow_big_lds(grad_tile_ping_kernel<TileSquare>, TileSquare::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_tile_counted_kernel, TileTall::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, true>, TileBig::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, false, TileSmall>, TileSmall::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<true, false, TileSmall>, TileSmall::kLdsBytes)) return false;
@@ -1546,15 +1573,19 @@ static void launch_grad_tiles(const void* H, const void* W, const int32_t* label
         hipLaunchKernelGGL((grad_tile_kernel<false, TileSmall>), dim3(4 * n_row_tiles * n_v_tiles), dim3(kThreads), grad_tile_lds<TileSmall>(),
                            stream, H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
                            2 * n_row_tiles, v0, 2 * n_v_tiles, G, panel, panel_shift, v_off, V_total, none, perm, count, first_row);
-    else if (tall_grad_tiles(n_row_tiles, n_v_tiles, D)) {
+    else if (count)                                   // (row0 is 0: rows and scalars of the step itself)
+        hipLaunchKernelGGL(grad_tile_counted_kernel, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), TileTall::kLdsBytes, stream,
+                           H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, v0, n_v_tiles,
+                           G, panel, panel_shift, v_off, V_total, perm, count, first_row, device_cu_count());
+    else if (tall_grad_tiles(n_row_tiles, n_v_tiles, (int)D, device_cu_count())) {
         const int tiles = (n_v_tiles * 256 + TileTall::BM - 1) / TileTall::BM;
         hipLaunchKernelGGL(grad_tile_ping_kernel<TileTall>, dim3(n_row_tiles * tiles), dim3(kThreads), TileTall::kLdsBytes, stream,
                            H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           n_row_tiles, v0, n_v_tiles * 256, tiles, G, panel, panel_shift, v_off, V_total, perm, count, first_row);
+                           n_row_tiles, v0, n_v_tiles * 256, tiles, G, panel, panel_shift, v_off, V_total, perm);
     } else
         hipLaunchKernelGGL(grad_tile_ping_kernel<TileSquare>, dim3(n_row_tiles * n_v_tiles), dim3(kThreads), TileSquare::kLdsBytes, stream,
                            H, W, labels, lse, dloss, mean_scale, N, D, V, ignore_index, label_smoothing, z_loss, row0,
-                           n_row_tiles, v0, n_v_tiles * 256, n_v_tiles, G, panel, panel_shift, v_off, V_total, perm, count, first_row);
+                           n_row_tiles, v0, n_v_tiles * 256, n_v_tiles, G, panel, panel_shift, v_off, V_total, perm);
 }
 
 // Both contractions of counted rows (mode 9), the row table behind the stages; tile: counted_contraction_kind.  (All of them

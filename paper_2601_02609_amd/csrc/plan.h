@@ -47,19 +47,11 @@ static bool use_small_tiles(int64_t row_tiles, int64_t vocab_tiles) {
     return row_tiles * vocab_tiles * 2 <= device_cu_count();
 }
 
-// Tiles of a forward whose vocabulary lies in S splits, and of a launch of row_tiles x vocab_tiles (of 256 x 256) gradient tiles:
-// 384 x 256 (true) or 256 x 256, see PingTile.  Both kernels cut a split at half tiles.
+// Tiles of a forward whose vocabulary lies in S splits: 384 x 256 (true) or 256 x 256, see PingTile.  Either cuts a split at half tiles.
 static bool tall_forward_tiles(int64_t V, int64_t S) {
     const int64_t tall = (V + 191) / 192, square = (V + 127) / 128;
     return (double)((tall + S - 1) / S) * 192.0 * 0.92 <= (double)((square + S - 1) / S) * 128.0;
 }
-static bool tall_grad_tiles(int64_t row_tiles, int64_t vocab_tiles, int64_t D) {
-    const int64_t cus = device_cu_count(), slices = D / 64;
-    const double tall = (double)((row_tiles * ((vocab_tiles * 2 + 2) / 3) + cus - 1) / cus) * ((double)slices * 1.96 + 8.0);
-    const double square = (double)((row_tiles * vocab_tiles + cus - 1) / cus) * ((double)slices * 1.42 + 6.0);
-    return tall <= square;
-}
-
 struct Plan {
     int TT, VT, S;              // forward: token tiles, vocabulary tiles, vocabulary splits
     int64_t Nb, Vc;             // backward: rows per row block, vocabulary columns per chunk (multiples of 256)
