@@ -854,7 +854,8 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_tile_ping_kernel(
 }
 
 // Counted rows (see grad_tile_kernel): the taller or the square tiles, whichever take less time for the row tiles that are left
-// (tall_grad_tiles).  28 of 32 row tiles x 40 at D = 896: 1120 square ones are five rounds of 256 compute units, 756 tall ones three.
+// (tall_grad_tiles).  28 of 32 row tiles x 40 at D = 896: 1120 square ones are five rounds of 256 compute units, 756 tall ones three:
+// 139 -> 120 us (both forms in one kernel: the registers of the taller one, 252, and all of the LDS, as that one has by itself).
 __global__ __launch_bounds__(TileTall::kThreads, 2) void grad_tile_counted_kernel(
         const void* __restrict__ H, const void* __restrict__ W, const int32_t* __restrict__ labels,
         const float* __restrict__ lse, const float* __restrict__ dloss, const float* __restrict__ mean_scale,
