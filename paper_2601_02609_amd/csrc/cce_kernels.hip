@@ -207,10 +207,25 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_kernel(
     }
 }
 
+// Lanes 32 ... 63 of a and lanes 0 ... 31 of b change places; the same of the odd rows of 16 lanes of a and the even ones of b.
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float((uint32_t)s[0]);
+    b = __uint_as_float((uint32_t)s[1]);
+}
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float((uint32_t)s[0]);
+    b = __uint_as_float((uint32_t)s[1]);
+}
+
 // The same on tiles of two groups of wavefronts (see PingTile), bf16 operands.  The vocabulary split is cut at multiples of half
 // a tile's rows (a last half tile costs half), and a workgroup's slices follow each other without a gap: the first slice of a
-// vocabulary tile is requested in front of the last products of the one before and lands under its epilogue.  A token column lies in
-// four lane groups: each keeps the (max, sum) of a quarter of the columns.
+// vocabulary tile is requested in front of the last products of the one before.  A token column lies in four lane groups: each
+// keeps the (max, sum) of a quarter of the columns.  A tile's parts are formed in each lane by itself and get to those groups by
+// lanes that change places, 12 instructions a tile without LDS: a common maximum by 32 shuffles through LDS in front of the
+// exponentials made forwards of few slices slower than lse_partial_kernel's (256 x 256 tiles, us, that one / shuffles / this:
+// 29040 x 64 x 32290 239 / 291 / 257, 8883 x 128 x 97046 290 / 323 / 290, 23189 x 256 x 84156 992 / 1048 / 969).
 template <bool SUMZ, class Cfg>
 __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_ping_kernel(
         const void* __restrict__ H, const void* __restrict__ W,
@@ -305,36 +320,44 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void lse_partial_ping_kernel(
                 }
         }
 #pragma unroll
-        for (int j = 0; j < Cfg::NB; ++j) {
-            float tmax = -INFINITY;
+        for (int q = 0; q < Cfg::NB / 4; ++q) {
+            float m[4], d[4], z[4];                   // of columns 4 q ... 4 q + 3, this lane's rows
 #pragma unroll
-            for (int i = 0; i < Cfg::NA; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-            const float m = tmax * kLog2e, ms = (m == -INFINITY) ? 0.f : m;
-            float sum = 0.f;
-#pragma unroll
-            for (int i = 0; i < Cfg::NA; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sum += fast_exp2(fmaf(acc[i][j][r], kLog2e, -ms));
-            sum += __shfl_xor(sum, 16);
-            sum += __shfl_xor(sum, 32);
-            float nm = run_m[j >> 2], nd = run_d[j >> 2];
-            md_merge(nm, nd, m, sum);
-            run_m[j >> 2] = g == (j & 3) ? nm : run_m[j >> 2];
-            run_d[j >> 2] = g == (j & 3) ? nd : run_d[j >> 2];
-            if (SUMZ) {
-                float sz = 0.f;
+            for (int e = 0; e < 4; ++e) {
+                const int j = 4 * q + e;
+                float tmax = -INFINITY;
 #pragma unroll
                 for (int i = 0; i < Cfg::NA; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) sz += (acc[i][j][r] == -INFINITY) ? 0.f : acc[i][j][r];
-                sz += __shfl_xor(sz, 16);
-                sz += __shfl_xor(sz, 32);
-                run_z[j >> 2] += g == (j & 3) ? sz : 0.f;
+                    for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, acc[i][j][r]);
+                m[e] = tmax * kLog2e;
+                const float ms = (m[e] == -INFINITY) ? 0.f : m[e];
+                d[e] = 0.f;
+                z[e] = 0.f;
+#pragma unroll
+                for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) d[e] += fast_exp2(fmaf(acc[i][j][r], kLog2e, -ms));
+                if (SUMZ) {
+#pragma unroll
+                    for (int i = 0; i < Cfg::NA; ++i)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) z[e] += (acc[i][j][r] == -INFINITY) ? 0.f : acc[i][j][r];
+                }
             }
+            // the lane groups' parts of four columns become one column each: 32 lanes, then 16 lanes change places
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                swap_halves(m[e], m[e + 2]);
+                swap_halves(d[e], d[e + 2]);
+                md_merge(m[e], d[e], m[e + 2], d[e + 2]);
+                if (SUMZ) { swap_halves(z[e], z[e + 2]); z[e] += z[e + 2]; }
+            }
+            swap_rows(m[0], m[1]);
+            swap_rows(d[0], d[1]);
+            md_merge(m[0], d[0], m[1], d[1]);
+            md_merge(run_m[q], run_d[q], m[0], d[0]);
+            if (SUMZ) { swap_rows(z[0], z[1]); run_z[q] += z[0] + z[1]; }
         }
         pp.tile_end();
     }
