@@ -1557,6 +1557,8 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_tile_ping_kernel<TileTall>, TileTall::kLdsBytes)) return false;
     if (!allow_big_lds(grad_tile_ping_kernel<TileSquare>, TileSquare::kLdsBytes)) return false;
     if (!allow_big_lds(grad_tile_counted_kernel, TileTall::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_kernel<false, false>, TileBig::kLdsBytes)) return false;
+    if (!allow_big_lds(lse_partial_kernel<true, false>, TileBig::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, true>, TileBig::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<false, false, TileSmall>, TileSmall::kLdsBytes)) return false;
     if (!allow_big_lds(lse_partial_kernel<true, false, TileSmall>, TileSmall::kLdsBytes)) return false;
@@ -1771,22 +1773,29 @@ static int forward_impl(const void* hidden, const void* weight, const int32_t* l
         if (fp8_in)
             hipLaunchKernelGGL((lse_partial_kernel<false, true>), dim3(grid), dim3(kThreads), TileBig::kLdsBytes, stream,
                                hidden, weight, (int)N, (int)D, (int)V, p.TT, p.VT, p.S, partials, sumz, tile_fp8, fwd_perm, clear, rows_splits);
-        else if (p.small_tiles && smooth)
-            hipLaunchKernelGGL((lse_partial_kernel<true, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
-        else if (p.small_tiles)
-            hipLaunchKernelGGL((lse_partial_kernel<false, false, TileSmall>), dim3(p.fwd_tt() * S), dim3(kThreads), TileSmall::kLdsBytes, stream,
-                               hidden, weight, (int)N, (int)D, (int)V, p.fwd_tt(), p.fwd_vt(), S, partials, sumz, fp8, fwd_perm, clear, rows_splits);
         else {
-#define CCE_LAUNCH_FORWARD(SUMZ, CFG) \
-    hipLaunchKernelGGL((lse_partial_ping_kernel<SUMZ, CFG>), dim3(grid), dim3(kThreads), CFG::kLdsBytes, stream, \
-                       hidden, weight, (int)N, (int)D, (int)V, p.TT, p.S, partials, sumz, fwd_perm, clear, rows_splits)
-            const bool tall = tall_forward_tiles(V, p.S);
-            if (smooth && tall) CCE_LAUNCH_FORWARD(true, TileTall);
-            else if (smooth) CCE_LAUNCH_FORWARD(true, TileSquare);
-            else if (tall) CCE_LAUNCH_FORWARD(false, TileTall);
-            else CCE_LAUNCH_FORWARD(false, TileSquare);
+#define CCE_LAUNCH_FORWARD(CFG, WORK, TOKEN_TILES, VOCAB_TILES) \
+    do { \
+        if (smooth) hipLaunchKernelGGL((lse_partial_kernel<true, false, CFG>), dim3(WORK), dim3(kThreads), CFG::kLdsBytes, stream, \
+                                       hidden, weight, (int)N, (int)D, (int)V, TOKEN_TILES, VOCAB_TILES, S, partials, sumz, fp8, fwd_perm, clear, rows_splits); \
+        else hipLaunchKernelGGL((lse_partial_kernel<false, false, CFG>), dim3(WORK), dim3(kThreads), CFG::kLdsBytes, stream, \
+                                hidden, weight, (int)N, (int)D, (int)V, TOKEN_TILES, VOCAB_TILES, S, partials, sumz, fp8, fwd_perm, clear, rows_splits); \
+    } while (0)
+#define CCE_LAUNCH_PING_FORWARD(CFG) \
+    do { \
+        if (smooth) hipLaunchKernelGGL((lse_partial_ping_kernel<true, CFG>), dim3(grid), dim3(kThreads), CFG::kLdsBytes, stream, \
+                                       hidden, weight, (int)N, (int)D, (int)V, p.TT, S, partials, sumz, fwd_perm, clear, rows_splits); \
+        else hipLaunchKernelGGL((lse_partial_ping_kernel<false, CFG>), dim3(grid), dim3(kThreads), CFG::kLdsBytes, stream, \
+                                hidden, weight, (int)N, (int)D, (int)V, p.TT, S, partials, sumz, fwd_perm, clear, rows_splits); \
+    } while (0)
+            switch (forward_tile(p, D)) {
+                case kForwardSmall: CCE_LAUNCH_FORWARD(TileSmall, p.fwd_tt() * S, p.fwd_tt(), p.fwd_vt()); break;
+                case kForwardBig: CCE_LAUNCH_FORWARD(TileBig, grid, p.TT, p.VT); break;
+                case kForwardSquare: CCE_LAUNCH_PING_FORWARD(TileSquare); break;
+                case kForwardTall: CCE_LAUNCH_PING_FORWARD(TileTall); break;
+            }
 #undef CCE_LAUNCH_FORWARD
+#undef CCE_LAUNCH_PING_FORWARD
         }
     }
     hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream,

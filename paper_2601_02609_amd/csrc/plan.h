@@ -47,11 +47,6 @@ static bool use_small_tiles(int64_t row_tiles, int64_t vocab_tiles) {
     return row_tiles * vocab_tiles * 2 <= device_cu_count();
 }
 
-// Tiles of a forward whose vocabulary lies in S splits: 384 x 256 (true) or 256 x 256, see PingTile.  Either cuts a split at half tiles.
-static bool tall_forward_tiles(int64_t V, int64_t S) {
-    const int64_t tall = (V + 191) / 192, square = (V + 127) / 128;
-    return (double)((tall + S - 1) / S) * 192.0 * 0.92 <= (double)((square + S - 1) / S) * 128.0;
-}
 struct Plan {
     int TT, VT, S;              // forward: token tiles, vocabulary tiles, vocabulary splits
     int64_t Nb, Vc;             // backward: rows per row block, vocabulary columns per chunk (multiples of 256)
@@ -590,6 +585,33 @@ struct ForwardCost {
         return (double)(rounds * ((p.VT + p.S - 1) / p.S)) * ((double)(D / 64) * 1.55 + 4.0);
     }
 };
+
+// Tiles of a bf16 forward beyond the 128 x 128 ones: TileBig's 256 x 256 loop, or 256 x 256 or 384 x 256 outputs by two
+// groups of wavefronts (PingTile), whichever is rated fastest.  A workgroup walks a split of the vocabulary, of whole tiles (TileBig)
+// or cut at half tiles, whose last half tile brings fewer products but the loads and the epilogue of a whole one: 0.65 of its slices.
+// Fitted to 399 forwards of 200 to 32768 rows, D 64 to 4096, V 1000 to 151936, in each of the three forms (3.7 % standard
+// deviation): a slice takes longer the more of the compute units are busy, TileBig's most (power), and an epilogue costs two or three
+// slices.  So TileBig has launches that leave units idle and those of few slices and tiles to a workgroup, the taller tiles long
+// ones; TileBig's 1.5 % are the error of the rating (390 other forwards: 1.9 % faster than on TileBig on average and none over 2 %
+// slower beyond the noise; without them 17, by up to 7 %).  us of TileBig / square / tall: 13265 x 64 x 10636 44.8 / 48.2 / 48.7,
+// 903 x 768 x 9581 (152 workgroups of one tile) 22.1 / 24.0 / 31.3, 4606 x 1664 x 6680 90.1 / 84.7 / 97.6, 16384 x 2048 x 151936
+// 7983 / 7576 / 6977.  (Rows that are counted on the device: by the splits of all rows; those calls are long, and the taller
+// tiles theirs.)
+enum ForwardTile { kForwardSmall, kForwardBig, kForwardSquare, kForwardTall };
+static ForwardTile forward_tile(const Plan& p, int64_t D) {
+    if (p.small_tiles) return kForwardSmall;
+    const int cus = device_cu_count();
+    const int64_t work = (int64_t)p.TT * p.S, rounds = (work + cus - 1) / cus;
+    const double busy = (double)work / (double)(rounds * cus), slices = (double)(D / 64);
+    auto halves = [&](int64_t unit) { return ((p.cols + unit - 1) / unit + p.S - 1) / p.S; };       // half tiles of the longest split
+    auto us = [&](double launch, double round, double tile, double slice, double slice_busy, int64_t half) {
+        const double products = (double)(half / 2) + 0.65 * (double)(half % 2);
+        return launch + (double)rounds * (round + (double)((half + 1) / 2) * tile + products * slices * (slice + slice_busy * busy));
+    };
+    const double big = 0.985 * us(5.1, 1.8, 2.33, 0.56, 0.89, 2 * ((p.VT + p.S - 1) / p.S));
+    const double square = us(5.2, 2.4, 2.5, 0.75, 0.63, halves(128)), tall = us(6.7, 2.5, 3.7, 1.12, 0.78, halves(192));
+    return tall <= square && tall <= big ? kForwardTall : square < big ? kForwardSquare : kForwardBig;
+}
 
 // Row blocks from the last to the first with dHidden's front rows as scratch: the partition of the
 // row tiles with the least modelled time (f(R) = min over a of [block of rows R - a .. R] + f(R - a)).

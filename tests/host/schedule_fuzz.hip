@@ -15,6 +15,7 @@ namespace cce { thread_local int g_last_hip_error = 0; }
 static long priced = 0;
 #define CCE_PLAN_PRICED() ((void)++priced)
 #include "../../paper_2601_02609_amd/csrc/plan.h"
+#include "../../paper_2601_02609_amd/csrc/wg_map.h"
 
 using namespace cce;
 
@@ -212,6 +213,20 @@ static void check_planning_cost() {
         }
 }
 
+// The gradient tiles of a call, launch by launch: 384 x 256 ones, 256 x 256 ones, and of the taller ones those whose last
+// tile crosses the end of the vocabulary or lies wholly behind it.
+struct TileCounts {
+    int tall = 0, square = 0, crossing = 0, behind = 0;
+    void launch(int64_t row_tiles, int64_t v0, int64_t v_tiles, int64_t D, int64_t V) {
+        if (use_small_tiles(row_tiles, v_tiles)) return;
+        if (!tall_grad_tiles((int)row_tiles, (int)v_tiles, (int)D, device_cu_count())) { ++square; return; }
+        const int64_t last = v0 + ((v_tiles * 256 + 383) / 384 - 1) * 384;       // first column of the last tile
+        ++tall;
+        crossing += last < V && last + 384 > V;
+        behind += last >= V;
+    }
+};
+
 // What a call runs, as one line of "word=number": rows N of which B = 0 (all) or M take part.
 static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free) {
     Plan p; Schedule s;
@@ -223,6 +238,7 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
     plan_backward(&p, rows, D, V, compact, dw_free, workspace_to_ask_for(asked, N, D, V, compact), &s);
     int chunks = 0, in_dw = 0, part_steps = 0, least_h = 1 << 30, most_h = 0, most_w = 0, sums_dh = 0, chunks_dh = 0, small = 0, steps = 0, same_tiles = 0, paired = 0, most_rows = 0;
     const int64_t dt = (D + gemm_tile_of_kind(s.kind).bn - 1) / gemm_tile_of_kind(s.kind).bn;
+    TileCounts tiles;
     if (s.use) {
         for (int64_t v = 0; v < V; ++chunks) {
             const ScheduleChunk c = schedule_chunk(s, D, V - v);
@@ -233,6 +249,7 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
             part_steps += c.rows < s.a ? 1 : 0;
             for (int64_t r = 0; r < p.TT; r += c.rows) {            // (steps of the first block's sizes)
                 const int64_t t = p.TT - r < c.rows ? p.TT - r : c.rows, tw = (t + s.split_w - 1) / s.split_w;
+                if (r < s.a) tiles.launch(t, v, c.b, D, V);
                 const int plain = contraction_kind(s.kind, D, t * nh * dt, kh * 4, v > 0, s.split_acc != 0, c.b * ((t + tw - 1) / tw) * dt, tw * 4,
                                                    r > 0 || !dw_free, false, Knobs::read());
                 const int kind = counted_contraction_kind(s.kind, D, t, c.b, dt, v > 0, r > 0 || !dw_free, Knobs::read());
@@ -248,14 +265,25 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
     } else {
         least_h = most_h = most_w = 1;
         for (int i = 0; i < s.n_blocks; ++i) { sums_dh += s.blocks[i].acc_in_dh; chunks_dh += s.blocks[i].g_in_dh; }
+        const int n = s.n_blocks ? s.n_blocks : 1;
+        for (int i = 0; i < n; ++i) {
+            const int64_t a = s.n_blocks ? s.blocks[i].a : p.Nb / 256 < p.TT ? p.Nb / 256 : p.TT, b = s.n_blocks ? s.blocks[i].b : p.Vc / 256;
+            for (int64_t v = 0; v < p.VT; v += b) tiles.launch(a, v * 256, p.VT - v < b ? p.VT - v : b, D, V);
+        }
     }
+    const ForwardTile fwd = forward_tile(p, D);
+    const int64_t unit = fwd == kForwardTall ? 192 : 128, units = (V + unit - 1) / unit;
+    int halves = 0;                          // splits that end in a half tile
+    for (int64_t i = 0; (fwd == kForwardTall || fwd == kForwardSquare) && i < p.S; ++i) halves += (int)(((i + 1) * units / p.S - i * units / p.S) % 2);
     printf("schedule=%d chunks=%d in_dw=%d row_parts=%d parts_h=%d least_parts_h=%d parts_w=%d split_sums=%d row_blocks=%d "
            "dhidden_blocks=%d sums_in_dhidden=%d chunks_in_dhidden=%d small_tiles=%d paired=%d paired_row_tiles=%d forward_skip=%d forward_skip_fp8=%d "
-           "backward_skip=%d backward_skip_fp8=%d same_tiles=%d\n",
+           "backward_skip=%d backward_skip_fp8=%d same_tiles=%d forward_big=%d forward_square=%d forward_tall=%d forward_halves=%d "
+           "tall=%d square=%d tall_crossing=%d tall_behind=%d tall_mapped=%d\n",
            (int)s.use, chunks, in_dw, part_steps, most_h, least_h, most_w, s.use ? s.split_acc : 0, s.use ? (p.TT + s.a - 1) / s.a : 0,
            s.n_blocks, sums_dh, chunks_dh, small, paired, most_rows, (int)forward_skip(p, D, false).use, (int)(D % 128 == 0 && forward_skip(p, D, true).use),
            (int)(!compact && backward_skip(p, s, D, false).use), (int)(!compact && D % 128 == 0 && backward_skip(p, s, D, true).use),
-           (int)(steps > 0 && same_tiles == steps));
+           (int)(steps > 0 && same_tiles == steps), (int)(fwd == kForwardBig), (int)(fwd == kForwardSquare), (int)(fwd == kForwardTall), halves,
+           tiles.tall, tiles.square, tiles.crossing, tiles.behind, compact && !s.use ? tiles.tall : 0);    // (a schedule gathers the rows)
 }
 
 // The label scan in front of a forward that leaves ignored rows out is one workgroup, 0.4 ns a row: it has to be small beside the forward.

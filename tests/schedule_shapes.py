@@ -53,6 +53,30 @@ COUNTED = {
     (2100, 4096, 70001): dict(forward=dict(forward_skip=1)),
 }
 
+# logit tiles: forward_big / forward_square / forward_tall (the loop of 256 x 256 tiles, 256 x 256 and 384 x 256 tiles of two groups of
+# wavefronts), forward_halves splits that end in half a tile; tall / square launches of gradient tiles of 384 / 256 columns, tall_crossing /
+# tall_behind those whose last tile crosses / lies behind the end of the vocabulary, tall_mapped through a row map.  A quarter of the rows ignored
+LOGIT_TILES = {
+    (924, 320, 95232): dict(rows=dict(forward_tall=1, tall=2)),                            # 248 tiles of 384
+    (1180, 256, 74497): dict(rows=dict(forward_tall=1, forward_halves=3)),                 # one column behind 194
+    (257, 640, 92736): dict(rows=dict(forward_tall=1, forward_halves=1)),                  # half a tile behind 241
+    (924, 256, 95999): dict(rows=dict(forward_tall=1, forward_halves=4, tall=1)),          # one column short of 250
+    (4865, 128, 34176): dict(rows=dict(forward_tall=1, forward_halves=10)),                # two K slices
+    (4352, 128, 147584): dict(compact=dict(forward_tall=1, forward_halves=11, tall=18, tall_behind=1)),
+    (4352, 320, 23552): dict(rows=dict(forward_tall=1, forward_halves=11, tall=5, tall_crossing=1)),
+    (4865, 320, 28031): dict(rows=dict(forward_tall=1, forward_halves=2, tall=7, tall_behind=1)),
+    (412, 64, 34049): dict(rows=dict(forward_big=1, tall_behind=1)),                       # one K slice
+    (3484, 512, 6401): dict(compact=dict(tall_mapped=1, tall_behind=1)),
+    (7425, 704, 6272): dict(compact=dict(tall_mapped=1, tall_crossing=1)),
+    (668, 896, 42752): dict(rows=dict(forward_square=1, forward_halves=2, square=2)),      # 167 tiles of 256
+    (412, 2112, 30721): dict(rows=dict(forward_square=1, forward_halves=1, square=1),      # one column behind 120
+                             compact=dict(forward_square=1, forward_halves=1, square=1)),
+    (257, 1856, 32640): dict(rows=dict(forward_square=1, forward_halves=1, square=1)),     # half a tile behind 127
+    (257, 1408, 32511): dict(rows=dict(forward_square=1, square=1)),                       # one column short of that
+    (903, 768, 9581): dict(rows=dict(forward_big=1)),                                      # one tile to a workgroup, units idle
+    (1281, 192, 11713): dict(rows=dict(forward_big=1, tall=1, tall_crossing=1), compact=dict(forward_big=1)),
+}
+
 
 def n_ignored(N, against_forced=False):
     return N // 7 if against_forced else int(round(0.2 * N))

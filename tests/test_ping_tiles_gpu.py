@@ -1,6 +1,8 @@
-"""GPU parity at the edges of the tiles of two groups of wavefronts (384 x 256 and 256 x 256, see PingTile in
-csrc/gemm_core.h): vocabularies that end on, in front of and behind a tile, half a tile and a chunk's last tile, row counts
-around a tile, one K slice, with and without label smoothing and row skipping.  Oracle and tolerances as in test_parity_gpu.py."""
+"""GPU parity with the oracle where vocabularies end on, in front of and behind a tile, half a tile and a chunk's last tile, row
+counts around a tile, one K slice, with and without label smoothing and row skipping.  Launches this small run their forwards on
+the loop of 256 x 256 tiles and nearly all of their gradient tiles on 256 x 256 ones of two groups of wavefronts (see PingTile in
+csrc/gemm_core.h); the edges of the 384 x 256 ones, and of forwards on either: test_logit_tiles_gpu.py.  Oracle and tolerances as in
+test_parity_gpu.py."""
 import numpy as np
 import pytest
 import torch

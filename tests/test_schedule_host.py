@@ -67,6 +67,14 @@ def test_counted_shapes_take_the_routes_they_are_listed_for(fuzz):
         assert not short, (call, form, short, got)
 
 
+def test_logit_tiles_are_those_they_are_listed_for(fuzz):
+    calls, wanted = zip(*[((N, D, V, N - N // 4 if form == "compact" else 0, 1), (form, want))
+                          for (N, D, V), forms in S.LOGIT_TILES.items() for form, want in forms.items()])
+    for call, (form, want), got in zip(calls, wanted, orders(fuzz, calls)):
+        short = {k: (got[k], v) for k, v in want.items() if got[k] < v}
+        assert not short, (call, form, short, got)
+
+
 def test_drawn_calls_meet_the_orders(fuzz):
     """More than half of the calls of test_random_schedules leave the plan's own tiling, and every kind of order is among them."""
     calls = []
