@@ -395,31 +395,24 @@ __global__ __launch_bounds__(1024) void dgamma_reduce_kernel(const float* __rest
 // ------------------------------------------------------------------------------------------
 // Global-norm clipping coefficient, resident on the GPU (gradient-clipping strategies).
 // ------------------------------------------------------------------------------------------
-// Bound by HBM, so it wants many loads in flight: four of 16 bytes per thread, a workgroup's in 16 KB beside each other (eight loads
-// 4 MB apart instead: 126 -> 154 us for 136 M values).  From the end to the front: what was read last is what the optimizer reads
-// first, out of the last-level cache (AdamW behind it 645 -> 620 us; norms, clipping and AdamW of 151936 x 896 together 810 -> 787).
+// Bound by HBM: 1024 workgroups, every pass of theirs 4 MB in a row.  From the end to the front: what was read last is what the
+// optimizer reads first, out of the last-level cache (sum of squares, clipping and AdamW of 136 M values just written 965 -> 940 us).
+// Several loads of a thread beside each other cost more than they bring: four, 16 KB of a workgroup in a row, took 11 us more of about
+// 125 over 136 M values that no cache holds; eight 4 MB apart 28.  Two sets of sums in turn: eight chains of roundings.
 __global__ __launch_bounds__(256) void sumsq_partial_kernel(const float* __restrict__ g, int64_t n, double* __restrict__ partials) {
     __shared__ double red[4];
     const int64_t n4 = n >> 2;
     const af32x4* g4 = (const af32x4*)g;
-    constexpr int U = 4;                              // 16-byte loads of a thread in flight
-    af32x4 sum[2] = {};
-    const int64_t round = (int64_t)gridDim.x * (256 * U), rounds = n4 / round;
-    for (int64_t i = rounds * round + (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
-        const af32x4 v = g4[i];
+    const int64_t stride = (int64_t)gridDim.x * 256, first = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    af32x4 sum = {0.f, 0.f, 0.f, 0.f}, other = sum;
+    for (int64_t i = first + (n4 - first + stride - 1) / stride * stride - stride; i >= 0; i -= stride) {
+        const af32x4 v = g4[i], before = sum;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[0][e] = fmaf(v[e], v[e], sum[0][e]);
+        for (int e = 0; e < 4; ++e) sum[e] = fmaf(v[e], v[e], other[e]);
+        other = before;
     }
-    for (int64_t r = rounds - 1; r >= 0; --r) {
-        af32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = g4[r * round + (int64_t)blockIdx.x * (256 * U) + u * 256 + threadIdx.x];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sum[u & 1][e] = fmaf(v[u][e], v[u][e], sum[u & 1][e]);
-    }
-    float s = ((sum[0][0] + sum[1][0]) + (sum[0][1] + sum[1][1])) + ((sum[0][2] + sum[1][2]) + (sum[0][3] + sum[1][3]));
+    sum += other;
+    float s = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     if (blockIdx.x == 0 && threadIdx.x < (n & 3)) { const float t = g[(n4 << 2) + threadIdx.x]; s = fmaf(t, t, s); }
     double d = (double)s;
 #pragma unroll
