@@ -886,6 +886,7 @@ __global__ __launch_bounds__(TileTall::kThreads, 2) void grad_tile_counted_kerne
         uint16_t* __restrict__ G, uint32_t panel, int panel_shift, int v_off, int V_total,
         const int32_t* __restrict__ perm, const int32_t* __restrict__ count, int first_row, int cus) {
     N = rows_left(count, first_row, N);
+    if (N <= 0) return;
     const int n_row_tiles = (N + 255) / 256;
     if (count[1]) {                                   // every row takes part: no lookup in front of the first slice
         H = (const char*)H + (size_t)first_row * ((size_t)D * 2);
