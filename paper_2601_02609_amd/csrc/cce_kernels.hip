@@ -219,8 +219,9 @@ __device__ __forceinline__ void swap_rows(float& a, float& b) {
     b = __uint_as_float((uint32_t)s[1]);
 }
 
-// The same on tiles of two groups of wavefronts (see PingTile), bf16 operands.  The vocabulary split is cut at multiples of half
-// a tile's rows (a last half tile costs half), and a workgroup's slices follow each other without a gap: the first slice of a
+// The same on tiles of two groups of wavefronts (see PingTile), bf16 operands, where that is faster (forward_tile).  The vocabulary
+// split is cut at multiples of half a tile's rows (a last half tile saves a third of its slices' time: half of the products and of A's
+// fragments, none of the loads nor of the epilogue), and a workgroup's slices follow each other without a gap: the first slice of a
 // vocabulary tile is requested in front of the last products of the one before.  A token column lies in four lane groups: each
 // keeps the (max, sum) of a quarter of the columns.  A tile's parts are formed in each lane by itself and get to those groups by
 // lanes that change places, 12 instructions a tile without LDS: a common maximum by 32 shuffles through LDS in front of the

@@ -611,7 +611,8 @@ __device__ __forceinline__ void gemm_mainloop_fp8(f32x16 (&acc)[Cfg::TM][Cfg::TN
 // multiplies, the other reads its next fragments from LDS and requests the next slice, a barrier at every turn.  A
 // wavefront owns NA x NB blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16: lane l holds column l % 16, rows 4 (l / 16) + 0 .. 3),
 // 4 x 2 wavefronts a tile of 64 NA x 32 NB.  Fragments need no second buffer (the other group's products hide their
-// latency), which leaves the registers for 384 x 256 outputs: a sixth fewer operand bytes per product than 256 x 256 from
+// latency), which leaves the registers for 384 x 256 outputs (gradient tiles 252; the forward all 256 and 13 values of a lane in
+// scratch, 17 with label smoothing, of which it fetches ten and writes one to three a tile, none in a slice): a sixth fewer operand bytes per product than 256 x 256 from
 // L2, a fifth fewer from LDS, and the 16 x 16 form draws less power than the 32 x 32 one, whose smaller number of
 // instructions the turns make up for.  What bounds it is power: 18432 x 8192 x 4096 in one launch after the other, random /
 // constant operands, TFLOP/s: TileBig's loop 1 400 / 1 920; these turns with 32 x 32 x 16 at 256 x 256 1 425 / 2 015, at

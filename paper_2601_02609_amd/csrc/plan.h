@@ -39,7 +39,7 @@ static int device_cu_count() {
 }
 
 
-// Logit tiles of 128 x 128 instead of 256 x 256: where a launch has so few of the large ones that four
+// Logit tiles of 128 x 128 instead of 256 x 256 (TileBig's loop): where a launch has so few of the large ones that four
 // times as many small ones are at most two rounds of the compute units.  One round: 322 x 1856 x 1015
 // (8 large tiles) 102.8 -> 58.2 us a step; two: forward / backward of 500 x 2048 x 10000 (80) 47 / 101 ->
 // 42 / 93 us, of 3399 x 1088 x 1802 (112) 33 / 76 -> 31 / 72.  Beyond, the large tiles move half the bytes.
@@ -180,7 +180,7 @@ static bool small_contractions(int kind, int64_t items, const Knobs& knobs) {
 // One compute unit runs one workgroup at a time.  Measured on MI355X with random bf16 data:
 // a 256 x 256 x 64 slice of the main loop takes about 2 us, a 256 x 128 x 64 one about 1.1 us;
 // a gradient-tile workgroup adds about 9 us (pipeline fill, softmax epilogue, store of the
-// tile), a contraction workgroup about 4 us.
+// tile), a contraction workgroup about 4 us.  (bf16 gradient tiles of two wavefront groups take less: see ScheduleModel::logit_tile.)
 struct BackwardModel {
     int cus; int64_t D; GemmTile tile;
     double t_tile() const { return (double)(D / 64) * 2.0 + 9.0; }
@@ -499,6 +499,8 @@ struct ScheduleModel {
         if (kind) *kind = tile.kind;
         return us;
     }
+    // (The loop of FP8 tiles and of bf16 ones before those of two wavefront groups, which take 5 - 15 % less, up to 30 % where the taller
+    // ones fill the rounds better, see tall_grad_tiles: the orders stay those that were measured with it.)
     double logit_tile() const { return (double)(D / 64) * 1.55 + 7.0; }
     // One step over a x b tiles.  FLOOR: with makespan_floor.
     template <bool FLOOR = false>
@@ -572,7 +574,7 @@ static int counted_contraction_kind(int kind, int64_t D, int64_t a, int64_t b, i
     return paired <= single ? 3 : kind;
 }
 
-// The forward under the same constants: rounds of workgroups that walk their vocabulary tiles, or of one
+// The forward under the same constants, to compare calls with and without row skipping (what its tiles take: forward_tile): rounds of workgroups that walk their vocabulary tiles, or of one
 // small tile each (500 x 2048 x 10000, two rounds of 32 slices: 42 us).
 struct ForwardCost {
     int cus; int64_t D;
@@ -592,8 +594,8 @@ struct ForwardCost {
 // Fitted to 399 forwards of 200 to 32768 rows, D 64 to 4096, V 1000 to 151936, in each of the three forms (3.7 % standard
 // deviation): a slice takes longer the more of the compute units are busy, TileBig's most (power), and an epilogue costs two or three
 // slices.  So TileBig has launches that leave units idle and those of few slices and tiles to a workgroup, the taller tiles long
-// ones; TileBig's 1.5 % are the error of the rating (390 other forwards: 1.9 % faster than on TileBig on average and none over 2 %
-// slower beyond the noise; without them 17, by up to 7 %).  us of TileBig / square / tall: 13265 x 64 x 10636 44.8 / 48.2 / 48.7,
+// ones; TileBig's 1.5 % are the error of the rating (640 other forwards: 1.9 - 2.7 % faster than on TileBig on average and up to
+// 2.5 % slower; without them up to 7 %).  us of TileBig / square / tall: 13265 x 64 x 10636 44.8 / 48.2 / 48.7,
 // 903 x 768 x 9581 (152 workgroups of one tile) 22.1 / 24.0 / 31.3, 4606 x 1664 x 6680 90.1 / 84.7 / 97.6, 16384 x 2048 x 151936
 // 7983 / 7576 / 6977.  (Rows that are counted on the device: by the splits of all rows; those calls are long, and the taller
 // tiles theirs.)
@@ -701,7 +703,7 @@ struct RowBlockPlanner {
 // A forward over all rows that leaves the ignored ones out: their number is found on the device, so the launch has the
 // workgroups of all rows and those beyond the rows that take part return at once; from the plan's partials on (the plan's own
 // are not needed then) lie the row map, the counts, FP8 scales in the order of those rows, and the partials: 256 per workgroup.
-// Taken from about 1 ms of forward on (1.15 PFLOP/s): 8192 x 896 x 151936 with 15 % ignored 1.87 -> 1.63 ms, 4099 x 2048 x 128256
+// Taken from about 1 ms of forward on (1.15 PFLOP/s, what 256 x 256 tiles of one loop reach; the taller tiles 5 - 13 % more): 8192 x 896 x 151936 with 15 % ignored 1.87 -> 1.63 ms, 4099 x 2048 x 128256
 // with 5 % 1.76 -> 1.68, 3000 x 2048 x 151936 with 25 % 1.59 -> 1.23, none ignored 1.591 -> 1.599.
 // The label scan is one workgroup: 4 us and 0.4 ns a row (131072 rows 55 us, a million 406), paid also where nothing is ignored.
 // It may take a fiftieth of the forward, whose products run at a rate that falls with D (2 N V (0.75 D + 72) fs: 131072 x 64 x 70000

@@ -67,7 +67,10 @@ __host__ __device__ __forceinline__ void group_map(int lin, int n_i, int n_j, in
 }
 
 // Gradient tiles of a launch over row_tiles x vocab_tiles (of 256 x 256): 384 x 256 (true) or 256 x 256, see PingTile, one to a
-// compute unit.  Thousandths of a microsecond per round: 1.96 / 1.42 a slice, 8 / 6 beside them (14 slices: 38.6 / 27.4 us measured).
+// compute unit.  Thousandths of a microsecond per round: 1.96 / 1.42 a slice, 8 / 6 beside them.  What decides is the ratio of two
+// rounds, 1.34 - 1.38 here; measured 1.3 - 1.45, less where the last round is full.  Of 80 launches (D 64 to 3584, 8 to 32 row tiles,
+// 12 to 64 vocabulary tiles) it picks the faster form of 79, at D = 64 once one that takes 3.5 % longer.  28 x 40 tiles at D = 896:
+// three rounds of 37.8 us or five of 26.1, rated 35.4 and 25.9.
 __host__ __device__ __forceinline__ bool tall_grad_tiles(int row_tiles, int vocab_tiles, int D, int cus) {
     const int slices = D / 64, tall_tiles = row_tiles * ((vocab_tiles * 2 + 2) / 3), square_tiles = row_tiles * vocab_tiles;
     const int64_t tall = (int64_t)((tall_tiles + cus - 1) / cus) * (slices * 1960 + 8000);
