@@ -592,7 +592,7 @@ struct ForwardCost {
 // groups of wavefronts (PingTile), whichever is rated fastest.  A workgroup walks a split of the vocabulary, of whole tiles (TileBig)
 // or cut at half tiles, whose last half tile brings fewer products but the loads and the epilogue of a whole one: 0.65 of its slices.
 // Fitted to 399 forwards of 200 to 32768 rows, D 64 to 4096, V 1000 to 151936, in each of the three forms (3.7 % standard
-// deviation): a slice takes longer the more of the compute units are busy, TileBig's most (power), and an epilogue costs two or three
+// deviation): a slice takes longer the more of the compute units are busy, TileBig's most (power), and an epilogue costs about two
 // slices.  So TileBig has launches that leave units idle and those of few slices and tiles to a workgroup, the taller tiles long
 // ones; TileBig's 1.5 % are the error of the rating (640 other forwards: 1.9 - 2.7 % faster than on TileBig on average and up to
 // 2.5 % slower; without them up to 7 %).  us of TileBig / square / tall: 13265 x 64 x 10636 44.8 / 48.2 / 48.7,
