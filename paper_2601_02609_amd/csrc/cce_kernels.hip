@@ -922,6 +922,10 @@ static_assert(counted_table_bytes<TileDuo>() % 512 == 0 && counted_table_bytes<T
 // Row skipping: the LDS table of one row block's row map (kRowTableBytes, plan.h) sits behind these.
 static_assert(kGemmLdsNarrow + kRowTableBytes <= 160 * 1024 && kGemmLdsBig + kRowTableBytes <= 160 * 1024 && kGemmLdsSmall + kRowTableBytes <= 160 * 1024, "row table must fit the LDS");
 
+// Tiles of two wavefront groups: the row table has room for the entries that a loop looks up behind its last slice, without use.
+constexpr int kTurnTableBytes = kRowTableBytes + 128;
+static_assert(TurnTile::kLdsBytes + kTurnTableBytes <= 160 * 1024, "row table must fit the LDS");
+
 // Output of a job, one of three forms:
 //   fp32 (the dW job): out_f32 (+)= C when `beta`.
 //   fp32 running sum + bf16 result (the dH job): out_f32 is a workspace accumulator over the
@@ -1200,18 +1204,205 @@ __device__ __forceinline__ void run_gemm_job(const GemmJob& j, int item, int row
     store_result<Cfg, A_KMAJOR, MODE>(acc, j, out_f32, beta, mi, ni, COUNTED && A_KMAJOR ? rows : j.m_valid, smem);
 }
 
+// Result of a work item on tiles of two wavefront groups (TurnTile), straight from the accumulators.  A lane holds four columns of
+// a result row in every block: fp32 results and what they are added to move 16 bytes at a time, two blocks to a 128-byte line.  In
+// the 16-bit forms lanes of neighbouring 16 change places first, so that a lane has eight columns of one of two blocks: 16 bytes of
+// either plane, 64 in a row.  Old values are fetched half a block column ahead.
+template <bool A_KMAJOR, int MODE>
+__device__ __forceinline__ void store_turn_result(f32x4 (&acc)[TurnTile::NA][TurnTile::NB], const GemmJob& j, float* out, bool beta, int row0, int col0, int m_valid, int wave) {
+    constexpr bool SPLIT = A_KMAJOR && (MODE & 1) != 0, ROWMAP = A_KMAJOR && (MODE & 6) != 0;
+    const int l = wave_lane(), lg = l >> 4;                     // (not from threadIdx: a register less over the loop)
+    const int col = col0 + (wave >> 2) * 128;                   // this wavefront's first column
+    row0 += (wave & 3) * 64 + (l & 15);             // this lane's row in block 0
+    const uint32_t ld = (uint32_t)j.ld_out;
+    const int pair_col = 16 * (lg & 1) + 4 * (lg & 2);          // 16-bit forms: this lane's eight columns of a pair of blocks
+    auto run = [&](auto pairs_tag) {
+        constexpr bool PAIRS = decltype(pairs_tag)::value;
+        // step (block column jb, half h): blocks 4 h ... 4 h + 3, 64 columns
+        f32x4 old[2][4];
+        int to[2] = {-1, -1};                                   // 16-bit forms: result row, by the block column's parity
+        auto fetch = [&](int set, int jb, int h) {
+            const int row = row0 + 16 * jb, c0 = col + 64 * h;
+            const bool ok = row < m_valid;
+            if (PAIRS && h == 0) to[jb & 1] = !ok ? -1 : ROWMAP ? j.row_map[row] : row;
+            if (!SPLIT && !beta) return;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) old[set][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (c0 >= j.n_valid) return;
+            if constexpr (SPLIT) {
+                // upper halves of pair i / 2 (old[0], old[2]), lower halves
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int c = c0 + 32 * (i >> 1) + pair_col;
+                    const uint16_t* p = (i & 1) ? j.out_lo + (size_t)row * ld + c : j.out_hi + (size_t)to[jb & 1] * ld + c;
+                    if (beta && to[jb & 1] >= 0) old[set][i] = *(const f32x4*)p;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int c = PAIRS ? c0 + 32 * (i >> 1) + pair_col + 4 * (i & 1) : c0 + 16 * i + 4 * lg;
+                    if (ok) old[set][i] = *(const f32x4*)(out + (size_t)row * ld + c);
+                }
+            }
+        };
+        fetch(0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < 2 * TurnTile::NB; ++s) {
+            const int jb = s >> 1, h = s & 1, set = s & 1;
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + 1 < 2 * TurnTile::NB) fetch(set ^ 1, (s + 1) >> 1, (s + 1) & 1);
+            const int row = row0 + 16 * jb, c0 = col + 64 * h;
+            const bool ok = row < m_valid;
+            if (c0 >= j.n_valid) continue;
+            if constexpr (!PAIRS) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    f32x4 v = acc[4 * h + i][jb];
+                    if (beta) v += old[set][i];
+                    if (ok) *(f32x4*)(out + (size_t)row * ld + c0 + 16 * i + 4 * lg) = v;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    float x[8];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        x[r] = acc[4 * h + 2 * i][jb][r];
+                        x[4 + r] = acc[4 * h + 2 * i + 1][jb][r];
+                        swap_rows(x[r], x[4 + r]);
+                    }
+                    const int c = c0 + 32 * i + pair_col, t = to[jb & 1];
+                    if constexpr (SPLIT) {
+                        const u32x4 hi = __builtin_bit_cast(u32x4, old[set][2 * i]), lo = __builtin_bit_cast(u32x4, old[set][2 * i + 1]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            x[2 * e] += __builtin_bit_cast(float, (hi[e] << 16) | (lo[e] & 0xffffu));
+                            x[2 * e + 1] += __builtin_bit_cast(float, (hi[e] & 0xffff0000u) | (lo[e] >> 16));
+                        }
+                    } else if (beta) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) x[e] += old[set][2 * i + (e >> 2)][e & 3];
+                    }
+                    if (!SPLIT || j.final) {
+                        union { __bf16 h[8]; u32x4 u; } cv;
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) cv.h[e] = (__bf16)x[e];
+                        uint16_t* const result = MODE == 9 ? j.out_lo : j.out_hi;
+                        if (t >= 0) *(u32x4*)(result + (size_t)t * ld + c) = cv.u;
+                    } else {
+                        u32x4 hi, lo;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const uint32_t bx = __builtin_bit_cast(uint32_t, x[2 * e]), by = __builtin_bit_cast(uint32_t, x[2 * e + 1]);
+                            hi[e] = (by & 0xffff0000u) | (bx >> 16);
+                            lo[e] = (by << 16) | (bx & 0xffffu);
+                        }
+                        if (t >= 0) *(u32x4*)(j.out_hi + (size_t)t * ld + c) = hi;
+                        if (ok) *(u32x4*)(j.out_lo + (size_t)row * ld + c) = lo;
+                    }
+                }
+            }
+        }
+    };
+    if (col >= j.n_valid) return;
+    if (A_KMAJOR && (SPLIT || j.final)) run(std::true_type{});
+    else if constexpr (!SPLIT) run(std::false_type{});
+}
+
+// One work item on such tiles (modes as for run_gemm_job).
+template <bool A_KMAJOR, int MODE>
+__device__ __forceinline__ void run_turn_item(const GemmJob& j, int item, int rows, CCE_LDS char* smem) {
+    typedef TurnTile Cfg;
+    constexpr bool COUNTED = (MODE & 8) != 0, KSPLIT = (MODE & 3) == 0 && !COUNTED;
+    int part = 0;
+    if (KSPLIT && j.n_split > 1) {
+        const int per = j.n_work / j.n_split;
+        part = item / per;
+        item -= part * per;
+    }
+    const int row0 = item / j.n_tiles * Cfg::BN, col0 = item % j.n_tiles * Cfg::BM;       // consecutive items share rows of the chunk
+    const int k0 = KSPLIT ? part * j.split_k : 0;
+    int k_rows = j.b_k_n - k0;                                  // rows of X that take part
+    if (KSPLIT && k_rows > j.split_k) k_rows = j.split_k;
+    if (COUNTED && !A_KMAJOR) k_rows = rows;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    float* const out_f32 = part == 0 ? j.out_f32 : j.part + (size_t)(part - 1) * j.part_stride;
+    const bool beta = part < j.beta_n;
+
+    constexpr int MAP = A_KMAJOR ? 0 : COUNTED ? 2 : (MODE & 2) != 0 ? 1 : 0;
+    const char* X = (const char*)j.B + (size_t)k0 * (size_t)(j.ldb * 2);
+    if constexpr (MAP == 1) {                                   // (see run_gemm_job)
+        CCE_LDS uint32_t* tab = (CCE_LDS uint32_t*)(smem + Cfg::kLdsBytes);
+        const int32_t some = __builtin_amdgcn_readfirstlane(j.row_map[-j.first_row]);
+        for (int i = threadIdx.x; i < j.k_total; i += kThreads) {
+            const int32_t row = i < j.b_k_n ? j.row_map[i] : -1;
+            tab[i] = some < 0 ? 0u : (uint32_t)(row < 0 ? some : row) * (uint32_t)(j.ldb * 2);
+        }
+        if (some < 0) X = j.zero_row;
+        __syncthreads();
+    }
+    if constexpr (MAP == 2) {                                   // (see run_gemm_job)
+        if (rows == 0) {                                        // none takes part: there is no chunk
+            if (!beta)
+                for (int i = threadIdx.x; i < Cfg::BN * 64; i += kThreads) {
+                    const int row = row0 + i / 64, col = col0 + i % 64 * 4;
+                    if (row < j.m_valid && col < j.n_valid) *(f32x4*)(out_f32 + (size_t)row * (uint32_t)j.ld_out + col) = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            return;
+        }
+        CCE_LDS uint16_t* tab = (CCE_LDS uint16_t*)(smem + Cfg::kLdsBytes);
+        constexpr int kQuads = kRowTableBytes / 2 / (4 * kThreads);
+        const int32_t last = j.row_map[rows > 0 ? rows - 1 : 0];
+        const int n = (rows + 255) / 256 * 256;
+        i32x4 m[kQuads];
+#pragma unroll
+        for (int u = 0; u < kQuads; ++u) {
+            const int i = 4 * (u * kThreads + (int)threadIdx.x);
+            if (i < n) m[u] = *(const i32x4*)(j.row_map + i);
+        }
+#pragma unroll
+        for (int u = 0; u < kQuads; ++u) {
+            const int i = 4 * (u * kThreads + (int)threadIdx.x);
+            if (i < n) {
+                const i32x4 v = m[u];
+                *(CCE_LDS u32x2*)(tab + i) = u32x2{(uint32_t)(v.x < 0 ? last : v.x) | (uint32_t)(v.y < 0 ? last : v.y) << 16,
+                                                   (uint32_t)(v.z < 0 ? last : v.z) | (uint32_t)(v.w < 0 ? last : v.w) << 16};
+            }
+        }
+        __syncthreads();
+    }
+    TurnLoop<A_KMAJOR, MAP> loop;
+    loop.init(smem, wave, X, (uint32_t)(j.ldb * 2), col0, j.n_valid, k_rows, j.A, j.panel, row0, k0);
+    if (MAP == 1) loop.kmap = (const CCE_LDS uint32_t*)(smem + Cfg::kLdsBytes);
+    if (MAP == 2) loop.kmap16 = (const CCE_LDS uint16_t*)(smem + Cfg::kLdsBytes);
+    __builtin_amdgcn_s_waitcnt(0x0f70);                         // vmcnt(0): see run_gemm_job
+    const int KT = loop.slices(k_rows);
+    if (col0 + 128 * loop.group >= j.n_valid) {                 // (its columns lie behind the matrix: loads and barriers only)
+        loop.idle(KT);
+        return;
+    }
+    f32x4 acc[Cfg::NA][Cfg::NB];
+#pragma unroll
+    for (int a = 0; a < Cfg::NA; ++a)
+#pragma unroll
+        for (int b = 0; b < Cfg::NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    loop.run(acc, KT);
+    store_turn_result<A_KMAJOR, MODE>(acc, j, out_f32, beta, row0, col0, COUNTED && A_KMAJOR ? rows : j.m_valid, wave);
+}
+
 template <class Cfg, int MODE>
 __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_gemm_kernel(const GemmJob first, const GemmJob second) {
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     CCE_LDS char* smem = (CCE_LDS char*)smem_generic;
     constexpr bool COUNTED = (MODE & 8) != 0;
+    constexpr int kRows = std::is_same<Cfg, TurnTile>::value ? 256 : Cfg::BM;        // result rows of an item
     int rows = 0, n1 = first.n_work, n2 = second.n_work;
     bool swapped = false;
     if constexpr (COUNTED) {
         // Items and reductions of the rows that take part: the dH job's items follow them, the dW job's reduction.
         rows = rows_left(first.count, first.first_row, first.rows);
         const int tiles = (rows + 255) / 256;
-        auto items = [&](const GemmJob& j) { return j.a_kmajor ? tiles * (256 / Cfg::BM) * j.n_tiles : (tiles == 0 && j.beta_n ? 0 : j.n_work); };
+        auto items = [&](const GemmJob& j) { return j.a_kmajor ? tiles * (256 / kRows) * j.n_tiles : (tiles == 0 && j.beta_n ? 0 : j.n_work); };
         auto length = [&](const GemmJob& j) { return j.a_kmajor ? j.k_total : tiles * 256; };
         swapped = length(first) < length(second);               // longer reduction first
         n1 = items(swapped ? second : first);
@@ -1223,13 +1414,18 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void grad_gemm_kernel(const GemmJ
     if (n1 >= 8 && n2 >= 8) {
         xcd_two_job_map(blockIdx.x, n1, n2, in_first, item);
     } else {
-        const int lin = xcd_round_id(blockIdx.x, n1 + n2, 2048 / Cfg::NW);
+        const int lin = xcd_round_id(blockIdx.x, n1 + n2, 131072 / Cfg::kThreads);
         in_first = lin < n1;
         item = in_first ? lin : lin - n1;
     }
     const GemmJob& j = in_first != swapped ? first : second;
-    if (j.a_kmajor) run_gemm_job<Cfg, true, MODE>(j, item, rows, smem);
-    else run_gemm_job<Cfg, false, (MODE & 10)>(j, item, rows, smem);
+    if constexpr (std::is_same<Cfg, TurnTile>::value) {
+        if (j.a_kmajor) run_turn_item<true, MODE>(j, item, rows, smem);
+        else run_turn_item<false, (MODE & 10)>(j, item, rows, smem);
+    } else {
+        if (j.a_kmajor) run_gemm_job<Cfg, true, MODE>(j, item, rows, smem);
+        else run_gemm_job<Cfg, false, (MODE & 10)>(j, item, rows, smem);
+    }
 }
 
 // E4M3 scale bytes of the rows that take part, in their order and the grouped layout (see ScaleGroup); one dword, i.e.
@@ -1587,6 +1783,12 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TileNarrow, 9>, kGemmLdsNarrow + kRowTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileSmall, 9>, kGemmLdsSmall + kRowTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TileDuo, 9>, kGemmLdsDuo + counted_table_bytes<TileDuo>())) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TurnTile, 0>, TurnTile::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TurnTile, 1>, TurnTile::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TurnTile, 2>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TurnTile, 3>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TurnTile, 4>, TurnTile::kLdsBytes)) return false;
+    if (!allow_big_lds(grad_gemm_kernel<TurnTile, 9>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
     done[dev] = true;
     return true;
 }
@@ -1616,10 +1818,28 @@ static void launch_grad_tiles(const void* H, const void* W, const int32_t* label
                            n_row_tiles, v0, n_v_tiles * 256, n_v_tiles, G, panel, panel_shift, v_off, V_total, perm);
 }
 
+// A launch on tiles of two wavefront groups: the jobs' items in those tiles.
+template <int MODE>
+static void launch_turn_contractions(GemmJob first, GemmJob second, hipStream_t stream) {
+    auto items = [&](GemmJob& j) {
+        j.n_tiles = (j.n_valid + TurnTile::BM - 1) / TurnTile::BM;
+        if (j.n_work > 0) j.n_work = (j.m_valid + TurnTile::BN - 1) / TurnTile::BN * j.n_tiles * j.n_split;
+    };
+    items(first);
+    items(second);
+    ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
+    hipLaunchKernelGGL((grad_gemm_kernel<TurnTile, MODE>), dim3(first.n_work + second.n_work), dim3(kThreads),
+                       TurnTile::kLdsBytes + ((MODE & 10) ? kTurnTableBytes : 0), stream, first, second);
+}
+
 // Both contractions of counted rows (mode 9), the row table behind the stages; tile: counted_contraction_kind.  (All of them
 // 256 x 128 one to a unit, backwards without ignored rows were 2.3 % behind those that do not look for them at
 // 5200 x 2048 x 65001, 4.5 % at 8192 x 512 x 140000, 5.8 % at 2527 x 3584 x 68330: 0.9, 0.8 and 0.4 so.)
-static void launch_counted_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+static void launch_counted_contractions(int kind, bool turn, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+    if (turn) {
+        launch_turn_contractions<9>(first, second, stream);
+        return;
+    }
     const int work = first.n_work + second.n_work;
     ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
     if (kind == 3)
@@ -1633,7 +1853,11 @@ static void launch_counted_contractions(int kind, const GemmJob& first, const Ge
 
 // A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
 template <int MODE>
-static void launch_contractions(int kind, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+static void launch_contractions(int kind, bool turn, const GemmJob& first, const GemmJob& second, hipStream_t stream) {
+    if (turn) {
+        launch_turn_contractions<MODE>(first, second, stream);
+        return;
+    }
     const int work = first.n_work + second.n_work;
     ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
     if (kind == 3)
@@ -1947,7 +2171,9 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 const int kind = counted ? counted_contraction_kind(sc.kind, D, row_tiles, v_tiles, d_tiles, planes_written > 0, dw_beta, knobs)
                                          : contraction_kind(sc.kind, D, (int64_t)row_tiles * n_split_h * d_tiles, kh * 4, planes_written > 0, sc.split_acc != 0,
                                                             (int64_t)v_tiles * n_split_w * d_tiles, kw * 4, dw_beta, false, knobs);
-                const int panel_shift = kind == 3 ? 5 : 6;                // log2 of the K slice of the contractions' tiles
+                const bool turn = turn_contractions(kind, D, row_tiles, n_split_h, kh * 4, planes_written > 0, v_tiles, n_split_w, kw * 4,
+                                                          dw_beta, false, knobs);
+                const int panel_shift = turn || kind == 3 ? 5 : 6;    // log2 of the K slice of the contractions' tiles
                 const uint32_t panel = (uint32_t)(row_tiles * 256) << panel_shift;
                 uint16_t* G = ch.in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
                                          : (uint16_t*)(ws + sc.off_g);
@@ -2012,7 +2238,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                     dh.first_row = dw.first_row = (int)row0;
                     dw.B = hidden;
                     dh.row_map = dw.row_map = counted->perm + row0;
-                    launch_counted_contractions(kind, dh, dw, stream);
+                    launch_counted_contractions(kind, turn, dh, dw, stream);
                     continue;
                 }
                 const bool dh_first = kh >= kw;                          // longer items first
@@ -2022,14 +2248,14 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                     // this dH job writes dHidden, which still holds the rows the dW job reads
                     GemmJob none = dh;
                     none.n_work = 0;
-                    launch_contractions<0>(kind, dw, none, stream);
-                    launch_contractions<4>(kind, dh, none, stream);
+                    launch_contractions<0>(kind, turn, dw, none, stream);
+                    launch_contractions<4>(kind, turn, dh, none, stream);
                 } else if (dh.final && cc) {
-                    launch_contractions<4>(kind, first, second, stream);
+                    launch_contractions<4>(kind, turn, first, second, stream);
                 } else if (sc.split_acc) {
-                    launch_contractions<1>(kind, first, second, stream);
+                    launch_contractions<1>(kind, turn, first, second, stream);
                 } else {
-                    launch_contractions<0>(kind, first, second, stream);
+                    launch_contractions<0>(kind, turn, first, second, stream);
                 }
                 if (dw.n_split > 1) {
                     const int64_t groups = cols * (D / 4);
@@ -2159,11 +2385,13 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         const GemmTile gt = gemm_tile_of_kind(contraction_kind(blk.kind, D, (int64_t)st.row_tiles * d_tiles, st.v_tiles * 4,
                                                !st.first_chunk, blk.split_acc != 0, (int64_t)st.v_tiles * d_tiles, st.row_tiles * 4,
                                                !st.first_block || accumulate_dW, cc != nullptr, knobs));
+        const bool turn = turn_contractions(gt.kind, D, st.row_tiles, 1, st.v_tiles * 4, !st.first_chunk, st.v_tiles, 1, st.row_tiles * 4,
+                                                  !st.first_block || accumulate_dW, cc != nullptr, knobs);
         const int per256 = 256 / gt.bm;                           // contraction row tiles per 256 rows
         uint16_t* G = (uint16_t*)((blk.g_in_dh ? (char*)dHidden : ws) + blk.off_g);
         char* acc = (blk.acc_in_dh ? (char*)dHidden : ws) + blk.off_acc;     // fp32 dH sums, or their lower halves (see GemmJob)
         const int ldg = st.v_tiles * 256;                       // the chunk is stored densely padded
-        const int panel_shift = gt.kind == 3 ? 5 : 6;            // log2 of the K slice of the contractions' tiles
+        const int panel_shift = turn || gt.kind == 3 ? 5 : 6;            // log2 of the K slice of the contractions' tiles
         const uint32_t panel = (uint32_t)(st.row_tiles * 256) << panel_shift;
         const int n_rows_h = (int)N;
         // 1. gradient tiles of this [row block x chunk]
@@ -2213,9 +2441,14 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         const GemmJob& second = dh_first ? dw : dh;
         const int work = dh.n_work + dw.n_work;
 
-        {
+        const int mode = (blk.split_acc ? 1 : 0) | (cc ? 2 : 0);
+        if (turn) {
+            if (mode == 0) launch_turn_contractions<0>(first, second, stream);
+            else if (mode == 1) launch_turn_contractions<1>(first, second, stream);
+            else if (mode == 2) launch_turn_contractions<2>(first, second, stream);
+            else launch_turn_contractions<3>(first, second, stream);
+        } else {
             ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
-            const int mode = (blk.split_acc ? 1 : 0) | (cc ? 2 : 0);
 #define CCE_LAUNCH_GEMM(CFG, MODE, LDS) \
     hipLaunchKernelGGL((grad_gemm_kernel<CFG, MODE>), dim3(work), dim3(kThreads), (LDS) + ((MODE) >= 2 ? kRowTableBytes : 0), stream, first, second)
             if (gt.kind == 3) {

@@ -792,6 +792,210 @@ struct PingLoads {
     }
 };
 
+// ------------------------------------------------------------------------------------------
+// Contractions on 256 x 256 tiles of two groups of wavefronts that take turns (see PingTile), X K-slow, the chunk in either way.
+// X, a matrix row per k (hidden or weight rows), gives 256 of its D columns, the gradient chunk G 256 of its rows or columns:
+// C[g, x] with X as the A operand, so that a lane holds four consecutive columns of a result row.  2 x 4 wavefronts of 128 x 64,
+// group = wavefront row: where the tile's second 128 columns lie behind the matrix, that group only loads (the other one's turns
+// then follow each other: 0.66 of the time).  One turn per slice of 32: every fragment of a slice is read at once, 32 products to
+// 24 transpose reads of 8 bytes a lane, the loads of a later slice among the products.
+//
+// LDS layout, a lane's 16 bytes at lane * 16 of a wavefront's 1 KB: X in blocks of 64 columns, [block][32 k][128 B], the 32-byte
+// unit u of a row at u ^ (bit 1 of k + 2 bit 3 of k); G K-slow in blocks of 32 columns (a panel's width), [block][32 k][64 B], at
+// u ^ bit 3 of k: the 8 k-rows x 32 bytes that two lane groups of a transpose read touch per clock cover all 64 banks (measured
+// 243 of 256 B/clk).  G K-major: [row][64 B], chunk c at c ^ bits 2, 3 of the row.
+//
+// What bounds it is power.  4096 x 24576 x 4096 in one launch after the other, TFLOP/s on random / constant operands: 256 x 256 by
+// gemm_mainloop 1 436 / 1 892, 256 x 128 1 292 / 1 786, these 1 583 / 2 158 (with the loads in the reading turns, three stages
+// 1 436 / 1 898; 256 x 384 outputs, which have the registers for that form alone, 1 655 / 2 209 and in place no faster: items half as
+// long again, a launch's last round emptier).
+struct TurnTile {
+    static constexpr int NA = 8, NB = 4, BM = 256, BN = 256, BK = 32, STAGES = 4;        // BM: columns of X, BN: rows / columns of G
+    static constexpr int kThreads = 512;
+    static constexpr int kXStage = BM * BK * 2, kStage = (BM + BN) * BK * 2, kLdsBytes = STAGES * kStage;
+    static constexpr int kXLoads = 2, kLoads = 4;               // 16-byte loads per thread and slice
+};
+
+// The calling lane's number, without the thread id.
+__device__ __forceinline__ int wave_lane() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
+// MAP: the k-rows of X are reached through a table in LDS, as in OperandTile.
+template <bool G_KMAJOR, int MAP>
+struct TurnLoop {
+    typedef TurnTile Cfg;
+    CCE_LDS char* smem;
+    const char* x;               // uniform: the next slice's first row (MAP: row 0 of the matrix), columns of load 0
+    const char* g;               // uniform: the next slice
+    uint32_t x_step;             // from load 0's columns to load 1's
+    uint32_t x_off, g_off;       // this thread's place in a slice (MAP: in the next slice)
+    uint32_t ld, panel, lds0;
+    int rows;                    // valid k-rows of X from the next slice on
+    int k;                       // MAP: first table entry of the next slice
+    const CCE_LDS uint32_t* kmap;
+    const CCE_LDS uint16_t* kmap16;
+    uint32_t xa, ga;             // fragment addresses in a stage, of unit 0 (the others by xor)
+    int wave, group;
+
+    // (from the lane number at each use: kept over the loop they would take registers that the accumulators need)
+    __device__ __forceinline__ int x_row() const { return 8 * (wave & 3) + (wave_lane() >> 3); }
+    __device__ __forceinline__ uint32_t x_chunk() const {
+        const int row = x_row();
+        return (uint32_t)(((wave_lane() & 7) ^ (2 * (((row >> 1) & 1) | (((row >> 3) & 1) << 1)))) * 16);
+    }
+
+    // X: matrix with rows of ld_bytes and n_cols columns, from the reduction's first row on (MAP: from its first row on), of which
+    // k_rows are valid (at least one); the tile's columns from col0 on.  G: the chunk, its rows (K-major) or columns from free0 on,
+    // from k0 on; panels of 32 columns.
+    __device__ __forceinline__ void init(CCE_LDS char* smem_, int wave_, const void* X, uint32_t ld_bytes, int col0, int n_cols, int k_rows,
+                                         const uint16_t* G, uint32_t panel_elements, int free0, int k0) {
+        smem = smem_;
+        ld = ld_bytes;
+        panel = panel_elements * 2u;
+        rows = k_rows;
+        const int l = wave_lane();
+        wave = wave_;
+        group = wave >> 2;
+        lds0 = (uint32_t)(uintptr_t)smem + (uint32_t)wave * 1024u;
+        // load i of X: block 2 i + wave / 4 of 64 columns (blocks behind the matrix: its last one)
+        const int last = (n_cols - 1 - col0) >> 6;
+        const int b0 = group < last ? group : last, b1 = 2 + group < last ? 2 + group : last;
+        x = (const char*)X + (size_t)(col0 + b0 * 64) * 2;
+        x_step = (uint32_t)(b1 - b0) * 128u;
+        x_off = (uint32_t)x_row() * ld + x_chunk();
+        k = 0;
+        kmap = nullptr;
+        kmap16 = nullptr;
+        if (G_KMAJOR) {
+            g = (const char*)G + (size_t)(k0 / 32) * panel + (size_t)free0 * 64;
+            const int row = wave * 16 + (l >> 2);
+            g_off = (uint32_t)(row * 64 + (((l & 3) ^ ((row >> 2) & 3)) << 4));
+        } else {
+            g = (const char*)G + (size_t)(free0 / 32) * panel + (size_t)k0 * 64;
+            const int row = 16 * (wave & 1) + (l >> 2);
+            g_off = (uint32_t)(wave >> 1) * panel + (uint32_t)(row * 64 + (((l & 3) ^ (2 * ((row >> 3) & 1))) << 4));
+        }
+        const int wn = wave & 3, h = l >> 4, jj = l & 15;
+        const int kr = 8 * h + (jj >> 2), q = jj & 3;           // transpose reads: this lane's k-row (and the one 4 on), its 8 bytes
+        xa = (uint32_t)(group * (2 * 32 * 128) + kr * 128 + (((kr >> 1) & 1) | (((kr >> 3) & 1) << 1)) * 32 + q * 8);
+        const int row = wn * 16 * Cfg::NB + jj;
+        ga = (uint32_t)Cfg::kXStage + (G_KMAJOR ? (uint32_t)(row * 64 + ((h ^ ((row >> 2) & 3)) << 4))
+                                                : (uint32_t)(wn * (Cfg::NB / 2) * (32 * 64) + kr * 64 + ((kr >> 3) & 1) * 32 + q * 8));
+    }
+    // MAP: x_off of the slice whose first table entry is k.
+    __device__ __forceinline__ void look_up() {
+        x_off = (MAP == 1 ? kmap[k + x_row()] : __umul24((uint32_t)kmap16[k + x_row()], ld)) + x_chunk();
+    }
+    // A slice of `rows` valid rows: behind the last one that one again, whose products meet the chunk's zeros.
+    __device__ __forceinline__ void ragged() {
+        if (MAP == 0) x_off = (uint32_t)(x_row() < rows ? x_row() : rows - 1) * ld + x_chunk();
+    }
+    __device__ __forceinline__ void load(int stage, int i) const {
+        const uint32_t to = lds0 + (uint32_t)stage * Cfg::kStage + (uint32_t)i * 8192u;
+        if (i < Cfg::kXLoads) load16_to_lds_sbase(x + i * x_step, x_off, to);
+        else load16_to_lds_sbase(g + (size_t)((uint32_t)(i - Cfg::kXLoads) * (G_KMAJOR ? 8192u : 4u * panel)), g_off, to);
+    }
+    static __device__ __forceinline__ void barrier() { asm volatile("s_barrier" ::: "memory"); }
+    static __device__ __forceinline__ bf16x8 transposed(const CCE_LDS char* p, int four_rows) {
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CCE_LDS s16x4*)p);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CCE_LDS s16x4*)(p + four_rows));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+
+    // Slices that hold k_rows rows; MAP: the table has entries for as many whole slices and one more (any that may be read).
+    static __device__ __forceinline__ int slices(int k_rows) {
+        const int n = (k_rows + 31) / 32;
+        return n < Cfg::STAGES ? Cfg::STAGES : n;
+    }
+
+    // KT slices of 32 (at least STAGES).  Without ON (columns behind the matrix) loads and barriers only.  Group 0 reads in turn 2 t and multiplies
+    // in 2 t + 1, group 1 one turn later, a barrier behind every turn.  Slice t + STAGES - 1 is requested in the multiplying turns of
+    // slice t, into the stage of slice t - 1, whose fragments every wavefront has by then (lgkmcnt(0) in front of the barriers); slice t + 1 has landed when a wavefront leaves its reading turn of slice t (its own loads, vmcnt), which is in
+    // front of the barrier that precedes group 0's reading turn of t + 1.
+    template <bool ON>
+    __device__ __forceinline__ void turns(f32x4 (&acc)[Cfg::NA][Cfg::NB], int KT) {
+        constexpr int S = Cfg::STAGES, NL = Cfg::kLoads;
+        for (int s = 0; s < S - 1; ++s) {
+            if (MAP) look_up();
+            else if (rows < 32) ragged();
+#pragma unroll
+            for (int i = 0; i < NL; ++i) load(s, i);
+            g += G_KMAJOR ? (size_t)panel : (size_t)2048;
+            k += 32;
+            if (rows > 32) {
+                rows -= 32;
+                if (MAP == 0) x += (size_t)(32u * ld);
+            }
+        }
+        if (MAP) look_up();
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((S - 2) * NL) : "memory");
+        if (group) barrier();
+        int cur = 0;
+        auto slice = [&](auto more_tag) {
+            constexpr bool MORE = decltype(more_tag)::value;    // another slice is requested
+            const CCE_LDS char* const st = smem + cur * Cfg::kStage;
+            const int to = cur == 0 ? S - 1 : cur - 1;
+            bf16x8 a[Cfg::NA], b[Cfg::NB];
+            __builtin_amdgcn_sched_barrier(0);
+            if (ON) {
+#pragma unroll
+                for (int i = 0; i < Cfg::NA; ++i) a[i] = transposed(st + (xa ^ (uint32_t)((i & 3) * 32)) + (i >> 2) * (32 * 128), 4 * 128);
+#pragma unroll
+                for (int j = 0; j < Cfg::NB; ++j) {
+                    if (G_KMAJOR) b[j] = *(const CCE_LDS bf16x8*)(st + ga + j * 1024);
+                    else b[j] = transposed(st + (ga ^ (uint32_t)((j & 1) * 32)) + (j >> 1) * (32 * 64), 4 * 64);
+                }
+            }
+            if (MORE) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(NL) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int NM = Cfg::NA * Cfg::NB, GAP = NM / (NL + 1);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int j = m / Cfg::NA, i = j & 1 ? Cfg::NA - 1 - m % Cfg::NA : m % Cfg::NA;
+                if (ON) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                if (MORE && m % GAP == GAP - 1 && m / GAP < NL) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    load(to, m / GAP);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (MORE) {
+                g += G_KMAJOR ? (size_t)panel : (size_t)2048;
+                if (MAP == 0) {
+                    x += (size_t)(32u * ld);
+                } else {
+                    k += 32;
+                    look_up();
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            cur = cur == S - 1 ? 0 : cur + 1;
+        };
+        rows -= 32 * (KT - S);                                  // of the last slice, the only ragged one beyond the first STAGES - 1
+        // (both loops rolled: slices in a row, without a loop, cost some 40 registers)
+#pragma nounroll
+        for (int t = S - KT; t <= 0; ++t) {
+            if (t == 0 && rows < 32) ragged();
+            slice(std::true_type{});
+            barrier();
+        }
+#pragma nounroll
+        for (int t = S - 1;;) {
+            slice(std::false_type{});
+            if (--t == 0) break;
+            barrier();
+        }
+        if (!group) barrier();
+        barrier();
+    }
+
+    __device__ __forceinline__ void run(f32x4 (&acc)[Cfg::NA][Cfg::NB], int KT) { turns<true>(acc, KT); }
+    __device__ __forceinline__ void idle(int KT) {
+        f32x4 none[Cfg::NA][Cfg::NB];
+        turns<false>(none, KT);
+    }
+};
+
 // Tile coordinates of accumulator element acc[bm][bn][r] of the calling lane.
 template <class Cfg>
 __device__ __forceinline__ int acc_row(int bm, int r) {

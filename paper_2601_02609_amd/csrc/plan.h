@@ -13,6 +13,7 @@
 #include "../../include/cce.h"
 #include "gemm_core.h"
 #include "host_util.h"
+#include "wg_map.h"
 
 #ifndef CCE_PLAN_PRICED
 #define CCE_PLAN_PRICED() ((void)0)     // a makespan was searched for: counted by the host tests
@@ -136,11 +137,17 @@ static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2,
 static double makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
     return c1 >= c2 ? two_class_makespan(cus, n1, c1, n2, c2) : two_class_makespan(cus, n2, c2, n1, c1);
 }
-// A bound that it never falls below, without the search: all work spread evenly, the rounds of the longer job.
+// A bound that it never falls below, without the search: all work spread evenly, the rounds of the longer job, the items of the unit
+// with most of them (k = items / units, rounded up): k short ones, and one more or one of them long where the units with fewer than
+// k cannot hold all long ones.
 static double makespan_floor(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
-    const double even = ((double)n1 * c1 + (double)n2 * c2) / (double)cus;
+    double most = ((double)n1 * c1 + (double)n2 * c2) / (double)cus;
     const double rounds = c1 >= c2 ? (double)((n1 + cus - 1) / cus) * c1 : (double)((n2 + cus - 1) / cus) * c2;
-    return even > rounds ? even : rounds;
+    most = rounds > most ? rounds : most;
+    const int64_t n = n1 + n2, k = (n + cus - 1) / cus, n_long = c1 >= c2 ? n1 : n2;
+    const double c_long = c1 >= c2 ? c1 : c2, c_short = n1 == 0 ? c2 : n2 == 0 ? c1 : c1 < c2 ? c1 : c2;
+    const double each = (double)k * c_short + (n_long > (k * cus - n) * (k - 1) ? (c_long < 2.0 * c_short ? c_long - c_short : c_short) : 0.0);
+    return each > most ? each : most;
 }
 // Floors and times are sums in different orders: what lies above by less than this is not passed over.
 constexpr double kAbove = 1.0 + 1e-9;
@@ -459,6 +466,70 @@ static inline ScheduleChunk schedule_chunk(const ScheduleSteps& sc, int64_t D, i
     }
 }
 
+// Completion time of items of several lengths, handed to `cus` units from the longest to the shortest, each unit taking the next one
+// when it becomes free.  Units that become free at the same time are counted together.
+struct ItemClass { double us; int64_t n; };
+static double item_makespan(int64_t cus, ItemClass* items, int n_classes) {
+    constexpr int kMost = 48;
+    struct Free { double at; int64_t n; } free_at[kMost + 1];
+    int groups = 1;
+    free_at[0] = {0.0, cus};
+    double end = 0.0;
+    for (int i = 1; i < n_classes; ++i)
+        for (int k = i; k > 0 && items[k].us > items[k - 1].us; --k) { const ItemClass t = items[k]; items[k] = items[k - 1]; items[k - 1] = t; }
+    for (int i = 0; i < n_classes; ++i) {
+        for (int64_t left = items[i].n; left > 0;) {
+            const int64_t take = free_at[0].n < left ? free_at[0].n : left;
+            const double at = free_at[0].at + items[i].us;
+            left -= take;
+            end = at > end ? at : end;
+            free_at[0].n -= take;
+            if (free_at[0].n == 0) {
+                for (int k = 1; k < groups; ++k) free_at[k - 1] = free_at[k];
+                --groups;
+            }
+            int k = groups;
+            while (k > 0 && free_at[k - 1].at > at) --k;
+            if (k > 0 && at - free_at[k - 1].at < 1e-6) { free_at[k - 1].n += take; continue; }
+            if (groups == kMost) { free_at[k > 0 ? k - 1 : 0].n += take; continue; }      // (as good as free then)
+            for (int q = groups; q > k; --q) free_at[q] = free_at[q - 1];
+            free_at[k] = {at, take};
+            ++groups;
+        }
+    }
+    return end;
+}
+
+// Contractions on tiles of two wavefront groups (TurnTile), microseconds: a 256 x 256 x 64 slice 1.38, 13 beside the slices (first
+// slice, epilogue), 6 more where the item adds to its output, 0.66 of all that where half of its columns lie behind the matrix.
+// Rated / measured: 1008 items of 32 x 40 tiles at D = 3584 859 / 866, 768 of 64 x 32 at D = 2048 758 / 789, 1120 of 16 x 64 at D = 3584
+// 741 / 720, 512 of 16 x 16 at D = 4096 212 / 228, 256 of 32 x 32 at D = 896 196 / 181.
+struct TurnModel {
+    int64_t cus, D;
+    // Launches of fewer items leave too many compute units idle (128 items where 256 x 128 tiles are 256: 105 us for 77): not rated.
+    bool enough(int64_t tiles) const { return 5 * tiles * ((D + 255) / 256) >= 3 * cus; }
+    static double item(double slices, bool half, bool beta) { return (half ? 0.66 : 1.0) * (slices * 1.38 + 13.0 + (beta ? 6.0 : 0.0)); }
+    // a x b tiles of 256, reductions of s_dh and s_dw slices in parts_h and parts_w parts.  FLOOR: a bound it never falls below.
+    template <bool FLOOR = false>
+    double us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
+        const int64_t all = (D + 255) / 256, half = D % 256 != 0 && D % 256 <= 128 ? 1 : 0;
+        if (FLOOR || half == 0) {
+            const double c_dh = item((double)s_dh, false, dh_beta), c_dw = item((double)s_dw, false, dw_beta);
+            const int64_t n_dh = a * parts_h, n_dw = b * parts_w;
+            if (!FLOOR) return makespan(cus, n_dh * all, c_dh, n_dw * all, c_dw);
+            const double whole = makespan_floor(cus, n_dh * (all - half), c_dh, n_dw * (all - half), c_dw);
+            if (half == 0) return whole;
+            const double even = ((double)n_dh * c_dh + (double)n_dw * c_dw) * ((double)all - 0.34) / (double)cus;
+            const double each = (double)(((n_dh + n_dw) * all + cus - 1) / cus) * 0.66 * (c_dh < c_dw ? c_dh : c_dw);
+            const double most = even > each ? even : each;
+            return whole > most ? whole : most;
+        }
+        ItemClass c[4] = {{item((double)s_dh, false, dh_beta), a * parts_h * (all - half)}, {item((double)s_dh, true, dh_beta), a * parts_h * half},
+                          {item((double)s_dw, false, dw_beta), b * parts_w * (all - half)}, {item((double)s_dw, true, dw_beta), b * parts_w * half}};
+        return item_makespan(cus, c, 4);
+    }
+};
+
 // Time model of the schedules, microseconds, from launches timed on MI355X with random data: a
 // 256 x 256 x 64 slice 1.58, a 256 x 128 x 64 one 0.79; a gradient tile adds 7 to its slices, a
 // contraction tile 13 / 9 (first slice, epilogue) and 2 more where it adds to its output; a
@@ -470,10 +541,12 @@ struct ScheduleModel {
                                 // took with its bounds checks (0.85 us against 0.76); byte offsets take less, see OperandTile
     int64_t dt;                 // output tiles across D
     bool one_to_unit = false;   // 256 x 128 tiles: not two to a compute unit
+    bool turns = false;         // tiles of two wavefront groups (256 x 256) where those are faster
     bool duo() const { return tile.kind == 1 && !mapped && !one_to_unit; }
     ScheduleModel() = default;
     ScheduleModel(int cus_, int64_t D_, GemmTile tile_, bool mapped_ = false)
         : cus(cus_), D(D_), tile(tile_), mapped(mapped_), dt((D_ + tile_.bn - 1) / tile_.bn) {}
+    ScheduleModel with_turns(bool on) const { ScheduleModel m = *this; m.turns = on; return m; }
     // (32-bit divisions: a search makes tens of thousands of them, and 64-bit ones take twice as long)
     static int64_t ceil_div(int64_t a, int64_t b) { return (int64_t)(((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b); }
     double slice() const { return tile.kind == 0 ? 1.58 : 0.79; }
@@ -481,8 +554,9 @@ struct ScheduleModel {
     double duo_item(int64_t slices, bool beta, bool split) const { return (double)slices * 1.53 + 10.0 + (beta ? 6.0 : 0.0) + (split ? 8.0 : 0.0); }
     int64_t d_tiles() const { return dt; }
     // What an item costs at least, of either form.
-    double least_slice() const { return duo() ? 0.765 : slice(); }
-    double least_item() const { return duo() ? 5.0 : item(0, false); }
+    double least_slice(bool turn) const { return turn ? (tile.kind == 0 ? 1.38 : 0.69) : duo() ? 0.765 : slice(); }
+    double least_item(bool turn) const { return duo() ? 5.0 : turn ? 6.0 : item(0, false); }
+    bool may_turn(int64_t a, int64_t b, int split_h, int split_w) const { return turns && TurnModel{cus, D}.enough(a * split_h + b * split_w); }
     // Both contractions of a step; *kind becomes the tile they take.  (Narrow tiles are searched for only where they could win.)
     template <bool FLOOR = false>
     double contractions(int64_t n_dh, int64_t s_dh, bool dh_beta, bool split, int64_t n_dw, int64_t s_dw, bool dw_beta, int* kind = nullptr) const {
@@ -499,6 +573,24 @@ struct ScheduleModel {
         if (kind) *kind = tile.kind;
         return us;
     }
+    // The same of a x b tiles in parts_h and parts_w parts where tiles of two wavefront groups may be taken: the faster ones.  The form
+    // with the lower floor is priced first, the other one only if its floor is 5 % below that.
+    template <bool FLOOR>
+    double with_turns_us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, bool split, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
+        const TurnModel turn{cus, D};
+        if (!turn.enough(a * parts_h + b * parts_w))
+            return contractions<FLOOR>(a * dt * parts_h, s_dh, dh_beta, split, b * dt * parts_w, s_dw, dw_beta);
+        const int64_t n_dh = a * dt * parts_h, n_dw = b * dt * parts_w;
+        const double f_turn = turn.template us<true>(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta);
+        const double f_other = contractions<true>(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta);
+        const bool first = f_turn <= f_other;
+        double us = first ? f_turn : f_other;
+        if (FLOOR) return us;
+        us = first ? turn.us(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta) : contractions(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta);
+        if ((first ? f_other : f_turn) * 1.05 >= us) return us;
+        const double other = first ? contractions(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta) : turn.us(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta);
+        return other < us ? other : us;
+    }
     // (The loop of FP8 tiles and of bf16 ones before those of two wavefront groups, which take 5 - 15 % less, up to 30 % where the taller
     // ones fill the rounds better, see tall_grad_tiles: the orders stay those that were measured with it.)
     double logit_tile() const { return (double)(D / 64) * 1.55 + 7.0; }
@@ -507,7 +599,8 @@ struct ScheduleModel {
     double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta, bool split = false) const {
         const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);       // K tiles per part
         const int64_t n_dh = a * dt * ceil_div(b, kh), n_dw = b * dt * ceil_div(a, kw);
-        const double mk = contractions<FLOOR>(n_dh, kh * 4, dh_beta, split, n_dw, kw * 4, dw_beta);
+        const double mk = turns ? with_turns_us<FLOOR>(a, ceil_div(b, kh), kh * 4, dh_beta, split, b, ceil_div(a, kw), kw * 4, dw_beta)
+                                : contractions<FLOOR>(n_dh, kh * 4, dh_beta, split, n_dw, kw * 4, dw_beta);
         const double g = (double)(a * b) * 131072.0, w = (double)b * 512.0 * (double)D;
         const double tiles_us = (double)((a * b + cus - 1) / cus) * logit_tile();
         const double tiles_mem = (g + w) / 4.5e6;
@@ -520,10 +613,11 @@ struct ScheduleModel {
     // at most `b_max`: all work spread evenly, the serial reduction of one item per step or all bytes at the rate
     // of HBM, and what each step costs by itself.
     double floor_us(int64_t a, int64_t b, int64_t b_max, int split_h, int split_w) const {
-        const double ab = (double)(a * b), per_item = least_item();
+        const bool turn = may_turn(a, b_max < b ? b_max : b, split_h, split_w);
+        const double ab = (double)(a * b), per_item = least_item(turn);
         const double steps = (double)ceil_div(b, b_max);
         const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);
-        double even = (8.0 * ab * (double)dt * least_slice() + ((double)(b * ceil_div(a, kw)) + (double)a * steps) * (double)dt * per_item) / (double)cus;
+        double even = (8.0 * ab * (double)dt * least_slice(turn) + ((double)(b * ceil_div(a, kw)) + (double)a * steps) * (double)dt * per_item) / (double)cus;
         const double dh_item = (double)(kh * 4) * slice() + steps * per_item, dw_item = steps * ((double)(kw * 4) * slice() + per_item);
         if (dh_item > even) even = dh_item;
         if (dw_item > even) even = dw_item;
@@ -534,10 +628,11 @@ struct ScheduleModel {
                (split_w > 1 ? 4.0 * steps + w * 2.0 * (double)(split_w + 1) / 4.0e6 : 0.0);
     }
     // The part of it that grows with the width, per vocabulary tile.
-    double floor_per_tile(int64_t a, int64_t b_max) const {
-        const double per_item = least_item(), steps = 1.0 / (double)b_max;
+    double floor_per_tile(int64_t a, int64_t b_max, int split_h, int split_w) const {
+        const bool turn = may_turn(a, b_max, split_h, split_w);
+        const double per_item = least_item(turn), steps = 1.0 / (double)b_max;
         return (double)a * logit_tile() / (double)cus + 8.0 * steps +
-               (8.0 * (double)a * (double)dt * least_slice() + (1.0 + (double)a * steps) * (double)dt * per_item) / (double)cus;
+               (8.0 * (double)a * (double)dt * least_slice(turn) + (1.0 + (double)a * steps) * (double)dt * per_item) / (double)cus;
     }
 };
 
@@ -572,6 +667,19 @@ static int counted_contraction_kind(int kind, int64_t D, int64_t a, int64_t b, i
         single += one;
     }
     return paired <= single ? 3 : kind;
+}
+
+// Whether a launch over e_h x e_w tiles takes tiles of two wavefront groups instead of `kind` (contraction_kind); parts_h / parts_w parts of s_h and s_w
+// slices each.  From the shape of the launch alone, so that calls that count their rows and calls that compute all of them agree.
+static bool turn_contractions(int kind, int64_t D, int64_t e_h, int64_t parts_h, int64_t s_h, bool beta_h, int64_t e_w, int64_t parts_w, int64_t s_w,
+                              bool beta_w, bool row_map, const Knobs& knobs) {
+    const int cus = device_cu_count();
+    if (kind == 2 || knobs.gemm_cols != 0 || !TurnModel{cus, D}.enough(e_h * parts_h + e_w * parts_w)) return false;
+    const ScheduleModel m{cus, D, gemm_tile_of_kind(kind == 0 ? 0 : 1), row_map};
+    const int64_t per256 = 256 / m.tile.bm;
+    const double other = m.contractions(e_h * parts_h * per256 * m.d_tiles(), s_h, beta_h, false, e_w * parts_w * per256 * m.d_tiles(), s_w, beta_w);
+    const double us = TurnModel{cus, D}.us(e_h, parts_h, s_h, beta_h, e_w, parts_w, s_w, beta_w);
+    return us < other;
 }
 
 // The forward under the same constants, to compare calls with and without row skipping (what its tiles take: forward_tile): rounds of workgroups that walk their vocabulary tiles, or of one
@@ -735,6 +843,11 @@ static ForwardSkip forward_skip(const Plan& p, int64_t D, bool fp8) {
     return f;
 }
 
+// Whether a backward over all rows may leave the ignored ones out (see backward_skip, which looks at its order too).
+static bool may_skip_backward(const Plan& p, int64_t D) {
+    return !p.forced && p.TT >= 8 && p.TT <= kRowTableBytes / 512 && 2.0 * (double)p.rows * (double)p.cols * (double)D >= 1.15e12;
+}
+
 // The schedule of a backward over N rows (row skipping: the compact ones) for the workspace laid out
 // by `p`.  dw_free: dW is overwritten, so its unwritten rows may hold a gradient chunk.  Forced
 // tilings, tiles and accumulators keep the Plan's order.  Nothing that takes `limit` or longer is looked for.
@@ -744,9 +857,10 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     const int cus = device_cu_count();
     Schedule best = {};
     const int TT = p.TT, VT = p.VT;
+    const bool turns = (double)N * (double)D * (double)V >= 2e10;      // (smaller ones have too few tiles of 256 for them)
     const size_t region = (compact ? p.off_count : p.total) - p.off_dhacc;
     {   // the Plan's order under the same model
-        const ScheduleModel m{cus, D, gemm_tile_of_kind(p.gemm_kind), compact};
+        const ScheduleModel m = ScheduleModel(cus, D, gemm_tile_of_kind(p.gemm_kind), compact).with_turns(turns);
         const int64_t a = p.Nb / 256, b = p.Vc / 256, nch = (VT + b - 1) / b;
         auto block_us = [&](int64_t aa, bool later) {
             return (nch > 1 ? (double)(nch - 1) * m.step(aa, b, 1, 1, true, later, p.split_acc != 0) : 0.0) +
@@ -757,13 +871,19 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         if (nblk > 1) best.plan_us += (nblk > 2 ? (double)(nblk - 2) * block_us(a, true) : 0.0) + block_us(TT - (nblk - 1) * a, true);
         if (p.split_acc) best.plan_us += (double)(nblk * nch) * (compact ? 9.0 : 2.0);
     }
-    // A schedule has to be rated 10 % faster: the model is that far off between orders of much
-    // different chunk sizes (6963 rows x 896 x 151936 was rated 8 % faster and measured 1 % slower).
-    best.us = 0.90 * best.plan_us;
-    if (limit < best.us) best.us = limit;
+    // A schedule has to be rated 10 % faster, one without K parts 4 % where launches may be on tiles of two wavefront groups, whose times
+    // the model has more closely.  (Of 46 drawn calls of 3e10 products on, none is slower with 4 % than with 10 % by more than the
+    // runs differ, seven are 4 to 8 % faster, among them 10621 x 128 x 118991, 1041 x 2880 x 49282 and 2042 x 2880 x 86534;
+    // 16384 x 2048 x 151936 31.0 -> 30.4 ms.)  Such an order with its sums in planes counts for 4 % less than it is rated where it may
+    // leave ignored rows out (backward_skip), which the rating does not know.
+    const bool may_skip = turns && !compact && may_skip_backward(p, D);
+    const double parts_us = 0.90 * best.plan_us < limit ? 0.90 * best.plan_us : limit;
+    double rated = (turns ? 0.96 : 0.90) * best.plan_us;        // of the best so far
+    rated = rated < limit ? rated : limit;
+    best.us = rated;
     const int caps[] = {4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256, 384, 1 << 30};
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
-    const ScheduleModel models[2] = {{cus, D, gemm_tile_of_kind(0)}, {cus, D, gemm_tile_of_kind(1)}};
+    const ScheduleModel models[2] = {ScheduleModel(cus, D, gemm_tile_of_kind(0)).with_turns(turns), ScheduleModel(cus, D, gemm_tile_of_kind(1)).with_turns(turns)};
     // (row blocks add to dW with every block, as do the orders with dHidden's front rows, and both are rated with the same
     // items: one to a unit, though a launch of theirs may take two, so that the choice among them stays the one that was measured)
     ScheduleModel block_models[2] = {models[0], models[1]};
@@ -789,11 +909,13 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         sc.plane_h = (rows < N ? rows : N) * D;
         sc.plane_w = cols_max * D;
         const int nblk = (TT + a - 1) / a;
+        const double worth = may_skip && kind == 1 && split_acc && a == TT ? 0.96 : 1.0;
+        const double most = sh > 1 || sw > 1 ? (rated < parts_us ? rated : parts_us) : rated / worth;
         // beside the steps: the sum of the planes, the gathered rows
         const double sum_us = sh > 1 ? (double)nblk * (8.0 + (double)sh * (double)sc.plane_h * 4.0 / 4.0e6) : 0.0;
         const double gather_us = compact ? (double)nblk * 5.0 + (double)N * (double)D * 4.0 / 4.0e6 : 0.0;
         const double extra = sum_us + gather_us;
-        if (m.floor_us(TT, VT, sc.b, sh, sw) + (double)(nblk - 1) * 8.0 + extra > best.us * kAbove) return;
+        if (m.floor_us(TT, VT, sc.b, sh, sw) + (double)(nblk - 1) * 8.0 + extra > most * kAbove) return;
         auto lay_out = [&](int planes) {
             sc.off_acc = p.off_dhacc;
             sc.off_part_w = sc.off_acc + (size_t)round_up((int64_t)planes * sc.plane_h * (split_acc ? 2 : 4), 256);
@@ -807,7 +929,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         bool ok = sh == 1 && !split_acc && row_parts == 1 && lay_out(0) && schedule_chunk(sc, D, V).b == VT;
         if (!ok) ok = lay_out(sh) && (!one_chunk || schedule_chunk(sc, D, V).b == VT);
         if (!ok) return;
-        const double per_tile = m.floor_per_tile(a, sc.b);
+        const double per_tile = m.floor_per_tile(a, sc.b, sh, sw);
         double block_us[2] = {0.0, 0.0};        // first row block, later ones (they add to dW)
         for (int later = 0; later < (one_chunk ? 2 : 1); ++later) {
             ScheduleChunk last = {-1, 0, false}; double last_us = 0.0;
@@ -820,7 +942,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                     last_us = known ? *known : 0.0;
                     const int64_t rest = VT - v / 256 - c.b;
                     const double least = last_us > 0.0 ? last_us : (double)(a / c.rows) * m.template step<true>(c.rows, c.b, sh, sw, v > 0, later > 0 || !dw_free);
-                    if (block_us[later] + least + (double)rest * per_tile + extra > best.us * kAbove) return;
+                    if (block_us[later] + least + (double)rest * per_tile + extra > most * kAbove) return;
                     if (last_us == 0.0)
                         for (int r = 0; r < a; r += c.rows)
                             last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free, split_acc != 0) + (split_acc ? 2.0 : 0.0);
@@ -828,12 +950,13 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                     last = c;
                 }
                 block_us[later] += last_us;
-                if (block_us[later] >= best.us) return;
+                if (block_us[later] >= most) return;
                 v += c.b * 256;
             }
         }
         sc.us = block_us[0] + (double)(nblk - 1) * block_us[1] + sum_us + gather_us;
-        if (sc.us < best.us) {
+        if (sc.us < most) {
+            rated = sc.us * worth;
             sc.use = true;
             sc.plan_us = best.plan_us;
             (ScheduleSteps&)best = sc;
@@ -848,7 +971,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                 if (sh > 1 && (sh > VT || TT * dt * (sh / 2) > 2 * cus)) break;     // parts beyond two rounds of tiles
                 for (int sw : splits) {
                     if (sw > 1 && (sw > TT || VT * dt * (sw / 2) > 2 * cus)) break;
-                    if (m.floor_us(TT, VT, VT, sh, sw) > best.us * kAbove) continue;
+                    if (m.floor_us(TT, VT, VT, sh, sw) > (sh > 1 || sw > 1 || !may_skip ? rated : rated / 0.96) * kAbove) continue;
                     int prev = 0;
                     for (int cap : caps) {
                         const int b = cap < VT ? cap : VT;
@@ -871,12 +994,12 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         }
     }
     if (!p.forced && TT > 1 && TT <= 256) {
-        // 5 %: steps like the Plan's own, which the model ranks more closely than chunks of other widths
-        double bound = best.use ? best.us : 0.95 * best.plan_us;
+        // 5 %, 2 %: steps like the Plan's own, which the model ranks more closely than chunks of other widths
+        double bound = best.use ? rated : (turns ? 0.98 : 0.95) * best.plan_us;
         if (limit < bound) bound = limit;
         RowBlockPlanner rp;
-        rp.m[0] = {cus, D, gemm_tile_of_kind(0), compact};
-        rp.m[1] = {cus, D, gemm_tile_of_kind(1), compact};
+        rp.m[0] = ScheduleModel(cus, D, gemm_tile_of_kind(0), compact).with_turns(turns);
+        rp.m[1] = ScheduleModel(cus, D, gemm_tile_of_kind(1), compact).with_turns(turns);
         rp.TT = TT; rp.VT = VT; rp.D = D; rp.region = region; rp.off0 = p.off_dhacc; rp.compact = compact; rp.dw_free = dw_free;
         rp.prepare();
         const double us = rp.best(TT, bound);
@@ -984,9 +1107,8 @@ struct BackwardSkip { bool use; size_t off_perm, off_labels, off_lse, off_dloss,
 static BackwardSkip backward_skip(const Plan& p, const Schedule& sc, int64_t D, bool fp8) {
     BackwardSkip b = {};
     // (256 x 128 tiles: no order with the planes was ever planned with 256 x 256 ones)
-    if (!sc.use || sc.kind != 1 || !sc.split_acc || sc.a < p.TT || sc.split_h != 1 || sc.split_w != 1 || p.TT < 8 || p.TT > kRowTableBytes / 512) return b;
-    if (g_force_row_skipping.load(std::memory_order_relaxed) == 1 || p.forced) return b;
-    if (2.0 * (double)p.rows * (double)p.cols * (double)D < 1.15e12) return b;
+    if (!sc.use || sc.kind != 1 || !sc.split_acc || sc.a < p.TT || sc.split_h != 1 || sc.split_w != 1 || !may_skip_backward(p, D)) return b;
+    if (g_force_row_skipping.load(std::memory_order_relaxed) == 1) return b;
     const size_t each = (size_t)p.TT * 1024;
     b.off_perm = p.off_partials;
     b.off_labels = b.off_perm + each;
