@@ -24,6 +24,7 @@
 #include "../../include/cce_shard.h"
 #include "../../include/cce_fp8.h"
 #include "../../include/cce_compact.h"
+#include "fused_backward.h"
 #include "gemm_core.h"
 #include "host_util.h"
 #include "plan.h"
@@ -1789,6 +1790,10 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TurnTile, 3>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TurnTile, 4>, TurnTile::kLdsBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TurnTile, 9>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
+    if (!allow_big_lds(fused_backward_kernel<64, false>, FusedTile<64, false>::kLdsBytes)) return false;
+    if (!allow_big_lds(fused_backward_kernel<64, true>, FusedTile<64, true>::kLdsBytes)) return false;
+    if (!allow_big_lds(fused_backward_kernel<128, false>, FusedTile<128, false>::kLdsBytes)) return false;
+    if (!allow_big_lds(fused_backward_kernel<128, true>, FusedTile<128, true>::kLdsBytes)) return false;
     done[dev] = true;
     return true;
 }
@@ -2275,6 +2280,42 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
     }
 }
 
+// The backward of all rows without a gradient chunk, see fused_backward.h.
+static void run_fused(const FusedChoice& f, const Plan& p, const void* hidden, const void* weight, const int32_t* labels, const float* lse,
+                      const float* dloss, const float* mean_scale, int64_t N, int64_t D, int64_t V, int64_t v_off, int64_t V_total,
+                      int32_t ignore_index, float label_smoothing, float z_loss, void* dHidden, float* dW, int accumulate_dW, char* ws,
+                      hipStream_t stream) {
+    FusedArgs a;
+    a.H = (const uint16_t*)hidden; a.W = (const uint16_t*)weight;
+    a.labels = labels; a.lse = lse; a.dloss = dloss; a.mean_scale = mean_scale;
+    a.N = (int)N; a.V = (int)V; a.V_total = (int)V_total; a.v_off = (int)v_off; a.ignore_index = ignore_index;
+    a.label_smoothing = label_smoothing; a.z_loss = z_loss;
+    a.dHidden = (uint16_t*)dHidden; a.dW = dW; a.beta = accumulate_dW ? 1 : 0;
+    a.stride_h = N * D; a.stride_w = V * D;
+    a.planes_h = (float*)(ws + p.off_dhacc);
+    a.planes_w = a.planes_h + (f.parts_h > 1 ? (size_t)f.parts_h * (size_t)a.stride_h : (size_t)0);
+    a.parts_h = f.parts_h; a.parts_w = f.parts_w; a.len_h = f.len_h; a.len_w = f.len_w; a.n_h = f.n_h; a.n_w = f.n_w;
+    const int dh_first = f.len_h >= f.len_w ? 1 : 0;
+    {
+        ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
+        const dim3 grid((unsigned)(f.n_h + f.n_w));
+        if (D == 64 && f.shared) hipLaunchKernelGGL((fused_backward_kernel<64, true>), grid, dim3(256), (FusedTile<64, true>::kLdsBytes), stream, a, dh_first);
+        else if (D == 64) hipLaunchKernelGGL((fused_backward_kernel<64, false>), grid, dim3(256), (FusedTile<64, false>::kLdsBytes), stream, a, dh_first);
+        else if (f.shared) hipLaunchKernelGGL((fused_backward_kernel<128, true>), grid, dim3(256), (FusedTile<128, true>::kLdsBytes), stream, a, dh_first);
+        else hipLaunchKernelGGL((fused_backward_kernel<128, false>), grid, dim3(256), (FusedTile<128, false>::kLdsBytes), stream, a, dh_first);
+    }
+    if (f.parts_h > 1) {
+        const int64_t groups = N * (D / 4);
+        hipLaunchKernelGGL(dh_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream, (const float*)a.planes_h, f.parts_h,
+                           a.stride_h, groups, (int)(D / 4), (uint16_t*)dHidden, (const int32_t*)nullptr);
+    }
+    if (f.parts_w > 1) {
+        const int64_t groups = V * (D / 4);
+        hipLaunchKernelGGL(dw_planes_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, stream, dW, (const float*)a.planes_w,
+                           f.parts_w - 1, a.stride_w, groups);
+    }
+}
+
 // Backward over the V rows of `weight`, which are the rows [v_off, v_off + V) of a matrix of
 // V_total rows that `labels`, label smoothing and the validity of a row refer to.
 static int backward_impl(const void* hidden, const void* weight, const int32_t* labels,
@@ -2300,13 +2341,15 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
     if (!variant_ok(label_smoothing, z_loss)) return CCE_ERR_INVALID;
     if (v_off < 0 || V_total > (1 << 30) || v_off + V > V_total) return CCE_ERR_INVALID;
     Schedule sc;
+    FusedChoice fused = {};
     if (cc) {
         p = cc->plan;
         sc = cc->order;
     } else {
         int rc = check_common(hidden, weight, labels, N, D, V, workspace, workspace_bytes, &p);
         if (rc != CCE_OK) return rc;
-        plan_backward(&p, N, D, V, false, !accumulate_dW, workspace_bytes, &sc);
+        if (!fp8_in) fused = fused_backward_choice(p, N, D, V);
+        if (!fused.use) plan_backward(&p, N, D, V, false, !accumulate_dW, workspace_bytes, &sc);
     }
     if (!ensure_kernel_attributes()) return CCE_ERR_HIP;
     hipStream_t stream = (hipStream_t)stream_;
@@ -2317,6 +2360,12 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
     if (!dloss)
         hipLaunchKernelGGL(mean_scale_kernel, dim3(1), dim3(1024), 0, stream,
                            labels, (int)N, (int)V_total, ignore_index, grad_scale, mean_scale);
+    if (fused.use) {
+        run_fused(fused, p, hidden, weight, labels, lse, dloss, mean_scale, N, D, V, v_off, V_total, ignore_index, label_smoothing, z_loss,
+                  dHidden, dW, accumulate_dW, ws, stream);
+        if (!hip_ok(hipGetLastError())) return CCE_ERR_HIP;
+        return CCE_OK;
+    }
     const int grad_lds = kGradTileLds;
 
     const BackwardSkip skip = cc || V_total != V ? BackwardSkip{} : backward_skip(p, sc, D, fp8_in != nullptr);

@@ -1129,6 +1129,55 @@ static bool order_uses_dhidden(const Plan& p, const Schedule& sc) {
     return false;
 }
 
+// Backwards of all rows at D = 64 and 128 without a gradient chunk (see fused_backward.h): how the launch's two jobs are cut.  The streamed
+// ranges are cut into parts of whole tiles of 128 rows where the stationary tiles alone leave compute units idle; a part of the
+// dH job writes a plane, and so does one of the dW job from the second on, summed by a small launch each.  From the shape and the planned
+// layout alone (the workspace asked for), so that calls of a shape agree.
+// Over a gradient chunk / this, us: 256 x 64 x 1000 14.9 / 7.0, 2000 x 64 x 5000 34 / 22, 600 x 64 x 150000 226 / 86, 8192 x 64 x 151936
+// 3426 / 715, 28457 x 64 x 48721 3352 / 794, 500 x 128 x 3000 15.9 / 11.3, 1000 x 128 x 50000 109 / 82, 22053 x 128 x 77882
+// 4148 / 1812: it was the faster one of all 16 shapes that were timed, so every call that can takes it (FP8 logits and row skipping cannot).
+struct FusedChoice { bool use, shared; int parts_h, parts_w, len_h, len_w, n_h, n_w; double us; };
+static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, int64_t V) {
+    FusedChoice best = {};
+    best.us = 1e300;
+    if (p.forced || (D != 64 && D != 128)) return best;
+    struct Key { int64_t N, D, V; size_t region; int cus; FusedChoice choice; bool valid; };
+    constexpr int kCached = 16;
+    static thread_local Key cache[kCached] = {};
+    static thread_local int cache_next = 0;
+    const int cus = device_cu_count();
+    const size_t region = p.total - p.off_dhacc;
+    for (const Key& k : cache)
+        if (k.valid && k.N == N && k.D == D && k.V == V && k.region == region && k.cus == cus) return k.choice;
+    const int64_t tiles_n = (N + 127) / 128, tiles_v = (V + 127) / 128;
+    const int cuts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+    for (int shared = 0; shared < 2; ++shared) {
+        // stationary rows of an item, items to a unit, microseconds of a streamed tile beside the unit's other items and alone
+        const int64_t rows = shared ? 32 : D == 64 ? 256 : 128, slots = (D == 64 && shared ? 4 : 2) * cus;
+        const double beside = shared ? (D == 64 ? 1.36 : 1.2) : D == 64 ? 4.55 : 4.05, alone = shared ? (D == 64 ? 0.75 : 1.0) : D == 64 ? 2.9 : 2.65;
+        const double fixed = 4.0;
+        for (int ph : cuts) {
+            const int64_t len_h = (tiles_v + ph - 1) / ph, n_h_parts = (tiles_v + len_h - 1) / len_h;
+            if (n_h_parts != ph) continue;
+            for (int pw : cuts) {
+                const int64_t len_w = (tiles_n + pw - 1) / pw;
+                if ((tiles_n + len_w - 1) / len_w != pw) continue;
+                const double plane_h = ph > 1 ? (double)ph * (double)(N * D * 4) : 0.0, plane_w = (double)(pw - 1) * (double)(V * D * 4);
+                if (plane_h + plane_w + 1024.0 > (double)region) continue;
+                const int64_t n_h = (N + rows - 1) / rows * ph, n_w = (V + rows - 1) / rows * pw;
+                if (n_h + n_w > 1 << 20) continue;
+                const double tile = n_h + n_w <= cus ? alone : beside;
+                const double us = makespan(slots, n_h, (double)len_h * tile + fixed, n_w, (double)len_w * tile + fixed) +
+                                  (ph > 1 ? 4.0 + plane_h / 4.0e6 : 0.0) + (pw > 1 ? 4.0 + plane_w / 4.0e6 : 0.0);
+                if (us < best.us) best = {true, shared != 0, ph, pw, (int)len_h, (int)len_w, (int)n_h, (int)n_w, us};
+            }
+        }
+    }
+    cache[cache_next] = {N, D, V, region, cus, best, true};
+    cache_next = (cache_next + 1) % kCached;
+    return best;
+}
+
 // Modelled time of the backward that plan_backward would choose in a workspace of the size asked for.
 static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free) {
     Schedule s;
