@@ -466,67 +466,25 @@ static inline ScheduleChunk schedule_chunk(const ScheduleSteps& sc, int64_t D, i
     }
 }
 
-// Completion time of items of several lengths, handed to `cus` units from the longest to the shortest, each unit taking the next one
-// when it becomes free.  Units that become free at the same time are counted together.
-struct ItemClass { double us; int64_t n; };
-static double item_makespan(int64_t cus, ItemClass* items, int n_classes) {
-    constexpr int kMost = 48;
-    struct Free { double at; int64_t n; } free_at[kMost + 1];
-    int groups = 1;
-    free_at[0] = {0.0, cus};
-    double end = 0.0;
-    for (int i = 1; i < n_classes; ++i)
-        for (int k = i; k > 0 && items[k].us > items[k - 1].us; --k) { const ItemClass t = items[k]; items[k] = items[k - 1]; items[k - 1] = t; }
-    for (int i = 0; i < n_classes; ++i) {
-        for (int64_t left = items[i].n; left > 0;) {
-            const int64_t take = free_at[0].n < left ? free_at[0].n : left;
-            const double at = free_at[0].at + items[i].us;
-            left -= take;
-            end = at > end ? at : end;
-            free_at[0].n -= take;
-            if (free_at[0].n == 0) {
-                for (int k = 1; k < groups; ++k) free_at[k - 1] = free_at[k];
-                --groups;
-            }
-            int k = groups;
-            while (k > 0 && free_at[k - 1].at > at) --k;
-            if (k > 0 && at - free_at[k - 1].at < 1e-6) { free_at[k - 1].n += take; continue; }
-            if (groups == kMost) { free_at[k > 0 ? k - 1 : 0].n += take; continue; }      // (as good as free then)
-            for (int q = groups; q > k; --q) free_at[q] = free_at[q - 1];
-            free_at[k] = {at, take};
-            ++groups;
-        }
-    }
-    return end;
-}
-
 // Contractions on tiles of two wavefront groups (TurnTile), microseconds: a 256 x 256 x 64 slice 1.38, 13 beside the slices (first
-// slice, epilogue), 6 more where the item adds to its output, 0.66 of all that where half of its columns lie behind the matrix.
+// slice, epilogue), 6 more where the item adds to its output.  A last column tile whose second half lies behind the matrix takes 0.66
+// of that, which is counted on in launches of four rounds and more: items go out in the order of their rows, not the short ones last
+// (19 x 14 tiles at D = 3456, 266 items, rated as if the 19 halves filled in: 248 -> 267 us a step).
 // Rated / measured: 1008 items of 32 x 40 tiles at D = 3584 859 / 866, 768 of 64 x 32 at D = 2048 758 / 789, 1120 of 16 x 64 at D = 3584
 // 741 / 720, 512 of 16 x 16 at D = 4096 212 / 228, 256 of 32 x 32 at D = 896 196 / 181.
 struct TurnModel {
     int64_t cus, D;
     // Launches of fewer items leave too many compute units idle (128 items where 256 x 128 tiles are 256: 105 us for 77): not rated.
     bool enough(int64_t tiles) const { return 5 * tiles * ((D + 255) / 256) >= 3 * cus; }
-    static double item(double slices, bool half, bool beta) { return (half ? 0.66 : 1.0) * (slices * 1.38 + 13.0 + (beta ? 6.0 : 0.0)); }
+    static double item(double slices, bool beta) { return slices * 1.38 + 13.0 + (beta ? 6.0 : 0.0); }
     // a x b tiles of 256, reductions of s_dh and s_dw slices in parts_h and parts_w parts.  FLOOR: a bound it never falls below.
     template <bool FLOOR = false>
     double us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
-        const int64_t all = (D + 255) / 256, half = D % 256 != 0 && D % 256 <= 128 ? 1 : 0;
-        if (FLOOR || half == 0) {
-            const double c_dh = item((double)s_dh, false, dh_beta), c_dw = item((double)s_dw, false, dw_beta);
-            const int64_t n_dh = a * parts_h, n_dw = b * parts_w;
-            if (!FLOOR) return makespan(cus, n_dh * all, c_dh, n_dw * all, c_dw);
-            const double whole = makespan_floor(cus, n_dh * (all - half), c_dh, n_dw * (all - half), c_dw);
-            if (half == 0) return whole;
-            const double even = ((double)n_dh * c_dh + (double)n_dw * c_dw) * ((double)all - 0.34) / (double)cus;
-            const double each = (double)(((n_dh + n_dw) * all + cus - 1) / cus) * 0.66 * (c_dh < c_dw ? c_dh : c_dw);
-            const double most = even > each ? even : each;
-            return whole > most ? whole : most;
-        }
-        ItemClass c[4] = {{item((double)s_dh, false, dh_beta), a * parts_h * (all - half)}, {item((double)s_dh, true, dh_beta), a * parts_h * half},
-                          {item((double)s_dw, false, dw_beta), b * parts_w * (all - half)}, {item((double)s_dw, true, dw_beta), b * parts_w * half}};
-        return item_makespan(cus, c, 4);
+        const int64_t across = (D + 255) / 256, n_dh = a * parts_h * across, n_dw = b * parts_w * across;
+        const double c_dh = item((double)s_dh, dh_beta), c_dw = item((double)s_dw, dw_beta);
+        const bool halves = D % 256 != 0 && D % 256 <= 128 && n_dh + n_dw >= 4 * cus;
+        const double whole = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
+        return halves ? whole * ((double)across - 0.34) / (double)across : whole;
     }
 };
 
@@ -574,7 +532,7 @@ struct ScheduleModel {
         return us;
     }
     // The same of a x b tiles in parts_h and parts_w parts where tiles of two wavefront groups may be taken: the faster ones.  The form
-    // with the lower floor is priced first, the other one only if its floor is 5 % below that.
+    // with the lower floor is priced first, the other one only if its floor is 7 % below that.
     template <bool FLOOR>
     double with_turns_us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, bool split, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
         const TurnModel turn{cus, D};
@@ -587,7 +545,7 @@ struct ScheduleModel {
         double us = first ? f_turn : f_other;
         if (FLOOR) return us;
         us = first ? turn.us(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta) : contractions(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta);
-        if ((first ? f_other : f_turn) * 1.05 >= us) return us;
+        if ((first ? f_other : f_turn) * 1.07 >= us) return us;
         const double other = first ? contractions(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta) : turn.us(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta);
         return other < us ? other : us;
     }
@@ -853,11 +811,11 @@ static bool may_skip_backward(const Plan& p, int64_t D) {
 // tilings, tiles and accumulators keep the Plan's order.  Nothing that takes `limit` or longer is looked for.
 // A shape that is seen once pays for this search, so orders whose floor is not below the best so far
 // are passed over: of the thousands of orders a few hundred are priced, the one chosen stays the same.
-static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out, double limit = 1e300) {
+static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out, double limit = 1e300, bool may_turn = true) {
     const int cus = device_cu_count();
     Schedule best = {};
     const int TT = p.TT, VT = p.VT;
-    const bool turns = (double)N * (double)D * (double)V >= 2e10;      // (smaller ones have too few tiles of 256 for them)
+    const bool turns = may_turn && (double)N * (double)D * (double)V >= 2e10;      // (smaller ones have too few tiles of 256 for them)
     const size_t region = (compact ? p.off_count : p.total) - p.off_dhacc;
     {   // the Plan's order under the same model
         const ScheduleModel m = ScheduleModel(cus, D, gemm_tile_of_kind(p.gemm_kind), compact).with_turns(turns);
@@ -1022,14 +980,14 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
 // both forms of the backward.  (Where only one form is rated so the model is not sure enough: of 13 such
 // shapes added to dW, nine gained 5 ... 28 % on the larger layout and 40 x 2240 x 108256 and 58 x 1408 x 95496 lost 3 and 5.)
 // Kept per thread for the last shapes, the oldest goes first.
-static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc) {
+static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc, bool may_turn = true) {
     Plan roomy;
     const bool room = room_for_planes(*p, D, &roomy) && roomy.total <= workspace_bytes;
     const int cus = device_cu_count(), f = dw_free ? 1 : 0;
     // chosen: basic or roomy (or not decided); order[form] of the chosen layout, or of the basic one before that
     enum Layout { kOpen, kBasic, kRoomy };
     struct Key {
-        int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, room, valid;
+        int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, room, may_turn, valid;
         Layout layout; bool have[2]; Schedule order[2];
     };
     constexpr int kCached = 16;
@@ -1038,27 +996,27 @@ static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact
     Key* k = nullptr;
     for (Key& c : cache)
         if (c.valid && c.N == N && c.D == D && c.V == V && c.total == p->total && c.budget == p->budget && c.cus == cus &&
-            c.forced == p->forced && c.compact == compact && c.room == room) k = &c;
+            c.forced == p->forced && c.compact == compact && c.room == room && c.may_turn == may_turn) k = &c;
     if (!k) {
         k = &cache[cache_next];
         cache_next = (cache_next + 1) % kCached;
         k->N = N; k->D = D; k->V = V; k->total = p->total; k->budget = p->budget; k->cus = cus;
-        k->forced = p->forced; k->compact = compact; k->room = room; k->valid = true;
+        k->forced = p->forced; k->compact = compact; k->room = room; k->may_turn = may_turn; k->valid = true;
         k->layout = room ? kOpen : kBasic;
         k->have[0] = k->have[1] = false;
     }
     auto basic = [&](int form) {
-        if (!k->have[form]) make_schedule(*p, N, D, V, compact, form != 0, &k->order[form]);
+        if (!k->have[form]) make_schedule(*p, N, D, V, compact, form != 0, &k->order[form], 1e300, may_turn);
         k->have[form] = true;
     };
     if (k->layout != kRoomy) basic(f);
     if (k->layout == kOpen) {
         Schedule own, other;
-        make_schedule(roomy, N, D, V, compact, f != 0, &own, 0.9 * k->order[f].us);
+        make_schedule(roomy, N, D, V, compact, f != 0, &own, 0.9 * k->order[f].us, may_turn);
         k->layout = kBasic;
         if (own.use) {
             basic(1 - f);
-            make_schedule(roomy, N, D, V, compact, f == 0, &other, 0.9 * k->order[1 - f].us);
+            make_schedule(roomy, N, D, V, compact, f == 0, &other, 0.9 * k->order[1 - f].us, may_turn);
             if (other.use) {
                 k->layout = kRoomy;
                 k->order[f] = own;
@@ -1178,10 +1136,12 @@ static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, in
     return best;
 }
 
-// Modelled time of the backward that plan_backward would choose in a workspace of the size asked for.
+// Modelled time of the backward that plan_backward would choose in a workspace of the size asked for, without tiles of two wavefront
+// groups: the choice of row skipping stays the one that was measured (rated with them, 4612 x 3456 x 1820 with 2767 valid rows no longer
+// skips them and takes 264 us for 243).
 static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free) {
     Schedule s;
-    plan_backward(&p, N, D, V, compact, dw_free, (size_t)-1, &s);
+    plan_backward(&p, N, D, V, compact, dw_free, (size_t)-1, &s, false);
     return s.us;
 }
 
