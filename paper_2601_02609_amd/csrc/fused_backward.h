@@ -89,6 +89,10 @@ __device__ __forceinline__ void fused_item(const FusedArgs& a, int item, CCE_LDS
         if (!DW) {
             const FusedToken t = fused_token(a, row);
             nl2[b] = t.nl2; sp[b] = t.sp; ncs[b] = t.ncs; ch[b] = t.ch; label[b] = t.label;
+            if (t.nl2 == -INFINITY) {                           // takes no part: a gradient of zero whatever its hidden row holds
+#pragma unroll
+                for (int k = 0; k < KS; ++k) s[b][k] = __builtin_bit_cast(bf16x8, i32x4{0, 0, 0, 0});
+            }
         }
     }
     f32x4 out[DB][RB];

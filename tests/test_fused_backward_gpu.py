@@ -73,3 +73,23 @@ def test_fused_backward_matches_torch_and_chunks(N, V, form, D):
         if valid.any():
             assert rel(dH, r_dH) <= 1e-2 and rel(dW, r_dW) <= 1e-2, (forced, rel(dH, r_dH), rel(dW, r_dW))
     assert rel(got[0][1], got[1][1]) <= 1e-5 and rel(got[0][0], got[1][0]) <= 1e-3, (rel(got[0][1], got[1][1]), rel(got[0][0], got[1][0]))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_ignored_rows_of_nan_have_zero_gradients(D):
+    """dHidden alone: such rows meet dW's contraction, as they do over a chunk."""
+    from paper_2601_02609_amd import binding as B
+    N, V = 300, 700
+    g = torch.Generator(device="cuda").manual_seed(D)
+    H = torch.randn(N, D, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, D, device="cuda", generator=g) * (2.5 / D ** 0.5)).bfloat16()
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    y[::3] = IGN
+    lse = torch.logsumexp(H.float() @ W.float().t(), 1)
+    dl = torch.full((N,), 1.0 / N, device="cuda")
+    ws = B.alloc_workspace(N, D, V)
+    clean, _ = B.cce_backward(H, W, y, lse, dl, IGN, workspace=ws)
+    H[::3] = float("nan")
+    dH, _ = B.cce_backward(H, W, y, lse, dl, IGN, workspace=ws)
+    torch.cuda.synchronize()
+    assert not dH[::3].any() and torch.equal(dH, clean)
