@@ -1739,6 +1739,12 @@ template <class Cfg> constexpr int grad_tile_lds() {
 }
 constexpr int kGradTileLds = grad_tile_lds<TileBig>();       // (FP8 logits)
 
+template <int D, bool SHARED>
+static bool allow_fused_lds() {
+    return allow_big_lds(fused_backward_kernel<D, SHARED, false>, FusedTile<D, SHARED>::kLdsBytes) &&
+           allow_big_lds(fused_backward_kernel<D, SHARED, true>, FusedTile<D, SHARED>::kLdsBytes);
+}
+
 // The MFMA kernels use more dynamic LDS than the default limit: raise it once per device
 // (not per call, so that the compute calls consist of kernel launches only).
 static bool ensure_kernel_attributes() {
@@ -1790,10 +1796,10 @@ static bool ensure_kernel_attributes() {
     if (!allow_big_lds(grad_gemm_kernel<TurnTile, 3>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TurnTile, 4>, TurnTile::kLdsBytes)) return false;
     if (!allow_big_lds(grad_gemm_kernel<TurnTile, 9>, TurnTile::kLdsBytes + kTurnTableBytes)) return false;
-    if (!allow_big_lds(fused_backward_kernel<64, false>, FusedTile<64, false>::kLdsBytes)) return false;
-    if (!allow_big_lds(fused_backward_kernel<64, true>, FusedTile<64, true>::kLdsBytes)) return false;
-    if (!allow_big_lds(fused_backward_kernel<128, false>, FusedTile<128, false>::kLdsBytes)) return false;
-    if (!allow_big_lds(fused_backward_kernel<128, true>, FusedTile<128, true>::kLdsBytes)) return false;
+    if (!allow_fused_lds<64, false>()) return false;
+    if (!allow_fused_lds<64, true>()) return false;
+    if (!allow_fused_lds<128, false>()) return false;
+    if (!allow_fused_lds<128, true>()) return false;
     done[dev] = true;
     return true;
 }
@@ -1854,6 +1860,13 @@ static void launch_counted_contractions(int kind, bool turn, const GemmJob& firs
         hipLaunchKernelGGL((grad_gemm_kernel<TileSmall, 9>), dim3(work), dim3(kThreads), kGemmLdsSmall + kRowTableBytes, stream, first, second);
     else
         hipLaunchKernelGGL((grad_gemm_kernel<TileNarrow, 9>), dim3(work), dim3(kThreads), kGemmLdsNarrow + kRowTableBytes, stream, first, second);
+}
+
+template <int D, bool SHARED>
+static void launch_fused(const FusedArgs& a, int dh_first, hipStream_t stream) {
+    const dim3 grid((unsigned)(a.n_h + a.n_w));
+    if (a.label_smoothing == 0.f) hipLaunchKernelGGL((fused_backward_kernel<D, SHARED, false>), grid, dim3(256), (FusedTile<D, SHARED>::kLdsBytes), stream, a, dh_first);
+    else hipLaunchKernelGGL((fused_backward_kernel<D, SHARED, true>), grid, dim3(256), (FusedTile<D, SHARED>::kLdsBytes), stream, a, dh_first);
 }
 
 // A launch of one or both contractions (modes 0, 1 and 4 of grad_gemm_kernel).
@@ -2298,11 +2311,10 @@ static void run_fused(const FusedChoice& f, const Plan& p, const void* hidden, c
     const int dh_first = f.len_h >= f.len_w ? 1 : 0;
     {
         ProfSpan span(CCE_KERNEL_GRAD_GEMM, stream);
-        const dim3 grid((unsigned)(f.n_h + f.n_w));
-        if (D == 64 && f.shared) hipLaunchKernelGGL((fused_backward_kernel<64, true>), grid, dim3(256), (FusedTile<64, true>::kLdsBytes), stream, a, dh_first);
-        else if (D == 64) hipLaunchKernelGGL((fused_backward_kernel<64, false>), grid, dim3(256), (FusedTile<64, false>::kLdsBytes), stream, a, dh_first);
-        else if (f.shared) hipLaunchKernelGGL((fused_backward_kernel<128, true>), grid, dim3(256), (FusedTile<128, true>::kLdsBytes), stream, a, dh_first);
-        else hipLaunchKernelGGL((fused_backward_kernel<128, false>), grid, dim3(256), (FusedTile<128, false>::kLdsBytes), stream, a, dh_first);
+        if (D == 64 && f.shared) launch_fused<64, true>(a, dh_first, stream);
+        else if (D == 64) launch_fused<64, false>(a, dh_first, stream);
+        else if (f.shared) launch_fused<128, true>(a, dh_first, stream);
+        else launch_fused<128, false>(a, dh_first, stream);
     }
     if (f.parts_h > 1) {
         const int64_t groups = N * (D / 4);

@@ -93,3 +93,34 @@ def test_ignored_rows_of_nan_have_zero_gradients(D):
     dH, _ = B.cce_backward(H, W, y, lse, dl, IGN, workspace=ws)
     torch.cuda.synchronize()
     assert not dH[::3].any() and torch.equal(dH, clean)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,V,mean,eps", [(301, 701, False, 0.0), (301, 701, False, 0.1), (1023, 259, True, 0.0), (9001, 9001, False, 0.0),
+                                          (9001, 9001, False, 0.1)])
+def test_rows_that_take_no_part_may_overflow(N, V, mean, eps, D):
+    """Any finite hidden values, also such that a logit overflows fp32, in ignored rows and rows with a bad label, the last row among
+    them (ragged tiles repeat it): the bits of the same call with those rows zero."""
+    from paper_2601_02609_amd import binding as B
+    print(f"[overflow] N={N} D={D} V={V} smoothing={eps}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N + D)
+    H = torch.randn(N, D, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, D, device="cuda", generator=g) * (2.5 / D ** 0.5)).bfloat16()
+    y = torch.randint(0, V, (N,), device="cuda", generator=g, dtype=torch.int32)
+    out = torch.rand(N, device="cuda", generator=g) < 0.2
+    out[-1] = True
+    y[out] = torch.tensor([IGN, V, -7], device="cuda", dtype=torch.int32)[torch.arange(int(out.sum()), device="cuda") % 3]
+    H[out] = 0.0
+    lse = torch.logsumexp(H.float() @ W.float().t(), 1)
+    dl = torch.full((N,), 1.0 / N, device="cuda")
+    ws = B.alloc_workspace(N, D, V)
+    signs = torch.randint(0, 2, (int(out.sum()), D), device="cuda", generator=g).float().mul_(2.0).sub_(1.0) * 3e38
+    assert not torch.isfinite(signs @ W.float().t()).all()
+    got = []
+    for rows in (torch.zeros_like(signs), signs):
+        H[out] = rows.bfloat16()
+        got.append(B.cce_backward_ex(H, W, y, lse, None if mean else dl, IGN, label_smoothing=eps, workspace=ws))
+    torch.cuda.synchronize()
+    (dH0, dW0), (dH, dW) = got
+    assert torch.isfinite(dW).all() and torch.isfinite(dH.float()).all()
+    assert torch.equal(dH, dH0) and torch.equal(dW, dW0) and not dH[out].any()
