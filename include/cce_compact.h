@@ -23,8 +23,8 @@
  * are those of the kept rows only -- check cce_read_status where the bound is not certain.
  * The hidden row of a row that is not valid is never loaded by these calls, so it may hold
  * anything, NaN and Inf included (cce_forward / cce_backward ask for finite values there: small calls compute every row).  (Where the calls
- * decide not to skip rows, see cce_get_row_skipping, every row is processed and nothing is
- * dropped or flagged.)  max_valid_rows >= N
+ * decide not to skip rows, see cce_get_row_skipping, every row is processed, as by cce_forward / cce_backward, and
+ * nothing is dropped or flagged.)  max_valid_rows >= N
  * is allowed (nothing is skipped then).
  */
 #ifndef CCE_COMPACT_H_

@@ -1143,7 +1143,12 @@ static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, in
 // Modelled time of the backward that plan_backward would choose in a workspace of the size asked for, without tiles of two wavefront
 // groups: the choice of row skipping stays the one that was measured (rated with them, 4612 x 3456 x 1820 with 2767 valid rows no longer
 // skips them and takes 264 us for 243).
+// Over all rows at D = 64 and 128 it is the one without a gradient chunk.
 static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free) {
+    if (!compact) {
+        const FusedChoice f = fused_backward_choice(p, N, D, V);
+        if (f.use) return f.us;
+    }
     Schedule s;
     plan_backward(&p, N, D, V, compact, dw_free, (size_t)-1, &s, false);
     return s.us;
@@ -1160,6 +1165,8 @@ static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact,
 // and calls that lost 7 ... 13 % against skipping (1402 x 2432 x 112762 with 1191 valid: 3054 us for 3454); 6 % on the
 // sum of both: 1.0 %, but 4 ... 9 % lost where only one form gains (4974 x 384 x 124212 with 4477 valid).  At 4 % the
 // model is wrong too often (16384 x 2048 x 151936 with 15565 valid, rated 0.956, takes 1.07).
+// At D = 64 and 128 all rows without a chunk are the faster ones up to some 60 % ignored: of 44 shapes with 5 ... 80 % two skip, the
+// faster form each time (8699 x 64 x 68133 with 80 % 332 us for 481, 24548 x 64 x 92355 with 5 % 4 575 for 1 767).
 static bool skipping_pays(const Plan& plain, const Plan& comp, int64_t N, int64_t M, int64_t D, int64_t V) {
     const ForwardCost fwd{device_cu_count(), D};
     double least = 1e300, most = 0.0;

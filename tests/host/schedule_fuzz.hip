@@ -314,6 +314,21 @@ static void check_row_skipping_modes() {
     g_force_row_skipping.store(0);
 }
 
+// Row skipping is rated against the backward that all rows take: at D = 64 and 128 the one without a gradient chunk.
+static void check_skipping_is_rated() {
+    const struct { int64_t N, D, V, M; bool skip; } calls[] = {
+        {8192, 64, 151936, 6963, false}, {8192, 128, 151936, 6963, false}, {22053, 128, 77882, 18745, false}, {2000, 64, 50000, 1500, false},
+        {4000, 128, 20000, 2400, false}, {30884, 64, 23325, 23163, false}, {8699, 64, 68133, 1740, true}, {4791, 128, 54305, 958, true},
+        {8192, 896, 151936, 6963, true}, {32768, 3584, 151936, 31130, false}, {16384, 2048, 151936, 15565, false}};
+    for (auto& c : calls) {
+        Plan p;
+        bool skip = !c.skip;
+        if (plan_row_skipping(c.N, c.D, c.V, c.M, 0, &p, &skip) && skip == c.skip) continue;
+        ++failures;
+        fprintf(stderr, "FAIL row skipping %lld x %lld x %lld with %lld valid rows: %d\n", (long long)c.N, (long long)c.D, (long long)c.V, (long long)c.M, (int)skip);
+    }
+}
+
 int main(int argc, char** argv) {
     if (argc > 2) {                          // N D V M dw_free, any number of times
         for (int i = 1; i + 4 < argc; i += 5) print_form(atoll(argv[i]), atoll(argv[i + 1]), atoll(argv[i + 2]), atoll(argv[i + 3]), atoi(argv[i + 4]) != 0);
@@ -324,6 +339,7 @@ int main(int argc, char** argv) {
     check_planning_cost();
     check_scan_is_priced();
     check_row_skipping_modes();
+    check_skipping_is_rated();
     // shapes the schedules exist for: few rows against a full vocabulary; a small vocabulary
     bool dw_free = true; int64_t N = 509, D = 896, V = 151936, B = 0;
     CHECK(check(N, D, V, B, dw_free));
