@@ -811,11 +811,11 @@ static bool may_skip_backward(const Plan& p, int64_t D) {
 // tilings, tiles and accumulators keep the Plan's order.  Nothing that takes `limit` or longer is looked for.
 // A shape that is seen once pays for this search, so orders whose floor is not below the best so far
 // are passed over: of the thousands of orders a few hundred are priced, the one chosen stays the same.
-static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out, double limit = 1e300, bool may_turn = true) {
+static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, Schedule* out, double limit = 1e300) {
     const int cus = device_cu_count();
     Schedule best = {};
     const int TT = p.TT, VT = p.VT;
-    const bool turns = may_turn && (double)N * (double)D * (double)V >= 2e10;      // (smaller ones have too few tiles of 256 for them)
+    const bool turns = (double)N * (double)D * (double)V >= 2e10;      // (smaller ones have too few tiles of 256 for them)
     const size_t region = (compact ? p.off_count : p.total) - p.off_dhacc;
     {   // the Plan's order under the same model
         const ScheduleModel m = ScheduleModel(cus, D, gemm_tile_of_kind(p.gemm_kind), compact).with_turns(turns);
@@ -980,14 +980,14 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
 // both forms of the backward.  (Where only one form is rated so the model is not sure enough: of 13 such
 // shapes added to dW, nine gained 5 ... 28 % on the larger layout and 40 x 2240 x 108256 and 58 x 1408 x 95496 lost 3 and 5.)
 // Kept per thread for the last shapes, the oldest goes first.
-static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc, bool may_turn = true) {
+static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free, size_t workspace_bytes, Schedule* sc) {
     Plan roomy;
     const bool room = room_for_planes(*p, D, &roomy) && roomy.total <= workspace_bytes;
     const int cus = device_cu_count(), f = dw_free ? 1 : 0;
     // chosen: basic or roomy (or not decided); order[form] of the chosen layout, or of the basic one before that
     enum Layout { kOpen, kBasic, kRoomy };
     struct Key {
-        int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, room, may_turn, valid;
+        int64_t N, D, V; size_t total, budget; int cus; bool forced, compact, room, valid;
         Layout layout; bool have[2]; Schedule order[2];
     };
     constexpr int kCached = 16;
@@ -996,27 +996,27 @@ static void plan_backward(Plan* p, int64_t N, int64_t D, int64_t V, bool compact
     Key* k = nullptr;
     for (Key& c : cache)
         if (c.valid && c.N == N && c.D == D && c.V == V && c.total == p->total && c.budget == p->budget && c.cus == cus &&
-            c.forced == p->forced && c.compact == compact && c.room == room && c.may_turn == may_turn) k = &c;
+            c.forced == p->forced && c.compact == compact && c.room == room) k = &c;
     if (!k) {
         k = &cache[cache_next];
         cache_next = (cache_next + 1) % kCached;
         k->N = N; k->D = D; k->V = V; k->total = p->total; k->budget = p->budget; k->cus = cus;
-        k->forced = p->forced; k->compact = compact; k->room = room; k->may_turn = may_turn; k->valid = true;
+        k->forced = p->forced; k->compact = compact; k->room = room; k->valid = true;
         k->layout = room ? kOpen : kBasic;
         k->have[0] = k->have[1] = false;
     }
     auto basic = [&](int form) {
-        if (!k->have[form]) make_schedule(*p, N, D, V, compact, form != 0, &k->order[form], 1e300, may_turn);
+        if (!k->have[form]) make_schedule(*p, N, D, V, compact, form != 0, &k->order[form]);
         k->have[form] = true;
     };
     if (k->layout != kRoomy) basic(f);
     if (k->layout == kOpen) {
         Schedule own, other;
-        make_schedule(roomy, N, D, V, compact, f != 0, &own, 0.9 * k->order[f].us, may_turn);
+        make_schedule(roomy, N, D, V, compact, f != 0, &own, 0.9 * k->order[f].us);
         k->layout = kBasic;
         if (own.use) {
             basic(1 - f);
-            make_schedule(roomy, N, D, V, compact, f == 0, &other, 0.9 * k->order[1 - f].us, may_turn);
+            make_schedule(roomy, N, D, V, compact, f == 0, &other, 0.9 * k->order[1 - f].us);
             if (other.use) {
                 k->layout = kRoomy;
                 k->order[f] = own;
@@ -1140,17 +1140,15 @@ static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, in
     return best;
 }
 
-// Modelled time of the backward that plan_backward would choose in a workspace of the size asked for, without tiles of two wavefront
-// groups: the choice of row skipping stays the one that was measured (rated with them, 4612 x 3456 x 1820 with 2767 valid rows no longer
-// skips them and takes 264 us for 243).
-// Over all rows at D = 64 and 128 it is the one without a gradient chunk.
+// Modelled time of the backward that a call would run in a workspace of the size asked for: plan_backward's order, or over all rows at
+// D = 64 and 128 the launch without a gradient chunk.
 static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact, bool dw_free) {
     if (!compact) {
         const FusedChoice f = fused_backward_choice(p, N, D, V);
         if (f.use) return f.us;
     }
     Schedule s;
-    plan_backward(&p, N, D, V, compact, dw_free, (size_t)-1, &s, false);
+    plan_backward(&p, N, D, V, compact, dw_free, (size_t)-1, &s);
     return s.us;
 }
 
@@ -1159,24 +1157,23 @@ static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact,
 // launches worse.  `comp` is the plan for M compact rows, `plain` the one for all N.  15 us stand for the small
 // launches (500 x 256 x 3000 with 300 valid rows: 29 -> 43 us, 1500 x 512 x 2000 with 900: 41 -> 53).  The forward
 // and the workspace query do not know whether the backward will overwrite dW or add to it, and the two run in
-// different orders: skipping is taken where the schedules' model rates one of the two 6 % faster and the other
-// no slower.  Over 130 drawn shapes with 5 ... 60 % of the rows ignored, both forms timed, that is 0.8 % above the
-// better side on average, with one choice slower than all rows (1.02).  The overwriting form alone, with 30 us: 1.8 %,
-// and calls that lost 7 ... 13 % against skipping (1402 x 2432 x 112762 with 1191 valid: 3054 us for 3454); 6 % on the
-// sum of both: 1.0 %, but 4 ... 9 % lost where only one form gains (4974 x 384 x 124212 with 4477 valid).  At 4 % the
-// model is wrong too often (16384 x 2048 x 151936 with 15565 valid, rated 0.956, takes 1.07).
+// different orders: skipping is taken where the schedules' model, with the tiles that each would run, rates it 3.3 % faster on the mean
+// of the two.  Of 3700 drawn shapes of D 192 to 4096 with 5 ... 60 % of the rows ignored this answers 120 otherwise than ratings without tiles of
+// two wavefront groups, one of the two forms 6 % faster and the other no slower: 75 of those, both forms of both calls timed, are 0.6 %
+// above the better side on average and were 8.0 (17712 x 1280 x 4257 with 15 % 654 us for 810; 8950 x 384 x 4089 with 10 % loses 5 %); 86
+// others 0.5 and 0.6 %.  At 2.5 % the model is wrong where it costs most (16384 x 2048 x 151936 with 15565 valid, rated 0.95 and
+// 0.999, takes 1.08 and 1.10).
 // At D = 64 and 128 all rows without a chunk are the faster ones up to some 60 % ignored: of 44 shapes with 5 ... 80 % two skip, the
 // faster form each time (8699 x 64 x 68133 with 80 % 332 us for 481, 24548 x 64 x 92355 with 5 % 4 575 for 1 767).
 static bool skipping_pays(const Plan& plain, const Plan& comp, int64_t N, int64_t M, int64_t D, int64_t V) {
     const ForwardCost fwd{device_cu_count(), D};
-    double least = 1e300, most = 0.0;
-    for (int dw_free = 1; dw_free >= 0 && most < 1.0; --dw_free) {
-        const double rated = (backward_us(comp, M, D, V, true, dw_free != 0) + fwd.us(comp) + 15.0) /
-                             (backward_us(plain, N, D, V, false, dw_free != 0) + fwd.us(plain));
-        least = rated < least ? rated : least;
-        most = rated > most ? rated : most;
+    double rated[2] = {0.0, 0.0};
+    for (int dw_free = 1; dw_free >= 0; --dw_free) {
+        rated[dw_free] = (backward_us(comp, M, D, V, true, dw_free != 0) + fwd.us(comp) + 15.0) /
+                         (backward_us(plain, N, D, V, false, dw_free != 0) + fwd.us(plain));
+        if (rated[1] > 1.1) return false;       // (the two are never that far apart)
     }
-    return least < 0.94 && most < 1.0;
+    return rated[0] + rated[1] < 2.0 * 0.967;
 }
 
 // Whether a call with at most M = max_valid_rows < N valid rows skips the others; mode as in

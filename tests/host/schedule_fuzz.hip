@@ -314,12 +314,14 @@ static void check_row_skipping_modes() {
     g_force_row_skipping.store(0);
 }
 
-// Row skipping is rated against the backward that all rows take: at D = 64 and 128 the one without a gradient chunk.
+// Row skipping is rated with the launches that run: over all rows at D = 64 and 128 the one without a gradient chunk, tiles of two
+// wavefront groups elsewhere.
 static void check_skipping_is_rated() {
     const struct { int64_t N, D, V, M; bool skip; } calls[] = {
         {8192, 64, 151936, 6963, false}, {8192, 128, 151936, 6963, false}, {22053, 128, 77882, 18745, false}, {2000, 64, 50000, 1500, false},
         {4000, 128, 20000, 2400, false}, {30884, 64, 23325, 23163, false}, {8699, 64, 68133, 1740, true}, {4791, 128, 54305, 958, true},
-        {8192, 896, 151936, 6963, true}, {32768, 3584, 151936, 31130, false}, {16384, 2048, 151936, 15565, false}};
+        {8192, 896, 151936, 6963, true}, {32768, 3584, 151936, 31130, false}, {16384, 2048, 151936, 15565, false},
+        {17712, 1280, 4257, 15055, true}, {4300, 1344, 11822, 3870, true}, {19587, 1472, 12343, 16649, true}, {9452, 3136, 13619, 8034, true}};
     for (auto& c : calls) {
         Plan p;
         bool skip = !c.skip;
