@@ -137,13 +137,17 @@ static double two_class_makespan(int64_t cus, int64_t n1, double c1, int64_t n2,
 static double makespan(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
     return c1 >= c2 ? two_class_makespan(cus, n1, c1, n2, c2) : two_class_makespan(cus, n2, c2, n1, c1);
 }
-// A bound that it never falls below, without the search: all work spread evenly, the rounds of the longer job, the items of the unit
-// with most of them (k = items / units, rounded up): k short ones, and one more or one of them long where the units with fewer than
-// k cannot hold all long ones.
+// A bound that it never falls below, without the search: all work spread evenly, the rounds of the longer job.
+// TIGHT: also the items of the unit with most of them (k = items / units, rounded up): k short ones, and one more or one of them long
+// where the units with fewer than k cannot hold all long ones.  It takes as long as a search does, so only tilings that the first bound leaves
+// and what would be searched are asked for it (asked for all: plans of twelve shapes 1.2 ms for 0.87, orders 3.6 for 3.1).
+enum Floor { kPrice = 0, kFloor = 1, kTightFloor = 2 };      // of a step: its time, or one of the two bounds
+template <bool TIGHT = false>
 static double makespan_floor(int64_t cus, int64_t n1, double c1, int64_t n2, double c2) {
     double most = ((double)n1 * c1 + (double)n2 * c2) / (double)cus;
     const double rounds = c1 >= c2 ? (double)((n1 + cus - 1) / cus) * c1 : (double)((n2 + cus - 1) / cus) * c2;
     most = rounds > most ? rounds : most;
+    if (!TIGHT) return most;
     const int64_t n = n1 + n2, k = (n + cus - 1) / cus, n_long = c1 >= c2 ? n1 : n2;
     const double c_long = c1 >= c2 ? c1 : c2, c_short = n1 == 0 ? c2 : n2 == 0 ? c1 : c1 < c2 ? c1 : c2;
     const double each = (double)k * c_short + (n_long > (k * cus - n) * (k - 1) ? (c_long < 2.0 * c_short ? c_long - c_short : c_short) : 0.0);
@@ -196,12 +200,12 @@ struct BackwardModel {
 
     // One step = the gradient tiles, then the contractions, of an [a x b] block of 256 x 256
     // tiles: two launches that follow each other on the caller's stream.  FLOOR: with makespan_floor.
-    template <bool FLOOR = false>
+    template <int FLOOR = kPrice>
     double step(int a, int b, bool dw_beta) const {
         const int dt = d_tiles(), per256 = 256 / tile.bm;
         const int n_dh = a * per256 * dt, n_dw = b * per256 * dt;
         const double c_dh = t_gemm(b), c_dw = t_gemm(a);
-        const double mk = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
+        const double mk = FLOOR ? makespan_floor<FLOOR == kTightFloor>(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
         // fp32 accumulator traffic of the step at ~3 TB/s
         const double bytes = (double)a * 256 * D * 8.0 + (dw_beta ? (double)b * 256 * D * 8.0 : (double)b * 256 * D * 4.0);
         return ((a * b + cus - 1) / cus) * t_tile() + mk + bytes / 3.0e6 + 4.0;
@@ -214,7 +218,7 @@ struct BackwardModel {
         return even_us + (double)(nblk * nch) * 4.0 + (double)(256 * D) / 3.0e6 * (8.0 * (double)TT * nch + (double)VT * (8.0 * nblk - 4.0));
     }
     // The whole backward of TT x VT tiles in blocks of a x b.
-    template <bool FLOOR = false>
+    template <int FLOOR = kPrice>
     double backward(int TT, int VT, int a, int b) const {
         const int nblk = (TT + a - 1) / a, a_last = TT - (nblk - 1) * a;
         const int nch = (VT + b - 1) / b, b_last = VT - (nch - 1) * b;
@@ -310,7 +314,8 @@ static bool make_plan(int64_t N, int64_t D, int64_t V, Plan* p, int64_t budget_r
                 const int nblk = (p->TT + a - 1) / a, nch = (p->VT + b - 1) / b;
                 const double split_us = acc_bytes == 2 ? (double)nblk * nch * (compact ? 9.0 : 2.0) : 0.0;
                 if (model.quick_floor(even_us, p->TT, p->VT, nblk, nch) + split_us > best_cost * kAbove) continue;
-                if (model.backward<true>(p->TT, p->VT, a, b) + split_us > best_cost * kAbove) continue;
+                if (model.backward<kFloor>(p->TT, p->VT, a, b) + split_us > best_cost * kAbove) continue;
+                if (model.backward<kTightFloor>(p->TT, p->VT, a, b) + split_us > best_cost * kAbove) continue;
                 const double cost = model.backward(p->TT, p->VT, a, b) + split_us;
                 if (cost <= best_cost) { best_cost = cost; *a_out = a; *b_out = b; }
             }
@@ -478,12 +483,12 @@ struct TurnModel {
     bool enough(int64_t tiles) const { return 5 * tiles * ((D + 255) / 256) >= 3 * cus; }
     static double item(double slices, bool beta) { return slices * 1.38 + 13.0 + (beta ? 6.0 : 0.0); }
     // a x b tiles of 256, reductions of s_dh and s_dw slices in parts_h and parts_w parts.  FLOOR: a bound it never falls below.
-    template <bool FLOOR = false>
+    template <int FLOOR = kPrice>
     double us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
         const int64_t across = (D + 255) / 256, n_dh = a * parts_h * across, n_dw = b * parts_w * across;
         const double c_dh = item((double)s_dh, dh_beta), c_dw = item((double)s_dw, dw_beta);
         const bool halves = D % 256 != 0 && D % 256 <= 128 && n_dh + n_dw >= 4 * cus;
-        const double whole = FLOOR ? makespan_floor(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
+        const double whole = FLOOR ? makespan_floor<FLOOR == kTightFloor>(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
         return halves ? whole * ((double)across - 0.34) / (double)across : whole;
     }
 };
@@ -516,13 +521,13 @@ struct ScheduleModel {
     double least_item(bool turn) const { return duo() ? 5.0 : turn ? 6.0 : item(0, false); }
     bool may_turn(int64_t a, int64_t b, int split_h, int split_w) const { return turns && TurnModel{cus, D}.enough(a * split_h + b * split_w); }
     // Both contractions of a step; *kind becomes the tile they take.  (Narrow tiles are searched for only where they could win.)
-    template <bool FLOOR = false>
+    template <int FLOOR = kPrice>
     double contractions(int64_t n_dh, int64_t s_dh, bool dh_beta, bool split, int64_t n_dw, int64_t s_dw, bool dw_beta, int* kind = nullptr) const {
         const double c_dh = item(s_dh, dh_beta), c_dw = item(s_dw, dw_beta) + (mapped ? (double)s_dw * 0.11 * slice() : 0.0);
-        const double least = makespan_floor(cus, n_dh, c_dh, n_dw, c_dw);
+        const double least = makespan_floor<FLOOR != kFloor>(cus, n_dh, c_dh, n_dw, c_dw);
         double duo_us = 1e300;
         if (duo()) {
-            duo_us = duo_makespan<FLOOR>(cus, n_dh, duo_item(s_dh, dh_beta, split), n_dw, duo_item(s_dw, dw_beta, false));
+            duo_us = duo_makespan<FLOOR != kPrice>(cus, n_dh, duo_item(s_dh, dh_beta, split), n_dw, duo_item(s_dw, dw_beta, false));
             if (kind) *kind = 3;
             if (duo_us <= least) return duo_us;
         }
@@ -533,14 +538,14 @@ struct ScheduleModel {
     }
     // The same of a x b tiles in parts_h and parts_w parts where tiles of two wavefront groups may be taken: the faster ones.  The form
     // with the lower floor is priced first, the other one only if its floor is 7 % below that.
-    template <bool FLOOR>
+    template <int FLOOR>
     double with_turns_us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, bool split, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
         const TurnModel turn{cus, D};
         if (!turn.enough(a * parts_h + b * parts_w))
             return contractions<FLOOR>(a * dt * parts_h, s_dh, dh_beta, split, b * dt * parts_w, s_dw, dw_beta);
         const int64_t n_dh = a * dt * parts_h, n_dw = b * dt * parts_w;
-        const double f_turn = turn.template us<true>(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta);
-        const double f_other = contractions<true>(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta);
+        const double f_turn = turn.template us<FLOOR ? FLOOR : kTightFloor>(a, parts_h, s_dh, dh_beta, b, parts_w, s_dw, dw_beta);
+        const double f_other = contractions<FLOOR ? FLOOR : kTightFloor>(n_dh, s_dh, dh_beta, split, n_dw, s_dw, dw_beta);
         const bool first = f_turn <= f_other;
         double us = first ? f_turn : f_other;
         if (FLOOR) return us;
@@ -553,7 +558,7 @@ struct ScheduleModel {
     // ones fill the rounds better, see tall_grad_tiles: the orders stay those that were measured with it.)
     double logit_tile() const { return (double)(D / 64) * 1.55 + 7.0; }
     // One step over a x b tiles.  FLOOR: with makespan_floor.
-    template <bool FLOOR = false>
+    template <int FLOOR = kPrice>
     double step(int64_t a, int64_t b, int split_h, int split_w, bool dh_beta, bool dw_beta, bool split = false) const {
         const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);       // K tiles per part
         const int64_t n_dh = a * dt * ceil_div(b, kh), n_dw = b * dt * ceil_div(a, kw);
@@ -693,7 +698,7 @@ struct RowBlockPlanner {
     Priced priced[1 + 64][2][2][3];
     static constexpr double kNone = 1e300;
 
-    template <bool FLOOR = false>
+    template <int FLOOR = kPrice>
     double block_us(const RowBlock& k, bool beta) const {
         const int64_t nch = (VT + k.b - 1) / k.b;
         const ScheduleModel& mm = m[k.kind];
@@ -749,7 +754,7 @@ struct RowBlockPlanner {
                         const bool beta = R < TT || !dw_free;
                         Priced& known = priced[a][split][kind][j];           // chunks in the workspace are alike for every R
                         const bool hit = known.b == k.b && known.beta == beta;
-                        if (!hit && block_us<true>(k, beta) + states[R - a].us > least * kAbove) continue;
+                        if (!hit && block_us<kFloor>(k, beta) + states[R - a].us > least * kAbove) continue;
                         const double us = hit ? known.us : block_us(k, beta);
                         known = {k.b, beta, us};
                         if (us + states[R - a].us > least * kAbove) continue;
@@ -899,7 +904,7 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                                               ? &chunk_us[kind][split_acc][v > 0][(a + c.rows - 1) / c.rows - 1][c.b] : nullptr;
                     last_us = known ? *known : 0.0;
                     const int64_t rest = VT - v / 256 - c.b;
-                    const double least = last_us > 0.0 ? last_us : (double)(a / c.rows) * m.template step<true>(c.rows, c.b, sh, sw, v > 0, later > 0 || !dw_free);
+                    const double least = last_us > 0.0 ? last_us : (double)(a / c.rows) * m.template step<kFloor>(c.rows, c.b, sh, sw, v > 0, later > 0 || !dw_free);
                     if (block_us[later] + least + (double)rest * per_tile + extra > most * kAbove) return;
                     if (last_us == 0.0)
                         for (int r = 0; r < a; r += c.rows)
