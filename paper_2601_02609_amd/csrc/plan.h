@@ -487,10 +487,12 @@ struct TurnModel {
     double us(int64_t a, int64_t parts_h, int64_t s_dh, bool dh_beta, int64_t b, int64_t parts_w, int64_t s_dw, bool dw_beta) const {
         const int64_t across = (D + 255) / 256, n_dh = a * parts_h * across, n_dw = b * parts_w * across;
         const double c_dh = item((double)s_dh, dh_beta), c_dw = item((double)s_dw, dw_beta);
-        const bool halves = D % 256 != 0 && D % 256 <= 128 && n_dh + n_dw >= 4 * cus;
         const double whole = FLOOR ? makespan_floor<FLOOR == kTightFloor>(cus, n_dh, c_dh, n_dw, c_dw) : makespan(cus, n_dh, c_dh, n_dw, c_dw);
-        return halves ? whole * ((double)across - 0.34) / (double)across : whole;
+        return halves(a * parts_h + b * parts_w) ? whole * half_columns() : whole;
     }
+    // Whether a last column tile whose second half lies behind the matrix is counted on, and what is left of the launch then.
+    bool halves(int64_t tiles) const { return D % 256 != 0 && D % 256 <= 128 && tiles * ((D + 255) / 256) >= 4 * cus; }
+    double half_columns() const { const double across = (double)((D + 255) / 256); return (across - 0.34) / across; }
 };
 
 // Time model of the schedules, microseconds, from launches timed on MI355X with random data: a
@@ -516,10 +518,20 @@ struct ScheduleModel {
     double item(int64_t slices, bool beta) const { return (double)slices * slice() + (tile.kind == 0 ? 13.0 : 9.0) + (beta ? 2.0 : 0.0); }
     double duo_item(int64_t slices, bool beta, bool split) const { return (double)slices * 1.53 + 10.0 + (beta ? 6.0 : 0.0) + (split ? 8.0 : 0.0); }
     int64_t d_tiles() const { return dt; }
-    // What an item costs at least, of either form.
-    double least_slice(bool turn) const { return turn ? (tile.kind == 0 ? 1.38 : 0.69) : duo() ? 0.765 : slice(); }
-    double least_item(bool turn) const { return duo() ? 5.0 : turn ? 6.0 : item(0, false); }
-    bool may_turn(int64_t a, int64_t b, int split_h, int split_w) const { return turns && TurnModel{cus, D}.enough(a * split_h + b * split_w); }
+    // Whether launches of at most a x b tiles may be on tiles of two wavefront groups, and the least part of their time that such a launch
+    // is rated with.
+    struct MayTurn { bool on; double part; };
+    MayTurn may_turn(int64_t a, int64_t b, int split_h, int split_w) const {
+        const TurnModel turn{cus, D};
+        const int64_t tiles = a * split_h + b * split_w;
+        const bool on = turns && turn.enough(tiles);
+        return {on, on && turn.halves(tiles) ? turn.half_columns() : 1.0};
+    }
+    // What an item costs at least, of either form: a slice and what is beside the slices of the work spread evenly, and a slice of one
+    // item's reduction.  (Tiles of two wavefront groups are 256 columns wide, two of these at 256 x 128.)
+    double least_slice(MayTurn turn) const { return turn.on ? (tile.kind == 0 ? 1.38 * turn.part : 0.69) : duo() ? 0.765 : slice(); }
+    double least_item(MayTurn turn) const { return duo() ? 5.0 : turn.on ? (tile.kind == 0 ? 13.0 * turn.part : 6.0) : item(0, false); }
+    double least_chain(MayTurn turn) const { return turn.on && tile.kind == 0 ? 1.38 * turn.part : slice(); }
     // Both contractions of a step; *kind becomes the tile they take.  (Narrow tiles are searched for only where they could win.)
     template <int FLOOR = kPrice>
     double contractions(int64_t n_dh, int64_t s_dh, bool dh_beta, bool split, int64_t n_dw, int64_t s_dw, bool dw_beta, int* kind = nullptr) const {
@@ -576,12 +588,13 @@ struct ScheduleModel {
     // at most `b_max`: all work spread evenly, the serial reduction of one item per step or all bytes at the rate
     // of HBM, and what each step costs by itself.
     double floor_us(int64_t a, int64_t b, int64_t b_max, int split_h, int split_w) const {
-        const bool turn = may_turn(a, b_max < b ? b_max : b, split_h, split_w);
+        const MayTurn turn = may_turn(a, b_max < b ? b_max : b, split_h, split_w);
         const double ab = (double)(a * b), per_item = least_item(turn);
         const double steps = (double)ceil_div(b, b_max);
         const int64_t kh = ceil_div(b, split_h), kw = ceil_div(a, split_w);
         double even = (8.0 * ab * (double)dt * least_slice(turn) + ((double)(b * ceil_div(a, kw)) + (double)a * steps) * (double)dt * per_item) / (double)cus;
-        const double dh_item = (double)(kh * 4) * slice() + steps * per_item, dw_item = steps * ((double)(kw * 4) * slice() + per_item);
+        const double chain = least_chain(turn);
+        const double dh_item = (double)(kh * 4) * chain + steps * per_item, dw_item = steps * ((double)(kw * 4) * chain + per_item);
         if (dh_item > even) even = dh_item;
         if (dw_item > even) even = dw_item;
         const double tiles_us = ab * logit_tile() / (double)cus;
@@ -592,7 +605,7 @@ struct ScheduleModel {
     }
     // The part of it that grows with the width, per vocabulary tile.
     double floor_per_tile(int64_t a, int64_t b_max, int split_h, int split_w) const {
-        const bool turn = may_turn(a, b_max, split_h, split_w);
+        const MayTurn turn = may_turn(a, b_max, split_h, split_w);
         const double per_item = least_item(turn), steps = 1.0 / (double)b_max;
         return (double)a * logit_tile() / (double)cus + 8.0 * steps +
                (8.0 * (double)a * (double)dt * least_slice(turn) + (1.0 + (double)a * steps) * (double)dt * per_item) / (double)cus;
@@ -906,9 +919,20 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
                     const int64_t rest = VT - v / 256 - c.b;
                     const double least = last_us > 0.0 ? last_us : (double)(a / c.rows) * m.template step<kFloor>(c.rows, c.b, sh, sw, v > 0, later > 0 || !dw_free);
                     if (block_us[later] + least + (double)rest * per_tile + extra > most * kAbove) return;
-                    if (last_us == 0.0)
-                        for (int r = 0; r < a; r += c.rows)
-                            last_us += m.step(a - r < c.rows ? a - r : c.rows, c.b, sh, sw, v > 0, later > 0 || r > 0 || !dw_free, split_acc != 0) + (split_acc ? 2.0 : 0.0);
+                    if (last_us == 0.0) {
+                        double step_us = 0.0;
+                        int step_rows = 0;
+                        bool step_beta = false;                 // (the row parts behind the first one are alike but for the last)
+                        for (int r = 0; r < a; r += c.rows) {
+                            const int rows = a - r < c.rows ? a - r : c.rows;
+                            const bool beta = later > 0 || r > 0 || !dw_free;
+                            if (rows != step_rows || beta != step_beta)
+                                step_us = m.step(rows, c.b, sh, sw, v > 0, beta, split_acc != 0) + (split_acc ? 2.0 : 0.0);
+                            step_rows = rows;
+                            step_beta = beta;
+                            last_us += step_us;
+                        }
+                    }
                     if (known) *known = last_us;
                     last = c;
                 }

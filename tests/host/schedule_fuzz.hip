@@ -192,6 +192,45 @@ static void check_makespan() {
     }
 }
 
+// The bounds that pass orders over against the priced time of orders: steps over all rows, or over a part of them, in chunks of any width
+// up to the widest.
+static void check_floors() {
+    int bad = 0;
+    for (int it = 0; it < 40000; ++it) {
+        const int64_t D = 64 * (it % 2 ? pick(1, 16) : pick(1, 64)), a = it % 3 ? pick(1, 40) : pick(1, 128), vt = pick(1, 300), widest = pick(1, it % 4 ? 64 : 300);
+        const int kind = (int)pick(0, 1), sh = (int)(it % 5 ? 1 : pick(1, 8)), sw = (int)(it % 7 ? 1 : pick(1, 8));
+        const bool turns = pick(0, 3) > 0, mapped = pick(0, 7) == 0, split = sh == 1 && pick(0, 1), dw_free = pick(0, 1);
+        const int parts = (int)(it % 11 ? 1 : pick(1, 4));
+        const ScheduleModel m = ScheduleModel(256, D, gemm_tile_of_kind(kind), mapped).with_turns(turns);
+        const int64_t rows = (a + parts - 1) / parts;
+        double us = 0.0;
+        for (int64_t v = 0; v < vt; ) {
+            int64_t b = pick(1, widest);
+            b = it % 2 ? widest : b;
+            b = b < vt - v ? b : vt - v;
+            for (int64_t r = 0; r < a; r += rows) {
+                const int64_t t = a - r < rows ? a - r : rows;
+                const double s = m.step(t, b, sh, sw, v > 0, r > 0 || !dw_free, split);
+                if (m.step<kFloor>(t, b, sh, sw, v > 0, r > 0 || !dw_free, split) > s * kAbove) bad |= 1;
+                if (m.step<kTightFloor>(t, b, sh, sw, v > 0, r > 0 || !dw_free, split) > s * kAbove) bad |= 2;
+                us += s;
+            }
+            v += b;
+        }
+        const int64_t most = widest < vt ? widest : vt;
+        if (m.floor_us(a, vt, most, sh, sw) > us * kAbove) bad |= 4;
+        if ((double)vt * m.floor_per_tile(a, most, sh, sw) > us * kAbove) bad |= 8;
+        if (bad) {
+            ++failures;
+            fprintf(stderr, "FAIL floor %d: D=%lld %lld x %lld in %lld, parts %d %d, row parts %d, kind %d turns %d mapped %d split %d: %.1f, %.1f per tile, %.1f\n", bad, (long long)D,
+                    (long long)a, (long long)vt, (long long)widest, sh, sw, parts, kind, (int)turns, (int)mapped, (int)split, m.floor_us(a, vt, most, sh, sw),
+                    (double)vt * m.floor_per_tile(a, most, sh, sw), us);
+            if (failures > 12) return;
+            bad = 0;
+        }
+    }
+}
+
 // What planning a backward for a shape seen once may cost: callers whose row count changes with every
 // batch pay it in front of their launches.  Counted in makespans searched for, which is what pricing an order
 // costs (the bounds that pass orders over are a few products each); limits a quarter above today's.
@@ -338,6 +377,7 @@ int main(int argc, char** argv) {
     }
     const int iters = argc > 1 ? atoi(argv[1]) : 2000;
     check_makespan();
+    check_floors();
     check_planning_cost();
     check_scan_is_priced();
     check_row_skipping_modes();
