@@ -2173,8 +2173,7 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
             const int64_t cols = V - v0 < (int64_t)v_tiles * 256 ? V - v0 : (int64_t)v_tiles * 256;
             const bool last = v0 + cols >= V;
             const int ldg = v_tiles * 256;
-            const int kh = (v_tiles + sc.split_h - 1) / sc.split_h;
-            const int n_split_h = (v_tiles + kh - 1) / kh;
+            int n_split_h = 1;
             // Steps over ch.rows row tiles each, all of the block's rows where the chunk is wide enough.
             for (int64_t s0 = 0; s0 < rows; s0 += (int64_t)ch.rows * 256) {
                 const int64_t srows = rows - s0 < (int64_t)ch.rows * 256 ? rows - s0 : (int64_t)ch.rows * 256;
@@ -2183,14 +2182,13 @@ static void run_schedule(const Schedule& sc, const void* hidden, const void* wei
                 const uint16_t* h_step = h_rows + (size_t)s0 * D;
                 const size_t g_bytes = (size_t)row_tiles * 256 * (size_t)ldg * 2;
                 // parts of the two reductions, in whole tiles of 256
-                const int kw = (row_tiles + sc.split_w - 1) / sc.split_w;
-                const int n_split_w = (row_tiles + kw - 1) / kw;
-                const bool dw_beta = row0 > 0 || accumulate_dW;
-                const int kind = counted ? counted_contraction_kind(sc.kind, D, row_tiles, v_tiles, d_tiles, planes_written > 0, dw_beta, knobs)
-                                         : contraction_kind(sc.kind, D, (int64_t)row_tiles * n_split_h * d_tiles, kh * 4, planes_written > 0, sc.split_acc != 0,
-                                                            (int64_t)v_tiles * n_split_w * d_tiles, kw * 4, dw_beta, false, knobs);
-                const bool turn = turn_contractions(kind, D, row_tiles, n_split_h, kh * 4, planes_written > 0, v_tiles, n_split_w, kw * 4,
-                                                          dw_beta, false, knobs);
+                const LaunchShape shape = launch_shape(row_tiles, v_tiles, sc.split_h, sc.split_w, planes_written > 0, row0 > 0 || accumulate_dW);
+                const int kh = shape.kh, kw = shape.kw, n_split_w = shape.parts_w;
+                const bool dw_beta = shape.dw_beta;
+                n_split_h = shape.parts_h;
+                const LaunchTiles tiles = launch_tiles(shape, D, sc.kind, sc.split_acc != 0, false, counted != nullptr, knobs);
+                const int kind = tiles.kind;
+                const bool turn = tiles.turn;
                 const int panel_shift = turn || kind == 3 ? 5 : 6;    // log2 of the K slice of the contractions' tiles
                 const uint32_t panel = (uint32_t)(row_tiles * 256) << panel_shift;
                 uint16_t* G = ch.in_tail ? (uint16_t*)((char*)dW + (((size_t)V * (size_t)D * 4 - g_bytes) & ~(size_t)255))
@@ -2443,11 +2441,10 @@ static int backward_impl(const void* hidden, const void* weight, const int32_t* 
         const Step& st = steps[k];
         const RowBlock& blk = *st.block;
         const int d_tiles = (int)((D + gemm_tile_of_kind(blk.kind).bn - 1) / gemm_tile_of_kind(blk.kind).bn);
-        const GemmTile gt = gemm_tile_of_kind(contraction_kind(blk.kind, D, (int64_t)st.row_tiles * d_tiles, st.v_tiles * 4,
-                                               !st.first_chunk, blk.split_acc != 0, (int64_t)st.v_tiles * d_tiles, st.row_tiles * 4,
-                                               !st.first_block || accumulate_dW, cc != nullptr, knobs));
-        const bool turn = turn_contractions(gt.kind, D, st.row_tiles, 1, st.v_tiles * 4, !st.first_chunk, st.v_tiles, 1, st.row_tiles * 4,
-                                                  !st.first_block || accumulate_dW, cc != nullptr, knobs);
+        const LaunchTiles tiles = launch_tiles(launch_shape(st.row_tiles, st.v_tiles, 1, 1, !st.first_chunk, !st.first_block || accumulate_dW), D,
+                                               blk.kind, blk.split_acc != 0, cc != nullptr, false, knobs);
+        const GemmTile gt = gemm_tile_of_kind(tiles.kind);
+        const bool turn = tiles.turn;
         const int per256 = 256 / gt.bm;                           // contraction row tiles per 256 rows
         uint16_t* G = (uint16_t*)((blk.g_in_dh ? (char*)dHidden : ws) + blk.off_g);
         char* acc = (blk.acc_in_dh ? (char*)dHidden : ws) + blk.off_acc;     // fp32 dH sums, or their lower halves (see GemmJob)

@@ -658,6 +658,23 @@ static bool turn_contractions(int kind, int64_t D, int64_t e_h, int64_t parts_h,
     return us < other;
 }
 
+// One contraction launch of a backward: row_tiles x v_tiles tiles of 256, the reductions of dH over the columns and of dW over the rows in parts
+// of at most kh and kw tiles; whether the jobs add to their outputs.
+struct LaunchShape { int row_tiles, v_tiles, kh, parts_h, kw, parts_w; bool dh_beta, dw_beta; };
+static LaunchShape launch_shape(int row_tiles, int v_tiles, int split_h, int split_w, bool dh_beta, bool dw_beta) {
+    const int kh = (v_tiles + split_h - 1) / split_h, kw = (row_tiles + split_w - 1) / split_w;
+    return {row_tiles, v_tiles, kh, (v_tiles + kh - 1) / kh, kw, (row_tiles + kw - 1) / kw, dh_beta, dw_beta};
+}
+// Its tiles: `kind` is the order's; row_map: the dW job reads its rows through a map; counted: rows counted on the device.
+struct LaunchTiles { int kind; bool turn; };
+static LaunchTiles launch_tiles(const LaunchShape& s, int64_t D, int kind, bool split_acc, bool row_map, bool counted, const Knobs& knobs) {
+    const int64_t d_tiles = (D + gemm_tile_of_kind(kind).bn - 1) / gemm_tile_of_kind(kind).bn;
+    const int taken = counted ? counted_contraction_kind(kind, D, s.row_tiles, s.v_tiles, d_tiles, s.dh_beta, s.dw_beta, knobs)
+                              : contraction_kind(kind, D, (int64_t)s.row_tiles * s.parts_h * d_tiles, s.kh * 4, s.dh_beta, split_acc,
+                                                 (int64_t)s.v_tiles * s.parts_w * d_tiles, s.kw * 4, s.dw_beta, row_map, knobs);
+    return {taken, turn_contractions(taken, D, s.row_tiles, s.parts_h, s.kh * 4, s.dh_beta, s.v_tiles, s.parts_w, s.kw * 4, s.dw_beta, row_map, knobs)};
+}
+
 // The forward under the same constants, to compare calls with and without row skipping (what its tiles take: forward_tile): rounds of workgroups that walk their vocabulary tiles, or of one
 // small tile each (500 x 2048 x 10000, two rounds of 32 slices: 42 us).
 struct ForwardCost {

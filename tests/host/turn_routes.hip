@@ -19,41 +19,34 @@ int main(int argc, char** argv) {
         plan_backward(&p, rows, D, V, compact, dw_free, workspace_to_ask_for(asked, N, D, V, compact), &s);
         const Knobs knobs = Knobs::read();
         const bool counted = !compact && backward_skip(p, s, D, false).use;
-        int launches = 0, turn = 0, planes = 0, sums = 0, adds = 0, parts = 0, mapped = 0;
-        auto count = [&](int kind, bool split, int64_t e_h, int64_t nh, int64_t s_h, bool beta_h, int64_t e_w, int64_t nw, int64_t s_w, bool beta_w, bool map) {
+        int launches = 0, turn = 0, planes = 0, sums = 0, adds = 0, parts_h = 0, parts_w = 0, mapped = 0;
+        auto count = [&](const LaunchShape& l, int kind, bool split, bool map) {
             ++launches;
-            if (!turn_contractions(kind, D, e_h, nh, s_h, beta_h, e_w, nw, s_w, beta_w, map, knobs)) return;
+            if (!launch_tiles(l, D, kind, split, map, counted, knobs).turn) return;
             ++turn;
-            planes += split; sums += !split; adds += beta_w; parts += nh > 1 || nw > 1; mapped += map;
+            planes += split; sums += !split; adds += l.dw_beta; parts_h += l.parts_h > 1; parts_w += l.parts_w > 1; mapped += map;
         };
         if (s.use) {
-            const int64_t dt = (D + gemm_tile_of_kind(s.kind).bn - 1) / gemm_tile_of_kind(s.kind).bn;
             for (int64_t v = 0; v < V; ) {
                 const ScheduleChunk c = schedule_chunk(s, D, V - v);
-                const int64_t kh = (c.b + s.split_h - 1) / s.split_h, nh = (c.b + kh - 1) / kh;
-                for (int64_t r = 0; r < s.a; r += c.rows) {
-                    const int64_t t = s.a - r < c.rows ? s.a - r : c.rows, kw = (t + s.split_w - 1) / s.split_w, nw = (t + kw - 1) / kw;
-                    const int kind = counted ? counted_contraction_kind(s.kind, D, t, c.b, dt, v > 0 || r > 0, r > 0 || !dw_free, knobs)
-                                             : contraction_kind(s.kind, D, t * nh * dt, kh * 4, v > 0, s.split_acc != 0, c.b * nw * dt, kw * 4, r > 0 || !dw_free, false, knobs);
-                    count(kind, s.split_acc != 0, t, nh, kh * 4, v > 0, c.b, nw, kw * 4, r > 0 || !dw_free, false);
-                }
+                for (int r = 0; r < s.a; r += c.rows)
+                    count(launch_shape(s.a - r < c.rows ? s.a - r : c.rows, (int)c.b, s.split_h, s.split_w, v > 0, r > 0 || !dw_free), s.kind, s.split_acc != 0, false);
                 v += c.b * 256;
             }
         } else {
             const int n = s.n_blocks ? s.n_blocks : (int)((p.TT * 256 + p.Nb - 1) / p.Nb);
             for (int q = 0; q < n; ++q) {
                 RowBlock k = s.n_blocks ? s.blocks[q] : RowBlock{(int)(q * (p.Nb / 256)), (int)(p.Nb / 256), (int)(p.Vc / 256), p.gemm_kind, p.split_acc, false, false, 0, 0};
-                const int64_t a = p.TT - k.r0 < k.a ? p.TT - k.r0 : k.a, dt = (D + gemm_tile_of_kind(k.kind).bn - 1) / gemm_tile_of_kind(k.kind).bn;
-                for (int64_t v = 0; v < p.VT; v += k.b) {
-                    const int64_t b = p.VT - v < k.b ? p.VT - v : k.b;
-                    const bool beta_w = q > 0 || !dw_free;
-                    count(contraction_kind(k.kind, D, a * dt, b * 4, v > 0, k.split_acc != 0, b * dt, a * 4, beta_w, compact, knobs), k.split_acc != 0, a, 1, b * 4, v > 0,
-                          b, 1, a * 4, beta_w, compact);
-                }
+                const int a = p.TT - k.r0 < k.a ? p.TT - k.r0 : k.a;
+                for (int v = 0; v < p.VT; v += k.b)
+                    count(launch_shape(a, p.VT - v < k.b ? p.VT - v : k.b, 1, 1, v > 0, q > 0 || !dw_free), k.kind, k.split_acc != 0, compact);
             }
         }
-        printf("launches=%d turn=%d planes=%d sums=%d adds=%d parts=%d mapped=%d counted=%d gathered=%d half=%d\n", launches, turn, planes, sums, adds, parts, mapped,
-               (int)(counted && turn > 0), (int)(compact && s.use && turn > 0), (int)(turn > 0 && D % 256 != 0 && D % 256 <= 128));
+        // (a call over all rows at D = 64 and 128 has no such launches)
+        const bool fused = !compact && fused_backward_choice(p, N, D, V).use;
+        printf("launches=%d turn=%d planes=%d sums=%d adds=%d parts=%d parts_w=%d mapped=%d counted=%d gathered=%d half=%d fused=%d\n", launches, fused ? 0 : turn, planes, sums,
+               adds, parts_h + parts_w, parts_w, mapped, (int)(counted && turn > 0), (int)(compact && s.use && turn > 0),
+               (int)(turn > 0 && D % 256 != 0 && D % 256 <= 128), (int)fused);
     }
     return 0;
 }
