@@ -13,7 +13,6 @@
 #include "../../include/cce.h"
 #include "gemm_core.h"
 #include "host_util.h"
-#include "wg_map.h"
 
 #ifndef CCE_PLAN_PRICED
 #define CCE_PLAN_PRICED() ((void)0)     // a makespan was searched for: counted by the host tests
