@@ -310,6 +310,13 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
             for (int64_t v = 0; v < p.VT; v += b) tiles.launch(a, v * 256, p.VT - v < b ? p.VT - v : b, D, V);
         }
     }
+    // All rows of bf16 calls at D = 64 and 128 run without a gradient chunk: nothing of the order above.
+    const bool fused = !compact && fused_backward_choice(p, N, D, V).use;
+    if (fused) {
+        s = Schedule{};
+        chunks = in_dw = part_steps = least_h = most_h = most_w = sums_dh = chunks_dh = small = steps = same_tiles = paired = most_rows = 0;
+        tiles = TileCounts();
+    }
     const ForwardTile fwd = forward_tile(p, D);
     const int64_t unit = fwd == kForwardTall ? 192 : 128, units = (V + unit - 1) / unit;
     int halves = 0;                          // splits that end in a half tile
@@ -317,12 +324,12 @@ static void print_form(int64_t N, int64_t D, int64_t V, int64_t M, bool dw_free)
     printf("schedule=%d chunks=%d in_dw=%d row_parts=%d parts_h=%d least_parts_h=%d parts_w=%d split_sums=%d row_blocks=%d "
            "dhidden_blocks=%d sums_in_dhidden=%d chunks_in_dhidden=%d small_tiles=%d paired=%d paired_row_tiles=%d forward_skip=%d forward_skip_fp8=%d "
            "backward_skip=%d backward_skip_fp8=%d same_tiles=%d forward_big=%d forward_square=%d forward_tall=%d forward_halves=%d "
-           "tall=%d square=%d tall_crossing=%d tall_behind=%d tall_mapped=%d\n",
+           "tall=%d square=%d tall_crossing=%d tall_behind=%d tall_mapped=%d fused=%d\n",
            (int)s.use, chunks, in_dw, part_steps, most_h, least_h, most_w, s.use ? s.split_acc : 0, s.use ? (p.TT + s.a - 1) / s.a : 0,
            s.n_blocks, sums_dh, chunks_dh, small, paired, most_rows, (int)forward_skip(p, D, false).use, (int)(D % 128 == 0 && forward_skip(p, D, true).use),
            (int)(!compact && backward_skip(p, s, D, false).use), (int)(!compact && D % 128 == 0 && backward_skip(p, s, D, true).use),
            (int)(steps > 0 && same_tiles == steps), (int)(fwd == kForwardBig), (int)(fwd == kForwardSquare), (int)(fwd == kForwardTall), halves,
-           tiles.tall, tiles.square, tiles.crossing, tiles.behind, compact && !s.use ? tiles.tall : 0);    // (a schedule gathers the rows)
+           tiles.tall, tiles.square, tiles.crossing, tiles.behind, compact && !s.use ? tiles.tall : 0, (int)fused);    // (a schedule gathers the rows)
 }
 
 // The label scan in front of a forward that leaves ignored rows out is one workgroup, 0.4 ns a row: it has to be small beside the forward.

@@ -6,18 +6,24 @@ exact count of valid rows, one in five ignored (one in seven in AGAINST_FORCED).
 Words (least values): chunks of the vocabulary, in_dw of them in unwritten rows of dW, row_parts chunks taken in steps over
 part of the rows, parts_h / parts_w K parts of dH / dW, varied (a chunk with fewer dH parts than another),
 split_sums (dH sums in two planes), row_blocks, dhidden_blocks (row blocks from the last to the first) with
-sums_in_dhidden / chunks_in_dhidden."""
+sums_in_dhidden / chunks_in_dhidden; fused: all rows at D = 64 and 128 without a gradient chunk, where the other words are zero."""
 
 # against the fp64 oracle
 AGAINST_ORACLE = {
-    (300, 64, 30011): dict(rows=dict(parts_h=8), accumulate=dict(parts_h=8), compact=dict(parts_h=8)),
+    (300, 64, 30011): dict(rows=dict(fused=1), accumulate=dict(fused=1), compact=dict(parts_h=8)),
+    (300, 192, 30011): dict(rows=dict(parts_h=8), accumulate=dict(parts_h=8), compact=dict(parts_h=8)),
     (80, 512, 30000): dict(rows=dict(parts_h=8), accumulate=dict(parts_h=8), compact=dict(parts_h=8)),       # one row tile
     (900, 1088, 9001): dict(rows=dict(parts_h=2), accumulate=dict(parts_h=2), compact=dict(parts_h=2)),      # D not a multiple of the tile
-    (3000, 64, 1100): dict(rows=dict(parts_w=2), accumulate=dict(parts_w=2), compact=dict(parts_w=2)),       # ragged last part
-    (9000, 64, 300): dict(rows=dict(parts_w=8), accumulate=dict(parts_w=8), compact=dict(parts_w=2, row_blocks=2)),
-    (5000, 128, 700): dict(rows=dict(parts_w=4), accumulate=dict(parts_w=4), compact=dict(parts_w=4)),
+    (3000, 64, 1100): dict(rows=dict(fused=1), accumulate=dict(fused=1), compact=dict(parts_w=2)),       # ragged last part
+    (3000, 320, 1100): dict(rows=dict(parts_w=2), accumulate=dict(parts_w=2), compact=dict(parts_w=2)),
+    (9000, 64, 300): dict(rows=dict(fused=1), accumulate=dict(fused=1), compact=dict(parts_w=2, row_blocks=2)),
+    (9000, 192, 300): dict(rows=dict(parts_w=8), accumulate=dict(parts_w=8)),
+    (5000, 128, 700): dict(rows=dict(fused=1), accumulate=dict(fused=1), compact=dict(parts_w=4)),
+    (5000, 256, 700): dict(rows=dict(parts_w=4), accumulate=dict(parts_w=4), compact=dict(parts_w=4)),
     (2445, 256, 8265): dict(rows=dict(row_blocks=2, parts_h=2)),
-    (3712, 64, 28036): dict(rows=dict(chunks=3, parts_h=4, parts_w=2, varied=1)),
+    (3712, 64, 28036): dict(rows=dict(fused=1)),
+    (2224, 192, 9419): dict(rows=dict(chunks=2, parts_h=4, parts_w=2, varied=1), accumulate=dict(chunks=2, parts_h=4, parts_w=2, varied=1)),
+    (522, 192, 41956): dict(rows=dict(chunks=3, parts_h=4, varied=1)),
     (323, 896, 54016): dict(rows=dict(chunks=2, in_dw=1, parts_h=2)),
     (707, 384, 30095): dict(compact=dict(chunks=2, parts_h=4, varied=1)),
 }
@@ -65,7 +71,7 @@ LOGIT_TILES = {
     (4352, 128, 147584): dict(compact=dict(forward_tall=1, forward_halves=11, tall=18, tall_behind=1)),
     (4352, 320, 23552): dict(rows=dict(forward_tall=1, forward_halves=11, tall=5, tall_crossing=1)),
     (4865, 320, 28031): dict(rows=dict(forward_tall=1, forward_halves=2, tall=7, tall_behind=1)),
-    (412, 64, 34049): dict(rows=dict(forward_big=1, tall_behind=1)),                       # one K slice
+    (412, 64, 34049): dict(rows=dict(forward_big=1, fused=1), compact=dict(tall_behind=1)),                       # one K slice
     (3484, 512, 6401): dict(compact=dict(tall_mapped=1, tall_behind=1)),
     (7425, 704, 6272): dict(compact=dict(tall_mapped=1, tall_crossing=1)),
     (668, 896, 42752): dict(rows=dict(forward_square=1, forward_halves=2, square=2)),      # 167 tiles of 256
@@ -97,4 +103,4 @@ def drawn(case):
                 accumulate=bool(rng.integers(0, 2)))
 
 
-N_DRAWN = 24
+N_DRAWN = 36

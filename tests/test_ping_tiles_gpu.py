@@ -1,7 +1,7 @@
 """GPU parity with the oracle where vocabularies end on, in front of and behind a tile, half a tile and a chunk's last tile, row
 counts around a tile, one K slice, with and without label smoothing and row skipping.  Launches this small run their forwards on
 the loop of 256 x 256 tiles and nearly all of their gradient tiles on 256 x 256 ones of two groups of wavefronts (see PingTile in
-csrc/gemm_core.h); the edges of the 384 x 256 ones, and of forwards on either: test_logit_tiles_gpu.py.  Oracle and tolerances as in
+csrc/gemm_core.h), at D = 64 and 128 under row skipping only; the edges of the 384 x 256 ones, and of forwards on either: test_logit_tiles_gpu.py.  Oracle and tolerances as in
 test_parity_gpu.py."""
 import numpy as np
 import pytest
@@ -17,7 +17,8 @@ IGN = -100
 # (rows, D, V): at least 129 tiles of 256 x 256, below which the 128 x 128 ones run
 SHAPES = [(1281, 64, 384 * 30), (1280, 64, 384 * 30 + 1), (1279, 128, 384 * 30 + 192), (1281, 192, 384 * 30 + 193), (1500, 64, 384 * 30 + 383),
           (1000, 64, 256 * 50), (1025, 128, 256 * 50 + 1), (1024, 64, 256 * 50 + 128), (900, 320, 256 * 50 + 129),
-          (4097, 64, 256 * 9 + 255), (7500, 64, 1537), (33, 256, 40001)]
+          (4097, 64, 256 * 9 + 255), (7500, 64, 1537), (33, 256, 40001),
+          (1281, 192, 384 * 30), (1280, 192, 384 * 30 + 1), (1000, 192, 256 * 50), (1025, 192, 256 * 50 + 1), (4097, 192, 256 * 9 + 255)]
 
 
 @pytest.mark.parametrize("eps", [0.0, 0.1])

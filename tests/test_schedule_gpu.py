@@ -171,7 +171,7 @@ def test_fp8_schedule_matches_forced_tiling(shape):
         assert float(h0[y == IGN].float().abs().max()) == 0.0 and e[0] <= 2e-3 and e[1] <= 2e-5
 
 
-@pytest.mark.parametrize("shape", [(7500, 640, 90001), (12001, 4096, 8001), (509, 896, 151936), (3712, 64, 28036)])
+@pytest.mark.parametrize("shape", [(7500, 640, 90001), (12001, 4096, 8001), (509, 896, 151936), (3712, 64, 28036), (2224, 192, 9419)])
 def test_shard_schedule_matches_forced_tiling(shape):
     """A share of the vocabulary that starts at row 20000 of a larger one, with label smoothing, z-loss and the mean
     reduction, in the orders of its own rows: against the forced tiling, bounds as above.  (Labels of other shares are valid and
@@ -204,11 +204,12 @@ def test_shard_schedule_matches_forced_tiling(shape):
 
 
 @pytest.mark.parametrize("cuts", [[30011], [9001, 39012]])
-def test_shards_in_schedules_match_the_undivided_oracle(cuts):
-    """Shares whose backwards run in K parts, summed and concatenated against the undivided oracle."""
+@pytest.mark.parametrize("D", [64, 192])
+def test_shards_in_schedules_match_the_undivided_oracle(cuts, D):
+    """Shares whose backwards run in K parts (D = 192) or parts of the vocabulary (D = 64), summed and concatenated against the undivided oracle."""
     from paper_2601_02609_amd import binding as B
     from tests.test_shard_gpu import parts_of, run_sharded
-    N, D, V = 300, 64, 60022
+    N, V = 300, 60022
     w = I.make_workload(I.custom_spec(N, D, V, seed=79, ignore_frac=0.15))
     _, loss, lse, dH, dW, _, status = run_sharded(B, w, parts_of(V, cuts), w.dloss_var, 0.1, 1e-3)
     o_loss, o_lse = O.forward(w.hidden, w.weight, w.labels, IGN, label_smoothing=0.1, z_loss=1e-3)

@@ -47,8 +47,9 @@ def test_non_default_stream_matches_default(B):
         assert torch.equal(a[k], b[k]), k
 
 
-def test_graph_capture_and_replay(B):
-    w = I.make_workload(I.custom_spec(520, 128, 2100, seed=42, ignore_frac=0.1))
+@pytest.mark.parametrize("D", [128, 320])             # without and with a gradient chunk
+def test_graph_capture_and_replay(B, D):
+    w = I.make_workload(I.custom_spec(520, D, 2100, seed=42, ignore_frac=0.1))
     ref, b = _buffers(B, w), _buffers(B, w)
     _step(B, ref)
     _step(B, b)                      # warm-up outside the capture (first-use set-up of the library)

@@ -17,6 +17,8 @@ SHAPES = [
     (3547, 1728, 3547, "accumulate", ("planes", "adds")),                    # 192 behind 6 x 256
     (286, 2048, 9128, "rows", ("parts", "sums")),
     (406, 1728, 11339, "accumulate", ("parts", "adds")),
+    (5728, 1408, 1459, "rows", ("parts_w", "sums", "half")),
+    (11340, 960, 1406, "accumulate", ("parts_w", "sums", "adds")),
     (3459, 1920, 2253, "compact", ("mapped", "sums", "half")),
     (5041, 1728, 3179, "compact", ("mapped", "planes")),
     (6151, 2816, 2893, "compact", ("gathered", "sums")),
