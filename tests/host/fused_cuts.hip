@@ -33,7 +33,16 @@ static int few_parts(int64_t N, int64_t D, int64_t V, int most) {
     return 1;
 }
 
-int main() {
+int main(int argc, char** argv) {
+    if (argc > 1) {                          // N D V, any number of times: how the launch is cut
+        for (int i = 1; i + 2 < argc; i += 3) {
+            const int64_t N = atoll(argv[i]), D = atoll(argv[i + 1]), V = atoll(argv[i + 2]);
+            Plan p;
+            const FusedChoice f = make_plan(N, D, V, &p) ? fused_backward_choice(p, N, D, V) : FusedChoice{};
+            printf("%d %d %d %d\n", (int)f.use, (int)f.shared, (int)(f.parts_h > 1), (int)(f.parts_w > 1));
+        }
+        return 0;
+    }
     int bad = 0, n = 0;
     bad += few_parts(228, 128, 12162, 24) + few_parts(228, 64, 12162, 24) + few_parts(900, 128, 12162, 8) + few_parts(160, 64, 12162, 24);
     srand(11);

@@ -10,6 +10,20 @@ pytestmark = pytest.mark.gpu
 IGN = -100
 
 
+# N, D, V, form, what the launch is cut into: (wavefronts share their rows, several parts of the vocabulary, of the tokens)
+FORMS = [
+    (60513, 64, 1203, "accumulate", (0, 0, 1)), (59621, 64, 2309, "mean", (0, 0, 1)),
+    (1199, 64, 61313, "variants", (0, 1, 0)), (1893, 64, 65361, "accumulate", (0, 1, 0)),
+    (3529, 64, 9829, "shard", (0, 1, 1)), (3573, 64, 9895, "variants", (0, 1, 1)), (3575, 64, 9981, "mean", (0, 1, 1)),
+    (1177, 64, 105, "shard", (1, 0, 1)), (101, 64, 1187, "variants", (1, 1, 0)), (1799, 64, 2621, "mean", (1, 1, 1)),
+    (22455, 128, 22417, "accumulate", (0, 0, 0)),
+    (20637, 128, 803, "accumulate", (0, 0, 1)), (24487, 128, 691, "variants", (0, 0, 1)),
+    (651, 128, 24227, "mean", (0, 1, 0)), (839, 128, 20837, "shard", (0, 1, 0)),
+    (5013, 128, 2907, "shard", (0, 1, 1)), (1715, 128, 9687, "accumulate", (0, 1, 1)),
+    (1025, 128, 101, "shard", (1, 0, 1)), (101, 128, 1187, "variants", (1, 1, 0)), (2527, 128, 1807, "accumulate", (1, 1, 1)),
+]
+
+
 def reference(H, W, y, dl, eps, lam, v_off, v_total, lse):
     """Gradients of this share of the vocabulary for the given lse of all of it, fp32."""
     valid = (y != IGN) & (y >= 0) & (y < v_total)
@@ -32,6 +46,16 @@ def rel(a, b):
     (3001, 2050, "accumulate"), (517, 20011, "shard"), (9001, 1283, "variants"), (4100, 9001, "rows"), (20011, 515, "shard"),
 ])
 def test_fused_backward_matches_torch_and_chunks(N, V, form, D):
+    check(N, D, V, form)
+
+
+@pytest.mark.parametrize("N,D,V,form", [f[:4] for f in FORMS])
+def test_every_cut_of_the_fused_backward(N, D, V, form):
+    """The forms that large calls take; test_fused_cuts_host.py asks the planner whether these shapes still take them."""
+    check(N, D, V, form)
+
+
+def check(N, D, V, form):
     from paper_2601_02609_amd import binding as B
     print(f"[fused] N={N} D={D} V={V} {form}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(N + D + V)
