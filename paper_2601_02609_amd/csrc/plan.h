@@ -1142,10 +1142,11 @@ static bool order_uses_dhidden(const Plan& p, const Schedule& sc) {
 // layout alone (the workspace asked for), so that calls of a shape agree.
 // Over a gradient chunk / this, us: 256 x 64 x 1000 14.9 / 7.0, 2000 x 64 x 5000 34 / 22, 600 x 64 x 150000 226 / 86, 8192 x 64 x 151936
 // 3426 / 715, 28457 x 64 x 48721 3352 / 794, 500 x 128 x 3000 15.9 / 11.3, 1000 x 128 x 50000 109 / 82, 22053 x 128 x 77882
-// 4148 / 1812: so every call that can takes it (FP8 logits and row skipping cannot).  The constants are fitted to 1 to 144 cuts each of 66 shapes,
-// a row to a million: 4 us and the bytes or, where those are few, the chain of one load behind the other, 0.31 us a plane, for a sum
-// of planes (rated by the bytes alone, 228 x 128 x 12162 was cut into 48 parts and took 26 us, for 17.5 in 16 parts and 21 over a
-// chunk; 900 x 128 x 12162 33 / 27.7 / 30).  Of 226 calls timed over a chunk and so, none is slower.
+// 4148 / 1812: so every call that can takes it (FP8 logits and row skipping cannot).  The constants are fitted to 1 to 144 cuts each of 102
+// shapes, a row to a million: 4 us and the bytes or, where those are few, the chain of one load behind the other, 0.39 us a plane, for a
+// sum of planes (rated by the bytes alone, 228 x 128 x 12162 was cut into 48 parts and took 26 us, for 17.5 in 16 parts and 21 over
+// a chunk; 900 x 128 x 12162 33 / 27.7 / 30).  What is chosen takes 2.3 % longer than the fastest cut on average, 23 % at most
+// (9129 x 64 x 18135 130 us for 105).  Of 226 calls timed over a chunk and so, none is slower.
 struct FusedChoice { bool use, shared; int parts_h, parts_w, len_h, len_w, n_h, n_w; double us; };
 static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, int64_t V) {
     FusedChoice best = {};
@@ -1161,11 +1162,11 @@ static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, in
         if (k.valid && k.N == N && k.D == D && k.V == V && k.region == region && k.cus == cus) return k.choice;
     const int64_t tiles_n = (N + 127) / 128, tiles_v = (V + 127) / 128;
     const int cuts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
-    auto planes_us = [](int planes, double bytes) { return planes == 0 ? 0.0 : 4.0 + (0.31 * planes > bytes / 4.0e6 ? 0.31 * planes : bytes / 4.0e6); };
+    auto planes_us = [](int planes, double bytes) { return planes == 0 ? 0.0 : 4.0 + (0.39 * planes > bytes / 3.2e6 ? 0.39 * planes : bytes / 3.2e6); };
     for (int shared = 0; shared < 2; ++shared) {
         // stationary rows of an item, items to a unit, microseconds of a streamed tile beside the unit's other items and alone
         const int64_t rows = shared ? 32 : D == 64 ? 256 : 128, slots = (D == 64 && shared ? 4 : 2) * cus;
-        const double beside = shared ? (D == 64 ? 1.22 : 1.2) : D == 64 ? 4.55 : 3.25, alone = shared ? (D == 64 ? 0.75 : 0.8) : D == 64 ? 2.9 : 2.65;
+        const double beside = shared ? (D == 64 ? 1.16 : 1.2) : D == 64 ? 3.64 : 3.25, alone = shared ? (D == 64 ? 0.79 : 0.8) : D == 64 ? 2.9 : 2.65;
         const double fixed = shared && D == 128 ? 2.9 : 4.0;
         for (int ph : cuts) {
             const int64_t len_h = (tiles_v + ph - 1) / ph, n_h_parts = (tiles_v + len_h - 1) / len_h;

@@ -24,7 +24,7 @@ static int check(int64_t N, int64_t D, int64_t V) {
     return ok ? 0 : 1;
 }
 
-// The sum of few rows' planes takes 0.31 us a plane: ranges of few tiles (96 here) are not cut into 48 parts because they can be.
+// The sum of few rows' planes takes 0.39 us a plane: ranges of few tiles (96 here) are not cut into 48 parts because they can be.
 static int few_parts(int64_t N, int64_t D, int64_t V, int most) {
     Plan p;
     const FusedChoice f = make_plan(N, D, V, &p) ? fused_backward_choice(p, N, D, V) : FusedChoice{};

@@ -15,12 +15,12 @@ FORMS = [
     (60513, 64, 1203, "accumulate", (0, 0, 1)), (59621, 64, 2309, "mean", (0, 0, 1)),
     (1199, 64, 61313, "variants", (0, 1, 0)), (1893, 64, 65361, "accumulate", (0, 1, 0)),
     (3529, 64, 9829, "shard", (0, 1, 1)), (3573, 64, 9895, "variants", (0, 1, 1)), (3575, 64, 9981, "mean", (0, 1, 1)),
-    (1177, 64, 105, "shard", (1, 0, 1)), (101, 64, 1187, "variants", (1, 1, 0)), (1799, 64, 2621, "mean", (1, 1, 1)),
+    (1177, 64, 105, "shard", (1, 0, 1)), (101, 64, 2503, "variants", (1, 1, 0)), (1799, 64, 2621, "mean", (1, 1, 1)),
     (22455, 128, 22417, "accumulate", (0, 0, 0)),
-    (20637, 128, 803, "accumulate", (0, 0, 1)), (24487, 128, 691, "variants", (0, 0, 1)),
-    (651, 128, 24227, "mean", (0, 1, 0)), (839, 128, 20837, "shard", (0, 1, 0)),
-    (5013, 128, 2907, "shard", (0, 1, 1)), (1715, 128, 9687, "accumulate", (0, 1, 1)),
-    (1025, 128, 101, "shard", (1, 0, 1)), (101, 128, 1187, "variants", (1, 1, 0)), (2527, 128, 1807, "accumulate", (1, 1, 1)),
+    (33001, 128, 2050, "accumulate", (0, 0, 1)), (40007, 128, 1283, "variants", (0, 0, 1)),
+    (617, 128, 30573, "mean", (0, 1, 0)), (3001, 128, 33001, "shard", (0, 1, 0)),
+    (4100, 128, 9001, "shard", (0, 1, 1)), (1715, 128, 9687, "accumulate", (0, 1, 1)),
+    (1025, 128, 101, "shard", (1, 0, 1)), (101, 128, 1187, "variants", (1, 1, 0)), (2259, 128, 3655, "accumulate", (1, 1, 1)),
 ]
 
 
