@@ -864,10 +864,10 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
         if (p.split_acc) best.plan_us += (double)(nblk * nch) * (compact ? 9.0 : 2.0);
     }
     // A schedule has to be rated 10 % faster, one without K parts 4 % where launches may be on tiles of two wavefront groups, whose times
-    // the model has more closely.  (Of 46 drawn calls of 3e10 products on, none is slower with 4 % than with 10 % by more than the
-    // runs differ, seven are 4 to 8 % faster, among them 10621 x 128 x 118991, 1041 x 2880 x 49282 and 2042 x 2880 x 86534;
-    // 16384 x 2048 x 151936 31.0 -> 30.4 ms.)  Such an order with its sums in planes counts for 4 % less than it is rated where it may
-    // leave ignored rows out (backward_skip), which the rating does not know: that stands for batches of which a tenth is padding.  Of 974
+    // the model has more closely.  (Of 70 drawn orders that 4 % and, for row blocks, 2 % decide otherwise than 10 % and 5 %, timed in 105 calls,
+    // the calls take 2.6 % less on average: a fifth less at best (11020 x 1920 x 1637 267 -> 210 us), 18 of them 3 to 13 % more (1822 x 3328 x
+    // 12641 with 15 % skipped, added to dW, 434 -> 489; 14251 x 320 x 93097 3857 -> 4155).  16384 x 2048 x 151936 31.0 -> 30.4 ms.)
+    // Such an order with its sums in planes counts for 4 % less than it is rated where it may leave ignored rows out (backward_skip), which the rating does not know: that stands for batches of which a tenth is padding.  Of 974
     // drawn shapes it decides 98; 24 of those, timed with and without, take 1.8 % longer where no row is ignored (up to 13.6 % where the other
     // order is in K parts: 1934 x 2560 x 127550 3871 us for 3446, 3762 before tiles of two wavefront groups), 0.3 % less with 5 % ignored and 6.0 % less with
     // 15 % (6523 x 2816 x 36339 3116 us for 3859).
