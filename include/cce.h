@@ -45,8 +45,9 @@
  *     dHidden sums of one row block (for large D only their lower halves: the upper
  *     halves then live in dHidden itself until the last vocabulary chunk rounds the
  *     sums to bf16 there; several planes of them where the reduction is cut into
- *     parts) and one bf16 [row block x vocab chunk] gradient chunk; it is at most 1 %
- *     of the materialised logits or 48 MB.  Contents are scratch: nothing
+ *     parts) and one bf16 [row block x vocab chunk] gradient chunk (D = 64 and 128: no
+ *     chunk, but fp32 planes of dHidden and dW where the work is cut into parts); it is
+ *     at most 1 % of the materialised logits or 48 MB.  Contents are scratch: nothing
  *     needs to survive between forward and backward except what the caller
  *     passes explicitly (lse).
  */
@@ -149,7 +150,8 @@ int cce_forward_static(const void* hidden, const void* weight, const int32_t* la
  *                                      may hold gradient tiles while the call runs);
  *                                      accumulate_dW != 0: the gradient is added to it
  * The logit gradient tile is rounded to bf16 (nearest even) before the two
- * contractions, which accumulate in fp32.
+ * contractions, which accumulate in fp32.  At D = 64 and 128, with nothing forced, the tiles stay in registers and
+ * each contraction forms its own; otherwise they pass through a gradient chunk in memory.
  */
 int cce_backward(const void* hidden, const void* weight, const int32_t* labels,
                  const float* lse, const float* dloss,
@@ -206,7 +208,7 @@ int cce_set_backward_tiling(int row_tiles, int vocab_tiles);
 /* The tiling (in 256-wide tiles) the backward uses for this shape: the forced one, else the
  * automatic choice.  Host only; the two outputs are host ints.  While nothing is forced, a shape
  * may run in another order where that is rated faster (chunks of several sizes, row blocks from the
- * last to the first, reductions cut into parts). */
+ * last to the first, reductions cut into parts), and D = 64 and 128 run without chunks, for which this tiling says nothing. */
 int cce_get_backward_tiling(int64_t N, int64_t D, int64_t V, int* row_tiles, int* vocab_tiles);
 
 /* Tuning / testing aid like cce_set_backward_tiling: force the output tile of the two gradient

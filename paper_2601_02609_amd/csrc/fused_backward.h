@@ -111,7 +111,8 @@ __device__ __forceinline__ void fused_item(const FusedArgs& a, int item, CCE_LDS
         for (int b = 0; b < RB; ++b) out[d][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // 16-byte chunk c of row r of a streamed tile lies at c ^ swizzle(r): the 16 rows of a K-major fragment meet every bank once, and so
-    // do the 8 rows x 32 bytes that two lane groups of a transpose read touch.
+    // do the 8 rows x 32 bytes that two lane groups of a transpose read touch.  (Over a quarter of the LDS's busy cycles count as conflicts all
+    // the same: 27 % at D = 64, 30 % at D = 128.)
     auto swizzle = [](int r) { return D == 64 ? (((r >> 1) & 3) << 1) | ((r >> 3) & 1) : ((r & 7) << 1) | ((r >> 3) & 1); };
     constexpr int CPR = D / 8, RPL = 64 / CPR;                  // chunks of a row, rows of a wavefront's load
     const int load_row = RPL * wave + l / CPR;

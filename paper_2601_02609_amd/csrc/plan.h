@@ -867,10 +867,11 @@ static void make_schedule(const Plan& p, int64_t N, int64_t D, int64_t V, bool c
     // the model has more closely.  (Of 70 drawn orders that 4 % and, for row blocks, 2 % decide otherwise than 10 % and 5 %, timed in 105 calls,
     // the calls take 2.6 % less on average: a fifth less at best (11020 x 1920 x 1637 267 -> 210 us), 18 of them 3 to 13 % more (1822 x 3328 x
     // 12641 with 15 % skipped, added to dW, 434 -> 489; 14251 x 320 x 93097 3857 -> 4155).  16384 x 2048 x 151936 31.0 -> 30.4 ms.)
-    // Such an order with its sums in planes counts for 4 % less than it is rated where it may leave ignored rows out (backward_skip), which the rating does not know: that stands for batches of which a tenth is padding.  Of 974
-    // drawn shapes it decides 98; 24 of those, timed with and without, take 1.8 % longer where no row is ignored (up to 13.6 % where the other
-    // order is in K parts: 1934 x 2560 x 127550 3871 us for 3446, 3762 before tiles of two wavefront groups), 0.3 % less with 5 % ignored and 6.0 % less with
-    // 15 % (6523 x 2816 x 36339 3116 us for 3859).
+    // Such an order with its sums in planes counts for 4 % less than it is rated where it may leave ignored rows out (backward_skip), which
+    // the rating does not know: that stands for batches of which a tenth is padding.  Of 974 drawn shapes it decides 98; 24 of those, timed
+    // with and without, take 1.8 % longer where no row is ignored (up to 13.6 % where the other order is in K parts: 1934 x 2560 x 127550
+    // 3871 us for 3446, 3762 before tiles of two wavefront groups), 0.3 % less with 5 % ignored and 6.0 % less with 15 % (6523 x 2816 x
+    // 36339 3116 us for 3859).
     const bool may_skip = turns && !compact && may_skip_backward(p, D);
     const double parts_us = 0.90 * best.plan_us < limit ? 0.90 * best.plan_us : limit;
     double rated = (turns ? 0.96 : 0.90) * best.plan_us;        // of the best so far
@@ -1211,7 +1212,7 @@ static double backward_us(Plan p, int64_t N, int64_t D, int64_t V, bool compact,
 // of the two.  Of 3700 drawn shapes of D 192 to 4096 with 5 ... 60 % of the rows ignored this answers 120 otherwise than ratings without tiles of
 // two wavefront groups, one of the two forms 6 % faster and the other no slower: 75 of those, both forms of both calls timed, are 0.6 %
 // above the better side on average and were 8.0 (17712 x 1280 x 4257 with 15 % 654 us for 810; 8950 x 384 x 4089 with 10 % loses 5 %); 86
-// others 0.5 and 0.6 %.  At 2.5 % the model is wrong where it costs most (16384 x 2048 x 151936 with 15565 valid, rated 0.95 and
+// others 0.7 and 0.9 %.  At 2.5 % the model is wrong where it costs most (16384 x 2048 x 151936 with 15565 valid, rated 0.95 and
 // 0.999, takes 1.08 and 1.10).
 // At D = 64 and 128 all rows without a chunk are the faster ones up to some 60 % ignored: of 44 shapes with 5 ... 80 % two skip, the
 // faster form each time (8699 x 64 x 68133 with 80 % 332 us for 481, 24548 x 64 x 92355 with 5 % 4 575 for 1 767).
