@@ -11,8 +11,8 @@
 //
 // Bound by the vector ALU: per logit and lane two multiply-adds, an exponential (16 clocks of a wavefront) and half a conversion, 26
 // clocks for 16 (D = 64) or 32 (D = 128) of products; what is reached is about their sum, 44 clocks a logit at D = 64.  Wavefronts of 64
-// stationary rows at D = 64, of 32 at D = 128, where twice the columns take the registers.  28457 x 64 x 48721: 3.35 ms in launches over
-// a gradient chunk (66 of them, 8.3 GB of chunk traffic), 0.79 ms; 22053 x 128 x 77882 4.15 and 1.81; 256 x 64 x 1000 14.9 us and 7.0.
+// stationary rows at D = 64, of 32 at D = 128, where twice the columns take the registers.  28457 x 64 x 48721: 3.32 ms in launches over
+// a gradient chunk (66 of them, 8.3 GB of chunk traffic), 0.74 ms; 22053 x 128 x 77882 4.12 and 1.81; 256 x 64 x 1000 15.2 us and 10.2.
 #pragma once
 
 #include "gemm_core.h"

@@ -1141,13 +1141,13 @@ static bool order_uses_dhidden(const Plan& p, const Schedule& sc) {
 // ranges are cut into parts of whole tiles of 128 rows where the stationary tiles alone leave compute units idle; a part of the
 // dH job writes a plane, and so does one of the dW job from the second on, summed by a small launch each.  From the shape and the planned
 // layout alone (the workspace asked for), so that calls of a shape agree.
-// Over a gradient chunk / this, us: 256 x 64 x 1000 14.9 / 7.0, 2000 x 64 x 5000 34 / 22, 600 x 64 x 150000 226 / 86, 8192 x 64 x 151936
-// 3426 / 715, 28457 x 64 x 48721 3352 / 794, 500 x 128 x 3000 15.9 / 11.3, 1000 x 128 x 50000 109 / 82, 22053 x 128 x 77882
-// 4148 / 1812: so every call that can takes it (FP8 logits and row skipping cannot).  The constants are fitted to 1 to 144 cuts each of 102
+// Over a gradient chunk / this, us: 256 x 64 x 1000 15.2 / 10.2, 2000 x 64 x 5000 31 / 21, 600 x 64 x 150000 224 / 78, 8192 x 64 x 151936
+// 3381 / 670, 28457 x 64 x 48721 3321 / 735, 500 x 128 x 3000 16.7 / 13.3, 1000 x 128 x 50000 107 / 79, 22053 x 128 x 77882 4119 / 1811:
+// so every call that can takes it (FP8 logits and row skipping cannot).  The constants are fitted to 1 to 144 cuts each of 102
 // shapes, a row to a million: 4 us and the bytes or, where those are few, the chain of one load behind the other, 0.39 us a plane, for a
 // sum of planes (rated by the bytes alone, 228 x 128 x 12162 was cut into 48 parts and took 26 us, for 17.5 in 16 parts and 21 over
 // a chunk; 900 x 128 x 12162 33 / 27.7 / 30).  What is chosen takes 2.3 % longer than the fastest cut on average, 23 % at most
-// (9129 x 64 x 18135 130 us for 105).  Of 226 calls timed over a chunk and so, none is slower.
+// (9129 x 64 x 18135 130 us for 105).  Of 273 calls timed over a chunk and so, none is slower.
 struct FusedChoice { bool use, shared; int parts_h, parts_w, len_h, len_w, n_h, n_w; double us; };
 static FusedChoice fused_backward_choice(const Plan& p, int64_t N, int64_t D, int64_t V) {
     FusedChoice best = {};
