@@ -803,7 +803,8 @@ struct PingLoads {
 // LDS layout, a lane's 16 bytes at lane * 16 of a wavefront's 1 KB: X in blocks of 64 columns, [block][32 k][128 B], the 32-byte
 // unit u of a row at u ^ (bit 1 of k + 2 bit 3 of k); G K-slow in blocks of 32 columns (a panel's width), [block][32 k][64 B], at
 // u ^ bit 3 of k: the 8 k-rows x 32 bytes that two lane groups of a transpose read touch per clock cover all 64 banks (measured
-// 229 of 256 B/clk, and 64 with the units in place; a seventh of the LDS's busy cycles count as conflicts).  G K-major: [row][64 B], chunk c at c ^ bits 2, 3 of the row.
+// 229 of 256 B/clk, and 64 with the units in place; a seventh of the LDS's busy cycles count as conflicts).  G K-major: [row][64 B],
+// chunk c at c ^ bits 2, 3 of the row.
 //
 // What bounds it is power.  4096 x 24576 x 4096 in one launch after the other, TFLOP/s on random / constant operands: 256 x 256 by
 // gemm_mainloop 1 436 / 1 892, 256 x 128 1 292 / 1 786, these 1 583 / 2 158 (with the loads in the reading turns, three stages
